@@ -22,6 +22,7 @@
 
 #include "common.h"
 #include "layout.h"
+#include "mfma.h"
 
 namespace dpvba {
 
@@ -95,12 +96,185 @@ __global__ void __launch_bounds__(256) patch_corr_kernel(int n_items, int p2, co
   }
 }
 
+// 3 x 3 patches (the odometry's) on the matrix cores.  The nine windows of one
+// edge overlap almost entirely (their points lie about a pixel apart), so
+// one wavefront per edge takes their union, clipped to the map, once: 16 map
+// pixels at a time against the patch's nine feature vectors (rows 9 .. 15 of
+// the 16 x 16 x 4 products are zero), every dot product accumulated in
+// float32.  Lane l holds row l % 16 of the patch features and pixel l % 16 of
+// the union at channels 16 s + 4 (l / 16) + c: both operands take the same
+// order of the channels, so they arrive as 16-byte loads straight into the
+// operand registers (two wavefronts per SIMD at least: the products then
+// stay in ordinary registers, without a move out of the accumulators).  The dots [9][union] go to LDS, and the 441 outputs of the edge
+// are combined from them and written contiguously.  Patches whose union
+// holds more than kCorrUnion pixels take their nine windows one by one.
+// Against one wavefront per (edge, pixel) this reads 100 to 144 map pixels an
+// edge instead of 576 and needs no reduction over lanes: 37,440 edges of 128
+// channels took 1,564 us and take 229 us (the products alone 109 us at the float32
+// matrix rate), 2.0 GB of map pixels read from the caches instead of 11 GB.
+constexpr int kCorrUnion = 256;            // pixels of a union window
+constexpr int kCorrLd = kCorrUnion + 4;    // row stride of the dots (the four row groups of a store on different banks)
+
+// Sum of the products of N groups of 16 channels, as a binary tree.
+template <int N>
+__device__ __forceinline__ floatx4_t corr_tree(const float4* g, const float4* f) {
+  if constexpr (N == 1) {
+    const floatx4_t zero = {0.f, 0.f, 0.f, 0.f};
+    return (Mfma<float>::step(g->x, f->x, zero) + Mfma<float>::step(g->y, f->y, zero)) +
+           (Mfma<float>::step(g->z, f->z, zero) + Mfma<float>::step(g->w, f->w, zero));
+  } else {
+    return corr_tree<N / 2>(g, f) + corr_tree<N - N / 2>(g + N / 2, f + N / 2);
+  }
+}
+
+template <int VPL>  // channels per lane quarter of 16 (D = 64 VPL)
+__global__ void __launch_bounds__(256, 2) patch_corr3_kernel(int n_edges, const float* __restrict__ gmap, int n_patches,
+                                                          const float* __restrict__ fmaps, int n_maps, int H, int W,
+                                                          const int* __restrict__ kk, const int* __restrict__ jj,
+                                                          const float* __restrict__ coords, float* __restrict__ corr,
+                                                          int* dev_err, int* host_err) {
+  constexpr int D = 64 * VPL, NS = D / 16, P2 = 9, G2 = kCorrGrid * kCorrGrid;
+  __shared__ float dots_s[4][P2 * kCorrLd];
+  __shared__ float4 pix_s[4][P2];  // window origin (x, y) as integers, fractional position
+  const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int e = blockIdx.x * 4 + wv;
+  if (e >= n_edges) return;  // whole wavefront; no workgroup barrier below
+  const int k = kk[e], fj = jj[e];
+  float* out = corr + (size_t)e * (P2 * G2);
+  if (k < 0 || k >= n_patches || fj < 0 || fj >= n_maps) {
+    for (int o = lane; o < P2 * G2; o += 64) out[o] = 0.f;
+    if (lane == 0) report_device_error(dev_err, host_err, kErrInput);
+    return;
+  }
+  float* dots = dots_s[wv];
+  float4* pixs = pix_s[wv];
+  const int r = lane & 15, q = lane >> 4;
+  const bool has = r < P2;
+  float4 g[NS];
+  {
+    const float4* gp = reinterpret_cast<const float4*>(gmap + ((size_t)k * P2 + (has ? r : 0)) * D) + q;
+#pragma unroll
+    for (int s = 0; s < NS; ++s) g[s] = has ? gp[4 * s] : make_float4(0.f, 0.f, 0.f, 0.f);
+  }
+  // pixel r's window: 8 x 8 map pixels from (floor(x) - 3, floor(y) - 3);
+  // points far outside or not finite leave it outside the map
+  int xl = 1 << 30, xh = -(1 << 30), yl = 1 << 30, yh = -(1 << 30);
+  if (has) {
+    const float2 xy = reinterpret_cast<const float2*>(coords)[(size_t)e * P2 + r];
+    const float xf = floorf(xy.x), yf = floorf(xy.y);
+    const bool finite = fabsf(xy.x) < 1e9f && fabsf(xy.y) < 1e9f;
+    const int wx0 = finite ? (int)xf - kCorrR : -(1 << 30), wy0 = finite ? (int)yf - kCorrR : -(1 << 30);
+    if (lane < P2) pixs[r] = make_float4(__int_as_float(wx0), __int_as_float(wy0), xy.x - xf, xy.y - yf);
+    const int a0 = max(wx0, 0), a1 = min(wx0 + kCorrGrid + 1, W), b0 = max(wy0, 0), b1 = min(wy0 + kCorrGrid + 1, H);
+    if (a0 < a1 && b0 < b1) {
+      xl = a0;
+      xh = a1;
+      yl = b0;
+      yh = b1;
+    }
+  }
+  int ux0 = xl, ux1 = xh, uy0 = yl, uy1 = yh;
+#pragma unroll
+  for (int h = 1; h < 16; h <<= 1) {
+    ux0 = min(ux0, __shfl_xor(ux0, h));
+    ux1 = max(ux1, __shfl_xor(ux1, h));
+    uy0 = min(uy0, __shfl_xor(uy0, h));
+    uy1 = max(uy1, __shfl_xor(uy1, h));
+  }
+  const float* fm = fmaps + (size_t)fj * H * W * D + 4 * q;
+  // an empty union (every window outside) has no pixels, and dots stays unread
+  const bool one = ux1 <= ux0 || (long long)(ux1 - ux0) * (uy1 - uy0) <= kCorrUnion;
+  const int n_group = one ? 1 : P2;
+  for (int gi = 0; gi < n_group; ++gi) {
+    // uniform over the wavefront
+    const int x0 = __builtin_amdgcn_readfirstlane(one ? ux0 : __shfl(xl, gi));
+    const int x1 = __builtin_amdgcn_readfirstlane(one ? ux1 : __shfl(xh, gi));
+    const int y0 = __builtin_amdgcn_readfirstlane(one ? uy0 : __shfl(yl, gi));
+    const int y1 = __builtin_amdgcn_readfirstlane(one ? uy1 : __shfl(yh, gi));
+    const int w = x1 - x0, n = x1 > x0 ? w * (y1 - y0) : 0;
+    const float rw = 1.f / (float)max(w, 1);
+    // pixel t of the union (row-major): t < 256, so the quotient is exact
+    auto pixel = [&](int t) {
+      const int tc = min(t, n - 1);
+      const int y = (int)(((float)tc + 0.5f) * rw), x = tc - y * w;
+      return reinterpret_cast<const float4*>(fm + ((size_t)(y0 + y) * W + (x0 + x)) * D);
+    };
+    if (n > 0) {
+      float4 f[NS];
+      const float4* fp = pixel(r);
+#pragma unroll
+      for (int s = 0; s < NS; ++s) f[s] = fp[4 * s];
+      for (int t0 = 0; t0 < n; t0 += 16) {
+        // the next 16 pixels load while this tile's products run (the last
+        // tile reloads its own last pixel)
+        float4 nf[NS];
+        const float4* np = pixel(t0 + 16 + r);
+#pragma unroll
+        for (int s = 0; s < NS; ++s) nf[s] = np[4 * s];
+        // every product step starts from zero and the steps are summed as a
+        // binary tree over the channels, like the sum over lanes that this
+        // replaces (one chain of 32 steps had 1.7 times its error)
+        const floatx4_t acc = corr_tree<NS>(g, f);
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          const int row = Mfma<float>::row(lane, v);
+          if (row < P2) dots[row * kCorrLd + t0 + r] = acc[v];
+        }
+#pragma unroll
+        for (int s = 0; s < NS; ++s) f[s] = nf[s];
+      }
+    }
+    // the wavefront's own LDS writes, in order: only the compiler must not
+    // move the reads above them
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    const int o0 = one ? 0 : gi * G2, o1 = one ? P2 * G2 : o0 + G2;
+    for (int o = o0 + lane; o < o1; o += 64) {
+      const int px = o / G2, ab = o - px * G2, a = ab / kCorrGrid, b = ab - a * kCorrGrid;
+      const float4 pp = pixs[px];
+      const int xx = __float_as_int(pp.x) + a, yy = __float_as_int(pp.y) + b;
+      const bool in0 = xx >= 0 && xx < W, in1 = xx + 1 >= 0 && xx + 1 < W;
+      const bool jn0 = yy >= 0 && yy < H, jn1 = yy + 1 >= 0 && yy + 1 < H;
+      const float* d = dots + px * kCorrLd + (yy - y0) * w + (xx - x0);
+      const float d00 = in0 && jn0 ? d[0] : 0.f, d01 = in1 && jn0 ? d[1] : 0.f;
+      const float d10 = in0 && jn1 ? d[w] : 0.f, d11 = in1 && jn1 ? d[w + 1] : 0.f;
+      const float fx = pp.z, fy = pp.w;
+      out[o] = (1.f - fx) * (1.f - fy) * d00 + fx * (1.f - fy) * d01 + (1.f - fx) * fy * d10 + fx * fy * d11;
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+  }
+}
+
 hipError_t launch_patch_correlation(int n_edges, int p, int dim, const float* gmap, int n_patches, const float* fmaps,
                                     int n_maps, int H, int W, const int* kk, const int* jj, const float* coords,
                                     float* corr, int* dev_err, int* host_err, hipStream_t st) {
   const int p2 = p * p;
   const long long items = (long long)n_edges * p2;
   if (items == 0) return hipSuccess;
+  // 3 x 3 patches whose features and maps can be read as 16-byte vectors (the
+  // rows are: dim is a multiple of 64).  Other patch sizes would leave more of
+  // the 16 rows empty (1 x 1) or need several row tiles, and keep one
+  // wavefront per patch pixel.
+  const bool aligned = (((uintptr_t)gmap | (uintptr_t)fmaps) & 15) == 0 && ((uintptr_t)coords & 7) == 0;
+  if (p == 3 && aligned) {
+    const int grid3 = (n_edges + 3) / 4;
+    switch (dim / 64) {
+#define DPVBA_CORR3_CASE(V)                                                                                        \
+  case V:                                                                                                          \
+    hipLaunchKernelGGL(patch_corr3_kernel<V>, dim3(grid3), dim3(256), 0, st, n_edges, gmap, n_patches, fmaps,      \
+                       n_maps, H, W, kk, jj, coords, corr, dev_err, host_err);                                     \
+    break;
+      DPVBA_CORR3_CASE(1)
+      DPVBA_CORR3_CASE(2)
+      DPVBA_CORR3_CASE(3)
+      DPVBA_CORR3_CASE(4)
+#undef DPVBA_CORR3_CASE
+      default:
+        return hipErrorInvalidValue;
+    }
+    return hipGetLastError();
+  }
   const int grid = (int)((items + 3) / 4);
   switch (dim / 64) {
 #define DPVBA_CORR_CASE(V)                                                                                         \
