@@ -193,8 +193,9 @@ dpvba_status dpvba_analyze(dpvba_ctx* ctx, const dpvba_graph* g, void* stream);
  * keep_order: 0 lets the analysis factor a reduced system of more than 252
  * unknowns in a reverse Cuthill-McKee order of the free poses (a symmetric
  * permutation: the same solution, a smaller envelope of fill when loop
- * closures couple distant keyframes; kept only if it shrinks the envelope),
- * 1 keeps the poses' own order.  Results are reported in the poses' order
+ * closures couple distant keyframes; kept only if it shrinks the envelope)
+ * and eliminate independent parts of it concurrently, 1 keeps the poses' own
+ * order.  Results are reported in the poses' order
  * either way.                                                             */
 typedef struct {
   int32_t tile_patches_fp32;
@@ -227,11 +228,12 @@ typedef struct {
 dpvba_status dpvba_get_analysis_info(const dpvba_ctx* ctx, int32_t precision,
                                      dpvba_analysis_info* info);
 
-/* Order of the free poses in the factored reduced system (host): block row
- * p of the Cholesky factor is free pose order[p] (0-based among the free
- * poses; pose n_fixed + order[p] of the graph).  The identity when the
- * analysis kept the poses' own order.  Envelope fill (DPV-SLAM Appendix A:
- * the Cholesky of the pose block is the solve's cost) follows this order.
+/* Order of the free poses in which the large reduced system is banded
+ * (host): place p is free pose order[p] (0-based among the free poses; pose
+ * n_fixed + order[p] of the graph).  The identity when the analysis kept the
+ * poses' own order.  The factor (DPV-SLAM Appendix A: the Cholesky of the
+ * pose block is the solve's cost) starts from this order and eliminates parts
+ * of it that do not depend on each other at the same time.
  *   order  [n] int32 (written), n = n_free of the analysis.
  * EINVAL for a NULL order or a different n, ESTATE before an analysis.    */
 dpvba_status dpvba_get_system_order(const dpvba_ctx* ctx, int32_t* order, int32_t n);

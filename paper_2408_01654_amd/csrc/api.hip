@@ -15,8 +15,8 @@
 #include <vector>
 
 #include "dpvba.h"
-#include "factor_plan.h"
 #include "layout.h"
+#include "sparse.h"
 #include "tileargs.h"
 
 namespace dpvba {
@@ -31,7 +31,8 @@ hipError_t launch_tile_finalize(const TileInfo* tiles, int n_tiles, int lds_byte
                                 const T* poses_final, T* poses_out, int n_frames, hipStream_t st);
 template <typename T>
 hipError_t launch_retract_copy(const T* poses_cur, T* poses_next, T* dx, int n_fixed, int n_frames,
-                               const int* status, hipStream_t st, const T* dx_sys = nullptr, const int* pos = nullptr);
+                               const int* status, hipStream_t st, const T* dx_sys = nullptr,
+                               const int* row0 = nullptr);
 template <typename T>
 int small_solve_grid(int lds_bytes);
 template <typename T>
@@ -41,10 +42,12 @@ hipError_t launch_pgo_init(const double* poses, int n, double* sims, const doubl
                            hipStream_t st);
 hipError_t launch_pgo_linearise(const double* sims, const double* C, const int* ea, const int* eb, int n_edges,
                                 double* r, double* J, double* cost, hipStream_t st);
-hipError_t launch_pgo_normal(const double* J, const double* r, const int* blk_pq, const int* blk_off,
-                             const int* blk_src, int n_blocks, const int* pose_off, const int* pose_src, int nf,
-                             double lambda, double lam_diag, double* H, double* d0, double* rhs, hipStream_t st);
-hipError_t launch_pgo_retract(double* sims, int n, int n_fixed, const double* dx, const int* status, hipStream_t st);
+hipError_t launch_pgo_normal(const double* J, const double* r, const int2* dst, const int* blk_off,
+                             const int* blk_src, int n_blocks, int ld, const int* pose_off, const int* pose_src,
+                             int nf, const int* row0, double lambda, double lam_diag, double* H, double* d0,
+                             double* rhs, hipStream_t st);
+hipError_t launch_pgo_retract(double* sims, int n, int n_fixed, const double* dx, const int* row0, const int* status,
+                              hipStream_t st);
 hipError_t launch_pgo_apply(const double* sims, int n, const int* patch_off, float* poses, float* inv_depth,
                             hipStream_t st);
 template <typename T>
@@ -55,22 +58,13 @@ hipError_t launch_patch_correlation(int n_edges, int p, int dim, const float* gm
 hipError_t launch_proximity_edges(const float* poses, int n, const int* patch_off, int first_recent, int min_gap,
                                   float r2, int max_t, int* counts, int* targets, long long* edge_off, int* ii,
                                   int* jj, int* kk, long long max_edges, hipStream_t st);
-template <typename T>
-hipError_t launch_gather(const T* part_S, const T* part_vec, const int* s_off, const int* s_src,
-                         const int* v_off, const int2* v_src, int n_free, T* S, T* rhs, T* dB, T lambda,
-                         T lam_diag, int mirror, T* diag_out, hipStream_t st, const int* pos);
-template <typename T>
-hipError_t launch_gather_env(const T* part_S, const T* part_vec, const int* s_off, const int* s_src,
-                             const int* v_off, const int2* v_src, int n_free, const int4* env, int n_env, T* S, T* rhs,
-                             T* dB, T lambda, T lam_diag, T* diag_out, hipStream_t st, const int* pos);
 template <typename TP, typename T>
-hipError_t launch_gather_env_as(const TP* part_S, const TP* part_vec, const int* s_off, const int* s_src,
-                                const int* v_off, const int2* v_src, int n_free, const int4* env, int n_env, T* S,
-                                T* rhs, T* dB, T lambda, T lam_diag, T* diag_out, hipStream_t st, const int* pos,
-                                int mirror);
-template <typename T>
-hipError_t launch_permute_blocks(const T* src, T* dst, const int* perm, int n_blk, int bw, int to_system,
-                                 hipStream_t st);
+hipError_t launch_gather_vec(const TP* part_vec, const int* v_off, const int2* v_src, int n_free, T* rhs, T* dB,
+                             const int* row0, hipStream_t st);
+template <typename TP, typename T>
+hipError_t launch_gather_as(const TP* part_S, const TP* part_vec, const int* s_off, const int* s_src,
+                            const int* v_off, const int2* v_src, int n_free, T* S, T* rhs, T* dB, T lambda,
+                            T lam_diag, int mirror, T* diag_out, hipStream_t st);
 template <typename T, typename P>
 hipError_t launch_edge_cost(const P* poses, const P* inv_depth, const float* patches, int p, const int* ii,
                             const int* jj, const int* kk, const float* target, const float* weight,
@@ -81,34 +75,18 @@ hipError_t launch_reproject(const float* poses, const float* inv_depth, const fl
                             const int* ii, const int* jj, const int* kk, int n_edges, float fx, float fy,
                             float cx, float cy, float z_min, float* coords, uint8_t* valid, hipStream_t st);
 template <typename T>
-hipError_t launch_chol_solve(T* S, const T* rhs, int n, T* dx, T* work_y, T* Linv_all, const T* d0, int* status,
-                             unsigned int* min_bits, int* flags, int epoch, int* err, int* host_err, hipStream_t st,
-                             bool cooperative = false, const PanelPlan* plan = nullptr);
+hipError_t launch_small_chol(const T* S, const T* rhs, int n, T* dx, int* status, unsigned int* min_bits,
+                             hipStream_t st);
 hipError_t launch_report_init(int* status, unsigned int* min_bits, int n, hipStream_t st, int* err_clear = nullptr);
-template <typename TP, typename T>
-hipError_t launch_gather_as(const TP* part_S, const TP* part_vec, const int* s_off, const int* s_src,
-                            const int* v_off, const int2* v_src, int n_free, T* S, T* rhs, T* dB, T lambda,
-                            T lam_diag, int mirror, T* diag_out, hipStream_t st, const int* pos);
-template <typename T>
-hipError_t launch_chol_factor(T* S, int n, int nrows, T* Linv_all, const T* d0, int* status, unsigned int* min_bits,
-                              hipStream_t st, const PanelPlan* plan);
-template <typename T>
-hipError_t launch_chol_apply(const T* L, int n, const T* Linv_all, const T* rhs, T* x, T* work_y, int* flags,
-                             int epoch, int* err, int* host_err, hipStream_t st, int backward_only = 0,
-                             bool cooperative = false, const PanelPlan* plan = nullptr, const int* skip = nullptr);
 // mixed-precision helpers (mixed.hip)
 template <typename Ti, typename To>
 hipError_t launch_convert(const Ti* src, To* dst, long long n, hipStream_t st);
-hipError_t launch_lower_to_f32(const double* S64, float* S32, int n, hipStream_t st,
-                               const PanelPlan* env = nullptr);
-hipError_t launch_residual64(const double* S, const double* s, const double* x, int n, double* r,
-                             unsigned long long* maxes, hipStream_t st, const PanelPlan* env = nullptr);
 hipError_t launch_accumulate(double* x, const float* c, int n, hipStream_t st, const int* skip = nullptr);
 hipError_t launch_refine_check(const unsigned long long* maxes, double tol, int* skip, hipStream_t st);
 hipError_t launch_refine_decide(const unsigned long long* maxes, const int* status32, double tol, int force,
                                 double* resid_out, int* fallback_out, int* host_flag, hipStream_t st);
-hipError_t launch_step_to_f32(const double* x, float* dx, int n, const int* fallback, const int* status64,
-                              int* status, hipStream_t st);
+hipError_t launch_step_to_f32(const double* x, const int* row0, float* dx, int n, const int* fallback,
+                              const int* status64, int* status, hipStream_t st);
 // batch kernels (batch.hip)
 template <typename TS>
 struct BatchArgs {
@@ -291,67 +269,109 @@ static int writeback_lds_bytes(const Tiling& tl, int tsize) {
 
 }  // namespace
 
-// Host side of a factor plan (factor_plan.h) and its device lists.
+// An elimination plan (blockplan.h) and its device lists.
 struct PlanStore {
-  std::vector<int32_t> reach, blocks_off;
-  DevBuf blocks, chain_lo, chain_hi, fq_dev, reach_dev;
-  PanelPlan plan{};
-  int n = 0;  // the system size the plan is for
+  BlockPlan h;
+  DevBuf row0, size, colptr, rowidx, level, tasks, children, updates, srcs, by_level, rptr, rlist, nptr, nlist,
+      pair_off, pairs;
+  DevBuf* bufs[16] = {&row0, &size, &colptr, &rowidx, &level, &tasks, &children, &updates, &srcs, &by_level, &rptr,
+                      &rlist, &nptr, &nlist, &pair_off, &pairs};
+  SparsePlan plan{};
+  bool valid = false;
 };
 
-// Factor plan of an n-row system of pose blocks of width bw whose block row
-// P couples first with block column fq[P] (<= P): per 64-column panel k the
-// reach and the 64-row blocks below the panel's diagonal block that hold a
-// row whose envelope starts in or before the panel (block 0 always listed:
-// the trailing update runs its look-ahead there).
-static hipError_t build_plan(const std::vector<int32_t>& fq, int bw, int n, PlanStore& ps, hipStream_t st) {
-  const int nb = (int)fq.size(), np = (n + 63) / 64;
-  std::vector<int32_t> last(nb, -1);
-  for (int Pp = 0; Pp < nb; ++Pp) last[fq[Pp]] = std::max(last[fq[Pp]], Pp);
-  for (int Qq = 1; Qq < nb; ++Qq) last[Qq] = std::max(last[Qq], last[Qq - 1]);
-  std::vector<int32_t> reach(np, n), boff{0}, bl;
-  for (int k = 0; k < np; ++k) {
-    const int qmax = std::min(64 * k + 63, n - 1) / bw;
-    reach[k] = std::min(n, bw * (std::max(last[qmax], qmax) + 1));
-    const int t0 = 64 * (k + 1);
-    auto active = [&](int r0, int r1) {  // any row of [r0, r1) (clipped to n)
-      for (int Pp = r0 / bw; Pp * bw < std::min(r1, n); ++Pp)
-        if (fq[Pp] <= qmax) return true;
-      return false;
-    };
-    for (int B = 0; t0 + 64 * B < n; ++B)
-      if (B == 0 || active(t0 + 64 * B, t0 + 64 * B + 64)) bl.push_back(B);
-    boff.push_back((int32_t)bl.size());
-  }
-  if (bl.empty()) bl.push_back(0);
-  // triangular-solve ranges per pair of 64-row blocks: block I's rows start
-  // at column block fcb[I] (the envelope), and the rows that reach block
-  // k's columns end at reach[k] (non-decreasing in k)
-  std::vector<int32_t> fcb(np);
-  for (int I = 0; I < np; ++I) {
-    int lo = I;
-    for (int Pp = (64 * I) / bw; Pp * bw < std::min(64 * I + 64, n); ++Pp) lo = std::min(lo, (bw * fq[Pp]) / 64);
-    fcb[I] = lo;
-  }
-  const int npair = (np + 1) / 2;
-  std::vector<int32_t> plo(npair), phi(npair);
-  for (int Q = 0; Q < npair; ++Q) {
-    const int I0 = 2 * Q, I1 = std::min(2 * Q + 1, np - 1);
-    plo[Q] = std::min(fcb[I0], fcb[I1]) / 2;
-    phi[Q] = std::max(Q, std::min(npair - 1, (reach[I1] - 1) / 128));
-  }
+// A 6 x 6 block of the reduced system: free poses P >= Q (their own order).
+struct PosePair {
+  int32_t P, Q;
+};
+
+// Uploads the lists of the plan ps.h; with pairs (a block-sparse reduced
+// system) also where each pose pair is gathered to and the original blocks
+// by block row.
+static hipError_t upload_plan(PlanStore& ps, const std::vector<PosePair>* pairs, hipStream_t st) {
+  const BlockPlan& h = ps.h;
   hipError_t e;
-  if ((e = upload(ps.chain_lo, plo, st)) != hipSuccess) return e;
-  if ((e = upload(ps.chain_hi, phi, st)) != hipSuccess) return e;
-  if ((e = upload(ps.fq_dev, fq, st)) != hipSuccess) return e;
-  if ((e = upload(ps.reach_dev, reach, st)) != hipSuccess) return e;
-  if ((e = upload(ps.blocks, bl, st)) != hipSuccess) return e;
-  ps.reach = reach;
-  ps.blocks_off = boff;
-  ps.plan = PanelPlan{ps.reach.data(),          ps.blocks_off.data(),     (const int*)ps.blocks.p,
-                      (const int*)ps.chain_lo.p, (const int*)ps.chain_hi.p, (const int*)ps.fq_dev.p,
-                      (const int*)ps.reach_dev.p, bw};
-  ps.n = n;
+  ps.valid = false;
+  if ((e = upload(ps.row0, h.row0, st)) != hipSuccess) return e;
+  if ((e = upload(ps.size, h.size, st)) != hipSuccess) return e;
+  if ((e = upload(ps.colptr, h.colptr, st)) != hipSuccess) return e;
+  if ((e = upload(ps.rowidx, h.rowidx, st)) != hipSuccess) return e;
+  if ((e = upload(ps.level, h.level, st)) != hipSuccess) return e;
+  if ((e = upload(ps.tasks, h.tasks, st)) != hipSuccess) return e;
+  if ((e = upload(ps.children, h.children, st)) != hipSuccess) return e;
+  if ((e = upload(ps.updates, h.updates, st)) != hipSuccess) return e;
+  if ((e = upload(ps.srcs, h.srcs, st)) != hipSuccess) return e;
+  if ((e = upload(ps.by_level, h.by_level, st)) != hipSuccess) return e;
+  if ((e = upload(ps.rptr, h.rptr, st)) != hipSuccess) return e;
+  if ((e = upload(ps.rlist, h.rlist, st)) != hipSuccess) return e;
+  if (pairs) {
+    struct Entry { int32_t id, x, y; };
+    std::vector<Entry> v;
+    v.reserve(pairs->size());
+    for (const PosePair& q : *pairs) {
+      // the pose whose rows come later gives the block row
+      const bool swap = h.row0[q.P] < h.row0[q.Q];
+      const int a = swap ? q.Q : q.P, b = swap ? q.P : q.Q;
+      const int I = h.row0[a] / kBlk, K = h.row0[b] / kBlk;
+      const int y = (h.row0[a] % kBlk) | (h.row0[b] % kBlk) << 8 | (swap ? 1 << 16 : 0) | (a == b ? 1 << 17 : 0);
+      v.push_back({h.find(I, K), (int32_t)((long long)q.P * (q.P + 1) / 2 + q.Q), y});
+    }
+    std::vector<int32_t> off(h.n_blocks() + 1, 0), flat(2 * v.size()), nptr(h.nb + 1, 0);
+    for (const Entry& t : v) {
+      if (t.id < 0) return hipErrorInvalidValue;  // a coupled pair is always a block of the plan
+      off[t.id + 1]++;
+    }
+    for (int q = 0; q < h.n_blocks(); ++q) off[q + 1] += off[q];
+    std::vector<int32_t> cur(off.begin(), off.end() - 1);
+    for (const Entry& t : v) {
+      flat[2 * cur[t.id]] = t.x;
+      flat[2 * cur[t.id]++ + 1] = t.y;
+    }
+    std::vector<std::vector<int32_t>> rows(h.nb);
+    for (int K = 0; K < h.nb; ++K)
+      for (int id = h.colptr[K]; id < h.colptr[K + 1]; ++id) {
+        if (off[id + 1] == off[id]) continue;
+        const int I = h.rowidx[id];
+        rows[I].insert(rows[I].end(), {K, 2 * id});
+        if (I != K) rows[K].insert(rows[K].end(), {I, 2 * id + 1});
+      }
+    std::vector<int32_t> nlist;
+    for (int I = 0; I < h.nb; ++I) {
+      nlist.insert(nlist.end(), rows[I].begin(), rows[I].end());
+      nptr[I + 1] = (int32_t)(nlist.size() / 2);
+    }
+    if ((e = upload(ps.pair_off, off, st)) != hipSuccess) return e;
+    if ((e = upload(ps.pairs, flat, st)) != hipSuccess) return e;
+    if ((e = upload(ps.nptr, nptr, st)) != hipSuccess) return e;
+    if ((e = upload(ps.nlist, nlist, st)) != hipSuccess) return e;
+  }
+  SparsePlan& p = ps.plan;
+  p.bw = h.bw;
+  p.n_pose = h.n_pose;
+  p.nb = h.nb;
+  p.n_level = h.n_level;
+  p.n_blocks = h.n_blocks();
+  p.row0 = (const int*)ps.row0.p;
+  p.size = (const int*)ps.size.p;
+  p.colptr = (const int*)ps.colptr.p;
+  p.rowidx = (const int*)ps.rowidx.p;
+  p.level = (const int*)ps.level.p;
+  p.tasks = (const LevelTask*)ps.tasks.p;
+  p.children = (const LevelChild*)ps.children.p;
+  p.updates = (const UpdateTask*)ps.updates.p;
+  p.srcs = (const UpdateSrc*)ps.srcs.p;
+  p.by_level = (const int*)ps.by_level.p;
+  p.rptr = (const int*)ps.rptr.p;
+  p.rlist = (const int2*)ps.rlist.p;
+  p.nptr = (const int*)ps.nptr.p;
+  p.nlist = (const int2*)ps.nlist.p;
+  p.pair_off = (const int*)ps.pair_off.p;
+  p.pairs = (const int2*)ps.pairs.p;
+  p.task_off = h.task_off.data();
+  p.upd_off = h.upd_off.data();
+  p.implicit_col = h.implicit_col.data();
+  p.colptr_h = h.colptr.data();
+  ps.valid = true;
   return hipSuccess;
 }
 
@@ -371,25 +391,16 @@ struct dpvba_ctx {
   // launch parity p at [4 p], large path [8], batch [12]); host_err:
   // host-visible sticky failure words (pinned, mapped), host_err_dev its
   // device address
-  DevBuf S, rhs, dB, d0, dx, wb, wy, Linv, edge_part, ticket, dev_err;
+  DevBuf S, rhs, dB, d0, dx, wy, Linv, edge_part, ticket, dev_err;
   int* host_err = nullptr;
   int* host_err_dev = nullptr;
   long long small_launches = 0;
-  DevBuf chain_flags;  // the triangular chain's value-and-epoch words (chain_words_bytes)
-  // sparsity plan of the float32 factor (factor_plan.h): per 64-column panel
-  // its reach and the 64-row blocks below its diagonal block that hold a row
-  // that can be non-zero in it
-  PlanStore ba_plan;  // the analysed graph's reduced system
-  // system order of the large solves: block p of the factored system is free
-  // pose sys_perm[p] (sys_pos its inverse); empty: the poses' own order
+  DevBuf chain_flags;  // the triangular solves' value-and-epoch words (sparse_words_bytes)
+  PlanStore ba_plan;   // the analysed graph's reduced system (beyond the one-workgroup solves)
+  // reverse Cuthill-McKee order of the free poses (empty: their own order),
+  // which the elimination plan starts from
   std::vector<int32_t> sys_perm_h;
-  DevBuf sys_perm, sys_pos, sys_x, sys_b;
-  // blocks of the envelope in the system order (int4: block row, block
-  // column, the poses' lower block, transposed) and the element size S was
-  // last zeroed for outside the envelope (0: not zeroed)
-  DevBuf env_blk;
-  int n_env = 0, s_env_elem = 0;
-  bool s32_zeroed = false;  // S32 zero outside the envelope (mixed path)
+  DevBuf sys_x;     // a solve's step in the plan's padded rows
   PlanStore pg_plan;  // the last pose graph's normal equations
   DevBuf one_inst;     // the analysed problem as a one-problem batch (small mixed solves)
   int chain_epoch = 0;
@@ -415,8 +426,8 @@ struct dpvba_ctx {
   } bt;
   // adjoint workspace
   // Sim(3) pose-graph optimisation workspace
-  DevBuf pg_C, pg_ea, pg_eb, pg_r, pg_J, pg_H, pg_rhs, pg_dx, pg_d0, pg_wy, pg_Linv, pg_flags, pg_status, pg_mb,
-      pg_cost, pg_blk_pq, pg_blk_off, pg_blk_src, pg_pose_off, pg_pose_src, pg_perm, pg_xs;
+  DevBuf pg_C, pg_ea, pg_eb, pg_r, pg_J, pg_H, pg_rhs, pg_dx, pg_d0, pg_Linv, pg_flags, pg_status, pg_mb,
+      pg_cost, pg_blk_pq, pg_blk_off, pg_blk_src, pg_pose_off, pg_pose_src;
   int pg_epoch = 0;
   DevBuf bw_poses, bw_depth, bw_dx, bw_pbar, bw_dbar, bw_dxbar, bw_rhs, bw_up, bw_ud, bw_dd, bw_edge, bw_status,
       bw_minbits;
@@ -453,49 +464,14 @@ struct TraceScope {
   }
 };
 
-// Epoch of the next chained triangular solve (never 0, the flags' initial value).
-// The factor plan of the analysed graph for a reduced system of n rows (null
-// when it was not built for this n: the factor is then dense).
-static const PanelPlan* reach_of(const dpvba_ctx* c, int n) {
-  return c->ba_plan.n == n && n > 0 ? &c->ba_plan.plan : nullptr;
-}
-
-// Bytes of the triangular chain's value words for nblk 64-row blocks: two
-// passes, two 64-bit words per row (float64; float32 uses one).
-static size_t chain_words_bytes(size_t nblk) { return 2 * nblk * 64 * 2 * 8; }
-
-// The large solves of a reduced system of more than this many unknowns run
-// in the system order (the smaller ones are gathered inside their kernels).
+// The large solves of a reduced system of more than this many unknowns start
+// from the reverse Cuthill-McKee order of the poses.
 constexpr int kPermuteMinUnknowns = kBatchMaxUnknowns;
 
-// System-order permutation (device, block p = free pose perm[p]) of the
-// analysed graph's large solves, or null for the poses' own order.
-static const int* sys_perm_of(const dpvba_ctx* c) {
-  return !c->sys_perm_h.empty() && 6 * c->n_free > kPermuteMinUnknowns ? (const int*)c->sys_perm.p : nullptr;
-}
-static const int* sys_pos_of(const dpvba_ctx* c) { return sys_perm_of(c) ? (const int*)c->sys_pos.p : nullptr; }
-
-// Gather of the large path's damped reduced system into the context's S in
-// the system order: only the envelope's blocks (the rest of S zeroed once
-// per analysis and element type), or every lower block for the smaller
-// systems.
+// Whether a reduced system of n unknowns takes the block-sparse factor.
 template <typename T>
-static hipError_t gather_system(dpvba_ctx* c, const Tiling& tl, const T* part_S, const T* part_vec, T* S, T* rhs,
-                                T lambda, T lam_diag, T* d0, hipStream_t st) {
-  const int n = 6 * c->n_free;
-  if (c->n_env > 0 && n > kPermuteMinUnknowns && S == (T*)c->S.p) {
-    if (c->s_env_elem != (int)sizeof(T)) {
-      hipError_t e = launch_fill<T>(S, (long long)n * n, (T)0, st);
-      if (e != hipSuccess) return e;
-      c->s_env_elem = (int)sizeof(T);
-    }
-    return launch_gather_env<T>(part_S, part_vec, (const int*)tl.s_off.p, (const int*)tl.s_src.p,
-                                (const int*)tl.v_off.p, (const int2*)tl.v_src.p, c->n_free, (const int4*)c->env_blk.p,
-                                c->n_env, S, rhs, (T*)c->dB.p, lambda, lam_diag, d0, st, sys_pos_of(c));
-  }
-  return launch_gather<T>(part_S, part_vec, (const int*)tl.s_off.p, (const int*)tl.s_src.p, (const int*)tl.v_off.p,
-                          (const int2*)tl.v_src.p, c->n_free, S, rhs, (T*)c->dB.p, lambda, lam_diag, 0, d0, st,
-                          sys_pos_of(c));
+static bool is_sparse(int n) {
+  return n > small_solve_max_n((int)sizeof(T));
 }
 
 // Block row P of a symmetric block pattern starts at block column fq[P]
@@ -583,6 +559,7 @@ static std::vector<int32_t> rcm_order(const std::vector<std::vector<int32_t>>& a
   return order;
 }
 
+// Epoch of the next triangular solve (never 0, the words' initial value).
 static int next_epoch(dpvba_ctx* c) {
   c->chain_epoch = c->chain_epoch >= 0x3fffffff ? 1 : c->chain_epoch + 1;
   return c->chain_epoch;
@@ -629,7 +606,7 @@ dpvba_status dpvba_get_system_order(const dpvba_ctx* c, int32_t* order, int32_t 
   if (!c || !order) return DPVBA_EINVAL;
   if (!c->analysed) return DPVBA_ESTATE;
   if (n != c->n_free) return DPVBA_EINVAL;
-  const bool perm = sys_perm_of(c) != nullptr;
+  const bool perm = !c->sys_perm_h.empty();
   for (int p = 0; p < n; ++p) order[p] = perm ? c->sys_perm_h[p] : p;
   return DPVBA_OK;
 }
@@ -749,22 +726,22 @@ void dpvba_destroy(dpvba_ctx* c) {
   (void)hipSetDevice(c->device);
   DevBuf* bufs[] = {&c->part_S, &c->part_vec, &c->part_cost, &c->part_invalid, &c->U_s, &c->pscale_s,
                     &c->depth_s, &c->xh_s, &c->poses_a, &c->poses_b, &c->S, &c->rhs, &c->dB, &c->d0, &c->dx,
-                    &c->wb, &c->wy, &c->Linv, &c->edge_part, &c->ticket, &c->dev_err, &c->status, &c->min_bits, &c->devrep,
-                    &c->chain_flags, &c->one_inst, &c->ba_plan.blocks, &c->pg_plan.blocks,
-                    &c->ba_plan.chain_lo, &c->ba_plan.chain_hi, &c->pg_plan.chain_lo,
-                    &c->pg_plan.chain_hi, &c->ba_plan.fq_dev, &c->ba_plan.reach_dev, &c->pg_plan.fq_dev,
-                    &c->pg_plan.reach_dev, &c->sys_perm, &c->sys_pos, &c->sys_x, &c->sys_b, &c->env_blk,
+                    &c->wy, &c->Linv, &c->edge_part, &c->ticket, &c->dev_err, &c->status, &c->min_bits, &c->devrep,
+                    &c->chain_flags, &c->one_inst, &c->sys_x,
                     &c->pcount, &c->pedges, &c->pose_off, &c->pose_src, &c->patch_pos, &c->bw_poses, &c->bw_depth,
                     &c->bw_dx, &c->bw_pbar, &c->bw_dbar, &c->bw_dxbar, &c->bw_rhs, &c->bw_up, &c->bw_ud, &c->bw_dd,
                     &c->bw_edge, &c->bw_status, &c->bw_minbits, &c->S32, &c->x64, &c->r64, &c->rhs32, &c->c32,
                     &c->d0_32, &c->mx_max, &c->mx_resid, &c->mx_fb, &c->mx_flag, &c->pg_C, &c->pg_ea, &c->pg_eb,
-                    &c->pg_r, &c->pg_J, &c->pg_H, &c->pg_rhs, &c->pg_dx, &c->pg_d0, &c->pg_wy, &c->pg_Linv,
+                    &c->pg_r, &c->pg_J, &c->pg_H, &c->pg_rhs, &c->pg_dx, &c->pg_d0, &c->pg_Linv,
                     &c->pg_flags, &c->pg_status, &c->pg_mb, &c->pg_cost, &c->pg_blk_pq, &c->pg_blk_off,
-                    &c->pg_blk_src, &c->pg_pose_off, &c->pg_pose_src, &c->pg_perm, &c->pg_xs};
+                    &c->pg_blk_src, &c->pg_pose_off, &c->pg_pose_src};
   for (DevBuf* b : bufs)
     if (b->p) (void)hipFree(b->p);
   for (Tiling& t : c->tl)
     for (DevBuf* b : t.bufs)
+      if (b->p) (void)hipFree(b->p);
+  for (PlanStore* ps : {&c->ba_plan, &c->pg_plan})
+    for (DevBuf* b : ps->bufs)
       if (b->p) (void)hipFree(b->p);
   for (hipEvent_t e : c->ev) (void)hipEventDestroy(e);
   if (c->aux_start) (void)hipEventDestroy(c->aux_start);
@@ -1072,53 +1049,37 @@ dpvba_status dpvba_analyze_ex(dpvba_ctx* c, const dpvba_graph* g, const dpvba_tu
   HIP_TRY(upload_tiling(c->tl[0], H32, st));
   HIP_TRY(upload_tiling(c->tl[1], H64, st));
   {
-    // envelope of the reduced system: block row P starts at its first
-    // coupled block column fq[P] (a tile contributes to (P, Q)); Cholesky
-    // fill stays between that column and the diagonal, so the rows that can
-    // be non-zero in block column Q end at the last P with fq[P] <= Q
-    std::vector<std::vector<int32_t>> adj(n_free);
-    for (int Pp = 0; Pp < n_free; ++Pp) {
-      const long long base = (long long)Pp * (Pp + 1) / 2;
-      for (int Qq = 0; Qq < Pp; ++Qq)
-        if (H32.s_off[base + Qq + 1] > H32.s_off[base + Qq]) {
-          adj[Pp].push_back(Qq);
-          adj[Qq].push_back(Pp);
-        }
-    }
-    std::vector<int32_t> ident(n_free), pos(n_free);
-    for (int Pp = 0; Pp < n_free; ++Pp) ident[Pp] = Pp;
-    std::vector<int32_t> fq = first_coupled(adj, ident);
+    // coupled free poses (a tile contributes to their block), a base order,
+    // and the elimination plan of the systems that one workgroup does not solve
     c->sys_perm_h.clear();
-    if (6 * n_free > kPermuteMinUnknowns && !(tune && tune->keep_order)) {
-      // a symmetric permutation leaves the solution unchanged and can shrink
-      // the envelope (and the factor's work) by orders of magnitude when
-      // loop closures couple distant keyframes
-      const std::vector<int32_t> order = rcm_order(adj);
-      for (int p = 0; p < n_free; ++p) pos[order[p]] = p;
-      std::vector<int32_t> fq_r = first_coupled(adj, pos);
-      if (envelope_cost(fq_r) < 0.9 * envelope_cost(fq)) {
-        c->sys_perm_h = order;
-        fq = fq_r;
-        HIP_TRY(upload(c->sys_perm, order, st));
-        HIP_TRY(upload(c->sys_pos, pos, st));
+    c->ba_plan.valid = false;
+    if (6 * n_free > std::min(small_solve_max_n(4), small_solve_max_n(8))) {
+      std::vector<std::vector<int32_t>> adj(n_free);
+      std::vector<PosePair> pairs;
+      for (int Pp = 0; Pp < n_free; ++Pp) {
+        const long long base = (long long)Pp * (Pp + 1) / 2;
+        for (int Qq = 0; Qq < Pp; ++Qq)
+          if (H32.s_off[base + Qq + 1] > H32.s_off[base + Qq]) {
+            adj[Pp].push_back(Qq);
+            adj[Qq].push_back(Pp);
+            pairs.push_back({Pp, Qq});
+          }
+        pairs.push_back({Pp, Pp});
       }
-    }
-    c->ba_plan.n = 0;
-    HIP_TRY(build_plan(fq, 6, 6 * n_free, c->ba_plan, st));
-    c->n_env = 0;
-    c->s_env_elem = 0;
-    c->s32_zeroed = false;
-    if (6 * n_free > kPermuteMinUnknowns) {
-      std::vector<int32_t> env;
-      const bool perm = !c->sys_perm_h.empty();
-      for (int Ps = 0; Ps < n_free; ++Ps)
-        for (int Qs = fq[Ps]; Qs <= Ps; ++Qs) {
-          const int Pp = perm ? c->sys_perm_h[Ps] : Ps, Qq = perm ? c->sys_perm_h[Qs] : Qs;
-          const int a = std::max(Pp, Qq), b = std::min(Pp, Qq);
-          env.insert(env.end(), {Ps, Qs, (int32_t)((long long)a * (a + 1) / 2 + b), Pp < Qq ? 1 : 0});
-        }
-      HIP_TRY(upload(c->env_blk, env, st));
-      c->n_env = (int)(env.size() / 4);
+      const bool keep = tune && tune->keep_order;
+      std::vector<int32_t> ident(n_free), pos(n_free);
+      for (int Pp = 0; Pp < n_free; ++Pp) ident[Pp] = Pp;
+      if (6 * n_free > kPermuteMinUnknowns && !keep) {
+        // a symmetric permutation leaves the solution unchanged and can shrink
+        // the envelope (and the fill) by orders of magnitude when loop
+        // closures couple distant keyframes
+        const std::vector<int32_t> order = rcm_order(adj);
+        for (int p = 0; p < n_free; ++p) pos[order[p]] = p;
+        if (envelope_cost(first_coupled(adj, pos)) < 0.9 * envelope_cost(first_coupled(adj, ident)))
+          c->sys_perm_h = order;
+      }
+      c->ba_plan.h = build_block_plan(adj, c->sys_perm_h.empty() ? ident : c->sys_perm_h, 6, !keep);
+      HIP_TRY(upload_plan(c->ba_plan, &pairs, st));
     }
   }
   {
@@ -1152,7 +1113,9 @@ dpvba_status dpvba_analyze_ex(dpvba_ctx* c, const dpvba_graph* g, const dpvba_tu
   }
 
   const size_t n = 6 * (size_t)n_free;
-  const size_t nblk64 = (n + 63) / 64;
+  const bool sparse64 = c->ba_plan.valid, sparse32 = sparse64 && is_sparse<float>((int)n);
+  const size_t npad = sparse64 ? (size_t)kBlk * c->ba_plan.h.nb : n;  // rows of the padded vectors
+  const size_t blk_elems = sparse64 ? (size_t)c->ba_plan.h.n_blocks() * kBlk * kBlk : 0;
   auto mx = [&](long long a, long long b) { return (size_t)std::max(a, b); };
   HIP_TRY(ensure(c->part_S, std::max(H32.part_S * 4, H64.part_S * 8)));
   HIP_TRY(ensure(c->part_vec, std::max(H32.part_vec * 4, H64.part_vec * 8)));
@@ -1164,32 +1127,35 @@ dpvba_status dpvba_analyze_ex(dpvba_ctx* c, const dpvba_graph* g, const dpvba_tu
   HIP_TRY(ensure(c->xh_s, (size_t)P * 2 * 8));
   HIP_TRY(ensure(c->poses_a, (size_t)N * 7 * 8));
   HIP_TRY(ensure(c->poses_b, (size_t)N * 7 * 8));
-  HIP_TRY(ensure(c->S, (n + 1) * n * 8));  // the float32 large path appends s as row n
-  HIP_TRY(ensure(c->rhs, n * 8));
-  HIP_TRY(ensure(c->dB, n * 8));
-  HIP_TRY(ensure(c->d0, n * 8));
+  // the dense system of the one-workgroup solves, or block storage
+  HIP_TRY(ensure(c->S, std::max(n <= (size_t)kBatchMaxUnknowns ? (n + 1) * n * 8 : 0, blk_elems * 8)));
+  HIP_TRY(ensure(c->rhs, npad * 8));
+  HIP_TRY(ensure(c->dB, npad * 8));
+  HIP_TRY(ensure(c->d0, npad * 8));
   HIP_TRY(ensure(c->dx, n * 8));
-  HIP_TRY(ensure(c->wb, n * 8));
-  HIP_TRY(ensure(c->wy, n * 8));
-  HIP_TRY(ensure(c->sys_x, n * 8));
-  HIP_TRY(ensure(c->sys_b, n * 8));
-  HIP_TRY(ensure(c->Linv, nblk64 * 64 * 64 * 8));
-  // the triangular chain's value words: two passes, up to two words per row
-  if (c->chain_flags.bytes < chain_words_bytes(nblk64)) {
-    HIP_TRY(ensure(c->chain_flags, chain_words_bytes(nblk64)));
-    HIP_TRY(hipMemsetAsync(c->chain_flags.p, 0, c->chain_flags.bytes, st));
-    HIP_TRY(hipStreamSynchronize(st));
-    c->chain_epoch = 0;
+  HIP_TRY(ensure(c->wy, npad * 8));
+  HIP_TRY(ensure(c->sys_x, npad * 8));
+  if (sparse64) {
+    HIP_TRY(ensure(c->Linv, (size_t)c->ba_plan.h.nb * kBlk * kBlk * 8));
+    const size_t words = sparse_words_bytes(c->ba_plan.h.nb);
+    if (c->chain_flags.bytes < words) {
+      HIP_TRY(ensure(c->chain_flags, words));
+      HIP_TRY(hipMemsetAsync(c->chain_flags.p, 0, c->chain_flags.bytes, st));
+      HIP_TRY(hipStreamSynchronize(st));
+      c->chain_epoch = 0;
+    }
   }
   HIP_TRY(ensure(c->edge_part, ((size_t)(E + 255) / 256) * 8));
   HIP_TRY(ensure(c->status, 2 * DPVBA_MAX_ITERS * 4));  // [MAX, 2 MAX): float64 fallback solves
   HIP_TRY(ensure(c->min_bits, 2 * DPVBA_MAX_ITERS * 4));
-  HIP_TRY(ensure(c->S32, (n + 1) * n * 4));  // s appended as row n for the first solve
-  HIP_TRY(ensure(c->x64, n * 8));
-  HIP_TRY(ensure(c->r64, n * 8));
-  HIP_TRY(ensure(c->rhs32, n * 4));
-  HIP_TRY(ensure(c->c32, n * 4));
-  HIP_TRY(ensure(c->d0_32, n * 4));
+  if (sparse32) {  // mixed precision: the float32 factor and its vectors
+    HIP_TRY(ensure(c->S32, blk_elems * 4));
+    HIP_TRY(ensure(c->x64, npad * 8));
+    HIP_TRY(ensure(c->r64, npad * 8));
+    HIP_TRY(ensure(c->rhs32, npad * 4));
+    HIP_TRY(ensure(c->c32, npad * 4));
+    HIP_TRY(ensure(c->d0_32, npad * 4));
+  }
   HIP_TRY(ensure(c->mx_max, 16));
   HIP_TRY(ensure(c->mx_resid, DPVBA_MAX_ITERS * 8));
   HIP_TRY(ensure(c->mx_fb, DPVBA_MAX_ITERS * 4));
@@ -1390,9 +1356,9 @@ static hipError_t reduced_impl(dpvba_ctx* c, const dpvba_graph* g, const T* pose
                              nullptr, st);
     if (e != hipSuccess) return e;
   }
-  return launch_gather<T>((const T*)c->part_S.p, (const T*)c->part_vec.p, (const int*)tl.s_off.p,
-                          (const int*)tl.s_src.p, (const int*)tl.v_off.p, (const int2*)tl.v_src.p, c->n_free, S,
-                          rhs, (T*)c->dB.p, lambda, lam_diag, 1, (T*)c->d0.p, st, nullptr);
+  return launch_gather_as<T, T>((const T*)c->part_S.p, (const T*)c->part_vec.p, (const int*)tl.s_off.p,
+                                (const int*)tl.s_src.p, (const int*)tl.v_off.p, (const int2*)tl.v_src.p, c->n_free, S,
+                                rhs, (T*)c->dB.p, lambda, lam_diag, 1, (T*)nullptr, st);
 }
 
 // Float32 tile assembly gathered in float64 (the DPVBA_MIXED system).
@@ -1416,7 +1382,39 @@ static hipError_t reduced_mixed_impl(dpvba_ctx* c, const dpvba_graph* g, const f
   return launch_gather_as<float, double>((const float*)c->part_S.p, (const float*)c->part_vec.p,
                                          (const int*)tl.s_off.p, (const int*)tl.s_src.p, (const int*)tl.v_off.p,
                                          (const int2*)tl.v_src.p, c->n_free, S, rhs, (double*)c->dB.p,
-                                         (double)lambda, (double)lam_diag, 1, (double*)c->d0.p, st, nullptr);
+                                         (double)lambda, (double)lam_diag, 1, (double*)nullptr, st);
+}
+
+// Gathers the damped reduced system from the tiles' shares: block storage and
+// padded rows of the elimination plan, or a dense system for the
+// one-workgroup solve.
+template <typename T>
+static hipError_t gather_system(dpvba_ctx* c, const Tiling& tl, const T* part_S, const T* part_vec, T* S, T* rhs, T* d0,
+                                T lambda, T lam_diag, hipStream_t st) {
+  const int *so = (const int*)tl.s_off.p, *ss = (const int*)tl.s_src.p, *vo = (const int*)tl.v_off.p;
+  const int2* vs = (const int2*)tl.v_src.p;
+  T* dB = (T*)c->dB.p;
+  if (!is_sparse<T>(6 * c->n_free))
+    return launch_gather_as<T, T>(part_S, part_vec, so, ss, vo, vs, c->n_free, S, rhs, dB, lambda, lam_diag, 0, d0, st);
+  const SparsePlan& p = c->ba_plan.plan;
+  hipError_t e = launch_gather_vec<T, T>(part_vec, vo, vs, c->n_free, rhs, dB, p.row0, st);
+  if (e != hipSuccess) return e;
+  return launch_sparse_gather<T, T>(p, part_S, so, ss, S, dB, lambda, lam_diag, d0, rhs, nullptr, nullptr, st);
+}
+
+// Factors and solves the gathered system: the step in the plan's padded rows
+// (x, large systems; not zeroed when *status was set) or in the poses' order (x
+// = dx, the others).  rhs is overwritten by a large system.
+template <typename T>
+static hipError_t factor_solve(dpvba_ctx* c, T* S, T* rhs, const T* d0, T* x, int* status, unsigned int* mb, int* err,
+                               hipStream_t st) {
+  const int n = 6 * c->n_free;
+  if (!is_sparse<T>(n)) return launch_small_chol<T>(S, rhs, n, x, status, mb, st);
+  const SparsePlan& p = c->ba_plan.plan;
+  hipError_t e = launch_sparse_factor<T>(p, S, (T*)c->Linv.p, rhs, d0, status, mb, st);
+  if (e != hipSuccess) return e;
+  return launch_sparse_solve<T>(p, S, (const T*)c->Linv.p, nullptr, rhs, x, (unsigned long long*)c->chain_flags.p,
+                                next_epoch(c), err, c->host_err_dev, st, true, c->coop_launch);
 }
 
 template <typename T>
@@ -1433,11 +1431,7 @@ static hipError_t solve_impl(dpvba_ctx* c, const dpvba_graph* g, T* poses, T* de
   unsigned int* mb = ws.min_bits;
   T* pbuf[2] = {ws.pbuf0, ws.pbuf1};
   T* dx = ws.dx;
-  // the large iterations solve in the system order (workspaces of the
-  // context's own only)
-  const int* perm = ws_in ? nullptr : sys_perm_of(c);
-  // the float32 blocked factor takes s as row n of S: gather it there
-  T* rhs_s = !ws_in && sizeof(T) == 4 && n > small_solve_max_n(4) ? ws.S + (size_t)n * n : ws.rhs;
+  const bool sparse = is_sparse<T>(n);  // the step is then in the plan's padded rows until the retraction
   hipError_t e;
   // the call's failure word: that of the single launch's parity, else the large path's
   const int parity = (int)(c->small_launches & 1);
@@ -1495,24 +1489,18 @@ static hipError_t solve_impl(dpvba_ctx* c, const dpvba_graph* g, T* poses, T* de
       TraceScope ts(c, DPVBA_PHASE_GATHER, st);
       e = launch_report_reduce(ws.part_cost, ws.part_invalid, tl.n_tiles, &dev->cost[it], &dev->n_invalid[it], st);
       if (e == hipSuccess)
-        e = !ws_in ? gather_system<T>(c, tl, ws.part_S, ws.part_vec, ws.S, rhs_s, lambda, lam_diag, ws.d0, st)
-                   : launch_gather<T>(ws.part_S, ws.part_vec, (const int*)tl.s_off.p, (const int*)tl.s_src.p,
-                                    (const int*)tl.v_off.p, (const int2*)tl.v_src.p, c->n_free, ws.S, ws.rhs,
-                                    (T*)c->dB.p, lambda, lam_diag, 0, ws.d0, st, nullptr);
+        e = gather_system<T>(c, tl, ws.part_S, ws.part_vec, ws.S, ws.rhs, ws.d0, lambda, lam_diag, st);
     }
     if (e != hipSuccess) return e;
     {
       TraceScope ts(c, DPVBA_PHASE_FACTOR, st);
-      e = launch_chol_solve<T>(ws.S, rhs_s, n, perm ? (T*)c->sys_x.p : dx, (T*)c->wy.p, (T*)c->Linv.p, ws.d0,
-                               status + it, mb + it, (int*)c->chain_flags.p, next_epoch(c), err, c->host_err_dev, st,
-                               c->coop_launch, reach_of(c, n));
+      e = factor_solve<T>(c, ws.S, ws.rhs, ws.d0, sparse ? (T*)c->sys_x.p : dx, status + it, mb + it, err, st);
     }
     if (e != hipSuccess) return e;
     {
       TraceScope ts(c, DPVBA_PHASE_RETRACT, st);
-      // perm: the step leaves the system order here (stored into dx)
-      e = launch_retract_copy<T>(cur, next, dx, c->n_fixed, c->N, status + it, st, perm ? (const T*)c->sys_x.p : nullptr,
-                                 perm ? sys_pos_of(c) : nullptr);
+      e = launch_retract_copy<T>(cur, next, dx, c->n_fixed, c->N, status + it, st, sparse ? (const T*)c->sys_x.p : nullptr,
+                                 sparse ? c->ba_plan.plan.row0 : nullptr);
     }
     if (e != hipSuccess) return e;
   }
@@ -1597,24 +1585,13 @@ static hipError_t solve_mixed_impl(dpvba_ctx* c, const dpvba_graph* g, float* po
       e = launch_report_reduce((const double*)c->part_cost.p, (const int*)c->part_invalid.p, tl.n_tiles,
                                &dev->cost[it], &dev->n_invalid[it], st);
       if (e == hipSuccess && n > kBatchMaxUnknowns) {  // small systems are gathered by the one-problem batch
-        if (c->n_env > 0) {
-          // the envelope's blocks and their mirror images; S64 zero elsewhere
-          if (c->s_env_elem != 8) {
-            if ((e = launch_fill<double>(S64, (long long)n * n, 0.0, st)) != hipSuccess) return e;
-            c->s_env_elem = 8;
-          }
-          e = launch_gather_env_as<float, double>((const float*)c->part_S.p, (const float*)c->part_vec.p,
-                                                  (const int*)tl.s_off.p, (const int*)tl.s_src.p,
-                                                  (const int*)tl.v_off.p, (const int2*)tl.v_src.p, c->n_free,
-                                                  (const int4*)c->env_blk.p, c->n_env, S64, s64, (double*)c->dB.p,
-                                                  (double)lambda, (double)lam_diag, d064, st, sys_pos_of(c), 1);
-        } else {
-          e = launch_gather_as<float, double>((const float*)c->part_S.p, (const float*)c->part_vec.p,
-                                              (const int*)tl.s_off.p, (const int*)tl.s_src.p, (const int*)tl.v_off.p,
-                                              (const int2*)tl.v_src.p, c->n_free, S64, s64, (double*)c->dB.p,
-                                              (double)lambda, (double)lam_diag, 1, d064, st, sys_pos_of(c));
-          c->s_env_elem = 0;  // S now holds the whole float64 system
-        }
+        const SparsePlan& p = c->ba_plan.plan;
+        e = launch_gather_vec<float, double>((const float*)c->part_vec.p, (const int*)tl.v_off.p,
+                                             (const int2*)tl.v_src.p, c->n_free, s64, (double*)c->dB.p, p.row0, st);
+        if (e == hipSuccess)
+          e = launch_sparse_gather<float, double>(p, (const float*)c->part_S.p, (const int*)tl.s_off.p,
+                                                  (const int*)tl.s_src.p, S64, (const double*)c->dB.p, (double)lambda,
+                                                  (double)lam_diag, d064, s64, S32, d032, st);
       }
       if (e != hipSuccess) return e;
     }
@@ -1654,37 +1631,30 @@ static hipError_t solve_mixed_impl(dpvba_ctx* c, const dpvba_graph* g, float* po
     }
     if (n > 0) {
       TraceScope ts(c, DPVBA_PHASE_FACTOR, st);
-      const PanelPlan* env = c->n_env > 0 ? reach_of(c, n) : nullptr;  // envelope-limited conversion and residuals
-      if (env && !c->s32_zeroed) {
-        if ((e = launch_fill<float>(S32, (long long)n * n, 0.f, st)) != hipSuccess) return e;
-        c->s32_zeroed = true;
-      }
-      if ((e = launch_lower_to_f32(S64, S32, n, st, env)) != hipSuccess) return e;
-      if ((e = launch_convert<double, float>(d064, d032, n, st)) != hipSuccess) return e;
-      // s rides along as row n: the factor leaves y = L^-1 s there, so the
-      // first solve is the backward chain alone
-      float* y32 = S32 + (size_t)n * n;
-      if ((e = launch_convert<double, float>(s64, y32, n, st)) != hipSuccess) return e;
-      if ((e = launch_chol_factor<float>(S32, n, n + 1, Linv32, d032, status + it, mb + it, st, reach_of(c, n))) !=
-          hipSuccess)
+      const SparsePlan& p = c->ba_plan.plan;
+      const int np = kBlk * p.nb;
+      unsigned long long* words = (unsigned long long*)c->chain_flags.p;
+      // the factor leaves y = L^-1 s in y32, so the first solve is the backward pass alone
+      float* y32 = (float*)c->wy.p;
+      if ((e = launch_convert<double, float>(s64, y32, np, st)) != hipSuccess) return e;
+      if ((e = launch_sparse_factor<float>(p, S32, Linv32, y32, d032, status + it, mb + it, st)) != hipSuccess) return e;
+      if ((e = launch_sparse_solve<float>(p, S32, Linv32, nullptr, y32, c32, words, next_epoch(c), err, c->host_err_dev,
+                                          st, true, c->coop_launch)) != hipSuccess)
         return e;
-      if ((e = launch_chol_apply<float>(S32, n, Linv32, y32, c32, y32, (int*)c->chain_flags.p, next_epoch(c), err,
-                                    c->host_err_dev, st, 1, c->coop_launch, reach_of(c, n))) != hipSuccess)
-        return e;
-      if ((e = launch_convert<float, double>(c32, x64, n, st)) != hipSuccess) return e;
+      if ((e = launch_convert<float, double>(c32, x64, np, st)) != hipSuccess) return e;
       int* skip = (int*)c->mx_flag.p + 1;  // set on the device once the residual meets the tolerance
       for (int k = 0; k < n_refine; ++k) {
-        if ((e = launch_residual64(S64, s64, x64, n, r64, maxes, st, env)) != hipSuccess) return e;
+        if ((e = launch_sparse_residual(p, S64, s64, x64, r64, maxes, st)) != hipSuccess) return e;
         // the first step is always taken; a later one only while needed
         if (k > 0 && (e = launch_refine_check(maxes, kRefineTol, skip, st)) != hipSuccess) return e;
-        if ((e = launch_convert<double, float>(r64, rhs32, n, st)) != hipSuccess) return e;
-        if ((e = launch_chol_apply<float>(S32, n, Linv32, rhs32, c32, (float*)c->wy.p, (int*)c->chain_flags.p,
-                                      next_epoch(c), err, c->host_err_dev, st, 0, c->coop_launch, reach_of(c, n),
-                                      k > 0 ? skip : nullptr)) != hipSuccess)
+        if ((e = launch_convert<double, float>(r64, rhs32, np, st)) != hipSuccess) return e;
+        if ((e = launch_sparse_solve<float>(p, S32, Linv32, rhs32, y32, c32, words, next_epoch(c), err,
+                                            c->host_err_dev, st, false, c->coop_launch, k > 0 ? skip : nullptr)) !=
+            hipSuccess)
           return e;
-        if ((e = launch_accumulate(x64, c32, n, st, k > 0 ? skip : nullptr)) != hipSuccess) return e;
+        if ((e = launch_accumulate(x64, c32, np, st, k > 0 ? skip : nullptr)) != hipSuccess) return e;
       }
-      if ((e = launch_residual64(S64, s64, x64, n, r64, maxes, st, env)) != hipSuccess) return e;
+      if ((e = launch_sparse_residual(p, S64, s64, x64, r64, maxes, st)) != hipSuccess) return e;
       if ((e = launch_refine_decide(maxes, status + it, kRefineTol, force_fb ? 1 : 0, resid + it, fb + it,
                                     (int*)c->mx_flag.p, st)) != hipSuccess)
         return e;
@@ -1696,16 +1666,14 @@ static hipError_t solve_mixed_impl(dpvba_ctx* c, const dpvba_graph* g, float* po
         run64 = *c->host_flag != 0;
       }
       if (run64) {
-        if ((e = launch_chol_solve<double>(S64, s64, n, x64, (double*)c->wy.p, (double*)c->Linv.p, d064, status64 + it,
-                                           mb64 + it, (int*)c->chain_flags.p, next_epoch(c), err, c->host_err_dev,
-                                           st, c->coop_launch, reach_of(c, n))) != hipSuccess)
+        if ((e = launch_sparse_factor<double>(p, S64, (double*)c->Linv.p, s64, d064, status64 + it, mb64 + it, st)) !=
+            hipSuccess)
+          return e;
+        if ((e = launch_sparse_solve<double>(p, S64, (const double*)c->Linv.p, nullptr, s64, x64, words, next_epoch(c),
+                                             err, c->host_err_dev, st, true, c->coop_launch)) != hipSuccess)
           return e;
       }
-      // the step leaves the system order (perm: through c32, free by now)
-      const int* perm = sys_perm_of(c);
-      if ((e = launch_step_to_f32(x64, perm ? c32 : dx, n, fb + it, status64 + it, status + it, st)) != hipSuccess)
-        return e;
-      if (perm && (e = launch_permute_blocks<float>(c32, dx, perm, c->n_free, 6, 0, st)) != hipSuccess) return e;
+      if ((e = launch_step_to_f32(x64, p.row0, dx, n, fb + it, status64 + it, status + it, st)) != hipSuccess) return e;
     }
     {
       TraceScope ts(c, DPVBA_PHASE_RETRACT, st);
@@ -1859,13 +1827,20 @@ static hipError_t backward_impl(dpvba_ctx* c, const dpvba_graph* g, const T* pos
   const TileInfo* tiles = (const TileInfo*)tl.tiles.p;
   if ((e = launch_report_init(status, mb, 2 * DPVBA_MAX_ITERS, st, err)) != hipSuccess) return e;
   if ((e = launch_copy<T>(poses0, Xp, np7, st)) != hipSuccess) return e;
+  const bool sparse = is_sparse<T>(n);
+  const SparsePlan& plan = c->ba_plan.plan;
+  T* xs = (T*)c->sys_x.p;  // a large solve's result in the plan's padded rows
   auto gather = [&]() {
-    return gather_system<T>(c, tl, (const T*)c->part_S.p, (const T*)c->part_vec.p, (T*)c->S.p, (T*)c->rhs.p, lambda,
-                            lam_diag, (T*)c->d0.p, st);
+    return gather_system<T>(c, tl, (const T*)c->part_S.p, (const T*)c->part_vec.p, (T*)c->S.p, (T*)c->rhs.p,
+                            (T*)c->d0.p, lambda, lam_diag, st);
   };
-  const int* perm = sys_perm_of(c);
-  T* xs = (T*)c->sys_x.p;  // a solve's result in the system order
-  T* bs = (T*)c->sys_b.p;  // a right-hand side in the system order
+  // x = S^-1 b, zero if a pivot failed, in the poses' order (b: in the
+  // plan's padded rows for a large system, which overwrites it)
+  auto solve = [&](T* b, T* x, int* stt, unsigned int* mbt) {
+    hipError_t r = factor_solve<T>(c, (T*)c->S.p, b, (const T*)c->d0.p, sparse ? xs : x, stt, mbt, err, st);
+    if (r == hipSuccess && sparse) r = launch_sparse_rows_out<T>(plan, xs, x, stt, st);
+    return r;
+  };
   // replay: x_0 .. x_T, depths d_0 .. d_{T-1} in tile order, steps of the poses
   for (int it = 0; it < nit; ++it) {
     T* xt = Xp + it * np7;
@@ -1876,12 +1851,7 @@ static hipError_t backward_impl(dpvba_ctx* c, const dpvba_graph* g, const T* pos
     if ((e = launch_tile_iterate<T>(A, tl.lds_bytes, st)) != hipSuccess) return e;
     if ((e = launch_copy<T>((const T*)c->depth_s.p, Xd + it * ntp, ntp, st)) != hipSuccess) return e;
     if ((e = gather()) != hipSuccess) return e;
-    if ((e = launch_chol_solve<T>((T*)c->S.p, (const T*)c->rhs.p, n, perm ? xs : DX + (size_t)it * n, (T*)c->wy.p,
-                                  (T*)c->Linv.p, (const T*)c->d0.p, status + it, mb + it, (int*)c->chain_flags.p,
-                                  next_epoch(c), err, c->host_err_dev, st, c->coop_launch, reach_of(c, n))) !=
-        hipSuccess)
-      return e;
-    if (perm && (e = launch_permute_blocks<T>(xs, DX + (size_t)it * n, perm, c->n_free, 6, 0, st)) != hipSuccess) return e;
+    if ((e = solve((T*)c->rhs.p, DX + (size_t)it * n, status + it, mb + it)) != hipSuccess) return e;
     if ((e = launch_retract_copy<T>(xt, xt + np7, DX + (size_t)it * n, nf, N, status + it, st)) != hipSuccess)
       return e;
   }
@@ -1906,13 +1876,8 @@ static hipError_t backward_impl(dpvba_ctx* c, const dpvba_graph* g, const T* pos
                                    (T*)c->part_vec.p, (const int*)tl.v_off.p, (const int2*)tl.v_src.p, c->n_free,
                                    dxbar, stt, urhs, st)) != hipSuccess)
       return e;
-    if (perm && (e = launch_permute_blocks<T>(urhs, bs, perm, c->n_free, 6, 1, st)) != hipSuccess) return e;
-    if ((e = launch_chol_solve<T>((T*)c->S.p, perm ? bs : urhs, n, perm ? xs : up, (T*)c->wy.p, (T*)c->Linv.p,
-                                  (const T*)c->d0.p, status + DPVBA_MAX_ITERS + it, mb + DPVBA_MAX_ITERS + it,
-                                  (int*)c->chain_flags.p, next_epoch(c), err, c->host_err_dev, st, c->coop_launch,
-                                  reach_of(c, n))) != hipSuccess)
-      return e;
-    if (perm && (e = launch_permute_blocks<T>(xs, up, perm, c->n_free, 6, 0, st)) != hipSuccess) return e;
+    if (sparse && (e = launch_sparse_rows_in<T>(plan, urhs, (T*)c->rhs.p, st)) != hipSuccess) return e;
+    if ((e = solve(sparse ? (T*)c->rhs.p : urhs, up, status + DPVBA_MAX_ITERS + it, mb + DPVBA_MAX_ITERS + it)) != hipSuccess) return e;
     if ((e = launch_adjoint_backsub<T>(tiles, tl.n_tiles, tl.max_w6, (const int*)tl.blk_pose.p,
                                        (const T*)c->U_s.p, (const T*)c->pscale_s.p, dbar, up, dx_t, stt, ud, dd,
                                        st)) != hipSuccess)
@@ -1964,12 +1929,15 @@ dpvba_status dpvba_pgo_sim3(dpvba_ctx* c, int32_t n_frames, int32_t n_fixed, con
   std::vector<int32_t> ea(std::max(E, 1)), eb(std::max(E, 1));
   for (int e = 0; e < n_frames - 1; ++e) { ea[e] = e; eb[e] = e + 1; }
   for (int l = 0; l < n_loops; ++l) { ea[n_frames - 1 + l] = loop_j[l]; eb[n_frames - 1 + l] = loop_k[l]; }
-  // order of the free poses in the normal equations: a reverse Cuthill-McKee
-  // order where it shrinks the envelope (loop closures couple poses far
-  // apart in time), else their own; pos[f] = block row of free pose f
-  std::vector<int32_t> pos(std::max(nf, 0)), order;
-  for (int f = 0; f < nf; ++f) pos[f] = f;
-  if (nf > 0) {
+  // places of the free poses in the normal equations: an elimination plan
+  // from a reverse Cuthill-McKee order where that shrinks the envelope (loop
+  // closures couple poses far apart in time), or the poses' own order for a
+  // system that one workgroup solves; row_of[f]: free pose f's first row
+  const size_t n = 7 * (size_t)nf;
+  const bool sparse = is_sparse<double>((int)n);
+  std::vector<int32_t> row_of(std::max(nf, 0));
+  for (int f = 0; f < nf; ++f) row_of[f] = 7 * f;
+  if (sparse) {
     std::vector<std::vector<int32_t>> adj(nf);
     for (int e = 0; e < E; ++e) {
       const int fa = ea[e] - n_fixed, fb = eb[e] - n_fixed;
@@ -1982,32 +1950,40 @@ dpvba_status dpvba_pgo_sim3(dpvba_ctx* c, int32_t n_frames, int32_t n_fixed, con
       std::sort(a.begin(), a.end());
       a.erase(std::unique(a.begin(), a.end()), a.end());
     }
+    std::vector<int32_t> ident(nf), pos(nf);
+    for (int f = 0; f < nf; ++f) ident[f] = f;
     const std::vector<int32_t> cand = rcm_order(adj);
-    std::vector<int32_t> cpos(nf);
-    for (int p = 0; p < nf; ++p) cpos[cand[p]] = p;
-    if (envelope_cost(first_coupled(adj, cpos)) < 0.9 * envelope_cost(first_coupled(adj, pos))) {
-      order = cand;
-      pos = cpos;
-    }
+    for (int p = 0; p < nf; ++p) pos[cand[p]] = p;
+    const bool rcm = envelope_cost(first_coupled(adj, pos)) < 0.9 * envelope_cost(first_coupled(adj, ident));
+    c->pg_plan.h = build_block_plan(adj, rcm ? cand : ident, 7, true);
+    HIP_TRY(upload_plan(c->pg_plan, nullptr, st));
+    row_of = c->pg_plan.h.row0;
   }
-  // block lists of the free poses' normal equations (at their block rows),
-  // contributions in residual order
+  // block lists of the free poses' normal equations (by first row and first
+  // column), contributions in residual order
   std::map<std::pair<int, int>, std::vector<int32_t>> blocks;
   std::vector<std::vector<int32_t>> pose_list(std::max(nf, 0));
   for (int e = 0; e < E; ++e) {
     const int fa = ea[e] - n_fixed, fb = eb[e] - n_fixed;
-    const int pa = fa >= 0 ? pos[fa] : -1, pb = fb >= 0 ? pos[fb] : -1;
-    if (fa >= 0) { blocks[{pa, pa}].push_back(4 * e + 0); pose_list[pa].push_back(2 * e); }
-    if (fb >= 0) { blocks[{pb, pb}].push_back(4 * e + 3); pose_list[pb].push_back(2 * e + 1); }
+    const int pa = fa >= 0 ? row_of[fa] : -1, pb = fb >= 0 ? row_of[fb] : -1;
+    if (fa >= 0) { blocks[{pa, pa}].push_back(4 * e + 0); pose_list[fa].push_back(2 * e); }
+    if (fb >= 0) { blocks[{pb, pb}].push_back(4 * e + 3); pose_list[fb].push_back(2 * e + 1); }
     if (fa >= 0 && fb >= 0) {
       if (pa > pb) blocks[{pa, pb}].push_back(4 * e + 1);
       else blocks[{pb, pa}].push_back(4 * e + 2);
     }
   }
-  std::vector<int32_t> blk_pq, blk_off{0}, blk_src, pose_off{0}, pose_src;
+  std::vector<int32_t> blk_to, blk_off{0}, blk_src, pose_off{0}, pose_src;
   for (auto& kv : blocks) {
-    blk_pq.push_back(kv.first.first);
-    blk_pq.push_back(kv.first.second);
+    const int r = kv.first.first, q = kv.first.second;
+    int to = r * (int)n + q;  // dense, row-major
+    if (sparse) {
+      const int id = c->pg_plan.h.find(r / kBlk, q / kBlk);
+      if (id < 0) return DPVBA_EHIP;  // a coupled pair is always a block of the plan
+      to = id * kBlk * kBlk + (r % kBlk) * kBlk + q % kBlk;
+    }
+    blk_to.push_back(to);
+    blk_to.push_back(r == q ? r : -1);
     blk_src.insert(blk_src.end(), kv.second.begin(), kv.second.end());
     blk_off.push_back((int32_t)blk_src.size());
   }
@@ -2015,19 +1991,12 @@ dpvba_status dpvba_pgo_sim3(dpvba_ctx* c, int32_t n_frames, int32_t n_fixed, con
     pose_src.insert(pose_src.end(), l.begin(), l.end());
     pose_off.push_back((int32_t)pose_src.size());
   }
-  const size_t n = 7 * (size_t)nf, nblk64 = (n + 63) / 64;
-  if (nf > 0) {
-    // envelope of the normal equations: each free pose's first coupled free pose
-    std::vector<int32_t> fq(nf);
-    for (int Pp = 0; Pp < nf; ++Pp) fq[Pp] = Pp;
-    for (auto& kv : blocks) fq[kv.first.first] = std::min(fq[kv.first.first], kv.first.second);
-    c->pg_plan.n = 0;
-    HIP_TRY(build_plan(fq, 7, (int)n, c->pg_plan, st));
-  }
-  if (!order.empty()) HIP_TRY(upload(c->pg_perm, order, st));
+  const SparsePlan& plan = c->pg_plan.plan;
+  const size_t npad = sparse ? (size_t)kBlk * plan.nb : n;
+  const size_t h_elems = sparse ? (size_t)plan.n_blocks * kBlk * kBlk : n * n;
   HIP_TRY(upload(c->pg_ea, ea, st));
   HIP_TRY(upload(c->pg_eb, eb, st));
-  HIP_TRY(upload(c->pg_blk_pq, blk_pq, st));
+  HIP_TRY(upload(c->pg_blk_pq, blk_to, st));
   HIP_TRY(upload(c->pg_blk_off, blk_off, st));
   HIP_TRY(upload(c->pg_blk_src, blk_src, st));
   HIP_TRY(upload(c->pg_pose_off, pose_off, st));
@@ -2035,17 +2004,18 @@ dpvba_status dpvba_pgo_sim3(dpvba_ctx* c, int32_t n_frames, int32_t n_fixed, con
   HIP_TRY(ensure(c->pg_C, (size_t)std::max(E, 1) * 13 * 8));
   HIP_TRY(ensure(c->pg_r, (size_t)std::max(E, 1) * 7 * 8));
   HIP_TRY(ensure(c->pg_J, (size_t)std::max(E, 1) * 7 * 14 * 8));
-  HIP_TRY(ensure(c->pg_H, std::max<size_t>(n * n, 1) * 8));
-  HIP_TRY(ensure(c->pg_rhs, std::max<size_t>(n, 1) * 8));
-  HIP_TRY(ensure(c->pg_dx, std::max<size_t>(n, 1) * 8));
-  HIP_TRY(ensure(c->pg_xs, std::max<size_t>(n, 1) * 8));
-  HIP_TRY(ensure(c->pg_d0, std::max<size_t>(n, 1) * 8));
-  HIP_TRY(ensure(c->pg_wy, std::max<size_t>(n, 1) * 8));
-  HIP_TRY(ensure(c->pg_Linv, std::max<size_t>(nblk64, 1) * 64 * 64 * 8));
-  if (c->pg_flags.bytes < chain_words_bytes(nblk64)) {
-    HIP_TRY(ensure(c->pg_flags, chain_words_bytes(nblk64)));
-    HIP_TRY(hipMemsetAsync(c->pg_flags.p, 0, c->pg_flags.bytes, st));
-    c->pg_epoch = 0;
+  HIP_TRY(ensure(c->pg_H, std::max<size_t>(h_elems, 1) * 8));
+  HIP_TRY(ensure(c->pg_rhs, std::max<size_t>(npad, 1) * 8));
+  HIP_TRY(ensure(c->pg_dx, std::max<size_t>(npad, 1) * 8));
+  HIP_TRY(ensure(c->pg_d0, std::max<size_t>(npad, 1) * 8));
+  if (sparse) {
+    HIP_TRY(ensure(c->pg_Linv, (size_t)plan.nb * kBlk * kBlk * 8));
+    const size_t words = sparse_words_bytes(plan.nb);
+    if (c->pg_flags.bytes < words) {
+      HIP_TRY(ensure(c->pg_flags, words));
+      HIP_TRY(hipMemsetAsync(c->pg_flags.p, 0, c->pg_flags.bytes, st));
+      c->pg_epoch = 0;
+    }
   }
   HIP_TRY(ensure(c->pg_status, (DPVBA_MAX_PGO_ITERS + 1) * 4));
   HIP_TRY(ensure(c->pg_mb, (DPVBA_MAX_PGO_ITERS + 1) * 4));
@@ -2061,21 +2031,26 @@ dpvba_status dpvba_pgo_sim3(dpvba_ctx* c, int32_t n_frames, int32_t n_fixed, con
     HIP_TRY(launch_pgo_linearise(sims, (const double*)c->pg_C.p, (const int*)c->pg_ea.p, (const int*)c->pg_eb.p, E,
                                  (double*)c->pg_r.p, (double*)c->pg_J.p, costd + it, st));
     if (nf == 0) continue;
-    HIP_TRY(launch_fill<double>(H, (long long)(n * n), 0.0, st));
-    HIP_TRY(launch_pgo_normal((const double*)c->pg_J.p, (const double*)c->pg_r.p, (const int*)c->pg_blk_pq.p,
+    double* rhs = (double*)c->pg_rhs.p;
+    double* dx = (double*)c->pg_dx.p;
+    const double* d0 = (const double*)c->pg_d0.p;
+    unsigned int* mb = (unsigned int*)c->pg_mb.p + it;
+    const int* row0 = sparse ? plan.row0 : nullptr;
+    HIP_TRY(sparse ? launch_sparse_clear<double>(plan, H, rhs, st) : launch_fill<double>(H, (long long)(n * n), 0.0, st));
+    HIP_TRY(launch_pgo_normal((const double*)c->pg_J.p, (const double*)c->pg_r.p, (const int2*)c->pg_blk_pq.p,
                               (const int*)c->pg_blk_off.p, (const int*)c->pg_blk_src.p, (int)blocks.size(),
-                              (const int*)c->pg_pose_off.p, (const int*)c->pg_pose_src.p, nf, lambda, lam_diag, H,
-                              (double*)c->pg_d0.p, (double*)c->pg_rhs.p, st));
-    c->pg_epoch = c->pg_epoch >= 0x3fffffff ? 1 : c->pg_epoch + 1;
-    const bool perm = !order.empty();
-    HIP_TRY(launch_chol_solve<double>(H, (const double*)c->pg_rhs.p, (int)n, (double*)(perm ? c->pg_xs.p : c->pg_dx.p),
-                                      (double*)c->pg_wy.p, (double*)c->pg_Linv.p, (const double*)c->pg_d0.p,
-                                      status + it, (unsigned int*)c->pg_mb.p + it, (int*)c->pg_flags.p, c->pg_epoch,
-                                      err, c->host_err_dev, st, c->coop_launch, &c->pg_plan.plan));
-    if (perm)
-      HIP_TRY(launch_permute_blocks<double>((const double*)c->pg_xs.p, (double*)c->pg_dx.p, (const int*)c->pg_perm.p,
-                                            nf, 7, 0, st));
-    HIP_TRY(launch_pgo_retract(sims, n_frames, n_fixed, (const double*)c->pg_dx.p, status + it, st));
+                              sparse ? kBlk : (int)n, (const int*)c->pg_pose_off.p, (const int*)c->pg_pose_src.p, nf,
+                              row0, lambda, lam_diag, H, (double*)c->pg_d0.p, rhs, st));
+    if (sparse) {
+      c->pg_epoch = c->pg_epoch >= 0x3fffffff ? 1 : c->pg_epoch + 1;
+      HIP_TRY(launch_sparse_factor<double>(plan, H, (double*)c->pg_Linv.p, rhs, d0, status + it, mb, st));
+      HIP_TRY(launch_sparse_solve<double>(plan, H, (const double*)c->pg_Linv.p, nullptr, rhs, dx,
+                                          (unsigned long long*)c->pg_flags.p, c->pg_epoch, err, c->host_err_dev, st,
+                                          true, c->coop_launch));
+    } else {
+      HIP_TRY(launch_small_chol<double>(H, rhs, (int)n, dx, status + it, mb, st));
+    }
+    HIP_TRY(launch_pgo_retract(sims, n_frames, n_fixed, dx, row0, status + it, st));
   }
   HIP_TRY(launch_pgo_linearise(sims, (const double*)c->pg_C.p, (const int*)c->pg_ea.p, (const int*)c->pg_eb.p, E,
                                (double*)c->pg_r.p, (double*)c->pg_J.p, costd + n_iters, st));

@@ -12,12 +12,12 @@ namespace dpvba {
 // ... (six right-hand-side and six Diag(B) entries each), then a butterfly
 // over the lanes; fixed order, so the result is reproducible.  The shares
 // (type TP) are summed in the output type T, so float shares gathered into
-// double are combined without further rounding error.  With pos, free pose
-// P's rows go to block row pos[P] (a symmetric permutation of the system;
-// null: the poses' own order).
+// double are combined without further rounding error.  With row0, free pose
+// P's rows start at row0[P] (an elimination plan's padded order; null: the
+// poses' own order).
 template <typename TP, typename T>
 __global__ void __launch_bounds__(256) gather_vec_kernel(const TP* part_vec, const int* off, const int2* src,
-                                                         int n_free, T* rhs, T* dB, const int* pos) {
+                                                         int n_free, T* rhs, T* dB, const int* row0) {
   const int P_ = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
   if (P_ >= n_free) return;
   T v[6], d[6];
@@ -46,7 +46,7 @@ __global__ void __launch_bounds__(256) gather_vec_kernel(const TP* part_vec, con
         vv = v[m];
         dd = d[m];
       }
-    const int xd = 6 * (pos ? pos[P_] : P_) + lane;
+    const int xd = (row0 ? row0[P_] : 6 * P_) + lane;
     rhs[xd] = vv;
     dB[xd] = dd;
   }
@@ -55,12 +55,10 @@ __global__ void __launch_bounds__(256) gather_vec_kernel(const TP* part_vec, con
 // Gather of every lower 6x6 block (P >= Q) of the damped reduced system from
 // the tile partials (zero where no tile contributes), with the damping
 // lam_diag Diag(B) + lambda added to the diagonal.  `mirror` also writes the
-// upper triangle.  With pos, block (P, Q) goes to (pos[P], pos[Q]), as its
-// transpose into the lower triangle where pos[P] < pos[Q]; dB is then in
-// the permuted order (gather_vec_kernel with the same pos).
+// upper triangle.
 template <typename TP, typename T>
 __global__ void gather_S_kernel(const TP* part_S, const int* off, const int* src, int n_free, T* S,
-                                const T* dB, T lambda, T lam_diag, int mirror, T* diag_out, const int* pos) {
+                                const T* dB, T lambda, T lam_diag, int mirror, T* diag_out) {
   const long long g = (long long)blockIdx.x * blockDim.x + threadIdx.x;
   const long long nblk = (long long)n_free * (n_free + 1) / 2;
   if (g >= nblk * 36) return;
@@ -79,46 +77,7 @@ __global__ void gather_S_kernel(const TP* part_S, const int* off, const int* src
   }
   for (; q < hi; ++q) v += (T)part_S[src[q] + eo];
   const int n = 6 * n_free;
-  int row = 6 * Pb + r, col = 6 * Qb + c;
-  if (pos) {
-    const int Pd = pos[Pb], Qd = pos[Qb];
-    row = Pd >= Qd ? 6 * Pd + r : 6 * Qd + c;
-    col = Pd >= Qd ? 6 * Qd + c : 6 * Pd + r;
-  }
-  if (row == col) {
-    v += lam_diag * dB[row] + lambda;
-    if (diag_out) diag_out[row] = v;
-  }
-  S[(size_t)row * n + col] = v;
-  if (mirror && row != col) S[(size_t)col * n + row] = v;
-}
-
-// Gather of the blocks inside the envelope of the reduced system in its
-// system order only (env: per block its block row and column in that order,
-// the poses' lower block it comes from and whether it is that block's
-// transpose); the entries outside the envelope are zero and stay zero
-// through the factorisation, so the caller zeroes them once.  Same sums in
-// the same order as gather_S_kernel.  `mirror` also writes the upper
-// triangle.
-template <typename TP, typename T>
-__global__ void gather_S_env_kernel(const TP* part_S, const int* off, const int* src, const int4* env, int n_env,
-                                    int n, T* S, const T* dB, T lambda, T lam_diag, T* diag_out, int mirror) {
-  const long long g = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (g >= (long long)n_env * 36) return;
-  const int b = (int)(g / 36), e = (int)(g % 36), r = e / 6, c = e % 6;
-  const int4 E = env[b];
-  if (E.x == E.y && r < c) return;
-  const int eo = E.w ? r * 6 + c : c * 6 + r;  // the tiles store upper entries of their block pairs
-  const int lo = off[E.z], hi = off[E.z + 1];
-  T v = (T)0;
-  int q = lo;
-  for (; q + 4 <= hi; q += 4) {
-    const T v0 = (T)part_S[src[q] + eo], v1 = (T)part_S[src[q + 1] + eo];
-    const T v2 = (T)part_S[src[q + 2] + eo], v3 = (T)part_S[src[q + 3] + eo];
-    v += v0; v += v1; v += v2; v += v3;
-  }
-  for (; q < hi; ++q) v += (T)part_S[src[q] + eo];
-  const int row = 6 * E.x + r, col = 6 * E.y + c;
+  const int row = 6 * Pb + r, col = 6 * Qb + c;
   if (row == col) {
     v += lam_diag * dB[row] + lambda;
     if (diag_out) diag_out[row] = v;
@@ -291,69 +250,26 @@ hipError_t launch_report_finalize(dpvba_report* rep, const int* status, const un
 
 // ---------------------------------------------------------------- launchers
 
+// rhs and Diag(B) alone, at the rows of an elimination plan.
+template <typename TP, typename T>
+hipError_t launch_gather_vec(const TP* part_vec, const int* v_off, const int2* v_src, int n_free, T* rhs, T* dB,
+                             const int* row0, hipStream_t st) {
+  if (n_free == 0) return hipSuccess;
+  hipLaunchKernelGGL((gather_vec_kernel<TP, T>), dim3((n_free + 3) / 4), dim3(256), 0, st, part_vec, v_off, v_src,
+                     n_free, rhs, dB, row0);
+  return hipGetLastError();
+}
+
 template <typename TP, typename T>
 hipError_t launch_gather_as(const TP* part_S, const TP* part_vec, const int* s_off, const int* s_src,
                             const int* v_off, const int2* v_src, int n_free, T* S, T* rhs, T* dB, T lambda,
-                            T lam_diag, int mirror, T* diag_out, hipStream_t st, const int* pos) {
+                            T lam_diag, int mirror, T* diag_out, hipStream_t st) {
   if (n_free == 0) return hipSuccess;
-  hipLaunchKernelGGL((gather_vec_kernel<TP, T>), dim3((n_free + 3) / 4), dim3(256), 0, st, part_vec, v_off,
-                     v_src, n_free, rhs, dB, pos);
+  hipError_t e = launch_gather_vec<TP, T>(part_vec, v_off, v_src, n_free, rhs, dB, nullptr, st);
+  if (e != hipSuccess) return e;
   const long long tot = (long long)n_free * (n_free + 1) / 2 * 36;
   hipLaunchKernelGGL((gather_S_kernel<TP, T>), dim3((unsigned)((tot + 255) / 256)), dim3(256), 0, st, part_S,
-                     s_off, s_src, n_free, S, dB, lambda, lam_diag, mirror, diag_out, pos);
-  return hipGetLastError();
-}
-
-template <typename TP, typename T>
-hipError_t launch_gather_env_as(const TP* part_S, const TP* part_vec, const int* s_off, const int* s_src,
-                                const int* v_off, const int2* v_src, int n_free, const int4* env, int n_env, T* S,
-                                T* rhs, T* dB, T lambda, T lam_diag, T* diag_out, hipStream_t st, const int* pos,
-                                int mirror) {
-  if (n_free == 0) return hipSuccess;
-  const int n = 6 * n_free;
-  hipLaunchKernelGGL((gather_vec_kernel<TP, T>), dim3((n_free + 3) / 4), dim3(256), 0, st, part_vec, v_off, v_src,
-                     n_free, rhs, dB, pos);
-  const long long tot = (long long)n_env * 36;
-  if (tot > 0)
-    hipLaunchKernelGGL((gather_S_env_kernel<TP, T>), dim3((unsigned)((tot + 255) / 256)), dim3(256), 0, st, part_S,
-                       s_off, s_src, env, n_env, n, S, dB, lambda, lam_diag, diag_out, mirror);
-  return hipGetLastError();
-}
-
-template <typename T>
-hipError_t launch_gather_env(const T* part_S, const T* part_vec, const int* s_off, const int* s_src,
-                             const int* v_off, const int2* v_src, int n_free, const int4* env, int n_env, T* S, T* rhs,
-                             T* dB, T lambda, T lam_diag, T* diag_out, hipStream_t st, const int* pos) {
-  return launch_gather_env_as<T, T>(part_S, part_vec, s_off, s_src, v_off, v_src, n_free, env, n_env, S, rhs, dB,
-                                    lambda, lam_diag, diag_out, st, pos, 0);
-}
-
-template <typename T>
-hipError_t launch_gather(const T* part_S, const T* part_vec, const int* s_off, const int* s_src,
-                         const int* v_off, const int2* v_src, int n_free, T* S, T* rhs, T* dB, T lambda,
-                         T lam_diag, int mirror, T* diag_out, hipStream_t st, const int* pos) {
-  return launch_gather_as<T, T>(part_S, part_vec, s_off, s_src, v_off, v_src, n_free, S, rhs, dB, lambda, lam_diag,
-                                mirror, diag_out, st, pos);
-}
-
-// Row blocks of width bw between the poses' order and a permuted system
-// order: block p of the system is pose perm[p].  to_system: dst block p =
-// src block perm[p]; else dst block perm[p] = src block p.
-template <typename T>
-__global__ void permute_blocks_kernel(const T* src, T* dst, const int* perm, int n_blk, int bw, int to_system) {
-  const int x = blockIdx.x * blockDim.x + threadIdx.x;
-  if (x >= bw * n_blk) return;
-  const int p = x / bw, m = x - bw * p, q = bw * perm[p] + m;
-  if (to_system) dst[x] = src[q];
-  else dst[q] = src[x];
-}
-
-template <typename T>
-hipError_t launch_permute_blocks(const T* src, T* dst, const int* perm, int n_blk, int bw, int to_system,
-                                 hipStream_t st) {
-  if (n_blk == 0) return hipSuccess;
-  hipLaunchKernelGGL((permute_blocks_kernel<T>), dim3((bw * n_blk + 255) / 256), dim3(256), 0, st, src, dst, perm,
-                     n_blk, bw, to_system);
+                     s_off, s_src, n_free, S, dB, lambda, lam_diag, mirror, diag_out);
   return hipGetLastError();
 }
 
@@ -396,26 +312,13 @@ hipError_t launch_reproject(const float* poses, const float* inv_depth, const fl
 
 DPVBA_INSTANTIATE(float, float)
 DPVBA_INSTANTIATE(double, double)
-template hipError_t launch_gather<float>(const float*, const float*, const int*, const int*, const int*,
-                                         const int2*, int, float*, float*, float*, float, float, int, float*,
-                                         hipStream_t, const int*);
-template hipError_t launch_gather<double>(const double*, const double*, const int*, const int*, const int*,
-                                          const int2*, int, double*, double*, double*, double, double, int,
-                                          double*, hipStream_t, const int*);
-template hipError_t launch_gather_as<float, double>(const float*, const float*, const int*, const int*,
-                                                    const int*, const int2*, int, double*, double*, double*,
-                                                    double, double, int, double*, hipStream_t, const int*);
-template hipError_t launch_gather_env<float>(const float*, const float*, const int*, const int*, const int*,
-                                             const int2*, int, const int4*, int, float*, float*, float*, float, float,
-                                             float*, hipStream_t, const int*);
-template hipError_t launch_gather_env<double>(const double*, const double*, const int*, const int*, const int*,
-                                              const int2*, int, const int4*, int, double*, double*, double*, double,
-                                              double, double*, hipStream_t, const int*);
-template hipError_t launch_gather_env_as<float, double>(const float*, const float*, const int*, const int*,
-                                                        const int*, const int2*, int, const int4*, int, double*,
-                                                        double*, double*, double, double, double*, hipStream_t,
-                                                        const int*, int);
-template hipError_t launch_permute_blocks<float>(const float*, float*, const int*, int, int, int, hipStream_t);
-template hipError_t launch_permute_blocks<double>(const double*, double*, const int*, int, int, int, hipStream_t);
+#define DPVBA_GATHER_INSTANTIATE(TP, T)                                                                              \
+  template hipError_t launch_gather_vec<TP, T>(const TP*, const int*, const int2*, int, T*, T*, const int*,           \
+                                               hipStream_t);                                                         \
+  template hipError_t launch_gather_as<TP, T>(const TP*, const TP*, const int*, const int*, const int*, const int2*, \
+                                              int, T*, T*, T*, T, T, int, T*, hipStream_t);
+DPVBA_GATHER_INSTANTIATE(float, float)
+DPVBA_GATHER_INSTANTIATE(double, double)
+DPVBA_GATHER_INSTANTIATE(float, double)
 
 }  // namespace dpvba

@@ -10,12 +10,20 @@ namespace dpvba {
 
 // 1 / sqrt(d) of a positive pivot: the hardware reciprocal square root for
 // float32 (within about one unit in the last place, far inside the float32
-// path's tolerance; it keeps the per-column dependency chain short); the
-// correctly rounded form for float64.
+// path's tolerance; it keeps the per-column dependency chain short); for float64 one
+// third-order step on the hardware's estimate, within about one unit in the
+// last place like 1 / sqrt(d), whose division and root are two long chains.
 template <typename T>
 __device__ __forceinline__ T pivot_rsqrt(T d) {
-  if constexpr (sizeof(T) == 4) return __builtin_amdgcn_rsqf(d);
-  else return (T)1 / sqrt(d);
+  if constexpr (sizeof(T) == 4) {
+    return __builtin_amdgcn_rsqf(d);
+  } else {
+    // y (1 + e / 2 + 3 e^2 / 8), e = 1 - d y^2: the third-order step leaves
+    // e^3, far below the last bit
+    const T y = __builtin_amdgcn_rsq(d);
+    const T e = __builtin_fma(-d * y, y, (T)1);
+    return __builtin_fma(y * e, __builtin_fma(e, (T)0.375, (T)0.5), y);
+  }
 }
 
 // Smallest pivot / damped-diagonal ratio of columns 0..n-1 (the bits of a

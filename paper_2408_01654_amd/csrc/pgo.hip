@@ -15,7 +15,8 @@
 // forward-mode dual-number evaluation per perturbation direction (14 per
 // residual), so they are exact derivatives of the computed residual.  The
 // normal equations are assembled per 7 x 7 block in a fixed order (block
-// lists from the host), damped, and solved by the library's dense Cholesky.
+// lists from the host), damped, and solved by the block-sparse Cholesky
+// (sparse.hip; up to 160 unknowns: one workgroup's dense one).
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
@@ -239,17 +240,19 @@ __global__ void __launch_bounds__(256) pgo_cost_kernel(const double* r, int n, d
   if (threadIdx.x == 0) *out = part[0];
 }
 
-// One workgroup of 64 threads per 7 x 7 block (p >= q) of the free poses:
+// One workgroup of 64 threads per 7 x 7 block of the free poses (its row pose
+// not before its column pose in the elimination order):
 // H_pq = sum over its contributions (e, side_p, side_q) of J_side_p^T J_side_q,
 // in list order; diagonal blocks add the damping lambda (H_ii + 1) (lam_diag
 // = lambda for Levenberg-Marquardt, 0 for additive damping) and report the
-// damped diagonal.  Row-major n x n, lower blocks.
-__global__ void __launch_bounds__(64) pgo_assemble_kernel(const double* J, const int* blk_pq, const int* blk_off,
-                                                          const int* blk_src, int n, double lambda,
+// damped diagonal.  dst: per block the element of its first entry (row
+// stride ld) and, for a diagonal block, its first row (else -1).
+__global__ void __launch_bounds__(64) pgo_assemble_kernel(const double* J, const int2* dst, const int* blk_off,
+                                                          const int* blk_src, int ld, double lambda,
                                                           double lam_diag, double* H, double* d0) {
   const int b = blockIdx.x, t = threadIdx.x;
   if (t >= 49) return;
-  const int p = blk_pq[2 * b], q = blk_pq[2 * b + 1];
+  const int2 to = dst[b];
   const int rr = t / 7, cc = t - (t / 7) * 7;
   double s = 0.0;
   for (int x = blk_off[b]; x < blk_off[b + 1]; ++x) {
@@ -258,16 +261,17 @@ __global__ void __launch_bounds__(64) pgo_assemble_kernel(const double* J, const
     const double* Je = J + (size_t)e * 7 * 14;
     for (int i = 0; i < 7; ++i) s += Je[i * 14 + 7 * sp + rr] * Je[i * 14 + 7 * sq + cc];
   }
-  if (p == q && rr == cc) {
+  if (to.y >= 0 && rr == cc) {
     s += lam_diag * s + lambda;
-    d0[7 * p + rr] = s;
+    d0[to.y + rr] = s;
   }
-  H[(size_t)(7 * p + rr) * n + 7 * q + cc] = s;
+  H[(size_t)to.x + (size_t)rr * ld + cc] = s;
 }
 
 // rhs = -g over the free poses: g_p = sum over (e, side) of J_side^T r_e.
+// (row0: the poses' first rows, 7 p if null)
 __global__ void pgo_gradient_kernel(const double* J, const double* r, const int* pose_off, const int* pose_src,
-                                    int nf, double* rhs) {
+                                    int nf, const int* row0, double* rhs) {
   const int x = blockIdx.x * blockDim.x + threadIdx.x;
   if (x >= 7 * nf) return;
   const int p = x / 7, c = x - (x / 7) * 7;
@@ -276,16 +280,17 @@ __global__ void pgo_gradient_kernel(const double* J, const double* r, const int*
     const int e = pose_src[y] >> 1, side = pose_src[y] & 1;
     for (int i = 0; i < 7; ++i) s += J[((size_t)e * 7 + i) * 14 + 7 * side + c] * r[7 * (size_t)e + i];
   }
-  rhs[x] = -s;
+  rhs[(row0 ? row0[p] : 7 * p) + c] = -s;
 }
 
 // S_i <- S_i Exp(delta_i) for the free poses (quaternion composed with the
 // rotation's half-angle quaternion, renormalised); skipped if the solve failed.
-__global__ void pgo_retract_kernel(double* sims, int n, int n_fixed, const double* dx, const int* status) {
+__global__ void pgo_retract_kernel(double* sims, int n, int n_fixed, const double* dx, const int* row0,
+                                   const int* status) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n || i < n_fixed || (status && *status)) return;
   double* S = sims + 8 * (size_t)i;
-  const double* xi = dx + 7 * (size_t)(i - n_fixed);
+  const double* xi = dx + (row0 ? row0[i - n_fixed] : 7 * (i - n_fixed));
   double R[9];
   quat_to_rot<double, double>(S + 3, R);
   // t <- s R (W rho) + t
@@ -340,21 +345,23 @@ hipError_t launch_pgo_linearise(const double* sims, const double* C, const int* 
   return hipGetLastError();
 }
 
-hipError_t launch_pgo_normal(const double* J, const double* r, const int* blk_pq, const int* blk_off,
-                             const int* blk_src, int n_blocks, const int* pose_off, const int* pose_src, int nf,
-                             double lambda, double lam_diag, double* H, double* d0, double* rhs, hipStream_t st) {
+hipError_t launch_pgo_normal(const double* J, const double* r, const int2* dst, const int* blk_off,
+                             const int* blk_src, int n_blocks, int ld, const int* pose_off, const int* pose_src,
+                             int nf, const int* row0, double lambda, double lam_diag, double* H, double* d0,
+                             double* rhs, hipStream_t st) {
   const int n = 7 * nf;
   if (n_blocks > 0)
-    hipLaunchKernelGGL(pgo_assemble_kernel, dim3(n_blocks), dim3(64), 0, st, J, blk_pq, blk_off, blk_src, n, lambda,
+    hipLaunchKernelGGL(pgo_assemble_kernel, dim3(n_blocks), dim3(64), 0, st, J, dst, blk_off, blk_src, ld, lambda,
                        lam_diag, H, d0);
   if (nf > 0)
     hipLaunchKernelGGL(pgo_gradient_kernel, dim3((n + 255) / 256), dim3(256), 0, st, J, r, pose_off, pose_src, nf,
-                       rhs);
+                       row0, rhs);
   return hipGetLastError();
 }
 
-hipError_t launch_pgo_retract(double* sims, int n, int n_fixed, const double* dx, const int* status, hipStream_t st) {
-  hipLaunchKernelGGL(pgo_retract_kernel, dim3((n + 255) / 256), dim3(256), 0, st, sims, n, n_fixed, dx, status);
+hipError_t launch_pgo_retract(double* sims, int n, int n_fixed, const double* dx, const int* row0, const int* status,
+                              hipStream_t st) {
+  hipLaunchKernelGGL(pgo_retract_kernel, dim3((n + 255) / 256), dim3(256), 0, st, sims, n, n_fixed, dx, row0, status);
   return hipGetLastError();
 }
 

@@ -867,7 +867,7 @@ __global__ void __launch_bounds__(kTileThreads) tile_finalize_kernel(
 // Pose update of the large path: x_{t+1} = x_t Exp(dxi) for free poses.
 template <typename T>
 __global__ void retract_copy_kernel(const T* poses_cur, T* poses_next, T* dx, int n_fixed, int n_frames,
-                                    const int* status, const T* dx_sys, const int* pos) {
+                                    const int* status, const T* dx_sys, const int* row0) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n_frames) return;
   const T* pc = poses_cur + 7 * (size_t)i;
@@ -876,9 +876,10 @@ __global__ void retract_copy_kernel(const T* poses_cur, T* poses_next, T* dx, in
   if (i < n_fixed) return;
   const int f = i - n_fixed;
   T xi[6];
-  if (dx_sys) {  // the step in the system order: free pose f's block is pos[f]; stored back in the poses' order
+  if (dx_sys) {  // the step in a plan's padded rows; stored back in the poses' order, zero if the factor failed
+    const bool bad = status && *status;
     for (int m = 0; m < 6; ++m) {
-      xi[m] = dx_sys[6 * pos[f] + m];
+      xi[m] = bad ? (T)0 : dx_sys[row0[f] + m];
       dx[6 * f + m] = xi[m];
     }
   } else {
@@ -918,9 +919,9 @@ hipError_t launch_tile_finalize(const TileInfo* tiles, int n_tiles, int lds_byte
 
 template <typename T>
 hipError_t launch_retract_copy(const T* poses_cur, T* poses_next, T* dx, int n_fixed, int n_frames,
-                               const int* status, hipStream_t st, const T* dx_sys, const int* pos) {
+                               const int* status, hipStream_t st, const T* dx_sys, const int* row0) {
   hipLaunchKernelGGL((retract_copy_kernel<T>), dim3((n_frames + 127) / 128), dim3(128), 0, st, poses_cur,
-                     poses_next, dx, n_fixed, n_frames, status, dx_sys, pos);
+                     poses_next, dx, n_fixed, n_frames, status, dx_sys, row0);
   return hipGetLastError();
 }
 
