@@ -64,23 +64,29 @@ __host__ __device__ inline int imax(int a, int b) { return a > b ? a : b; }
 // Schur-row matrix U (K_pad x W_pad, rows = patches, columns = 6 n_blk
 // block columns plus one column for w / sqrt(C~), padded for 16x16x4
 // matrix-core tiles; rows 16-byte aligned), which first holds the
-// wavefronts' per-slot partial sums.  Then a byte region of per-cell records (target,
-// weight) that each lane overwrites with its edge's results, later reused
+// wavefronts' per-slot partial sums.  Then a region of eight planes of
+// cells, (patch k, slot s) at k slot_ld + s of each: the record (target, weight,
+// presence) that each lane overwrites with its edge's results, later reused
 // for per-slot source blocks and their sums (and in phase 0 for the block
-// step).  Then the block -> slot range tables.
+// step).  Planes with an odd row stride keep every access of a wavefront on
+// different LDS banks, along the slots (edges, Schur rows) and along the
+// patches (per-patch sums): cells of eight consecutive values put a
+// wavefront on 8 banks, and on 2 with 12 slots.  Then the block -> slot
+// range tables.
 struct TileLds {
   int slot, patch, hp, psum, m, u, total_T; // T offsets
   int K_pad, W_pad;
-  int cell_bytes, rec_bytes;                // per cell, region
+  int slot_ld, plane, rec_bytes;            // row stride and size (entries) of a plane of cells, region
   int blk_s0, blk_s1, tables;               // byte offsets in the table region
 };
 
 __host__ __device__ inline int round_up(int x, int m) { return (x + m - 1) / m * m; }
 
-// Row stride of a tile's Schur-row matrix; the stored rows of a tile are
-// the same K_pad x W_pad matrix (padding included), so they move as
-// contiguous 16-byte vectors.
-__host__ __device__ inline int tile_u_stride(int nb) { return round_up(6 * nb + 1, 16); }
+// Row stride of a tile's Schur-row matrix: 16-wide column tiles, and an odd
+// number of them, so that the four rows of a matrix-core operand start on
+// different LDS banks.  The stored rows of a tile are the same K_pad x W_pad
+// matrix (padding included), so they move as contiguous 16-byte vectors.
+__host__ __device__ inline int tile_u_stride(int nb) { return round_up(6 * nb + 1, 16) | 16; }
 __host__ __device__ inline int tile_u_rows(int K) { return round_up(K, 4); }
 
 // Per-slot source blocks (Ad^T M, Ad^T M Ad, Ad^T v: 80 entries with
@@ -109,8 +115,9 @@ __host__ __device__ inline TileLds tile_lds_plan(int K, int Tn, int nb, int tsiz
   L.m = L.psum + K * 8;
   L.u = round_up(L.m + Tn * kRedWidth, 4);
   L.total_T = L.u + imax(L.K_pad * L.W_pad, (nthreads / 64) * Tn * kRedWidth);  // U, or the wavefronts' slot partials
-  L.cell_bytes = imax(16, 8 * tsize);
-  L.rec_bytes = imax(K * Tn * L.cell_bytes, imax(Tn * kSlotBlk + kSrcSums + tile_bterm_entries(nb), L.W_pad) * tsize);
+  L.slot_ld = Tn | 1;
+  L.plane = K * L.slot_ld;
+  L.rec_bytes = imax(8 * L.plane * tsize, imax(Tn * kSlotBlk + kSrcSums + tile_bterm_entries(nb), L.W_pad) * tsize);
   L.blk_s0 = 0;
   L.blk_s1 = L.blk_s0 + nb;
   L.tables = L.blk_s1 + nb;

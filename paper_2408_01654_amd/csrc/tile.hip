@@ -130,8 +130,8 @@ __device__ __forceinline__ void tile_assemble(const IterArgs<T>& A, int tile, un
   T* sU = base + L.u;         // [Kp][Wp]; first the per-thread partial sums
   T* sWork = sU;
   unsigned char* rec = lds + align16(L.total_T * (int)sizeof(T));
-  const int cellT = L.cell_bytes / (int)sizeof(T);
-  T* sCell = reinterpret_cast<T*>(rec);  // [K*Tn][cellT]
+  const int ldS = L.slot_ld, PS = L.plane;
+  T* sCell = reinterpret_cast<T*>(rec);  // 8 planes of [K][ldS]
   T* sB = reinterpret_cast<T*>(rec);     // phase 2c: [Tn][kSlotBlk], then kSrcSums sums
   T* sDx = reinterpret_cast<T*>(rec);    // phase 0: [Wp] block step
   unsigned char* tab = rec + align16(L.rec_bytes);
@@ -148,8 +148,11 @@ __device__ __forceinline__ void tile_assemble(const IterArgs<T>& A, int tile, un
     }
   }
   const int* slot_blk = A.slot_blk + ti.slot_begin;
-  for (int s = tid; s < Tn; s += blockDim.x) {
-    const int b = slot_blk[s];
+  // the slots' relative poses, in T and (float32 plans) in float64 by different
+  // wavefronts; the rays on the ones after them
+  const int wave0 = tid >> 6, lane0 = tid & 63;
+  if (wave0 == 0 && lane0 < Tn) {
+    const int s = lane0, b = slot_blk[s];
     if (b >= 0) {  // slots follow the frame order, so a block's slots are consecutive
       if (s == 0 || slot_blk[s - 1] != b) sBlkS0[b] = (unsigned char)s;
       if (s == Tn - 1 || slot_blk[s + 1] != b) sBlkS1[b] = (unsigned char)(s + 1);
@@ -162,7 +165,12 @@ __device__ __forceinline__ void tile_assemble(const IterArgs<T>& A, int tile, un
     quat_to_rot<T, T>(pj + 3, Rj);
     for (int m = 0; m < 3; ++m) { tiv[m] = pi[m]; tj[m] = pj[m]; }
     relative_pose<T>(Ri, tiv, Rj, tj, sSlot + 18 * s, sSlot + 18 * s + 9);
-    if constexpr (sizeof(T) == 4) {
+  }
+  if constexpr (sizeof(T) == 4) {
+    if (wave0 == 1 && lane0 < Tn) {
+      const int s = lane0, j = A.slot_frame[ti.slot_begin + s];
+      const T* pi = A.poses_cur + 7 * (size_t)ti.frame;
+      const T* pj = A.poses_cur + 7 * (size_t)j;
       double Ri64[9], ti64[3], Rj64[9], tj64[3];
       quat_to_rot<double, T>(pi + 3, Ri64);
       quat_to_rot<double, T>(pj + 3, Rj64);
@@ -170,10 +178,12 @@ __device__ __forceinline__ void tile_assemble(const IterArgs<T>& A, int tile, un
       relative_pose<double>(Ri64, ti64, Rj64, tj64, sSlot64 + 12 * s, sSlot64 + 12 * s + 9);
     }
   }
+  constexpr int kRay0 = sizeof(T) == 4 ? 128 : 64;  // first thread of the rays
   const bool apply_prev =
       !A.first && A.dx_prev && !(A.status_prev && A.status_prev[ti.inst * A.status_stride]);
   const int pb = ti.patch_begin;
-  for (int k = tid; k < K; k += blockDim.x) {
+  for (int k = tid - kRay0; k < K; k += NT - kRay0) {
+    if (k < 0) break;
     T x0, x1, d, is = (T)0;
     if (A.first) {
       const int pk = A.tile_patch[pb + k];
@@ -227,6 +237,7 @@ __device__ __forceinline__ void tile_assemble(const IterArgs<T>& A, int tile, un
   // weight, or a negative weight, is used as given and reported.
   {
     const int ncell = K * Tn;
+    const float r_slot = 1.f / (float)Tn;
     const int* grid = A.edge_grid + ti.grid_begin;
     const float2* tgt = reinterpret_cast<const float2*>(A.target);
     const float2* wgt = reinterpret_cast<const float2*>(A.weight);
@@ -248,9 +259,13 @@ __device__ __forceinline__ void tile_assemble(const IterArgs<T>& A, int tile, un
       for (int u = 0; u < 8; ++u) {
         const int c = c0 + u * NT;
         if (c < ncell) {
-          unsigned char* cell = rec + (size_t)c * L.cell_bytes;
-          *reinterpret_cast<float4*>(cell) = make_float4(tg[u].x, tg[u].y, wt[u].x, wt[u].y);
-          *reinterpret_cast<int*>(cell + 16) = e[u] >= 0;
+          const int k = (int)(((float)c + 0.5f) * r_slot);  // c / Tn: exact, c < 2^20
+          T* cell = sCell + k * ldS + (c - k * Tn);
+          cell[0] = (T)tg[u].x;
+          cell[PS] = (T)tg[u].y;
+          cell[2 * PS] = (T)wt[u].x;
+          cell[3 * PS] = (T)wt[u].y;
+          cell[4 * PS] = (T)(e[u] >= 0 ? 1 : 0);
           bad_in |= e[u] >= 0 && !(wt[u].x >= 0.f && wt[u].y >= 0.f && wt[u].x <= FLT_MAX && wt[u].y <= FLT_MAX &&
                                    fabsf(tg[u].x) <= FLT_MAX && fabsf(tg[u].y) <= FLT_MAX);
         }
@@ -270,9 +285,9 @@ __device__ __forceinline__ void tile_assemble(const IterArgs<T>& A, int tile, un
   if (g < G) {
     const T* Rt = sSlot + 18 * s;
     for (int k = g; k < K; k += G) {
-      T* cell = sCell + (size_t)(k * Tn + s) * cellT;
-      const float4 r4 = *reinterpret_cast<const float4*>(cell);
-      const bool has = *reinterpret_cast<const int*>(reinterpret_cast<const unsigned char*>(cell) + 16) != 0;
+      T* cell = sCell + k * ldS + s;
+      const float4 r4 = make_float4((float)cell[0], (float)cell[PS], (float)cell[2 * PS], (float)cell[3 * PS]);
+      const bool has = cell[4 * PS] != (T)0;
       EdgeTerms<T> o;
       bool ok;
       if constexpr (sizeof(T) == 4)
@@ -303,7 +318,7 @@ __device__ __forceinline__ void tile_assemble(const IterArgs<T>& A, int tile, un
         out[7] = o.Jd[0] * wr0 + o.Jd[1] * wr1;
       }
 #pragma unroll
-      for (int m = 0; m < 8; ++m) cell[m] = out[m];
+      for (int m = 0; m < 8; ++m) cell[m * PS] = out[m];
     }
   }
   if (n_invalid) atomicAdd(&sInvalid, n_invalid);
@@ -352,27 +367,27 @@ __device__ __forceinline__ void tile_assemble(const IterArgs<T>& A, int tile, un
   //     slots in slot order, one the rotation part (with C and w), the other
   //     the translation part; (ii) C~, 1 / sqrt(C~) and w / sqrt(C~).
   const int src = ti.src_blk;
-  for (int idx = tid; idx < 2 * K; idx += blockDim.x) {
-    const int k = idx >> 1;
-    const bool tpart = idx & 1;  // 0: C, w and the rotation part; 1: the translation part
+  const bool tpart = (tid >> 6) & 1;  // 0: C, w and the rotation part; 1: the translation part (by wavefront)
+  for (int k = (tid & 63) + 64 * (tid >> 7); k < K; k += NT / 2) {
     T v[5] = {0, 0, 0, 0, 0};
+#pragma unroll 2
     for (int ss = 0; ss < Tn; ++ss) {
-      const T* cell = sCell + (size_t)(k * Tn + ss) * cellT;
+      const T* cell = sCell + k * ldS + ss;
       const T* R = sSlot + 18 * ss;
       const T* tt = R + 9;
       T c[8];
       if (!tpart) {
 #pragma unroll
-        for (int m = 0; m < 3; ++m) c[m] = cell[m];
-        c[6] = cell[6];
-        c[7] = cell[7];
+        for (int m = 0; m < 3; ++m) c[m] = cell[m * PS];
+        c[6] = cell[6 * PS];
+        c[7] = cell[7 * PS];
         v[0] += c[6];
         v[1] += c[7];
 #pragma unroll
         for (int q = 0; q < 3; ++q) v[2 + q] -= R[q] * c[0] + R[3 + q] * c[1] + R[6 + q] * c[2];
       } else {
 #pragma unroll
-        for (int m = 0; m < 6; ++m) c[m] = cell[m];
+        for (int m = 0; m < 6; ++m) c[m] = cell[m * PS];
         const T b0 = c[3] - (tt[1] * c[2] - tt[2] * c[1]);
         const T b1 = c[4] - (tt[2] * c[0] - tt[0] * c[2]);
         const T b2 = c[5] - (tt[0] * c[1] - tt[1] * c[0]);
@@ -418,9 +433,9 @@ __device__ __forceinline__ void tile_assemble(const IterArgs<T>& A, int tile, un
         for (int m = 0; m < 6; ++m) v[m] = sPs[8 * k + 2 + m] * is;
       } else {
         for (int ss = sBlkS0[b]; ss < sBlkS1[b]; ++ss) {
-          const T* cell = sCell + (size_t)(k * Tn + ss) * cellT;
+          const T* cell = sCell + k * ldS + ss;
 #pragma unroll
-          for (int m = 0; m < 6; ++m) v[m] += cell[m];
+          for (int m = 0; m < 6; ++m) v[m] += cell[m * PS];
         }
 #pragma unroll
         for (int m = 0; m < 6; ++m) v[m] *= is;
@@ -525,55 +540,60 @@ __device__ __forceinline__ void tile_assemble(const IterArgs<T>& A, int tile, un
   __syncthreads();
 
   // ---- phase 3: U^T U on the matrix cores, plus B; upper entries only.
-  // A work unit is row tile ta against up to four column tiles tb0 ..: the
-  // row operand is loaded once per step and the four accumulators are
-  // independent, so the loads of one step overlap the products of another.
+  // A work unit is row tile ta against up to two column tiles tb0 ..: the
+  // row operand is loaded once per step and the two accumulators are
+  // independent.  (Units of four left half of the wavefronts idle: 6 units
+  // for 13 blocks, 12 for 20.)
   T* outS = A.part_S + ti.part_begin;
   T* outV = A.part_vec + ti.vec_begin;
-  const int T16 = Wp / 16;
+  const int T16 = (W6 + 16) / 16;  // 16-wide tiles of the 6 n_blk + 1 columns
   const int nk = Kp / 4;
   const int lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);  // uniform: scalar unit loop
+  constexpr int kUnit = 2;
   for (int unit = wv;; unit += NT / 64) {
     int ta = 0, rem = unit;
-    while (ta < T16 && rem >= (T16 - ta + 3) / 4) {
-      rem -= (T16 - ta + 3) / 4;
+    while (ta < T16 && rem >= (T16 - ta + kUnit - 1) / kUnit) {
+      rem -= (T16 - ta + kUnit - 1) / kUnit;
       ++ta;
     }
     if (ta >= T16) break;
-    const int tb0 = ta + 4 * rem, nt = min(4, T16 - tb0);
-    typename Mfma<T>::acc_t acc[4];
+    const int tb0 = ta + kUnit * rem, nt = min(kUnit, T16 - tb0);
+    typename Mfma<T>::acc_t acc[kUnit];
     const T* ua = sU + (lane >> 4) * Wp + ta * 16 + (lane & 15);
     const T* ub = sU + (lane >> 4) * Wp + tb0 * 16 + (lane & 15);
-    switch (nt) {
-      case 1: utu_unit<T, 1>(ua, ub, nk, Wp, acc); break;
-      case 2: utu_unit<T, 2>(ua, ub, nk, Wp, acc); break;
-      case 3: utu_unit<T, 3>(ua, ub, nk, Wp, acc); break;
-      default: utu_unit<T, 4>(ua, ub, nk, Wp, acc); break;
+    if (nt == 1) utu_unit<T, 1>(ua, ub, nk, Wp, acc);
+    else utu_unit<T, 2>(ua, ub, nk, Wp, acc);
+    // block and entry of the lane's four rows
+    int ra[4], rr[4];
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const int row = min(ta * 16 + Mfma<T>::row(lane, v), W6 - 1);
+      ra[v] = row / 6;
+      rr[v] = row - 6 * ra[v];
     }
 #pragma unroll
-    for (int t = 0; t < 4; ++t) {
+    for (int t = 0; t < kUnit; ++t) {
       if (t >= nt) continue;
-      const int tb = tb0 + t;
       const typename Mfma<T>::acc_t accv = acc[t];
+      const int col = (tb0 + t) * 16 + (lane & 15);
+      const bool rhs = col == W6;  // right-hand side and Diag(B) of the rows
+      const int b = min(col, W6 - 1) / 6, c = min(col, W6 - 1) - 6 * b;
       // addresses of the four values' B terms first (no branches), so the
       // LDS reads issue together
       const T* t1[4];
       const T* t2[4];
-      bool ok[4], rhs[4];
+      bool ok[4];
       int dst[4];
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
-        const int row = ta * 16 + Mfma<T>::row(lane, v), col = tb * 16 + (lane & 15);
+        const int row = ta * 16 + Mfma<T>::row(lane, v);
         ok[v] = row <= col && row < W6 && col <= W6;
-        rhs[v] = col == W6;  // right-hand side and Diag(B) of row `row`
-        const int a = min(row, W6 - 1) / 6, r = min(row, W6 - 1) - 6 * (min(row, W6 - 1) / 6);
-        const int b = min(col, W6 - 1) / 6, c = min(col, W6 - 1) - 6 * (min(col, W6 - 1) / 6);
-        const int rc = r * 6 + c;
+        const int a = ra[v], r = rr[v], rc = r * 6 + c;
         const T* term = a == b ? sDg + 36 * a + rc
                                : (a == src ? sSr + 36 * b + rc : (b == src ? sSr + 36 * a + c * 6 + r : sZero));
-        t1[v] = !ok[v] ? sZero : (rhs[v] ? sRv + row : term);
-        t2[v] = ok[v] && rhs[v] ? sDv + row : sZero;
-        dst[v] = rhs[v] ? row : upper_pair_index(a, b, nb) * 36 + rc;
+        t1[v] = !ok[v] ? sZero : (rhs ? sRv + row : term);
+        t2[v] = ok[v] && rhs ? sDv + row : sZero;
+        dst[v] = rhs ? row : upper_pair_index(a, b, nb) * 36 + rc;
       }
       T x1[4], x2[4];
 #pragma unroll
@@ -584,7 +604,7 @@ __device__ __forceinline__ void tile_assemble(const IterArgs<T>& A, int tile, un
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
         if (!ok[v]) continue;
-        if (rhs[v]) {
+        if (rhs) {
           outV[dst[v]] = accv[v] + x1[v];
           outV[W6 + dst[v]] = x2[v];
         } else {
