@@ -2354,6 +2354,7 @@ static hipError_t batch_impl(dpvba_ctx* c, const dpvba_batch* b, T* poses, T* de
     A.part_vec = (T*)c->part_vec.p;
     A.part_cost = (double*)c->part_cost.p;
     A.part_invalid = (int*)c->part_invalid.p;
+    A.order = (const int*)tl.order.p;
     A.first = it == 0;
     A.dx_prev = it ? (const T*)c->dx.p : nullptr;
     A.status_prev = it ? status + it - 1 : nullptr;
@@ -2474,10 +2475,18 @@ dpvba_status dpvba_analyze_batch(dpvba_ctx* c, const dpvba_batch* b, const int32
     std::vector<int32_t> jq(jj.begin() + e0, jj.begin() + e0 + Eq);
     const int kcap32 = (tile_patches && tile_patches[q] > 0) ? tile_patches[q] : kDefaultTilePatches32;
     for (int t = 0; t < 2; ++t) {
+      // float32 tiles for two workgroups per CU where every patch fits one
+      // (256 windows: 26 us a tile with one workgroup per CU, 1,806 us a
+      // call against 2,403)
       HostTiling Hq;
-      if (!plan_tiling(Nq, nf, jq, X.pcount, X.pedges, X.frame_patches, t ? kDefaultTilePatches64 : kcap32,
-                       t ? 8 : 4, Hq))
-        return DPVBA_EINVAL;
+      bool ok = t == 0 && plan_tiling(Nq, nf, jq, X.pcount, X.pedges, X.frame_patches, kcap32, 4, Hq,
+                                      kLdsBudgetTwoPerCu);
+      if (!ok) {
+        Hq = HostTiling{};
+        ok = plan_tiling(Nq, nf, jq, X.pcount, X.pedges, X.frame_patches, t ? kDefaultTilePatches64 : kcap32,
+                         t ? 8 : 4, Hq);
+      }
+      if (!ok) return DPVBA_EINVAL;
       BatchInst& I = inst[t][q];
       I.frame_begin = f0;
       I.n_frames = Nq;
