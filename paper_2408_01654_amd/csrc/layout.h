@@ -72,12 +72,12 @@ __host__ __device__ inline int imax(int a, int b) { return a > b ? a : b; }
 // different LDS banks, along the slots (edges, Schur rows) and along the
 // patches (per-patch sums): cells of eight consecutive values put a
 // wavefront on 8 banks, and on 2 with 12 slots.  Then the block -> slot
-// range tables.
+// range tables and the rows' places in the share.
 struct TileLds {
   int slot, patch, hp, psum, m, u, total_T; // T offsets
   int K_pad, W_pad;
   int slot_ld, plane, rec_bytes;            // row stride and size (entries) of a plane of cells, region
-  int blk_s0, blk_s1, tables;               // byte offsets in the table region
+  int blk_s0, blk_s1, row_base, tables;     // byte offsets in the table region
 };
 
 __host__ __device__ inline int round_up(int x, int m) { return (x + m - 1) / m * m; }
@@ -120,7 +120,8 @@ __host__ __device__ inline TileLds tile_lds_plan(int K, int Tn, int nb, int tsiz
   L.rec_bytes = imax(8 * L.plane * tsize, imax(Tn * kSlotBlk + kSrcSums + tile_bterm_entries(nb), L.W_pad) * tsize);
   L.blk_s0 = 0;
   L.blk_s1 = L.blk_s0 + nb;
-  L.tables = L.blk_s1 + nb;
+  L.row_base = round_up(L.blk_s1 + nb, 16);  // per row of the 6 n_blk: its part of an entry's place in the share
+  L.tables = L.row_base + 4 * round_up(6 * nb, 16);
   return L;
 }
 

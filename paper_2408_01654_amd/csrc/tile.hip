@@ -20,6 +20,7 @@
 // All sums run in a fixed order, so results are reproducible bit for bit; no
 // floating-point atomics are used.
 #include <cfloat>
+#include <type_traits>
 
 #include "edge.h"
 #include "mfma.h"
@@ -91,23 +92,38 @@ __device__ void schur_row_dots(const T* U, int K, int Ws, const T* sX, T* dots, 
 template <typename T, int NT>
 __device__ __forceinline__ void utu_unit(const T* ua, const T* ub, int nk, int Wp,
                                          typename Mfma<T>::acc_t* acc) {
+  constexpr int D = 4;  // steps in flight: their operands are loaded before the products of the D steps before
 #pragma unroll
   for (int t = 0; t < NT; ++t) acc[t] = typename Mfma<T>::acc_t{0, 0, 0, 0};
-  // operands of step kq + 1 are loaded before the products of step kq
-  T fa = ua[0], fb[NT];
+  T fa[D], fb[D][NT];
 #pragma unroll
-  for (int t = 0; t < NT; ++t) fb[t] = ub[16 * t];
-  for (int kq = 0; kq < nk; ++kq) {
-    const int kn = min(kq + 1, nk - 1);  // the last step reloads its own operands
-    const T na = ua[kn * 4 * Wp];
-    T nb[NT];
+  for (int d = 0; d < D; ++d) {
+    const int k = min(d, nk - 1);
+    fa[d] = ua[k * 4 * Wp];
 #pragma unroll
-    for (int t = 0; t < NT; ++t) nb[t] = ub[kn * 4 * Wp + 16 * t];
+    for (int t = 0; t < NT; ++t) fb[d][t] = ub[k * 4 * Wp + 16 * t];
+  }
+  for (int kq = 0; kq < nk; kq += D) {
+    T na[D], nb[D][NT];
 #pragma unroll
-    for (int t = 0; t < NT; ++t) acc[t] = Mfma<T>::step(fa, fb[t], acc[t]);
-    fa = na;
+    for (int d = 0; d < D; ++d) {
+      const int k = min(kq + D + d, nk - 1);  // past the end: reloads the last step's operands, unused
+      na[d] = ua[k * 4 * Wp];
 #pragma unroll
-    for (int t = 0; t < NT; ++t) fb[t] = nb[t];
+      for (int t = 0; t < NT; ++t) nb[d][t] = ub[k * 4 * Wp + 16 * t];
+    }
+#pragma unroll
+    for (int d = 0; d < D; ++d)
+      if (kq + d < nk) {  // uniform
+#pragma unroll
+        for (int t = 0; t < NT; ++t) acc[t] = Mfma<T>::step(fa[d], fb[d][t], acc[t]);
+      }
+#pragma unroll
+    for (int d = 0; d < D; ++d) {
+      fa[d] = na[d];
+#pragma unroll
+      for (int t = 0; t < NT; ++t) fb[d][t] = nb[d][t];
+    }
   }
 }
 
@@ -137,6 +153,7 @@ __device__ __forceinline__ void tile_assemble(const IterArgs<T>& A, int tile, un
   unsigned char* tab = rec + align16(L.rec_bytes);
   unsigned char* sBlkS0 = tab + L.blk_s0;  // first slot of each block (its slots are consecutive)
   unsigned char* sBlkS1 = tab + L.blk_s1;  // one past its last slot
+  int* sRow = reinterpret_cast<int*>(tab + L.row_base);  // [6 n_blk] row's part of an entry's place in the share
   __shared__ int sInvalid;
 
   // ---- phase 0: block -> slot ranges, slot relative poses, previous depth step
@@ -179,6 +196,11 @@ __device__ __forceinline__ void tile_assemble(const IterArgs<T>& A, int tile, un
     }
   }
   constexpr int kRay0 = sizeof(T) == 4 ? 128 : 64;  // first thread of the rays
+  // entry (row, col) of the share lies at sRow[row] + 36 (col / 6) + col % 6
+  for (int x = tid; x < W6; x += NT) {
+    const int a = x / 6;
+    sRow[x] = (upper_pair_index(a, a, nb) - a) * 36 + (x - 6 * a) * 6;
+  }
   const bool apply_prev =
       !A.first && A.dx_prev && !(A.status_prev && A.status_prev[ti.inst * A.status_stride]);
   const int pb = ti.patch_begin;
@@ -232,7 +254,7 @@ __device__ __forceinline__ void tile_assemble(const IterArgs<T>& A, int tile, un
   __syncthreads();
   // records: (target, weight) per cell and, after them, whether the cell
   // holds an edge (cells without one are marked by the edge id, never by
-  // a value); batches of 8 cells per thread keep the index loads and the
+  // a value); batches of 4 or 2 cells per thread keep the index loads and the
   // dependent record loads in flight together.  A non-finite target or
   // weight, or a negative weight, is used as given and reported.
   {
@@ -242,21 +264,22 @@ __device__ __forceinline__ void tile_assemble(const IterArgs<T>& A, int tile, un
     const float2* tgt = reinterpret_cast<const float2*>(A.target);
     const float2* wgt = reinterpret_cast<const float2*>(A.weight);
     bool bad_in = false;
-    for (int c0 = tid; c0 < ncell; c0 += 8 * NT) {
-      int e[8];
+    auto batch = [&](auto n_, int c0) {
+      constexpr int N = decltype(n_)::value;
+      int e[N];
 #pragma unroll
-      for (int u = 0; u < 8; ++u) {
+      for (int u = 0; u < N; ++u) {
         const int c = c0 + u * NT;
         e[u] = c < ncell ? grid[c] : -1;
       }
-      float2 tg[8], wt[8];
+      float2 tg[N], wt[N];
 #pragma unroll
-      for (int u = 0; u < 8; ++u) {
+      for (int u = 0; u < N; ++u) {
         tg[u] = e[u] >= 0 ? tgt[e[u]] : make_float2(0.f, 0.f);
         wt[u] = e[u] >= 0 ? wgt[e[u]] : make_float2(0.f, 0.f);
       }
 #pragma unroll
-      for (int u = 0; u < 8; ++u) {
+      for (int u = 0; u < N; ++u) {
         const int c = c0 + u * NT;
         if (c < ncell) {
           const int k = (int)(((float)c + 0.5f) * r_slot);  // c / Tn: exact, c < 2^20
@@ -270,7 +293,10 @@ __device__ __forceinline__ void tile_assemble(const IterArgs<T>& A, int tile, un
                                    fabsf(tg[u].x) <= FLT_MAX && fabsf(tg[u].y) <= FLT_MAX);
         }
       }
-    }
+    };
+    int c0 = 0;  // uniform: first cell of the batch
+    for (; ncell - c0 > 2 * NT; c0 += 4 * NT) batch(std::integral_constant<int, 4>(), c0 + tid);
+    if (c0 < ncell) batch(std::integral_constant<int, 2>(), c0 + tid);
     if (bad_in) report_device_error(A.dev_err, A.host_err, kErrInput);
   }
   __syncthreads();
@@ -348,14 +374,18 @@ __device__ __forceinline__ void tile_assemble(const IterArgs<T>& A, int tile, un
   // ---- phase 2a: per-slot totals, the wavefronts' partials summed in order
   {
     const int nwv = (G * Tn + 63) / 64;  // wavefronts holding thread groups
+    const int step = 64 - (64 / Tn) * Tn;
     for (int idx = tid; idx < Tn * kRedWidth; idx += blockDim.x) {
       const int ss = idx / kRedWidth, m = idx % kRedWidth;
       T v = (T)0;
+      int o = 0;  // slot of wavefront w's first lane: 64 w mod Tn
       for (int w = 0; w < nwv; ++w) {
         // slot ss appears among the first Tn lanes of wavefront w unless the
         // wavefront holds fewer lanes than that
-        const int first = (ss - (64 * w) % Tn + Tn) % Tn;  // its first lane in wavefront w
+        const int first = ss >= o ? ss - o : ss - o + Tn;  // its first lane in wavefront w
         if (first < min(64, G * Tn - 64 * w)) v += sWork[(w * Tn + ss) * kRedWidth + m];
+        o += step;
+        if (o >= Tn) o -= Tn;
       }
       sM[ss * kRedWidth + m] = v;
     }
@@ -563,21 +593,25 @@ __device__ __forceinline__ void tile_assemble(const IterArgs<T>& A, int tile, un
     const T* ub = sU + (lane >> 4) * Wp + tb0 * 16 + (lane & 15);
     if (nt == 1) utu_unit<T, 1>(ua, ub, nk, Wp, acc);
     else utu_unit<T, 2>(ua, ub, nk, Wp, acc);
-    // block and entry of the lane's four rows
-    int ra[4], rr[4];
+    // Entries away from the diagonal blocks, the source pose and the
+    // right-hand side have no B term: most tiles only negate and store.
+    const int row0 = ta * 16, a_lo = row0 / 6, a_hi = min(row0 + 15, W6 - 1) / 6;  // uniform
+    int rb[4];
 #pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      const int row = min(ta * 16 + Mfma<T>::row(lane, v), W6 - 1);
-      ra[v] = row / 6;
-      rr[v] = row - 6 * ra[v];
-    }
+    for (int v = 0; v < 4; ++v) rb[v] = sRow[min(row0 + Mfma<T>::row(lane, v), W6 - 1)];
 #pragma unroll
     for (int t = 0; t < kUnit; ++t) {
       if (t >= nt) continue;
       const typename Mfma<T>::acc_t accv = acc[t];
-      const int col = (tb0 + t) * 16 + (lane & 15);
+      const int col0 = (tb0 + t) * 16, b_lo = col0 / 6, b_hi = (col0 + 15) / 6;
+      const int col = col0 + (lane & 15);
+      const int b = min(col, W6 - 1) / 6, c = min(col, W6 - 1) - 6 * b, cb = 36 * b + c;
+      if (b_lo > a_hi && col0 + 15 < W6 && !(src >= a_lo && src <= a_hi) && !(src >= b_lo && src <= b_hi)) {
+#pragma unroll
+        for (int v = 0; v < 4; ++v) outS[rb[v] + cb] = (T)0 - accv[v];
+        continue;
+      }
       const bool rhs = col == W6;  // right-hand side and Diag(B) of the rows
-      const int b = min(col, W6 - 1) / 6, c = min(col, W6 - 1) - 6 * b;
       // addresses of the four values' B terms first (no branches), so the
       // LDS reads issue together
       const T* t1[4];
@@ -586,14 +620,14 @@ __device__ __forceinline__ void tile_assemble(const IterArgs<T>& A, int tile, un
       int dst[4];
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
-        const int row = ta * 16 + Mfma<T>::row(lane, v);
+        const int row = row0 + Mfma<T>::row(lane, v), rc_ = min(row, W6 - 1);
         ok[v] = row <= col && row < W6 && col <= W6;
-        const int a = ra[v], r = rr[v], rc = r * 6 + c;
+        const int a = rc_ / 6, r = rc_ - 6 * a, rc = r * 6 + c;
         const T* term = a == b ? sDg + 36 * a + rc
                                : (a == src ? sSr + 36 * b + rc : (b == src ? sSr + 36 * a + c * 6 + r : sZero));
         t1[v] = !ok[v] ? sZero : (rhs ? sRv + row : term);
         t2[v] = ok[v] && rhs ? sDv + row : sZero;
-        dst[v] = rhs ? row : upper_pair_index(a, b, nb) * 36 + rc;
+        dst[v] = rhs ? row : rb[v] + cb;
       }
       T x1[4], x2[4];
 #pragma unroll
