@@ -1530,6 +1530,11 @@ static hipError_t solve_impl(dpvba_ctx* c, const dpvba_graph* g, T* poses, T* de
 // fixed number of steps, and the largest accepted relative residual.
 constexpr int kRefineSteps = 2;
 constexpr double kRefineTol = 1e-8;
+// The last refinement step is left out once the residual is this small.  A
+// residual rho leaves a relative step error of up to kappa rho: with kappa =
+// 1e6 (forward motion, additive damping) 1e-12 keeps it at float32 rounding,
+// where stopping at kRefineTol left up to 1e-4 of the pose step.
+constexpr double kRefineStop = 1e-12;
 
 // DPVBA_MIXED: float32 state and tile assembly, float64 gather of the
 // shares, float32 Cholesky with float64 iterative refinement, float64
@@ -1646,7 +1651,7 @@ static hipError_t solve_mixed_impl(dpvba_ctx* c, const dpvba_graph* g, float* po
       for (int k = 0; k < n_refine; ++k) {
         if ((e = launch_sparse_residual(p, S64, s64, x64, r64, maxes, st)) != hipSuccess) return e;
         // the first step is always taken; a later one only while needed
-        if (k > 0 && (e = launch_refine_check(maxes, kRefineTol, skip, st)) != hipSuccess) return e;
+        if (k > 0 && (e = launch_refine_check(maxes, kRefineStop, skip, st)) != hipSuccess) return e;
         if ((e = launch_convert<double, float>(r64, rhs32, np, st)) != hipSuccess) return e;
         if ((e = launch_sparse_solve<float>(p, S32, Linv32, rhs32, y32, c32, words, next_epoch(c), err,
                                             c->host_err_dev, st, false, c->coop_launch, k > 0 ? skip : nullptr)) !=
