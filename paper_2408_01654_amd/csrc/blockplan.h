@@ -26,15 +26,18 @@ namespace dpvba {
 
 constexpr int kBlk = 64;  // rows of a block
 
-// One block of block column K in its level's launch: target block `blk` (the
-// diagonal block, or the block of a row of the column), and the columns of
-// the level before that still have to be subtracted: child[j0 .. j0 + nj).
-struct LevelTask {
-  int32_t K, blk, j0, nj;
-};
 // Child column J of a LevelTask (K, I): blocks (K, J) and (I, J) (-1: none).
 struct LevelChild {
   int32_t kj, ij, J, pad;
+};
+// One block of block column K in its level's launch: target block `blk` (the
+// diagonal block dblk of `size` used rows, or the block of a row of the
+// column), and the columns of the level before that still have to be
+// subtracted: child[j0 .. j0 + nj), the first of them here too (a task then
+// has its first operands' places with its own record).
+struct LevelTask {
+  int32_t K, blk, dblk, size, j0, nj, pad[2];
+  LevelChild first;
 };
 // One block (I, J') that the columns of the level before update and that is
 // eliminated later: src[s0 .. s0 + ns); row = I for a diagonal block (whose
@@ -227,9 +230,10 @@ inline BlockPlan build_block_plan(const std::vector<std::vector<int32_t>>& adj, 
           kids.push_back(rows[K][q + 1]);
         }
       for (int q = p.colptr[K]; q < p.colptr[K + 1]; ++q) {
-        LevelTask t{K, q, (int32_t)p.children.size(), (int32_t)(kids.size() / 2)};
+        LevelTask t{K, q, p.colptr[K], p.size[K], (int32_t)p.children.size(), (int32_t)(kids.size() / 2), {0, 0}, {-1, -1, -1, 0}};
         for (size_t x = 0; x < kids.size(); x += 2)
           p.children.push_back(LevelChild{kids[x + 1], p.find(p.rowidx[q], kids[x]), kids[x], 0});
+        if (t.nj) t.first = p.children[t.j0];
         p.tasks.push_back(t);
       }
     }

@@ -640,6 +640,195 @@ __device__ __forceinline__ T row_bcast(T v, int c) {
   }
 }
 
+// acc -= x * (x of the row's lane C): row_newbcast inside the multiply-add, so
+// that a broadcast costs no instruction of its own (a separate move per
+// column entry is a third of a float32 panel's instructions, half of a
+// float64 one's).  Each statement opens with the two wait states a lane
+// broadcast needs after the write of x, which the compiler cannot see in here.
+// ROW_FMAC_n: columns C .. C + n - 1 of two rows a, b (na = -x_a, nb = -x_b).
+template <typename T> struct RowFmac;
+template <> struct RowFmac<float> {
+  // column C of both rows, then the row's entry (C, C) to every lane
+  template <int C>
+  static __device__ __forceinline__ float next(float* a, float* b, float x, float na, float nb) {
+    float d;
+    asm volatile("s_nop 1\n\t"
+                 "v_fmac_f32_dpp %0, %3, %4 row_newbcast:%6 row_mask:0xf bank_mask:0xf\n\t"
+                 "v_fmac_f32_dpp %1, %3, %5 row_newbcast:%6 row_mask:0xf bank_mask:0xf\n\t"
+                 "s_nop 0\n\t"
+                 "v_mov_b32_dpp %2, %0 row_newbcast:%6 row_mask:0xf bank_mask:0xf"
+                 : "+&v"(a[C]), "+&v"(b[C]), "=&v"(d)
+                 : "v"(x), "v"(na), "v"(nb), "n"(C));
+    return d;
+  }
+  template <int C>
+  static __device__ __forceinline__ void cols1(float* a, float* b, float x, float na, float nb) {
+    asm volatile("s_nop 1\n\t"
+                 "v_fmac_f32_dpp %0, %2, %3 row_newbcast:%5 row_mask:0xf bank_mask:0xf\n\t"
+                 "v_fmac_f32_dpp %1, %2, %4 row_newbcast:%5 row_mask:0xf bank_mask:0xf"
+                 : "+&v"(a[C + 0]), "+&v"(b[C + 0])
+                 : "v"(x), "v"(na), "v"(nb), "n"(C + 0));
+  }
+  template <int C>
+  static __device__ __forceinline__ void cols2(float* a, float* b, float x, float na, float nb) {
+    asm volatile("s_nop 1\n\t"
+                 "v_fmac_f32_dpp %0, %4, %5 row_newbcast:%7 row_mask:0xf bank_mask:0xf\n\t"
+                 "v_fmac_f32_dpp %1, %4, %6 row_newbcast:%7 row_mask:0xf bank_mask:0xf\n\t"
+                 "v_fmac_f32_dpp %2, %4, %5 row_newbcast:%8 row_mask:0xf bank_mask:0xf\n\t"
+                 "v_fmac_f32_dpp %3, %4, %6 row_newbcast:%8 row_mask:0xf bank_mask:0xf"
+                 : "+&v"(a[C + 0]), "+&v"(b[C + 0]), "+&v"(a[C + 1]), "+&v"(b[C + 1])
+                 : "v"(x), "v"(na), "v"(nb), "n"(C + 0), "n"(C + 1));
+  }
+  template <int C>
+  static __device__ __forceinline__ void cols4(float* a, float* b, float x, float na, float nb) {
+    asm volatile("s_nop 1\n\t"
+                 "v_fmac_f32_dpp %0, %8, %9 row_newbcast:%11 row_mask:0xf bank_mask:0xf\n\t"
+                 "v_fmac_f32_dpp %1, %8, %10 row_newbcast:%11 row_mask:0xf bank_mask:0xf\n\t"
+                 "v_fmac_f32_dpp %2, %8, %9 row_newbcast:%12 row_mask:0xf bank_mask:0xf\n\t"
+                 "v_fmac_f32_dpp %3, %8, %10 row_newbcast:%12 row_mask:0xf bank_mask:0xf\n\t"
+                 "v_fmac_f32_dpp %4, %8, %9 row_newbcast:%13 row_mask:0xf bank_mask:0xf\n\t"
+                 "v_fmac_f32_dpp %5, %8, %10 row_newbcast:%13 row_mask:0xf bank_mask:0xf\n\t"
+                 "v_fmac_f32_dpp %6, %8, %9 row_newbcast:%14 row_mask:0xf bank_mask:0xf\n\t"
+                 "v_fmac_f32_dpp %7, %8, %10 row_newbcast:%14 row_mask:0xf bank_mask:0xf"
+                 : "+&v"(a[C + 0]), "+&v"(b[C + 0]), "+&v"(a[C + 1]), "+&v"(b[C + 1]), "+&v"(a[C + 2]), "+&v"(b[C + 2]), "+&v"(a[C + 3]), "+&v"(b[C + 3])
+                 : "v"(x), "v"(na), "v"(nb), "n"(C + 0), "n"(C + 1), "n"(C + 2), "n"(C + 3));
+  }
+  template <int C>
+  static __device__ __forceinline__ void cols6(float* a, float* b, float x, float na, float nb) {
+    asm volatile("s_nop 1\n\t"
+                 "v_fmac_f32_dpp %0, %12, %13 row_newbcast:%15 row_mask:0xf bank_mask:0xf\n\t"
+                 "v_fmac_f32_dpp %1, %12, %14 row_newbcast:%15 row_mask:0xf bank_mask:0xf\n\t"
+                 "v_fmac_f32_dpp %2, %12, %13 row_newbcast:%16 row_mask:0xf bank_mask:0xf\n\t"
+                 "v_fmac_f32_dpp %3, %12, %14 row_newbcast:%16 row_mask:0xf bank_mask:0xf\n\t"
+                 "v_fmac_f32_dpp %4, %12, %13 row_newbcast:%17 row_mask:0xf bank_mask:0xf\n\t"
+                 "v_fmac_f32_dpp %5, %12, %14 row_newbcast:%17 row_mask:0xf bank_mask:0xf\n\t"
+                 "v_fmac_f32_dpp %6, %12, %13 row_newbcast:%18 row_mask:0xf bank_mask:0xf\n\t"
+                 "v_fmac_f32_dpp %7, %12, %14 row_newbcast:%18 row_mask:0xf bank_mask:0xf\n\t"
+                 "v_fmac_f32_dpp %8, %12, %13 row_newbcast:%19 row_mask:0xf bank_mask:0xf\n\t"
+                 "v_fmac_f32_dpp %9, %12, %14 row_newbcast:%19 row_mask:0xf bank_mask:0xf\n\t"
+                 "v_fmac_f32_dpp %10, %12, %13 row_newbcast:%20 row_mask:0xf bank_mask:0xf\n\t"
+                 "v_fmac_f32_dpp %11, %12, %14 row_newbcast:%20 row_mask:0xf bank_mask:0xf"
+                 : "+&v"(a[C + 0]), "+&v"(b[C + 0]), "+&v"(a[C + 1]), "+&v"(b[C + 1]), "+&v"(a[C + 2]), "+&v"(b[C + 2]), "+&v"(a[C + 3]), "+&v"(b[C + 3]), "+&v"(a[C + 4]), "+&v"(b[C + 4]), "+&v"(a[C + 5]), "+&v"(b[C + 5])
+                 : "v"(x), "v"(na), "v"(nb), "n"(C + 0), "n"(C + 1), "n"(C + 2), "n"(C + 3), "n"(C + 4), "n"(C + 5));
+  }
+};
+
+template <> struct RowFmac<double> {
+  // column C of both rows, then the row's entry (C, C) to every lane
+  template <int C>
+  static __device__ __forceinline__ double next(double* a, double* b, double x, double na, double nb) {
+    double d;
+    asm volatile("s_nop 1\n\t"
+                 "v_fmac_f64_dpp %0, %3, %4 row_newbcast:%6 row_mask:0xf bank_mask:0xf\n\t"
+                 "v_fmac_f64_dpp %1, %3, %5 row_newbcast:%6 row_mask:0xf bank_mask:0xf\n\t"
+                 "s_nop 0\n\t"
+                 "v_mov_b64_dpp %2, %0 row_newbcast:%6 row_mask:0xf bank_mask:0xf"
+                 : "+&v"(a[C]), "+&v"(b[C]), "=&v"(d)
+                 : "v"(x), "v"(na), "v"(nb), "n"(C));
+    return d;
+  }
+  template <int C>
+  static __device__ __forceinline__ void cols1(double* a, double* b, double x, double na, double nb) {
+    asm volatile("s_nop 1\n\t"
+                 "v_fmac_f64_dpp %0, %2, %3 row_newbcast:%5 row_mask:0xf bank_mask:0xf\n\t"
+                 "v_fmac_f64_dpp %1, %2, %4 row_newbcast:%5 row_mask:0xf bank_mask:0xf"
+                 : "+&v"(a[C + 0]), "+&v"(b[C + 0])
+                 : "v"(x), "v"(na), "v"(nb), "n"(C + 0));
+  }
+  template <int C>
+  static __device__ __forceinline__ void cols2(double* a, double* b, double x, double na, double nb) {
+    asm volatile("s_nop 1\n\t"
+                 "v_fmac_f64_dpp %0, %4, %5 row_newbcast:%7 row_mask:0xf bank_mask:0xf\n\t"
+                 "v_fmac_f64_dpp %1, %4, %6 row_newbcast:%7 row_mask:0xf bank_mask:0xf\n\t"
+                 "v_fmac_f64_dpp %2, %4, %5 row_newbcast:%8 row_mask:0xf bank_mask:0xf\n\t"
+                 "v_fmac_f64_dpp %3, %4, %6 row_newbcast:%8 row_mask:0xf bank_mask:0xf"
+                 : "+&v"(a[C + 0]), "+&v"(b[C + 0]), "+&v"(a[C + 1]), "+&v"(b[C + 1])
+                 : "v"(x), "v"(na), "v"(nb), "n"(C + 0), "n"(C + 1));
+  }
+  template <int C>
+  static __device__ __forceinline__ void cols4(double* a, double* b, double x, double na, double nb) {
+    asm volatile("s_nop 1\n\t"
+                 "v_fmac_f64_dpp %0, %8, %9 row_newbcast:%11 row_mask:0xf bank_mask:0xf\n\t"
+                 "v_fmac_f64_dpp %1, %8, %10 row_newbcast:%11 row_mask:0xf bank_mask:0xf\n\t"
+                 "v_fmac_f64_dpp %2, %8, %9 row_newbcast:%12 row_mask:0xf bank_mask:0xf\n\t"
+                 "v_fmac_f64_dpp %3, %8, %10 row_newbcast:%12 row_mask:0xf bank_mask:0xf\n\t"
+                 "v_fmac_f64_dpp %4, %8, %9 row_newbcast:%13 row_mask:0xf bank_mask:0xf\n\t"
+                 "v_fmac_f64_dpp %5, %8, %10 row_newbcast:%13 row_mask:0xf bank_mask:0xf\n\t"
+                 "v_fmac_f64_dpp %6, %8, %9 row_newbcast:%14 row_mask:0xf bank_mask:0xf\n\t"
+                 "v_fmac_f64_dpp %7, %8, %10 row_newbcast:%14 row_mask:0xf bank_mask:0xf"
+                 : "+&v"(a[C + 0]), "+&v"(b[C + 0]), "+&v"(a[C + 1]), "+&v"(b[C + 1]), "+&v"(a[C + 2]), "+&v"(b[C + 2]), "+&v"(a[C + 3]), "+&v"(b[C + 3])
+                 : "v"(x), "v"(na), "v"(nb), "n"(C + 0), "n"(C + 1), "n"(C + 2), "n"(C + 3));
+  }
+  template <int C>
+  static __device__ __forceinline__ void cols6(double* a, double* b, double x, double na, double nb) {
+    asm volatile("s_nop 1\n\t"
+                 "v_fmac_f64_dpp %0, %12, %13 row_newbcast:%15 row_mask:0xf bank_mask:0xf\n\t"
+                 "v_fmac_f64_dpp %1, %12, %14 row_newbcast:%15 row_mask:0xf bank_mask:0xf\n\t"
+                 "v_fmac_f64_dpp %2, %12, %13 row_newbcast:%16 row_mask:0xf bank_mask:0xf\n\t"
+                 "v_fmac_f64_dpp %3, %12, %14 row_newbcast:%16 row_mask:0xf bank_mask:0xf\n\t"
+                 "v_fmac_f64_dpp %4, %12, %13 row_newbcast:%17 row_mask:0xf bank_mask:0xf\n\t"
+                 "v_fmac_f64_dpp %5, %12, %14 row_newbcast:%17 row_mask:0xf bank_mask:0xf\n\t"
+                 "v_fmac_f64_dpp %6, %12, %13 row_newbcast:%18 row_mask:0xf bank_mask:0xf\n\t"
+                 "v_fmac_f64_dpp %7, %12, %14 row_newbcast:%18 row_mask:0xf bank_mask:0xf\n\t"
+                 "v_fmac_f64_dpp %8, %12, %13 row_newbcast:%19 row_mask:0xf bank_mask:0xf\n\t"
+                 "v_fmac_f64_dpp %9, %12, %14 row_newbcast:%19 row_mask:0xf bank_mask:0xf\n\t"
+                 "v_fmac_f64_dpp %10, %12, %13 row_newbcast:%20 row_mask:0xf bank_mask:0xf\n\t"
+                 "v_fmac_f64_dpp %11, %12, %14 row_newbcast:%20 row_mask:0xf bank_mask:0xf"
+                 : "+&v"(a[C + 0]), "+&v"(b[C + 0]), "+&v"(a[C + 1]), "+&v"(b[C + 1]), "+&v"(a[C + 2]), "+&v"(b[C + 2]), "+&v"(a[C + 3]), "+&v"(b[C + 3]), "+&v"(a[C + 4]), "+&v"(b[C + 4]), "+&v"(a[C + 5]), "+&v"(b[C + 5])
+                 : "v"(x), "v"(na), "v"(nb), "n"(C + 0), "n"(C + 1), "n"(C + 2), "n"(C + 3), "n"(C + 4), "n"(C + 5));
+  }
+};
+
+// Columns C .. 15.
+template <typename T, int C>
+__device__ __forceinline__ void row_fmac_rest(T* a, T* b, T x, T na, T nb) {
+  if constexpr (C + 6 <= 16) {
+    RowFmac<T>::template cols6<C>(a, b, x, na, nb);
+    row_fmac_rest<T, C + 6>(a, b, x, na, nb);
+  } else if constexpr (C + 4 <= 16) {
+    RowFmac<T>::template cols4<C>(a, b, x, na, nb);
+    row_fmac_rest<T, C + 4>(a, b, x, na, nb);
+  } else if constexpr (C + 2 <= 16) {
+    RowFmac<T>::template cols2<C>(a, b, x, na, nb);
+    row_fmac_rest<T, C + 2>(a, b, x, na, nb);
+  } else if constexpr (C < 16) {
+    RowFmac<T>::template cols1<C>(a, b, x, na, nb);
+  }
+}
+
+// Whether a reciprocal square root is that of a positive finite pivot.
+__device__ __forceinline__ bool good_rsqrt(float rs) { return __builtin_amdgcn_classf(rs, 0x180); }
+__device__ __forceinline__ bool good_rsqrt(double rs) { return __builtin_amdgcn_class(rs, 0x180); }
+
+// Cholesky of 16 columns on one wavefront, rows in registers: every 16-lane
+// row of the wavefront holds the 16 x 16 diagonal block in a (lane s: row s),
+// each lane one row below it in b.  Column c: scale it, update column c + 1
+// and start that column's pivot at once, so that the chain of pivots runs
+// beside the other columns' updates.  A pivot that is not positive and
+// finite sets bad and leaves its column unscaled.  Entries above the diagonal are never
+// read as results.
+template <typename T, int C = 0>
+__device__ __forceinline__ void chol16_columns(T* a, T* b, T rs, int& bad) {
+  const bool ok = good_rsqrt(rs);
+  bad |= !ok;
+  rs = ok ? rs : (T)1;
+  a[C] *= rs;
+  b[C] *= rs;
+  if constexpr (C < 15) {
+    const T x = a[C], na = -a[C], nb = -b[C];
+    const T d = RowFmac<T>::template next<C + 1>(a, b, x, na, nb);
+    const T rn = pivot_rsqrt<T>(d);
+    __builtin_amdgcn_sched_barrier(0);  // the estimate is under way before the other columns
+    row_fmac_rest<T, C + 2>(a, b, x, na, nb);
+    chol16_columns<T, C + 1>(a, b, rn, bad);
+  }
+}
+
+template <typename T>
+__device__ __forceinline__ void chol16(T* a, T* b, int& bad) {
+  chol16_columns<T>(a, b, pivot_rsqrt<T>(row_bcast(a[0], 0)), bad);
+}
+
 // Value of v on lane l (uniform) of the wavefront.
 template <typename T>
 __device__ __forceinline__ T lane_bcast(T v, int l) {

@@ -13,18 +13,20 @@
 //  * update tasks, one per block that is eliminated later: subtract the
 //    products of the columns of the level before.
 // The chain per level is one launch: loads, the diagonal block's update, four
-// 16-column panels, one product.  On 1000 keyframes with loop closures
-// (5,994 unknowns) an iteration's factor and solve take 26 launches of 15.4 us and
-// one of 34 us, against 94 dependent pairs of launches (10.4 + 5.5 us) and a
+// 16-column panels, one product; the panels' pivot chain is what bounds it
+// (14.2 of 33 thousand cycles before the columns were updated by fused
+// broadcast multiply-adds).  On 1000 keyframes with loop closures (5,994
+// unknowns) an iteration's factor and solve take 26 launches of 12.6 us and one
+// of 34 us, against 94 dependent pairs of launches (10.4 + 5.5 us) and a
 // triangular chain of 118 us when the blocks were eliminated one after another:
-// 9.09 -> 3.22 ms for five iterations.  A Sim(3) pose graph of 1000 keyframes
-// (float64) takes 8 levels of 20.5 us instead of 109 pairs of 22.4 + 5.0 us:
-// 35.9 -> 3.7 ms for ten iterations.
+// 9.09 -> 2.80 ms for five iterations.  A Sim(3) pose graph of 1000 keyframes
+// (float64) takes 8 levels of 14.3 us instead of 109 pairs of 22.4 + 5.0 us:
+// 36.1 -> 3.0 ms for ten iterations.
 //
-// Matrix-core operands come straight from memory: lane (r, q) of a 16-row
-// strip loads 16 bytes at column 4 V s + V q (V values of 16 bytes), so one
-// load feeds V product steps whose four column groups are (s, c) -- the same
-// permutation of the columns on both sides.
+// Blocks are staged in LDS by the whole workgroup (16 bytes a thread,
+// coalesced) and the matrix-core operands read from there: straight from
+// memory every wavefront loaded its own strips, three to six times a block
+// (13.7 us a level in float32, 19.6 us in float64).
 #include <algorithm>
 #include <cfloat>
 
@@ -43,37 +45,45 @@ template <typename T> struct V16;
 template <> struct V16<float> { typedef float type __attribute__((ext_vector_type(4))); };
 template <> struct V16<double> { typedef double type __attribute__((ext_vector_type(2))); };
 
-// 16 rows of a block as matrix-core operands (see the file comment).
-template <typename T>
-struct Strip {
-  static constexpr int V = 16 / (int)sizeof(T), NS = kBlk / (4 * V);
-  typename V16<T>::type x[NS];
-  __device__ __forceinline__ void load(const T* blk, int r0) {
-    const int lane = threadIdx.x & 63;
-    const typename V16<T>::type* p =
-        reinterpret_cast<const typename V16<T>::type*>(blk + (r0 + (lane & 15)) * kBlk) + (lane >> 4);
-#pragma unroll
-    for (int s = 0; s < NS; ++s) x[s] = p[4 * s];
-  }
-};
-
-template <typename T>
-__device__ __forceinline__ typename Mfma<T>::acc_t strip_mma(const Strip<T>& a, const Strip<T>& b,
-                                                             typename Mfma<T>::acc_t acc) {
-#pragma unroll
-  for (int s = 0; s < Strip<T>::NS; ++s)
-#pragma unroll
-    for (int c = 0; c < Strip<T>::V; ++c) acc = Mfma<T>::step(a.x[s][c], b.x[s][c], acc);
-  return acc;
-}
-
 // stride of a staged block: 16-row operand reads on different LDS banks
 template <typename T>
 __host__ __device__ constexpr int staged_ld() { return sizeof(T) == 4 ? kBlk + 4 : kBlk + 2; }
 
 template <typename T>
 __host__ __device__ constexpr int level_lds_elems() {
-  return 2 * kBlk * kLd + kBlk * staged_ld<T>() + kBlk + 8 * kBlk;
+  return 2 * kBlk * kLd + 2 * kBlk * staged_ld<T>() + kBlk + 8 * kBlk;
+}
+
+// A block on its way from memory to LDS: 16-byte vectors of 512 threads.
+template <typename T>
+struct Stage {
+  static constexpr int V = 16 / (int)sizeof(T), N = kBB / V / kLevelThreads;
+  typename V16<T>::type x[N];
+  __device__ __forceinline__ void load(const T* blk) {
+    const typename V16<T>::type* p = reinterpret_cast<const typename V16<T>::type*>(blk) + threadIdx.x;
+#pragma unroll
+    for (int u = 0; u < N; ++u) x[u] = p[u * kLevelThreads];
+  }
+  __device__ __forceinline__ void store(T* lds) const {
+#pragma unroll
+    for (int u = 0; u < N; ++u) {
+      const int q = (int)threadIdx.x + u * kLevelThreads, r = q / (kBlk / V), c = V * (q % (kBlk / V));
+      *reinterpret_cast<typename V16<T>::type*>(lds + r * staged_ld<T>() + c) = x[u];
+    }
+  }
+};
+
+// acc += X Y^T for rows rx .. of X and ry .. of Y (staged blocks).
+template <typename T>
+__device__ __forceinline__ typename Mfma<T>::acc_t staged_mma(const T* X, int rx, const T* Y, int ry,
+                                                              typename Mfma<T>::acc_t acc) {
+  constexpr int ld = staged_ld<T>();
+  const int lane = threadIdx.x & 63;
+  const T* x = X + (rx + (lane & 15)) * ld + (lane >> 4);
+  const T* y = Y + (ry + (lane & 15)) * ld + (lane >> 4);
+#pragma unroll
+  for (int k = 0; k < kBlk; k += 4) acc = Mfma<T>::step(x[k], y[k], acc);
+  return acc;
 }
 
 // Rank-16 update of the working matrix by panel p: the 16 x 16 blocks (bi, bk), bk =
@@ -110,63 +120,25 @@ __device__ __forceinline__ void diag_update_blocks(T* W, int p, int bk_lo, int b
 // takes row block q of the four that can be non-zero -- the A rows of the later
 // blocks, the identity rows of the earlier panels and of this one; the
 // identity rows of later panels are still zero in this column block).
-// Column entries travel by the DPP row broadcast, a vector-register move
-// within each 16-lane row, so the chain of 16 pivots takes no scalar
-// registers and no barrier.  Entries above the diagonal are never read as
-// results.  dd: the block's damped diagonal entries (pivot report).
+// Column entries travel by the DPP row broadcast inside the multiply-adds
+// (chol16), so the chain of 16 pivots takes no scalar registers and no barrier.
 template <typename T>
-__device__ __forceinline__ void diag_panel(T* W, int p, int size, const T* dd, int& bad, unsigned int& minr) {
+__device__ __forceinline__ void diag_panel(T* W, int p, int& bad) {
   const int lane = threadIdx.x & 63, s = lane & 15, q = lane >> 4, c0 = 16 * p;
   const int bq = q < 3 - p ? p + 1 + q : 4 + (q - (3 - p));
   T* wa = W + (c0 + s) * kLd + c0;
   T* wb = W + (16 * bq + s) * kLd + c0;
-  const T ddv = c0 + s < size ? dd[c0 + s] : (T)1;
   T ra[16], rb[16];
 #pragma unroll
   for (int c = 0; c < 16; ++c) {
     ra[c] = wa[c];
     rb[c] = wb[c];
   }
-  T dpiv = (T)0;  // lane c: the pivot of column c
-  auto pivot = [&](int c) {
-    const T d = row_bcast(ra[c], c);
-    dpiv = s == c ? d : dpiv;
-    const bool ok = d > (T)0 && d < (T)3.0e38;
-    bad |= !ok;
-    return ok ? pivot_rsqrt<T>(d) : (T)1;
-  };
-  // Column c: scale it, update column c + 1 and start its pivot at once, so
-  // that the chain of pivots runs beside the other columns' updates; the
-  // scheduling barriers keep a column's broadcasts in registers one column at a time.
-  T rs = pivot(0);
-#pragma unroll
-  for (int c = 0; c < 16; ++c) {
-    ra[c] *= rs;
-    rb[c] *= rs;
-    if (c < 15) {
-      const T l = row_bcast(ra[c], c + 1);  // L(c0 + c + 1, c0 + c)
-      ra[c + 1] -= ra[c] * l;
-      rs = pivot(c + 1);
-      rb[c + 1] -= rb[c] * l;
-    }
-#pragma unroll
-    for (int c2 = c + 2; c2 < 16; ++c2) {
-      const T l = row_bcast(ra[c], c2);
-      ra[c2] -= ra[c] * l;
-      rb[c2] -= rb[c] * l;
-    }
-    __builtin_amdgcn_sched_barrier(0);
-  }
+  chol16<T>(ra, rb, bad);
   // (the stores that depend on the lane come last: a branch here would sink
-  // the rows' updates below it and hold every broadcast of the panel)
+  // the rows' updates below it)
 #pragma unroll
   for (int c = 0; c < 16; ++c) wb[c] = rb[c];
-  // pivot report of the panel: lane s takes column c0 + s (a NaN counts as 0)
-  const float ratio = c0 + s < size ? (float)(dpiv / ddv) : 3.0e38f;
-  unsigned int m = __float_as_uint(ratio == ratio ? fmaxf(ratio, 0.f) : 0.f);
-#pragma unroll
-  for (int o = 8; o > 0; o >>= 1) m = min(m, (unsigned int)__shfl_xor((int)m, o));
-  minr = min(minr, m);
   if (q == 0) {
 #pragma unroll
     for (int c = 0; c < 16; ++c) wa[c] = ra[c];
@@ -175,19 +147,18 @@ __device__ __forceinline__ void diag_panel(T* W, int p, int size, const T* dd, i
 
 // One launch of the factor: workgroups [0, n_task) are the level's tasks,
 // the rest its updates (listed, or the pairs of rows of column impl).
-// float32: two workgroups per CU (128 registers), for the updates; float64
-// holds one (103 KB of LDS).
+// float32: two workgroups per CU (128 registers, 70 KB of LDS), for the
+// updates; float64 holds one (139 KB).
 template <typename T>
 __global__ void __launch_bounds__(kLevelThreads) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 4 : 2)))
-sparse_level_kernel(T* A, T* Linv, T* v, const T* d0, SparsePlan P,
-                                                                     const LevelTask* tasks, int n_task,
-                                                                     const UpdateTask* updates, int impl, int lev,
-                                                                     int* status, unsigned int* min_bits) {
+sparse_level_kernel(T* A, T* Linv, T* v, const T* d0, SparsePlan P, const LevelTask* tasks, int n_task,
+                    const UpdateTask* updates, int impl, int lev, int* status, unsigned int* min_bits) {
   extern __shared__ __align__(16) unsigned char dyn_lds[];
-  T* W = reinterpret_cast<T*>(dyn_lds);  // 128 x 64, row stride kLd
-  T* sM = W + 2 * kBlk * kLd;            // 64 x 64, row stride staged_ld
-  T* sb = sM + kBlk * staged_ld<T>();    // 64: the column's right-hand side
-  T* part = sb + kBlk;                   // 8 x 64 partial sums
+  T* sM = reinterpret_cast<T*>(dyn_lds);  // staged block of row I, then A_IK
+  T* sK = sM + kBlk * staged_ld<T>();     // staged block of row K
+  T* W = sK + kBlk * staged_ld<T>();      // 128 x 64, row stride kLd
+  T* sb = W + 2 * kBlk * kLd;             // 64: the column's right-hand side
+  T* part = sb + kBlk;                    // 8 x 64 partial sums
   constexpr int ldM = staged_ld<T>();
   const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
   typedef typename Mfma<T>::acc_t acc_t;
@@ -195,7 +166,8 @@ sparse_level_kernel(T* A, T* Linv, T* v, const T* d0, SparsePlan P,
   if ((int)blockIdx.x >= n_task) {
     // ---- update of a block that is eliminated by a later launch
     const int u = blockIdx.x - n_task;
-    int blk, ns, row, one_a = 0, one_b = 0, one_J = 0;
+    int blk, ns, row;
+    UpdateSrc one{0, 0, 0, 0};
     const UpdateSrc* src = nullptr;
     if (impl < 0) {
       const UpdateTask t = updates[u];
@@ -203,6 +175,7 @@ sparse_level_kernel(T* A, T* Linv, T* v, const T* d0, SparsePlan P,
       ns = t.ns;
       row = t.row;
       src = P.srcs + t.s0;
+      one = src[0];
     } else {  // pair a >= b of the column's rows
       int a = (int)((sqrtf(8.0f * (float)u + 1.0f) - 1.0f) * 0.5f);
       while (a * (a + 1) / 2 > u) --a;
@@ -219,32 +192,40 @@ sparse_level_kernel(T* A, T* Linv, T* v, const T* d0, SparsePlan P,
       blk = lo;
       ns = 1;
       row = a == b ? I : -1;
-      one_a = c0 + a;
-      one_b = c0 + b;
-      one_J = impl;
+      one = UpdateSrc{c0 + a, c0 + b, impl, 0};
     }
     T* tgt = A + (size_t)blk * kBB;
     const int tr = w & 3, tc0 = 2 * (w >> 2);  // 16-row strip tr, column tiles tc0 and tc0 + 1
-    const bool diag = row >= 0;                // only its lower 16 x 16 tiles
+    const bool diag = row >= 0;                // only its lower 16 x 16 tiles, and one operand block
     const bool on0 = !diag || tc0 <= tr, on1 = !diag || tc0 + 1 <= tr;
     acc_t acc0 = zero, acc1 = zero;
     T bsum = (T)0;
+    T old[8];  // the target's own entries
+#pragma unroll
+    for (int m = 0; m < 4; ++m) {
+      const T* d = tgt + (16 * tr + Mfma<T>::row(lane, m)) * kBlk + (lane & 15);
+      old[m] = on0 ? d[16 * tc0] : (T)0;
+      old[4 + m] = on1 ? d[16 * (tc0 + 1)] : (T)0;
+    }
+    Stage<T> gx, gy;
+    gx.load(A + (size_t)one.ij * kBB);
+    if (!diag) gy.load(A + (size_t)one.jj * kBB);
     for (int x = 0; x < ns; ++x) {
-      const int ij = src ? src[x].ij : one_a, jj = src ? src[x].jj : one_b, J = src ? src[x].J : one_J;
-      const T* X = A + (size_t)ij * kBB;
-      const T* Y = A + (size_t)jj * kBB;
-      if (on0) {
-        Strip<T> a, b;
-        a.load(X, 16 * tr);
-        b.load(Y, 16 * tc0);
-        acc0 = strip_mma<T>(a, b, acc0);
-        if (on1) {
-          b.load(Y, 16 * (tc0 + 1));
-          acc1 = strip_mma<T>(a, b, acc1);
-        }
+      const int J = one.J;
+      if (x) __syncthreads();  // the blocks before are still read
+      gx.store(sM);
+      if (!diag) gy.store(sK);
+      __syncthreads();
+      if (x + 1 < ns) {  // the next source's blocks load beside this one's products
+        one = src[x + 1];
+        gx.load(A + (size_t)one.ij * kBB);
+        if (!diag) gy.load(A + (size_t)one.jj * kBB);
       }
+      const T* Y = diag ? sM : sK;
+      if (on0) acc0 = staged_mma<T>(sM, 16 * tr, Y, 16 * tc0, acc0);
+      if (on1) acc1 = staged_mma<T>(sM, 16 * tr, Y, 16 * (tc0 + 1), acc1);
       if (diag) {  // row lane, columns 8 w ..
-        const T* xr = X + lane * kBlk + 8 * w;
+        const T* xr = sM + lane * ldM + 8 * w;
         const T* y = v + kBlk * J + 8 * w;
 #pragma unroll
         for (int m = 0; m < 8; ++m) bsum += xr[m] * y[m];
@@ -253,8 +234,8 @@ sparse_level_kernel(T* A, T* Linv, T* v, const T* d0, SparsePlan P,
 #pragma unroll
     for (int m = 0; m < 4; ++m) {
       T* d = tgt + (16 * tr + Mfma<T>::row(lane, m)) * kBlk + (lane & 15);
-      if (on0) d[16 * tc0] -= acc0[m];
-      if (on1) d[16 * (tc0 + 1)] -= acc1[m];
+      if (on0) d[16 * tc0] = old[m] - acc0[m];
+      if (on1) d[16 * (tc0 + 1)] = old[4 + m] - acc1[m];
     }
     if (diag) {
       part[kBlk * w + lane] = bsum;
@@ -271,90 +252,110 @@ sparse_level_kernel(T* A, T* Linv, T* v, const T* d0, SparsePlan P,
 
   // ---- task (I, K)
   const LevelTask t = tasks[blockIdx.x];
-  const int K = t.K, dblk = P.colptr[K], size = P.size[K];
-  const bool is_diag = t.blk == dblk;
+  const int K = t.K, size = t.size;
+  const bool is_diag = t.blk == t.dblk;
   const int np = (size + 15) >> 4;  // panels with a used column (the rest of the block is identity)
-  const T* DK = A + (size_t)dblk * kBB;
   T* tgt = A + (size_t)t.blk * kBB;
   if (w == 0) __builtin_amdgcn_s_setprio(3);
-  // identity half of W, and the damped diagonal
-  {
+  // everything that the task reads starts to load at once: the first child's
+  // blocks, the diagonal block (wavefronts 0..3: three, three, two and two of its
+  // ten lower 16 x 16 tiles) and A_IK (wavefronts 4..7: 16 rows each)
+  Stage<T> gk, gi;
+  bool has_i = !is_diag && t.nj > 0 && t.first.ij >= 0;
+  if (t.nj > 0) gk.load(A + (size_t)t.first.kj * kBB);
+  if (has_i) gi.load(A + (size_t)t.first.ij * kBB);
+  const int r0m = 16 * (w & 3);
+  const int nt = w < 2 ? 3 : 2;
+  auto ti = [&](int h) { return w == 0 ? (h ? 1 : 0) : (w == 1 ? 2 : 3); };
+  auto tj = [&](int h) { return w == 0 ? (h == 2 ? 1 : 0) : (w == 1 ? h : (w == 2 ? 2 + h : h)); };
+  T own[16];
+  if (w < 4) {
+    const T* DK = A + (size_t)t.dblk * kBB;
+#pragma unroll
+    for (int h = 0; h < 3; ++h)
+#pragma unroll
+      for (int m = 0; m < 4; ++m)
+        own[4 * h + m] = h < nt ? DK[(16 * ti(h) + Mfma<T>::row(lane, m)) * kBlk + 16 * tj(h) + (lane & 15)] : (T)0;
+  } else if (!is_diag) {
+#pragma unroll
+    for (int h = 0; h < 4; ++h)
+#pragma unroll
+      for (int m = 0; m < 4; ++m)
+        own[4 * h + m] = tgt[(r0m + Mfma<T>::row(lane, m)) * kBlk + 16 * h + (lane & 15)];
+  }
+  {  // identity half of W
     const int r = tid >> 3, c0 = 8 * (tid & 7);
     T* wr = W + (kBlk + r) * kLd + c0;
 #pragma unroll
     for (int c = 0; c < 8; ++c) wr[c] = (T)(c0 + c == r ? 1 : 0);
-    if (tid < kBlk) sb[tid] = d0[kBlk * K + tid];
   }
-  // the diagonal block less what the level before owes it: lower 16 x 16
-  // tiles w and w + 8 (< 10)
-#pragma unroll 1
-  for (int h = 0; h < 2; ++h) {
-    const int tile = w + 8 * h;
-    if (tile >= 10) break;
-    int ti = 0;
-    while ((ti + 1) * (ti + 2) / 2 <= tile) ++ti;
-    const int tj = tile - ti * (ti + 1) / 2;
-    T a0[4];
+  acc_t acc[4] = {zero, zero, zero, zero};
+  T bsum = (T)0;
+  int J = t.first.J;
+  // A_IK's (or, for the diagonal block's task, the right-hand side's) share of
+  // the staged child, on wavefronts 4..7
+  auto row_share = [&]() {
+    if (!is_diag) {
+      if (has_i) {
 #pragma unroll
-    for (int m = 0; m < 4; ++m) a0[m] = DK[(16 * ti + Mfma<T>::row(lane, m)) * kBlk + 16 * tj + (lane & 15)];
-    acc_t acc = zero;
-    for (int j = 0; j < t.nj; ++j) {
-      const T* X = A + (size_t)P.children[t.j0 + j].kj * kBB;
-      Strip<T> a, b;
-      a.load(X, 16 * ti);
-      b.load(X, 16 * tj);
-      acc = strip_mma<T>(a, b, acc);
+        for (int h = 0; h < 4; ++h) acc[h] = staged_mma<T>(sM, r0m, sK, 16 * h, acc[h]);
+      }
+    } else {
+      const T* xr = sK + lane * ldM + r0m;
+      const T* y = v + kBlk * J + r0m;
+#pragma unroll
+      for (int m = 0; m < 16; ++m) bsum += xr[m] * y[m];
     }
+  };
+  for (int j = 0; j < t.nj; ++j) {
+    if (j) {  // rare: a column with several children of the level before
+      if (w >= 4) row_share();
+      const LevelChild ch = P.children[t.j0 + j];
+      has_i = !is_diag && ch.ij >= 0;
+      J = ch.J;
+      gk.load(A + (size_t)ch.kj * kBB);
+      if (has_i) gi.load(A + (size_t)ch.ij * kBB);
+      __syncthreads();
+    }
+    gk.store(sK);
+    if (has_i) gi.store(sM);
+    __syncthreads();
+    if (w < 4) {
 #pragma unroll
-    for (int m = 0; m < 4; ++m)
-      W[(16 * ti + Mfma<T>::row(lane, m)) * kLd + 16 * tj + (lane & 15)] = a0[m] - acc[m];
+      for (int h = 0; h < 3; ++h)
+        if (h < nt) acc[h] = staged_mma<T>(sK, 16 * ti(h), sK, 16 * tj(h), acc[h]);
+    }
+  }
+  if (w < 4) {
+#pragma unroll
+    for (int h = 0; h < 3; ++h)
+      if (h < nt) {
+#pragma unroll
+        for (int m = 0; m < 4; ++m)
+          W[(16 * ti(h) + Mfma<T>::row(lane, m)) * kLd + 16 * tj(h) + (lane & 15)] = own[4 * h + m] - acc[h][m];
+      }
   }
   __syncthreads();
   int bad = 0;
-  unsigned int minr = __float_as_uint(3.0e38f);
   for (int p = 0; p < np; ++p) {
     if (w == 0) {
-      diag_panel<T>(W, p, size, sb, bad, minr);
+      diag_panel<T>(W, p, bad);
     } else if (w < 4) {
       // meanwhile wavefronts 1..3 finish panel p - 1: its update of the later column blocks
       if (p > 0) diag_update_blocks<T>(W, p - 1, p + 1, np - 1, w - 1, 3);
     } else if (p == 0) {
+      // and wavefronts 4..7 finish A_IK less what the level before owes it (in
+      // place of the rows of the staged block that only they read), or the
+      // right-hand side's share
+      if (t.nj > 0) row_share();
       if (!is_diag) {
-        // and wavefronts 4..7 form A_IK less what the level before owes it,
-        // 16 rows each
-        const int r0 = 16 * (w - 4);
-        acc_t acc[4] = {zero, zero, zero, zero};
-        for (int j = 0; j < t.nj; ++j) {
-          const LevelChild ch = P.children[t.j0 + j];
-          if (ch.ij < 0) continue;
-          Strip<T> a, b;
-          a.load(A + (size_t)ch.ij * kBB, r0);
 #pragma unroll
-          for (int tj = 0; tj < 4; ++tj) {
-            b.load(A + (size_t)ch.kj * kBB, 16 * tj);
-            acc[tj] = strip_mma<T>(a, b, acc[tj]);
-            __builtin_amdgcn_sched_barrier(0);  // one strip in registers at a time
-          }
-        }
+        for (int h = 0; h < 4; ++h)
 #pragma unroll
-        for (int tj = 0; tj < 4; ++tj)
-#pragma unroll
-          for (int m = 0; m < 4; ++m) {
-            const int r = r0 + Mfma<T>::row(lane, m), c = 16 * tj + (lane & 15);
-            sM[r * ldM + c] = tgt[r * kBlk + c] - acc[tj][m];
-          }
+          for (int m = 0; m < 4; ++m)
+            sM[(r0m + Mfma<T>::row(lane, m)) * ldM + 16 * h + (lane & 15)] = own[4 * h + m] - acc[h][m];
       } else {
-        // the column's right-hand side less the level before's share: row
-        // lane, 16 columns a wavefront
-        T s = (T)0;
-        for (int j = 0; j < t.nj; ++j) {
-          const LevelChild ch = P.children[t.j0 + j];
-          const T* xr = A + (size_t)ch.kj * kBB + lane * kBlk + 16 * (w - 4);
-          const T* y = v + kBlk * ch.J + 16 * (w - 4);
-#pragma unroll
-          for (int m = 0; m < 16; ++m) s += xr[m] * y[m];
-        }
-        part[kBlk * (w - 4) + lane] = s;
+        part[kBlk * (w - 4) + lane] = bsum;
       }
     }
     __syncthreads();
@@ -405,9 +406,17 @@ sparse_level_kernel(T* A, T* Linv, T* v, const T* d0, SparsePlan P,
     for (int m = 0; m < 8; ++m) s += part[kBlk * m + tid];
     v[kBlk * K + tid] = s;
   }
-  if (tid == 0) {  // wavefront 0 holds the report
-    if (bad) atomicOr(status, 1);
-    atomicMin(min_bits, minr);
+  if (w == 0) {  // wavefront 0 met the pivots; L_ii^2 / S_ii of the used columns
+    const T l = W[lane * kLd + lane];
+    const float ratio = lane < size ? (float)(l * l / d0[kBlk * K + lane]) : 3.0e38f;
+    unsigned int m = __float_as_uint(l > (T)0 && ratio == ratio ? fmaxf(ratio, 0.f) : 0.f);
+    if (lane >= size) m = __float_as_uint(3.0e38f);
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) m = min(m, (unsigned int)__shfl_xor((int)m, o));
+    if (lane == 0) {
+      if (bad) atomicOr(status, 1);
+      atomicMin(min_bits, m);
+    }
   }
 }
 
