@@ -79,10 +79,6 @@ hipError_t launch_small_chol(const T* S, const T* rhs, int n, T* dx, int* status
                              hipStream_t st);
 hipError_t launch_report_init(int* status, unsigned int* min_bits, int n, hipStream_t st, int* err_clear = nullptr);
 // mixed-precision helpers (mixed.hip)
-template <typename Ti, typename To>
-hipError_t launch_convert(const Ti* src, To* dst, long long n, hipStream_t st);
-hipError_t launch_accumulate(double* x, const float* c, int n, hipStream_t st, const int* skip = nullptr);
-hipError_t launch_refine_check(const unsigned long long* maxes, double tol, int* skip, hipStream_t st);
 hipError_t launch_refine_decide(const unsigned long long* maxes, const int* status32, double tol, int force,
                                 double* resid_out, int* fallback_out, int* host_flag, hipStream_t st);
 hipError_t launch_step_to_f32(const double* x, const int* row0, float* dx, int n, const int* fallback,
@@ -375,6 +371,16 @@ static hipError_t upload_plan(PlanStore& ps, const std::vector<PosePair>* pairs,
   return hipSuccess;
 }
 
+// Refinement of the float32 Cholesky solve against the float64 residual:
+// fixed number of steps, and the largest accepted relative residual.
+constexpr int kRefineSteps = 2;
+constexpr double kRefineTol = 1e-8;
+// The last refinement step is left out once the residual is this small.  A
+// residual rho leaves a relative step error of up to kappa rho: with kappa =
+// 1e6 (forward motion, additive damping) 1e-12 keeps it at float32 rounding,
+// where stopping at kRefineTol left up to 1e-4 of the pose step.
+constexpr double kRefineStop = 1e-12;
+
 struct dpvba_ctx {
   int device = 0;
   // analysed graph
@@ -409,7 +415,7 @@ struct dpvba_ctx {
   // pose (pose_off / pose_src = 2 e + side), tile-order position of a patch
   DevBuf pcount, pedges, pose_off, pose_src, patch_pos;
   // mixed precision: float32 factor, float64 iterate and residual, decision state
-  DevBuf S32, x64, r64, rhs32, c32, d0_32, mx_max, mx_resid, mx_fb, mx_flag;
+  DevBuf S32, x64, x64b, rhs32, c32, d0_32, mx_max, mx_resid, mx_fb, mx_flag;
   int* host_flag = nullptr;  // pinned
   // batch analysis
   struct Batch {
@@ -730,7 +736,7 @@ void dpvba_destroy(dpvba_ctx* c) {
                     &c->chain_flags, &c->one_inst, &c->sys_x,
                     &c->pcount, &c->pedges, &c->pose_off, &c->pose_src, &c->patch_pos, &c->bw_poses, &c->bw_depth,
                     &c->bw_dx, &c->bw_pbar, &c->bw_dbar, &c->bw_dxbar, &c->bw_rhs, &c->bw_up, &c->bw_ud, &c->bw_dd,
-                    &c->bw_edge, &c->bw_status, &c->bw_minbits, &c->S32, &c->x64, &c->r64, &c->rhs32, &c->c32,
+                    &c->bw_edge, &c->bw_status, &c->bw_minbits, &c->S32, &c->x64, &c->x64b, &c->rhs32, &c->c32,
                     &c->d0_32, &c->mx_max, &c->mx_resid, &c->mx_fb, &c->mx_flag, &c->pg_C, &c->pg_ea, &c->pg_eb,
                     &c->pg_r, &c->pg_J, &c->pg_H, &c->pg_rhs, &c->pg_dx, &c->pg_d0, &c->pg_Linv,
                     &c->pg_flags, &c->pg_status, &c->pg_mb, &c->pg_cost, &c->pg_blk_pq, &c->pg_blk_off,
@@ -1151,12 +1157,12 @@ dpvba_status dpvba_analyze_ex(dpvba_ctx* c, const dpvba_graph* g, const dpvba_tu
   if (sparse32) {  // mixed precision: the float32 factor and its vectors
     HIP_TRY(ensure(c->S32, blk_elems * 4));
     HIP_TRY(ensure(c->x64, npad * 8));
-    HIP_TRY(ensure(c->r64, npad * 8));
+    HIP_TRY(ensure(c->x64b, npad * 8));
     HIP_TRY(ensure(c->rhs32, npad * 4));
     HIP_TRY(ensure(c->c32, npad * 4));
     HIP_TRY(ensure(c->d0_32, npad * 4));
   }
-  HIP_TRY(ensure(c->mx_max, 16));
+  HIP_TRY(ensure(c->mx_max, 16 * (kRefineSteps + 1)));
   HIP_TRY(ensure(c->mx_resid, DPVBA_MAX_ITERS * 8));
   HIP_TRY(ensure(c->mx_fb, DPVBA_MAX_ITERS * 4));
   HIP_TRY(ensure(c->mx_flag, 16));
@@ -1526,16 +1532,6 @@ static hipError_t solve_impl(dpvba_ctx* c, const dpvba_graph* g, T* poses, T* de
   return hipMemcpyAsync(report, dev, sizeof(dpvba_report), hipMemcpyDeviceToHost, st);
 }
 
-// Refinement of the float32 Cholesky solve against the float64 residual:
-// fixed number of steps, and the largest accepted relative residual.
-constexpr int kRefineSteps = 2;
-constexpr double kRefineTol = 1e-8;
-// The last refinement step is left out once the residual is this small.  A
-// residual rho leaves a relative step error of up to kappa rho: with kappa =
-// 1e6 (forward motion, additive damping) 1e-12 keeps it at float32 rounding,
-// where stopping at kRefineTol left up to 1e-4 of the pose step.
-constexpr double kRefineStop = 1e-12;
-
 // DPVBA_MIXED: float32 state and tile assembly, float64 gather of the
 // shares, float32 Cholesky with float64 iterative refinement, float64
 // Cholesky when refinement does not reach kRefineTol (decided on the host
@@ -1563,7 +1559,7 @@ static hipError_t solve_mixed_impl(dpvba_ctx* c, const dpvba_graph* g, float* po
   float* S32 = (float*)c->S32.p;
   float* Linv32 = (float*)c->Linv.p;
   double* x64 = (double*)c->x64.p;
-  double* r64 = (double*)c->r64.p;
+  double* x64b = (double*)c->x64b.p;
   float* rhs32 = (float*)c->rhs32.p;
   float* c32 = (float*)c->c32.p;
   float* d032 = (float*)c->d0_32.p;
@@ -1637,31 +1633,33 @@ static hipError_t solve_mixed_impl(dpvba_ctx* c, const dpvba_graph* g, float* po
     if (n > 0) {
       TraceScope ts(c, DPVBA_PHASE_FACTOR, st);
       const SparsePlan& p = c->ba_plan.plan;
-      const int np = kBlk * p.nb;
       unsigned long long* words = (unsigned long long*)c->chain_flags.p;
       // the factor leaves y = L^-1 s in y32, so the first solve is the backward pass alone
       float* y32 = (float*)c->wy.p;
-      if ((e = launch_convert<double, float>(s64, y32, np, st)) != hipSuccess) return e;
+      if ((e = launch_sparse_refine_begin(p, s64, y32, maxes, n_refine + 1, st)) != hipSuccess) return e;
       if ((e = launch_sparse_factor<float>(p, S32, Linv32, y32, d032, status + it, mb + it, st)) != hipSuccess) return e;
       if ((e = launch_sparse_solve<float>(p, S32, Linv32, nullptr, y32, c32, words, next_epoch(c), err, c->host_err_dev,
                                           st, true, c->coop_launch)) != hipSuccess)
         return e;
-      if ((e = launch_convert<float, double>(c32, x64, np, st)) != hipSuccess) return e;
-      int* skip = (int*)c->mx_flag.p + 1;  // set on the device once the residual meets the tolerance
-      for (int k = 0; k < n_refine; ++k) {
-        if ((e = launch_sparse_residual(p, S64, s64, x64, r64, maxes, st)) != hipSuccess) return e;
-        // the first step is always taken; a later one only while needed
-        if (k > 0 && (e = launch_refine_check(maxes, kRefineStop, skip, st)) != hipSuccess) return e;
-        if ((e = launch_convert<double, float>(r64, rhs32, np, st)) != hipSuccess) return e;
-        if ((e = launch_sparse_solve<float>(p, S32, Linv32, rhs32, y32, c32, words, next_epoch(c), err,
-                                            c->host_err_dev, st, false, c->coop_launch, k > 0 ? skip : nullptr)) !=
+      // step k forms x from the solve before and its residual (pair k of the
+      // maxima); the first refinement solve is always taken, a later one and
+      // its correction only while the residual is above kRefineStop
+      double* xk = nullptr;
+      for (int k = 0; k <= n_refine; ++k) {
+        double* xo = k & 1 ? x64b : x64;
+        const unsigned long long* stop = k > 1 ? maxes + 2 * (k - 1) : nullptr;
+        if ((e = launch_sparse_residual(p, S64, s64, xk, c32, stop, kRefineStop, xo, rhs32, maxes + 2 * k, st)) !=
             hipSuccess)
           return e;
-        if ((e = launch_accumulate(x64, c32, np, st, k > 0 ? skip : nullptr)) != hipSuccess) return e;
+        xk = xo;
+        if (k == n_refine) break;
+        if ((e = launch_sparse_solve<float>(p, S32, Linv32, rhs32, y32, c32, words, next_epoch(c), err,
+                                            c->host_err_dev, st, false, c->coop_launch,
+                                            k > 0 ? maxes + 2 * k : nullptr, kRefineStop)) != hipSuccess)
+          return e;
       }
-      if ((e = launch_sparse_residual(p, S64, s64, x64, r64, maxes, st)) != hipSuccess) return e;
-      if ((e = launch_refine_decide(maxes, status + it, kRefineTol, force_fb ? 1 : 0, resid + it, fb + it,
-                                    (int*)c->mx_flag.p, st)) != hipSuccess)
+      if ((e = launch_refine_decide(maxes + 2 * n_refine, status + it, kRefineTol, force_fb ? 1 : 0, resid + it,
+                                    fb + it, (int*)c->mx_flag.p, st)) != hipSuccess)
         return e;
       bool run64 = force_fb;
       if (!force_fb) {
@@ -1674,11 +1672,11 @@ static hipError_t solve_mixed_impl(dpvba_ctx* c, const dpvba_graph* g, float* po
         if ((e = launch_sparse_factor<double>(p, S64, (double*)c->Linv.p, s64, d064, status64 + it, mb64 + it, st)) !=
             hipSuccess)
           return e;
-        if ((e = launch_sparse_solve<double>(p, S64, (const double*)c->Linv.p, nullptr, s64, x64, words, next_epoch(c),
+        if ((e = launch_sparse_solve<double>(p, S64, (const double*)c->Linv.p, nullptr, s64, xk, words, next_epoch(c),
                                              err, c->host_err_dev, st, true, c->coop_launch)) != hipSuccess)
           return e;
       }
-      if ((e = launch_step_to_f32(x64, p.row0, dx, n, fb + it, status64 + it, status + it, st)) != hipSuccess) return e;
+      if ((e = launch_step_to_f32(xk, p.row0, dx, n, fb + it, status64 + it, status + it, st)) != hipSuccess) return e;
     }
     {
       TraceScope ts(c, DPVBA_PHASE_RETRACT, st);

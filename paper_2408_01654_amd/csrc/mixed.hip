@@ -5,34 +5,14 @@
 // Given S64 (float64 block storage of an elimination plan) and s64 gathered from the float32 tile
 // shares: factor S32 = fl32(S64) once, solve, then repeat
 //   r = s64 - S64 x   (float64),   x += (L L^T)^-1 fl32(r)
-// a fixed number of times.  The iteration is accepted when
+// a fixed number of times (the last left out at a residual where it gains
+// nothing; sparse.hip holds the steps).  The iteration is accepted when
 // max |r| <= tol max |s64| after the last step; otherwise (or when the
 // float32 factorisation met a non-positive pivot) the caller re-solves with
 // a float64 Cholesky of S64.
 #include "common.h"
 
 namespace dpvba {
-
-template <typename Ti, typename To>
-__global__ void convert_kernel(const Ti* src, To* dst, long long n) {
-  const long long q = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (q < n) dst[q] = (To)src[q];
-}
-
-// x64 += c32 (nothing when *skip: that refinement step was not taken)
-__global__ void accumulate_kernel(double* x, const float* c, int n, const int* skip) {
-  const int q = blockIdx.x * blockDim.x + threadIdx.x;
-  if (q < n && !(skip && *skip)) x[q] += (double)c[q];
-}
-
-// *skip = the relative residual (largest |r_i| / largest |s_i|) already
-// meets the tolerance: the remaining refinement steps are not taken.
-__global__ void refine_check_kernel(const unsigned long long* m, double tol, int* skip) {
-  if (threadIdx.x != 0) return;
-  const double rmax = __longlong_as_double((long long)m[0]);
-  const double smax = __longlong_as_double((long long)m[1]);
-  *skip = (smax > 0.0 ? rmax / smax : rmax) <= tol;
-}
 
 // Accept or fall back; records the relative residual and the decision.
 __global__ void refine_decide_kernel(const unsigned long long* m, const int* status32, double tol, int force,
@@ -61,24 +41,6 @@ __global__ void step_to_f32_kernel(const double* x, const int* row0, float* dx, 
 
 static inline unsigned nblocks(long long n, int bs) { return (unsigned)((n + bs - 1) / bs); }
 
-template <typename Ti, typename To>
-hipError_t launch_convert(const Ti* src, To* dst, long long n, hipStream_t st) {
-  if (n <= 0) return hipSuccess;
-  hipLaunchKernelGGL((convert_kernel<Ti, To>), dim3(nblocks(n, 256)), dim3(256), 0, st, src, dst, n);
-  return hipGetLastError();
-}
-
-hipError_t launch_refine_check(const unsigned long long* maxes, double tol, int* skip, hipStream_t st) {
-  hipLaunchKernelGGL(refine_check_kernel, dim3(1), dim3(64), 0, st, maxes, tol, skip);
-  return hipGetLastError();
-}
-
-hipError_t launch_accumulate(double* x, const float* c, int n, hipStream_t st, const int* skip) {
-  if (n <= 0) return hipSuccess;
-  hipLaunchKernelGGL(accumulate_kernel, dim3(nblocks(n, 256)), dim3(256), 0, st, x, c, n, skip);
-  return hipGetLastError();
-}
-
 hipError_t launch_refine_decide(const unsigned long long* maxes, const int* status32, double tol, int force,
                                 double* resid_out, int* fallback_out, int* host_flag, hipStream_t st) {
   hipLaunchKernelGGL(refine_decide_kernel, dim3(1), dim3(64), 0, st, maxes, status32, tol, force, resid_out,
@@ -92,8 +54,5 @@ hipError_t launch_step_to_f32(const double* x, const int* row0, float* dx, int n
                      status64, status);
   return hipGetLastError();
 }
-
-template hipError_t launch_convert<double, float>(const double*, float*, long long, hipStream_t);
-template hipError_t launch_convert<float, double>(const float*, double*, long long, hipStream_t);
 
 }  // namespace dpvba

@@ -61,9 +61,16 @@ hipError_t launch_sparse_factor(const SparsePlan& p, T* A, T* Linv, T* v, const 
 template <typename T>
 hipError_t launch_sparse_solve(const SparsePlan& p, const T* A, const T* Linv, const T* b, T* y, T* x,
                                unsigned long long* words, int epoch, int* err, int* host_err, hipStream_t st,
-                               bool backward_only, bool cooperative, const int* skip = nullptr);
-// r = s - A x of the unfactored system; maxes[0], [1]: largest |r|, |s|.
-hipError_t launch_sparse_residual(const SparsePlan& p, const double* A, const double* s, const double* x, double* r,
+                               bool backward_only, bool cooperative, const unsigned long long* stop = nullptr,
+                               double tol = 0.0);
+// Refined solve of the unfactored system: y = fl32(s) and n_res pairs of maxima
+// cleared; then x_out = x_in + c (x_in null: c alone; without c when the
+// residual before, stop, is at or below tol), rhs = fl32(s - A x_out), maxes
+// [0], [1]: largest |r|, |s|.
+hipError_t launch_sparse_refine_begin(const SparsePlan& p, const double* s, float* y, unsigned long long* maxes,
+                                      int n_res, hipStream_t st);
+hipError_t launch_sparse_residual(const SparsePlan& p, const double* A, const double* s, const double* x_in,
+                                  const float* c, const unsigned long long* stop, double tol, double* x_out, float* rhs,
                                   unsigned long long* maxes, hipStream_t st);
 // Rows of the poses (bw each) into the padded order (zero elsewhere) and out
 // of it; out of it with *status set: zero.

@@ -478,18 +478,28 @@ __device__ __forceinline__ bool get_word(const unsigned long long* xw, int row, 
   return true;
 }
 
+// Whether a refinement's residual (m[0]: the largest |r_i|, m[1]: |s_i|) is
+// at or below tol; false without a residual, and for NaN.
+__device__ __forceinline__ bool refine_done(const unsigned long long* m, double tol) {
+  if (!m) return false;
+  const double rmax = __longlong_as_double((long long)m[0]), smax = __longlong_as_double((long long)m[1]);
+  return (smax > 0.0 ? rmax / smax : rmax) <= tol;
+}
+
 // Both triangular solves in one launch.  Block columns go to the workgroups
 // by level (forward) and then by descending level (backward): workgroup g
 // takes places g, g + G, ... of that order, so the first unfinished place is
 // always some resident workgroup's next one and nobody waits for a place
 // behind it.  A block's values are loaded before the wait for the vector they
 // multiply; the products are summed per thread over all blocks and reduced
-// once.  With *skip set on the device the whole call is a no-op.
+// once.  With stop given (the largest |r| and |s| of a refinement) the whole
+// call is a no-op when the residual is small enough.
 template <typename T>
 __global__ void __launch_bounds__(256) sparse_solve_kernel(SparsePlan P, const T* A, const T* Linv, const T* b, T* y,
                                                            T* x, unsigned long long* words, int epoch, int* err,
-                                                           int* host_err, int backward_only, const int* skip) {
-  if (skip && *skip) return;
+                                                           int* host_err, int backward_only, const unsigned long long* stop,
+                                                           double tol) {
+  if (refine_done(stop, tol)) return;
   __shared__ T vk[2][kBlk];
   __shared__ T part[4][kBlk];
   __shared__ T sa[kBlk];
@@ -657,44 +667,66 @@ __global__ void __launch_bounds__(256) sparse_clear_kernel(SparsePlan P, T* A, T
   if (diag && (int)threadIdx.x < kBlk) v[kBlk * I + threadIdx.x] = (T)0;
 }
 
-// r = s - A x, one workgroup per block row over the original blocks of the
-// symmetric matrix (the diagonal block's lower triangle counts for both);
-// the largest |r_i| and |s_i| are kept as ordered bits of non-negative doubles
-// (integer maxima, independent of the order of the atomics).
-__global__ void __launch_bounds__(256) sparse_residual_kernel(SparsePlan P, const double* A, const double* s,
-                                                              const double* x, double* r, unsigned long long* rmax,
-                                                              unsigned long long* smax) {
-  __shared__ double part[4][kBlk];
-  __shared__ double xs[kBlk];
+// One step of iterative refinement: x = x_in + c (x_in null: x = c; c left out
+// when the solve that makes it was, as refine_done(stop, tol)), r = s - A x,
+// and r rounded to float32 as the next solve's right-hand side.  One workgroup
+// per block row over the original blocks of the symmetric matrix (the
+// diagonal block's lower triangle counts for both); every row adds c to the x
+// it reads, and its own part of x goes to x_out.  The largest |r_i| and |s_i|
+// are kept as ordered bits of non-negative doubles (integer maxima, independent
+// of the order of the atomics; cleared by sparse_refine_begin_kernel).  Bound
+// by the latency of a row's blocks (up to 20 here): four are read at a time,
+// by 256 threads each (@R@).
+__global__ void __launch_bounds__(1024) sparse_residual_kernel(SparsePlan P, const double* A, const double* s,
+                                                               const double* x_in, const float* c,
+                                                               const unsigned long long* stop, double tol,
+                                                               double* x_out, float* rhs, unsigned long long* maxes) {
+  __shared__ double part[16][kBlk];
+  __shared__ double xs[4][kBlk];
   const int I = blockIdx.x, tid = threadIdx.x;
-  const int a = tid & 63, q = tid >> 6;
+  const int grp = tid >> 8, a = tid & 63, q = (tid >> 6) & 3;
+  const bool add = !refine_done(stop, tol);
+  auto x_at = [&](int row) { return x_in ? (add ? x_in[row] + (double)c[row] : x_in[row]) : (double)c[row]; };
   double v = 0.0;
-  for (int e = P.nptr[I]; e < P.nptr[I + 1]; ++e) {
-    const int2 je = P.nlist[e];
+  const int e0 = P.nptr[I], e1 = P.nptr[I + 1];
+  for (int eb = e0; eb < e1; eb += 4) {
+    const int e = eb + grp;
+    const bool on = e < e1;  // uniform in a group
+    const int2 je = P.nlist[on ? e : e1 - 1];
     const double* B = A + (size_t)(je.y >> 1) * kBB;
-    __syncthreads();
-    if (tid < kBlk) xs[tid] = x[kBlk * je.x + tid];
-    __syncthreads();
+    double b[16];
     if (je.x == I) {  // symmetric from the lower triangle
 #pragma unroll
       for (int m = 0; m < 16; ++m) {
-        const int c = 16 * q + m;
-        v += (c <= a ? B[a * kBlk + c] : B[c * kBlk + a]) * xs[c];
+        const int cc = 16 * q + m;
+        b[m] = cc <= a ? B[a * kBlk + cc] : B[cc * kBlk + a];
       }
     } else if (je.y & 1) {
 #pragma unroll
-      for (int m = 0; m < 16; ++m) v += B[(16 * q + m) * kBlk + a] * xs[16 * q + m];
+      for (int m = 0; m < 16; ++m) b[m] = B[(16 * q + m) * kBlk + a];
     } else {
 #pragma unroll
-      for (int m = 0; m < 16; ++m) v += B[a * kBlk + 16 * q + m] * xs[16 * q + m];
+      for (int m = 0; m < 16; ++m) b[m] = B[a * kBlk + 16 * q + m];
+    }
+    __syncthreads();
+    if (q == 0) xs[grp][a] = on ? x_at(kBlk * je.x + a) : 0.0;
+    __syncthreads();
+    if (on) {
+#pragma unroll
+      for (int m = 0; m < 16; ++m) v += b[m] * xs[grp][16 * q + m];
     }
   }
-  part[q][a] = v;
+  part[tid >> 6][a] = v;
   __syncthreads();
   if (tid < kBlk) {
+    double ax = 0.0;
+#pragma unroll
+    for (int m = 0; m < 16; m += 4)
+      ax += (part[m][tid] + part[m + 1][tid]) + (part[m + 2][tid] + part[m + 3][tid]);
     const double sv = s[kBlk * I + tid];
-    const double rv = sv - ((part[0][tid] + part[1][tid]) + (part[2][tid] + part[3][tid]));
-    r[kBlk * I + tid] = rv;
+    const double rv = sv - ax;
+    x_out[kBlk * I + tid] = x_at(kBlk * I + tid);
+    rhs[kBlk * I + tid] = (float)rv;
     unsigned long long rm = (unsigned long long)__double_as_longlong(fabs(rv));
     unsigned long long sm = (unsigned long long)__double_as_longlong(fabs(sv));
 #pragma unroll
@@ -704,14 +736,18 @@ __global__ void __launch_bounds__(256) sparse_residual_kernel(SparsePlan P, cons
       sm = so > sm ? so : sm;
     }
     if (tid == 0) {
-      atomicMax(rmax, rm);
-      atomicMax(smax, sm);
+      atomicMax(maxes, rm);
+      atomicMax(maxes + 1, sm);
     }
   }
 }
 
-__global__ void sparse_clear_max_kernel(unsigned long long* m) {
-  if (threadIdx.x < 2) m[threadIdx.x] = 0ull;
+// Start of a refined solve: the right-hand side in float32, and the cleared
+// maxima of its n_res residuals.
+__global__ void sparse_refine_begin_kernel(const double* s, float* y, int n, unsigned long long* maxes, int n_res) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < n) y[i] = (float)s[i];
+  if (i < 2 * n_res) maxes[i] = 0ull;
 }
 
 template <typename T>
@@ -787,27 +823,37 @@ static int solve_grid(int nb) {
 template <typename T>
 hipError_t launch_sparse_solve(const SparsePlan& p, const T* A, const T* Linv, const T* b, T* y, T* x,
                                unsigned long long* words, int epoch, int* err, int* host_err, hipStream_t st,
-                               bool backward_only, bool cooperative, const int* skip) {
+                               bool backward_only, bool cooperative, const unsigned long long* stop, double tol) {
   if (p.nb == 0) return hipSuccess;
   const int grid = solve_grid<T>(p.nb);
   if (grid < 1) return hipErrorCooperativeLaunchTooLarge;
   int back = backward_only ? 1 : 0;
   if (!cooperative) {
     hipLaunchKernelGGL((sparse_solve_kernel<T>), dim3(grid), dim3(256), 0, st, p, A, Linv, b, y, x, words, epoch, err,
-                       host_err, back, skip);
+                       host_err, back, stop, tol);
     return hipGetLastError();
   }
   SparsePlan copy = p;
   void* args[] = {(void*)&copy, (void*)&A,     (void*)&Linv, (void*)&b,        (void*)&y,    (void*)&x,
-                  (void*)&words, (void*)&epoch, (void*)&err,  (void*)&host_err, (void*)&back, (void*)&skip};
+                  (void*)&words, (void*)&epoch, (void*)&err,  (void*)&host_err, (void*)&back, (void*)&stop,
+                  (void*)&tol};
   return hipLaunchCooperativeKernel((const void*)sparse_solve_kernel<T>, dim3(grid), dim3(256), args, 0, st);
 }
 
-hipError_t launch_sparse_residual(const SparsePlan& p, const double* A, const double* s, const double* x, double* r,
+hipError_t launch_sparse_residual(const SparsePlan& p, const double* A, const double* s, const double* x_in,
+                                  const float* c, const unsigned long long* stop, double tol, double* x_out, float* rhs,
                                   unsigned long long* maxes, hipStream_t st) {
-  hipLaunchKernelGGL(sparse_clear_max_kernel, dim3(1), dim3(64), 0, st, maxes);
-  if (p.nb > 0)
-    hipLaunchKernelGGL(sparse_residual_kernel, dim3(p.nb), dim3(256), 0, st, p, A, s, x, r, maxes, maxes + 1);
+  if (p.nb == 0) return hipSuccess;
+  hipLaunchKernelGGL(sparse_residual_kernel, dim3(p.nb), dim3(1024), 0, st, p, A, s, x_in, c, stop, tol, x_out, rhs,
+                     maxes);
+  return hipGetLastError();
+}
+
+hipError_t launch_sparse_refine_begin(const SparsePlan& p, const double* s, float* y, unsigned long long* maxes,
+                                      int n_res, hipStream_t st) {
+  if (p.nb == 0) return hipSuccess;
+  hipLaunchKernelGGL(sparse_refine_begin_kernel, dim3((kBlk * p.nb + 255) / 256), dim3(256), 0, st, s, y, kBlk * p.nb,
+                     maxes, n_res);
   return hipGetLastError();
 }
 
@@ -844,7 +890,7 @@ template hipError_t launch_sparse_clear<double>(const SparsePlan&, double*, doub
                                               hipStream_t);                                                          \
   template hipError_t launch_sparse_solve<T>(const SparsePlan&, const T*, const T*, const T*, T*, T*,                 \
                                              unsigned long long*, int, int*, int*, hipStream_t, bool, bool,          \
-                                             const int*);                                                            \
+                                             const unsigned long long*, double);                                     \
   template hipError_t launch_sparse_rows_in<T>(const SparsePlan&, const T*, T*, hipStream_t);                         \
   template hipError_t launch_sparse_rows_out<T>(const SparsePlan&, const T*, T*, const int*, hipStream_t);
 DPVBA_SPARSE_INSTANTIATE(float)
