@@ -675,8 +675,9 @@ __global__ void __launch_bounds__(256) sparse_clear_kernel(SparsePlan P, T* A, T
 // it reads, and its own part of x goes to x_out.  The largest |r_i| and |s_i|
 // are kept as ordered bits of non-negative doubles (integer maxima, independent
 // of the order of the atomics; cleared by sparse_refine_begin_kernel).  Bound
-// by the latency of a row's blocks (up to 20 here): four are read at a time,
-// by 256 threads each (@R@).
+// by the latency of a row's blocks: four are read at a time, by 256 threads
+// each (317 keyframes: 18.1 -> 15.8 us a step, without the five launches of
+// 4.7 us around it).
 __global__ void __launch_bounds__(1024) sparse_residual_kernel(SparsePlan P, const double* A, const double* s,
                                                                const double* x_in, const float* c,
                                                                const unsigned long long* stop, double tol,
