@@ -445,14 +445,14 @@ dpvba_status dpvba_solve_backward(dpvba_ctx* ctx, const dpvba_graph* g, const fl
  * graphs[i], with the i-th entry of every array (host arrays of n device
  * pointers; grad_poses / grad_inv_depth may be NULL, or hold NULL entries,
  * for zero; reports NULL or n host reports, complete once `stream` has
- * completed).  The problems run concurrently,
- * each on a stream of its own context, ordered after the work already on
- * `stream`; `stream` waits for all of them.  Launches whose workgroups
- * wait for each other are cooperative here (dpvba_set_cooperative(1) for
- * the duration of the call), so concurrent grids cannot starve them; the
- * single-launch solver of small problems is then slower than alone, so
- * dpvba_solve_many pays off for large problems, and the adjoint (whose
- * small problems need no such launch) for any.  The contexts must be
+ * completed).  The problems run concurrently: small problems of a
+ * dpvba_solve_many without reports (6 x free poses + 1 <= 96 for all of them,
+ * DPVBA_FP32 or DPVBA_FP64) several to a launch on `stream`, cooperative when
+ * the contexts are set so; all others each on a stream of its own context,
+ * ordered after the work already on `stream`, and `stream` waits for all of
+ * them.  There, launches whose workgroups wait for each other are cooperative
+ * (dpvba_set_cooperative(1) for the duration of the call), so concurrent
+ * grids cannot starve them.  The contexts must be
  * distinct and on one device.  Returns the first failure
  * (every problem is still enqueued and joined); EINVAL for a bad n or
  * context list.                                                           */

@@ -592,9 +592,9 @@ def bundle_adjust(context: Context, graph: GraphTensors, poses0, inv_depth0, tar
 
 
 class _BundleAdjustMany(torch.autograd.Function):
-    """bundle_adjust over several problems: the forwards run one after
-    another on the current stream (ordinary launches: a small problem's
-    single-launch solver is fastest alone), the adjoints concurrently
+    """bundle_adjust over several problems: the forwards of small problems
+    (6 free poses + 1 <= 96) share launches (dpvba_solve_many), others run one
+    after another on the current stream; the adjoints run concurrently
     (dpvba_solve_backward_many).  Inputs: the per-problem targets and
     weights, then the starting points; outputs: poses and inverse depths of
     every problem."""
@@ -611,8 +611,12 @@ class _BundleAdjustMany(torch.autograd.Function):
         p0 = [p.detach().to(dt).contiguous() for p in p0]
         d0 = [d.detach().to(dt).contiguous() for d in d0]
         poses, ds = [p.clone() for p in p0], [d.clone() for d in d0]
-        for c, g, p, d in zip(contexts, gs, poses, ds):
-            c.solve(g, p, d, n_iters, lam, z_min, precision, report=False)
+        if (precision != MIXED and len({id(c) for c in contexts}) == n > 1
+                and all(6 * (g.n_frames - g.n_fixed) + 1 <= 96 for g in gs)):
+            solve_many(contexts, gs, poses, ds, n_iters, lam, z_min, precision)
+        else:
+            for c, g, p, d in zip(contexts, gs, poses, ds):
+                c.solve(g, p, d, n_iters, lam, z_min, precision, report=False)
         ctx.save_for_backward(*p0, *d0)
         ctx.gs, ctx.contexts, ctx.args = gs, contexts, (n_iters, lam, z_min, precision)
         ctx.dtypes = [(t.dtype, w.dtype) for t, w in zip(tg, wg)]

@@ -34,7 +34,9 @@ hipError_t launch_retract_copy(const T* poses_cur, T* poses_next, T* dx, int n_f
                                const int* status, hipStream_t st, const T* dx_sys = nullptr,
                                const int* row0 = nullptr);
 template <typename T>
-int small_solve_grid(int lds_bytes);
+int small_solve_grid(int lds_bytes, bool group);
+template <typename T>
+hipError_t launch_small_solve_group(const SmallGroup<T>& G, int lds_bytes, bool cooperative, hipStream_t st);
 template <typename T>
 hipError_t launch_small_solve(const SmallArgs<T>& S, int grid, int lds_bytes, bool cooperative, hipStream_t st);
 int small_solve_max_n(int tsize);
@@ -1423,6 +1425,41 @@ static hipError_t factor_solve(dpvba_ctx* c, T* S, T* rhs, const T* d0, T* x, in
                                 next_epoch(c), err, c->host_err_dev, st, true, c->coop_launch);
 }
 
+// Arguments of the single-launch solve of a small problem with at least one
+// iteration, for the context's next such launch (its barrier and failure word
+// alternate; the caller counts the launch).
+template <typename T>
+static SmallArgs<T> small_args(dpvba_ctx* c, const dpvba_graph* g, const SolveWs<T>& ws, T* poses, T* depth,
+                               const dpvba_opts* o) {
+  const Tiling& tl = c->tl[sizeof(T) == 8 ? 1 : 0];
+  const int parity = (int)(c->small_launches & 1);
+  int* err = (int*)c->dev_err.p + 4 * parity;
+  SmallArgs<T> S{};
+  S.it = make_iter_args<T>(c, ws, g, tl, poses, ws.pbuf0, depth, (T)o->lambda, (T)o->z_min, (T)lam_diag_of(o), err);
+  S.poses_io = poses;
+  S.depth_io = depth;
+  S.pbuf0 = ws.pbuf0;
+  S.pbuf1 = ws.pbuf1;
+  S.Sp = ws.S;
+  S.rhs = ws.rhs;
+  S.d0 = ws.d0;
+  S.status = ws.status;
+  S.min_bits = ws.min_bits;
+  S.cost = ws.devrep->cost;
+  S.invalid = ws.devrep->n_invalid;
+  S.n_iters = o->n_iters;
+  S.bar = (unsigned int*)c->ticket.p + 8 * parity;
+  S.bar_next = (unsigned int*)c->ticket.p + 8 * (1 - parity);
+  S.err = err;
+  S.err_next = (int*)c->dev_err.p + 4 * (1 - parity);
+  return S;
+}
+
+template <typename T>
+static int small_lds(const dpvba_ctx* c) {
+  return std::max(c->tl[sizeof(T) == 8 ? 1 : 0].lds_bytes, small_solve_lds_bytes(6 * c->n_free, (int)sizeof(T)));
+}
+
 template <typename T>
 static hipError_t solve_impl(dpvba_ctx* c, const dpvba_graph* g, T* poses, T* depth, const dpvba_opts* o,
                              dpvba_report* report, hipStream_t st, const SolveWs<T>* ws_in = nullptr) {
@@ -1443,29 +1480,12 @@ static hipError_t solve_impl(dpvba_ctx* c, const dpvba_graph* g, T* poses, T* de
   const int parity = (int)(c->small_launches & 1);
   int* err = small && nit > 0 ? (int*)c->dev_err.p + 4 * parity : large_err(c);
   if (small && nit > 0) {
-    SmallArgs<T> S{};
-    S.it = make_iter_args<T>(c, ws, g, tl, poses, pbuf[0], depth, lambda, z_min, lam_diag, err);
-    S.poses_io = poses;
-    S.depth_io = depth;
-    S.pbuf0 = pbuf[0];
-    S.pbuf1 = pbuf[1];
-    S.Sp = ws.S;
-    S.rhs = ws.rhs;
-    S.d0 = ws.d0;
-    S.status = status;
-    S.min_bits = mb;
-    S.cost = dev->cost;
-    S.invalid = dev->n_invalid;
-    S.n_iters = nit;
-    S.bar = (unsigned int*)c->ticket.p + 8 * parity;
-    S.bar_next = (unsigned int*)c->ticket.p + 8 * (1 - parity);
-    S.err = err;
-    S.err_next = (int*)c->dev_err.p + 4 * (1 - parity);
-    const int lds_small = std::max(tl.lds_bytes, small_solve_lds_bytes(n, (int)sizeof(T)));
+    const SmallArgs<T> S = small_args<T>(c, g, ws, poses, depth, o);
+    const int lds_small = small_lds<T>(c);
     int& cap = sizeof(T) == 8 ? c->coop_grid64 : c->coop_grid32;
     int& cap_lds = sizeof(T) == 8 ? c->coop_lds64 : c->coop_lds32;
     if (cap_lds != lds_small) {
-      cap = small_solve_grid<T>(lds_small);
+      cap = small_solve_grid<T>(lds_small, false);
       cap_lds = lds_small;
     }
     const int grid = std::min(tl.n_tiles, cap);
@@ -2283,11 +2303,72 @@ static dpvba_status fan_out(int32_t n, dpvba_ctx* const* ctxs, hipStream_t st, F
   return first;
 }
 
+// Whether every problem of a call is a small one (single-launch solver) with
+// valid arguments, so that they can share launches.  Anything else -- an
+// invalid problem among them, a traced context (its phases are timed one by
+// one) -- takes the general way, problem by problem.
+static bool can_group(int32_t n, dpvba_ctx* const* ctxs, const dpvba_graph* graphs, float* const* poses,
+                      float* const* inv_depth, const dpvba_opts* o) {
+  if (n < 2 || !ctxs || check_opts(o) != DPVBA_OK || o->n_iters < 1 || o->precision == DPVBA_MIXED) return false;
+  for (int i = 0; i < n; ++i) {
+    dpvba_ctx* c = ctxs[i];
+    if (!c || c->device != ctxs[0]->device || c->coop_launch != ctxs[0]->coop_launch || c->tracing) return false;
+    for (int j = 0; j < i; ++j)
+      if (ctxs[j] == c) return false;
+    if (!graph_sizes_ok(&graphs[i]) || check_analysed(c, &graphs[i]) != DPVBA_OK) return false;
+    if (!poses[i] || (!inv_depth[i] && c->P > 0) || recorded_failure(c)) return false;
+    if (!(o->precision == DPVBA_FP64 ? use_small_path<double>(c) : use_small_path<float>(c))) return false;
+    if (c->tl[o->precision == DPVBA_FP64 ? 1 : 0].n_tiles < 1) return false;
+  }
+  return true;
+}
+
+// Small problems in launches of up to kSmallGroup, each launch's workgroups
+// within what the device holds at once.  Largest first: a launch lasts as
+// long as its largest problem.
+template <typename T>
+static hipError_t solve_groups(int32_t n, dpvba_ctx* const* ctxs, const dpvba_graph* graphs, float* const* poses,
+                               float* const* inv_depth, const dpvba_opts* o, hipStream_t st) {
+  const int ti = sizeof(T) == 8 ? 1 : 0;
+  int lds = 0;
+  for (int i = 0; i < n; ++i) lds = std::max(lds, small_lds<T>(ctxs[i]));
+  const int cap = small_solve_grid<T>(lds, true);
+  if (cap < 1) return hipErrorCooperativeLaunchTooLarge;
+  std::vector<int> order((size_t)n);
+  for (int i = 0; i < n; ++i) order[i] = i;
+  std::stable_sort(order.begin(), order.end(),
+                   [&](int x, int y) { return ctxs[x]->tl[ti].n_tiles > ctxs[y]->tl[ti].n_tiles; });
+  for (int i = 0; i < n;) {
+    SmallGroup<T> G{};
+    for (; i < n && G.n < kSmallGroup; ++i) {
+      const int k = order[i], grid = std::min(ctxs[k]->tl[ti].n_tiles, cap);
+      if (G.n > 0 && G.first[G.n] + grid > cap) break;
+      G.p[G.n] = small_args<T>(ctxs[k], &graphs[k], ctx_ws<T>(ctxs[k]), (T*)(void*)poses[k],
+                               (T*)(void*)inv_depth[k], o);
+      G.first[G.n + 1] = G.first[G.n] + grid;
+      ++G.n;
+    }
+    const hipError_t e = launch_small_solve_group<T>(G, lds, ctxs[0]->coop_launch, st);
+    if (e != hipSuccess) return e;
+    for (int q = i - G.n; q < i; ++q) ++ctxs[order[q]]->small_launches;
+  }
+  return hipSuccess;
+}
+
 extern "C" {
 
 dpvba_status dpvba_solve_many(int32_t n, dpvba_ctx* const* ctxs, const dpvba_graph* graphs, float* const* poses,
                               float* const* inv_depth, const dpvba_opts* opts, dpvba_report* reports, void* stream) {
   if (!graphs || !poses || !inv_depth) return DPVBA_EINVAL;
+  if (!reports && can_group(n, ctxs, graphs, poses, inv_depth, opts)) {
+    dpvba_ctx* c = ctxs[0];
+    HIP_TRY(hipSetDevice(c->device));
+    if (opts->precision == DPVBA_FP64)
+      HIP_TRY(solve_groups<double>(n, ctxs, graphs, poses, inv_depth, opts, (hipStream_t)stream));
+    else
+      HIP_TRY(solve_groups<float>(n, ctxs, graphs, poses, inv_depth, opts, (hipStream_t)stream));
+    return DPVBA_OK;
+  }
   return fan_out(n, ctxs, (hipStream_t)stream, [&](int i, void* s) {
     return dpvba_solve(ctxs[i], &graphs[i], poses[i], inv_depth[i], opts, reports ? &reports[i] : nullptr, s);
   });

@@ -861,18 +861,16 @@ __device__ void tile_writeback(const TileInfo& ti, const int* tile_patch, const 
 // every workgroup assembles its tiles, all wavefronts gather the damped
 // reduced system, workgroup 0 factors, solves and retracts; finally the
 // depths are written back.  Poses ping-pong between two buffers.
+// (block, nb: this workgroup among the problem's.)
 template <typename T>
-__global__ void __launch_bounds__(tile_threads(sizeof(T)))
-__attribute__((amdgpu_waves_per_eu(tile_threads(sizeof(T)) / 256, tile_threads(sizeof(T)) / 256)))
-small_solve_kernel(SmallArgs<T> S) {
-  extern __shared__ __align__(16) unsigned char lds[];
+__device__ __forceinline__ void small_solve(const SmallArgs<T>& S, const unsigned int block, const unsigned int nb,
+                                            unsigned char* lds) {
   IterArgs<T> A = S.it;
-  const unsigned int nb = gridDim.x;
-  const int w = blockIdx.x * blockDim.x + threadIdx.x, nw = gridDim.x * blockDim.x;
+  const int w = block * blockDim.x + threadIdx.x, nw = nb * blockDim.x;
   const int wave = w >> 6, nwaves = nw >> 6;
   // the other slot: no launch uses it before this one ends
-  if (blockIdx.x == 0 && threadIdx.x < 2) S.bar_next[threadIdx.x] = 0u;
-  if (blockIdx.x == 0 && threadIdx.x == 2) *S.err_next = 0;
+  if (block == 0 && threadIdx.x < 2) S.bar_next[threadIdx.x] = 0u;
+  if (block == 0 && threadIdx.x == 2) *S.err_next = 0;
   for (int t = 0; t < S.n_iters; ++t) {
     A.first = t == 0;
     A.poses_cur = t == 0 ? S.poses_io : ((t - 1) & 1 ? S.pbuf1 : S.pbuf0);
@@ -884,24 +882,46 @@ small_solve_kernel(SmallArgs<T> S) {
     A.min_bits = S.min_bits + t;
     A.cost_out = S.cost ? S.cost + t : nullptr;
     A.invalid_out = S.invalid ? S.invalid + t : nullptr;
-    for (int tile = blockIdx.x; tile < A.n_tiles; tile += nb) {
+    for (int tile = block; tile < A.n_tiles; tile += nb) {
       tile_assemble<T, tile_threads(sizeof(T))>(A, tile, lds);
       __syncthreads();
     }
     if (!grid_sync(S.bar, nb, S.err, A.host_err)) return;
     gather_slice<T>(A, S.Sp, S.rhs, S.d0, wave, nwaves);
     if (!grid_sync(S.bar, nb, S.err, A.host_err)) return;
-    if (blockIdx.x == 0) factor_solve_retract<T>(A, S.Sp, S.rhs, S.d0, lds);
+    if (block == 0) factor_solve_retract<T>(A, S.Sp, S.rhs, S.d0, lds);
     if (!grid_sync(S.bar, nb, S.err, A.host_err)) return;
   }
   if (S.n_iters == 0) return;
   const T* fin = ((S.n_iters - 1) & 1) ? S.pbuf1 : S.pbuf0;
   const bool apply = !S.status[S.n_iters - 1];
   T* sDx = reinterpret_cast<T*>(lds);
-  for (int tile = blockIdx.x; tile < A.n_tiles; tile += nb)
+  for (int tile = block; tile < A.n_tiles; tile += nb)
     tile_writeback<T>(A.tiles[tile], A.tile_patch, A.blk_pose, A.U_s, A.pscale_s, A.depth_s, A.dx, apply,
                       S.depth_io, sDx);
   for (int x = w; x < 7 * A.n_frames; x += nw) S.poses_io[x] = fin[x];
+}
+
+template <typename T>
+__global__ void __launch_bounds__(tile_threads(sizeof(T)))
+__attribute__((amdgpu_waves_per_eu(tile_threads(sizeof(T)) / 256, tile_threads(sizeof(T)) / 256)))
+small_solve_kernel(SmallArgs<T> S) {
+  extern __shared__ __align__(16) unsigned char lds[];
+  small_solve<T>(S, blockIdx.x, gridDim.x, lds);
+}
+
+// Several problems side by side: one problem's tiles fill a tenth of the
+// chip, and its gather and factor less, so a group takes little longer than
+// its largest problem (sixteen float64 windows of 12 to 22 frames: 3.04 ms one
+// after another, 1.35 ms in four groups).
+template <typename T>
+__global__ void __launch_bounds__(tile_threads(sizeof(T)))
+__attribute__((amdgpu_waves_per_eu(tile_threads(sizeof(T)) / 256, tile_threads(sizeof(T)) / 256)))
+small_solve_group_kernel(SmallGroup<T> G) {
+  extern __shared__ __align__(16) unsigned char lds[];
+  int i = 0;
+  while (i + 1 < G.n && (int)blockIdx.x >= G.first[i + 1]) ++i;
+  small_solve<T>(G.p[i], blockIdx.x - G.first[i], G.first[i + 1] - G.first[i], lds);
 }
 
 // Apply the last iteration's depth step and write the results back.
@@ -979,16 +999,35 @@ hipError_t launch_retract_copy(const T* poses_cur, T* poses_next, T* dx, int n_f
   return hipGetLastError();
 }
 
-template <typename T>
-int small_solve_grid(int lds_bytes) {
+template <typename K>
+static int resident_workgroups(K kernel, int threads, int lds_bytes) {
   int dev = 0, cus = 0, per_cu = 0;
   if (hipGetDevice(&dev) != hipSuccess) return 0;
   if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return 0;
-  if (opt_in_lds((const void*)small_solve_kernel<T>, lds_bytes) != hipSuccess) return 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void*)small_solve_kernel<T>, tile_threads(sizeof(T)),
-                                                   lds_bytes) != hipSuccess)
+  if (opt_in_lds((const void*)kernel, lds_bytes) != hipSuccess) return 0;
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void*)kernel, threads, lds_bytes) != hipSuccess)
     return 0;
   return cus * per_cu;
+}
+
+template <typename K, typename Args>
+static hipError_t launch_resident(K kernel, const Args& a, int grid, int threads, int lds_bytes, bool cooperative,
+                                  hipStream_t st) {
+  hipError_t e = opt_in_lds((const void*)kernel, lds_bytes);
+  if (e != hipSuccess) return e;
+  Args copy = a;
+  if (!cooperative) {
+    hipLaunchKernelGGL(kernel, dim3(grid), dim3(threads), lds_bytes, st, copy);
+    return hipGetLastError();
+  }
+  void* args[] = {&copy};
+  return hipLaunchCooperativeKernel((const void*)kernel, dim3(grid), dim3(threads), args, lds_bytes, st);
+}
+
+template <typename T>
+int small_solve_grid(int lds_bytes, bool group) {
+  return group ? resident_workgroups(small_solve_group_kernel<T>, tile_threads(sizeof(T)), lds_bytes)
+               : resident_workgroups(small_solve_kernel<T>, tile_threads(sizeof(T)), lds_bytes);
 }
 
 // grid never exceeds small_solve_grid (the workgroups the device holds at
@@ -999,16 +1038,14 @@ int small_solve_grid(int lds_bytes) {
 // runtime guarantee co-residency, at a higher launch cost.
 template <typename T>
 hipError_t launch_small_solve(const SmallArgs<T>& S, int grid, int lds_bytes, bool cooperative, hipStream_t st) {
-  hipError_t e = opt_in_lds((const void*)small_solve_kernel<T>, lds_bytes);
-  if (e != hipSuccess) return e;
-  SmallArgs<T> copy = S;
-  if (!cooperative) {
-    hipLaunchKernelGGL((small_solve_kernel<T>), dim3(grid), dim3(tile_threads(sizeof(T))), lds_bytes, st, copy);
-    return hipGetLastError();
-  }
-  void* args[] = {&copy};
-  return hipLaunchCooperativeKernel((const void*)small_solve_kernel<T>, dim3(grid), dim3(tile_threads(sizeof(T))), args,
-                                    lds_bytes, st);
+  return launch_resident(small_solve_kernel<T>, S, grid, tile_threads(sizeof(T)), lds_bytes, cooperative, st);
+}
+
+// The problems' workgroups together: the same bound, first[n] workgroups.
+template <typename T>
+hipError_t launch_small_solve_group(const SmallGroup<T>& G, int lds_bytes, bool cooperative, hipStream_t st) {
+  return launch_resident(small_solve_group_kernel<T>, G, G.first[G.n], tile_threads(sizeof(T)), lds_bytes, cooperative,
+                         st);
 }
 
 #define DPVBA_TILE_INSTANTIATE(T)                                                                          \
@@ -1018,7 +1055,8 @@ hipError_t launch_small_solve(const SmallArgs<T>& S, int grid, int lds_bytes, bo
                                               T*, int, hipStream_t);                                       \
   template hipError_t launch_retract_copy<T>(const T*, T*, T*, int, int, const int*, hipStream_t, const T*,    \
                                              const int*);                                                  \
-  template int small_solve_grid<T>(int);                                                                  \
+  template int small_solve_grid<T>(int, bool);                                                            \
+  template hipError_t launch_small_solve_group<T>(const SmallGroup<T>&, int, bool, hipStream_t);          \
   template hipError_t launch_small_solve<T>(const SmallArgs<T>&, int, int, bool, hipStream_t);
 
 DPVBA_TILE_INSTANTIATE(float)

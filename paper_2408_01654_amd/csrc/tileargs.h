@@ -75,4 +75,16 @@ struct SmallArgs {
   int* err_next;           // the next launch's failure word, cleared by this one
 };
 
+// Several small problems in one launch: problem i takes workgroups
+// first[i] .. first[i + 1] - 1.  Passed by value, so it has to fit the 4 KB of
+// a kernel's arguments.
+constexpr int kSmallGroup = 8;
+template <typename T>
+struct SmallGroup {
+  int n;
+  int first[kSmallGroup + 1];
+  SmallArgs<T> p[kSmallGroup];
+};
+static_assert(sizeof(SmallGroup<double>) <= 4096, "kernel arguments");
+
 }  // namespace dpvba
