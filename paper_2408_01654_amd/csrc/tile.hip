@@ -795,12 +795,17 @@ __device__ __forceinline__ void factor_solve_retract(const IterArgs<T>& A, const
   __syncthreads();
 }
 
-// Grid-wide barrier of the single-launch solver: bar[0] counts arrivals,
-// bar[1] is the generation.  Every wait is bounded; on timeout the failure
-// is recorded and false returned, so no workgroup can spin forever.  A
-// launch uses one of two slots and clears the other for the next launch on
-// the stream, so arrivals left behind by a launch whose wait expired never
-// reach a later launch's barriers.
+// Barrier over the workgroups of one problem: bar[0] counts arrivals and
+// wraps to zero with the last, which advances the generation bar[1].  One
+// fence writes this workgroup's results back before its arrival (and
+// completes the load of the generation), one drops stale lines after the last
+// poll; the polls themselves order nothing, since an acquire in the loop
+// invalidates the caches under the workgroups that still run (a 22-frame
+// window 159.8 -> 153.6 us, 17 frames in float64 195.9 -> 178.5 us).  Every
+// wait is bounded; on timeout the failure is recorded and false returned, so
+// no workgroup can spin forever.  A launch uses one of two slots and clears
+// the other for the next launch on the stream, so arrivals left behind by a
+// launch whose wait expired never reach a later launch's barriers.
 constexpr long long kSpinLimit = 1LL << 19;  // polls of ~1000 cycles each: a timeout after ~0.2 s
 
 __device__ bool grid_sync(unsigned int* bar, unsigned int nblocks, int* err, int* host_err) {
@@ -808,15 +813,13 @@ __device__ bool grid_sync(unsigned int* bar, unsigned int nblocks, int* err, int
   __syncthreads();
   if (threadIdx.x == 0) {
     ok = 1;
-    __threadfence();
-    const unsigned int gen = __hip_atomic_load(&bar[1], __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_AGENT);
-    const unsigned int arrived = atomicAdd(&bar[0], 1u);
-    if (arrived == nblocks - 1) {
-      __hip_atomic_store(&bar[0], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      __hip_atomic_fetch_add(&bar[1], 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+    const unsigned int gen = __hip_atomic_load(&bar[1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+    if (atomicInc(&bar[0], nblocks - 1) == nblocks - 1) {
+      __hip_atomic_fetch_add(&bar[1], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     } else {
       long long spins = 0;
-      while (__hip_atomic_load(&bar[1], __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_AGENT) == gen) {
+      while (__hip_atomic_load(&bar[1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == gen) {
         __builtin_amdgcn_s_sleep(16);  // few polls of the shared word while workgroup 0 factors
         if (++spins > kSpinLimit) {
           ok = 0;
@@ -825,7 +828,7 @@ __device__ bool grid_sync(unsigned int* bar, unsigned int nblocks, int* err, int
         }
       }
     }
-    __threadfence();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
   }
   __syncthreads();
   return ok;
@@ -913,7 +916,7 @@ small_solve_kernel(SmallArgs<T> S) {
 // Several problems side by side: one problem's tiles fill a tenth of the
 // chip, and its gather and factor less, so a group takes little longer than
 // its largest problem (sixteen float64 windows of 12 to 22 frames: 3.04 ms one
-// after another, 1.35 ms in four groups).
+// after another, 0.75 ms in four groups).
 template <typename T>
 __global__ void __launch_bounds__(tile_threads(sizeof(T)))
 __attribute__((amdgpu_waves_per_eu(tile_threads(sizeof(T)) / 256, tile_threads(sizeof(T)) / 256)))
