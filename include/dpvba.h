@@ -446,9 +446,10 @@ dpvba_status dpvba_solve_backward(dpvba_ctx* ctx, const dpvba_graph* g, const fl
  * pointers; grad_poses / grad_inv_depth may be NULL, or hold NULL entries,
  * for zero; reports NULL or n host reports, complete once `stream` has
  * completed).  The problems run concurrently: small problems of a
- * dpvba_solve_many without reports (6 x free poses + 1 <= 96 for all of them,
- * DPVBA_FP32 or DPVBA_FP64) several to a launch on `stream`, cooperative when
- * the contexts are set so; all others each on a stream of its own context,
+ * dpvba_solve_many without reports or of dpvba_solve_backward_many
+ * (6 x free poses + 1 <= 96 for all of them, DPVBA_FP32 or DPVBA_FP64) several
+ * to a launch (dpvba_solve_many: on `stream`, cooperative when
+ * the contexts are set so); all others each on a stream of its own context,
  * ordered after the work already on `stream`, and `stream` waits for all of
  * them.  There, launches whose workgroups wait for each other are cooperative
  * (dpvba_set_cooperative(1) for the duration of the call), so concurrent

@@ -127,32 +127,27 @@ hipError_t launch_batch_report(const BatchInst* inst, int n_inst, const T* poses
                                const int* fallback, int stride, int n_iters, dpvba_report* rep, hipStream_t st);
 // adjoint kernels (adjoint.hip)
 template <typename T>
-hipError_t launch_edge_adjoint(const T* poses, const T* depth_t, const int* patch_pos, const float* patches, int p,
-                               const int* ii, const int* jj, const int* kk, const float* target,
-                               const float* weight, int n_edges, int n_fixed, T fx, T fy, T cx, T cy, T z_min,
-                               T lambda, const T* u_pose, const T* u_depth, const T* dxi, const T* dd,
-                               const int* status, T* grad_target, T* grad_weight, T* edge_xbar, hipStream_t st);
+hipError_t launch_adj_tile(const AdjGroup<T>& G, int n, int max_tiles, int lds_bytes, int it, bool replay,
+                           hipStream_t st);
 template <typename T>
-hipError_t launch_retract_adjoint(const T* poses_t, const T* dxi, const int* status, int n_fixed, int n_frames,
-                                  T* pbar, T* dxi_bar, hipStream_t st);
+hipError_t launch_adj_gather(const AdjGroup<T>& G, int n, int max_free, hipStream_t st);
 template <typename T>
-hipError_t launch_adjoint_rhs(const TileInfo* tiles, int n_tiles, const T* U_s, const T* pscale_s, const T* dbar,
-                              T* part_vec, const int* v_off, const int2* v_src, int n_free, const T* dxi_bar,
-                              const int* status, T* rhs, hipStream_t st);
+hipError_t launch_adj_system(const AdjGroup<T>& G, int n, int lds_bytes, int it, bool solve, hipStream_t st);
 template <typename T>
-hipError_t launch_adjoint_backsub(const TileInfo* tiles, int n_tiles, int max_w6, const int* blk_pose,
-                                  const T* U_s, const T* pscale_s, const T* dbar, const T* u_pose, const T* dxi,
-                                  const int* status, T* u_depth, T* dd, hipStream_t st);
+hipError_t launch_adj_begin(const AdjGroup<T>& G, int n, int n_frames, int n_tp, hipStream_t st);
 template <typename T>
-hipError_t launch_adjoint_reduce(const T* edge_xbar, const int* pose_off, const int* pose_src, int n_fixed,
-                                 int n_frames, T* pbar, const int* tile_patch, const int* pcount, const int* pedges,
-                                 int n_tp, T* dbar, hipStream_t st);
+hipError_t launch_edge_adjoint(const AdjGroup<T>& G, int n, int n_edges, int it, hipStream_t st);
 template <typename T>
-hipError_t launch_depth_to_tile(const T* src, const int* tile_patch, int n_tp, T* dst, hipStream_t st);
+hipError_t launch_adjoint_rhs(const AdjGroup<T>& G, int n, int n_tiles, hipStream_t st);
+template <typename T>
+hipError_t launch_vec_gather_add(const T* part_vec, const int* v_off, const int2* v_src, int n_free, const T* add,
+                                 const int* status, T* out, hipStream_t st);
+template <typename T>
+hipError_t launch_adjoint_backsub(const AdjGroup<T>& G, int n, int n_tiles, int max_w6, int it, hipStream_t st);
+template <typename T>
+hipError_t launch_adj_reduce(const AdjGroup<T>& G, int n, int n_free, int n_tp, int it, hipStream_t st);
 template <typename T>
 hipError_t launch_fill(T* x, long long n, T v, hipStream_t st);
-template <typename T>
-hipError_t launch_copy(const T* src, T* dst, long long n, hipStream_t st);
 hipError_t launch_report_finalize(dpvba_report* rep, const int* status, const unsigned int* min_bits,
                                   int n_iters, const int* err, hipStream_t st, const double* refine = nullptr,
                                   const int* fallback = nullptr);
@@ -1306,6 +1301,7 @@ static IterArgs<T> make_iter_args(dpvba_ctx* c, const SolveWs<T>& w, const dpvba
   A.poses_next = poses_next;
   A.depth_in = depth_in;
   A.depth_s = w.depth_s;
+  A.depth_prev = w.depth_s;
   A.xh_s = w.xh_s;
   A.U_s = w.U_s;
   A.pscale_s = w.pscale_s;
@@ -1813,109 +1809,157 @@ static hipError_t backward_workspace(dpvba_ctx* c, int N, long long ntp, long lo
   return ensure(c->bw_minbits, 2 * DPVBA_MAX_ITERS * 4);
 }
 
-// Adjoint of `n_iters` iterations started from (poses0, depth0): replays
-// the iterations storing x_t and the pose steps, then walks them backwards
-// (see adjoint.hip), recomputing each iteration's Schur system at x_t.
+// Arguments of one problem's adjoint; the workspace is sized by the analysis
+// (backward_workspace) for DPVBA_MAX_ITERS iterations.
 template <typename T>
-static hipError_t backward_impl(dpvba_ctx* c, const dpvba_graph* g, const T* poses0, const T* depth0,
-                                const dpvba_opts* o, const T* grad_poses, const T* grad_depth, T* grad_target,
-                                T* grad_weight, hipStream_t st) {
-  const T lambda = (T)o->lambda, z_min = (T)o->z_min, lam_diag = (T)lam_diag_of(o);
+static bool adj_args(dpvba_ctx* c, const dpvba_graph* g, const T* poses0, const T* depth0, const dpvba_opts* o,
+                     const T* grad_poses, const T* grad_depth, T* grad_target, T* grad_weight, AdjArgs<T>* out) {
   const Tiling& tl = c->tl[sizeof(T) == 8 ? 1 : 0];
-  const int N = c->N, nf = c->n_fixed, n = 6 * c->n_free, nit = o->n_iters, E = c->E;
-  int* err = large_err(c);
-  const long long ntp = tl.n_tp, np7 = 7LL * N;
-  const size_t ts = sizeof(T);
-  hipError_t e;
-  if ((e = launch_fill<T>(grad_target, 2LL * E, (T)0, st)) != hipSuccess) return e;
-  if ((e = launch_fill<T>(grad_weight, 2LL * E, (T)0, st)) != hipSuccess) return e;
-  if (nit == 0) return hipSuccess;
-  // workspace sized by the analysis (backward_workspace) for DPVBA_MAX_ITERS
-  if (c->bw_poses.bytes < (size_t)(nit + 1) * np7 * ts || c->bw_depth.bytes < (size_t)nit * ntp * ts ||
-      c->bw_edge.bytes < (size_t)E * 15 * ts)
-    return hipErrorInvalidValue;
-  T* Xp = (T*)c->bw_poses.p;
-  T* Xd = (T*)c->bw_depth.p;
-  T* DX = (T*)c->bw_dx.p;
-  T* pbar = (T*)c->bw_pbar.p;
-  T* dbar = (T*)c->bw_dbar.p;
-  T* dxbar = (T*)c->bw_dxbar.p;
-  T* urhs = (T*)c->bw_rhs.p;
-  T* up = (T*)c->bw_up.p;
-  T* ud = (T*)c->bw_ud.p;
-  T* dd = (T*)c->bw_dd.p;
-  T* exb = (T*)c->bw_edge.p;
-  int* status = (int*)c->bw_status.p;  // [0, MAX): replayed steps, [MAX, 2 MAX): adjoint solves
-  unsigned int* mb = (unsigned int*)c->bw_minbits.p;
-  const TileInfo* tiles = (const TileInfo*)tl.tiles.p;
-  if ((e = launch_report_init(status, mb, 2 * DPVBA_MAX_ITERS, st, err)) != hipSuccess) return e;
-  if ((e = launch_copy<T>(poses0, Xp, np7, st)) != hipSuccess) return e;
+  const size_t ts = sizeof(T), np7 = 7 * (size_t)c->N, ntp = (size_t)tl.n_tp, nit = (size_t)o->n_iters;
+  if (c->bw_poses.bytes < (nit + 1) * np7 * ts || c->bw_depth.bytes < nit * ntp * ts ||
+      c->bw_edge.bytes < (size_t)c->E * 15 * ts)
+    return false;
+  AdjArgs<T>& a = *out;
+  a.Xp = (T*)c->bw_poses.p;
+  a.Xd = (T*)c->bw_depth.p;
+  a.DX = (T*)c->bw_dx.p;
+  a.it = make_iter_args<T>(c, g, tl, a.Xp, nullptr, depth0, (T)o->lambda, (T)o->z_min, (T)lam_diag_of(o), large_err(c));
+  a.nit = o->n_iters;
+  a.n_edges = c->E;
+  a.n_tp = (int)ntp;
+  a.pbar = (T*)c->bw_pbar.p;
+  a.dbar = (T*)c->bw_dbar.p;
+  a.dxbar = (T*)c->bw_dxbar.p;
+  a.urhs = (T*)c->bw_rhs.p;
+  a.up = (T*)c->bw_up.p;
+  a.ud = (T*)c->bw_ud.p;
+  a.dd = (T*)c->bw_dd.p;
+  a.exb = (T*)c->bw_edge.p;
+  a.status = (int*)c->bw_status.p;
+  a.mb = (unsigned int*)c->bw_minbits.p;
+  a.Sp = (T*)c->S.p;
+  a.rhs = (T*)c->rhs.p;
+  a.d0 = (T*)c->d0.p;
+  a.poses0 = poses0;
+  a.grad_poses = grad_poses;
+  a.grad_depth = grad_depth;
+  a.grad_target = grad_target;
+  a.grad_weight = grad_weight;
+  a.ii = g->ii;
+  a.jj = g->jj;
+  a.kk = g->kk;
+  a.patch_pos = (const int*)c->patch_pos.p;
+  a.pose_off = (const int*)c->pose_off.p;
+  a.pose_src = (const int*)c->pose_src.p;
+  a.pcount = (const int*)c->pcount.p;
+  a.pedges = (const int*)c->pedges.p;
+  return true;
+}
+
+// Whether a problem's adjoint can share launches: the single-launch solver's
+// systems, with something in every launch.
+template <typename T>
+static bool adj_small(const dpvba_ctx* c) {
+  return use_small_path<T>(c) && c->n_free > 0 && c->E > 0 && c->tl[sizeof(T) == 8 ? 1 : 0].n_tiles > 0;
+}
+
+// Adjoint of nit >= 1 iterations of the m problems of G (contexts cs):
+// replays the iterations storing x_t and the pose steps, then walks them
+// backwards (see adjoint.hip), recomputing each iteration's Schur system at x_t
+// (the last one's is still there).  Either problems of the single-launch
+// solver (adj_small), or one problem of any size.  A window's adjoint of two
+// iterations is 20 launches, shared by up to kAdjGroup windows; one window at
+// a time it was 46, and sixteen windows waited for the host.
+template <typename T>
+static hipError_t backward_group(const AdjGroup<T>& G, int m, dpvba_ctx* const* cs, hipStream_t st) {
+  const int ti = sizeof(T) == 8 ? 1 : 0;
+  int tiles = 0, lds_tile = 0, lds_small = 0, w6 = 0, frames = 0, free_ = 0, ntp = 0, edges = 0;
+  for (int q = 0; q < m; ++q) {
+    const dpvba_ctx* c = cs[q];
+    const Tiling& tl = c->tl[ti];
+    tiles = std::max(tiles, tl.n_tiles);
+    lds_tile = std::max(lds_tile, tl.lds_bytes);
+    lds_small = std::max(lds_small, small_solve_lds_bytes(6 * c->n_free, (int)sizeof(T)));
+    w6 = std::max(w6, tl.max_w6);
+    frames = std::max(frames, c->N);
+    free_ = std::max(free_, c->n_free);
+    ntp = std::max(ntp, (int)tl.n_tp);
+    edges = std::max(edges, c->E);
+  }
+  dpvba_ctx* c = cs[0];
+  const AdjArgs<T>& a = G.p[0];
+  const bool small = adj_small<T>(c);
+  const int nit = a.nit, n = 6 * c->n_free;
   const bool sparse = is_sparse<T>(n);
   const SparsePlan& plan = c->ba_plan.plan;
   T* xs = (T*)c->sys_x.p;  // a large solve's result in the plan's padded rows
+  hipError_t e;
+  // the damped system of the tiles' shares
   auto gather = [&]() {
-    return gather_system<T>(c, tl, (const T*)c->part_S.p, (const T*)c->part_vec.p, (T*)c->S.p, (T*)c->rhs.p,
-                            (T*)c->d0.p, lambda, lam_diag, st);
+    if (small) return launch_adj_gather<T>(G, m, free_, st);
+    return gather_system<T>(c, c->tl[ti], a.it.part_S, a.it.part_vec, a.Sp, a.rhs, a.d0, a.it.lambda, a.it.lam_diag,
+                            st);
   };
   // x = S^-1 b, zero if a pivot failed, in the poses' order (b: in the
   // plan's padded rows for a large system, which overwrites it)
   auto solve = [&](T* b, T* x, int* stt, unsigned int* mbt) {
-    hipError_t r = factor_solve<T>(c, (T*)c->S.p, b, (const T*)c->d0.p, sparse ? xs : x, stt, mbt, err, st);
+    hipError_t r = factor_solve<T>(c, a.Sp, b, a.d0, sparse ? xs : x, stt, mbt, a.it.dev_err, st);
     if (r == hipSuccess && sparse) r = launch_sparse_rows_out<T>(plan, xs, x, stt, st);
     return r;
   };
-  // replay: x_0 .. x_T, depths d_0 .. d_{T-1} in tile order, steps of the poses
+  if ((e = launch_adj_begin<T>(G, m, frames, ntp, st)) != hipSuccess) return e;
   for (int it = 0; it < nit; ++it) {
-    T* xt = Xp + it * np7;
-    IterArgs<T> A = make_iter_args<T>(c, g, tl, xt, nullptr, depth0, lambda, z_min, lam_diag, err);
-    A.first = it == 0;
-    A.dx_prev = it ? DX + (size_t)(it - 1) * n : nullptr;
-    A.status_prev = it ? status + it - 1 : nullptr;
-    if ((e = launch_tile_iterate<T>(A, tl.lds_bytes, st)) != hipSuccess) return e;
-    if ((e = launch_copy<T>((const T*)c->depth_s.p, Xd + it * ntp, ntp, st)) != hipSuccess) return e;
+    if ((e = launch_adj_tile<T>(G, m, tiles, lds_tile, it, true, st)) != hipSuccess) return e;
     if ((e = gather()) != hipSuccess) return e;
-    if ((e = solve((T*)c->rhs.p, DX + (size_t)it * n, status + it, mb + it)) != hipSuccess) return e;
-    if ((e = launch_retract_copy<T>(xt, xt + np7, DX + (size_t)it * n, nf, N, status + it, st)) != hipSuccess)
-      return e;
+    if (small) {
+      e = launch_adj_system<T>(G, m, lds_small, it, false, st);
+    } else {
+      T* xt = a.Xp + (size_t)it * 7 * c->N;
+      T* dx = a.DX + (size_t)it * n;
+      e = solve(a.rhs, dx, a.status + it, a.mb + it);
+      if (e == hipSuccess)
+        e = launch_retract_copy<T>(xt, xt + 7 * (size_t)c->N, dx, c->n_fixed, c->N, a.status + it, st);
+    }
+    if (e != hipSuccess) return e;
   }
-  // adjoint of x_T
-  if (grad_poses) e = launch_copy<T>(grad_poses, pbar, np7, st);
-  else e = launch_fill<T>(pbar, np7, (T)0, st);
-  if (e != hipSuccess) return e;
-  if ((e = launch_depth_to_tile<T>(grad_depth, (const int*)tl.tile_patch.p, (int)ntp, dbar, st)) != hipSuccess)
-    return e;
+  if ((e = launch_adj_reduce<T>(G, m, free_, ntp, nit - 1, st)) != hipSuccess) return e;
   for (int it = nit - 1; it >= 0; --it) {
-    const T* xt = Xp + it * np7;
-    const T* dx_t = DX + (size_t)it * n;
-    const int* stt = status + it;
-    if ((e = launch_retract_adjoint<T>(xt, dx_t, stt, nf, N, pbar, dxbar, st)) != hipSuccess) return e;
-    IterArgs<T> A = make_iter_args<T>(c, g, tl, xt, nullptr, depth0, lambda, z_min, lam_diag, err);
-    A.first = 0;
-    A.dx_prev = nullptr;
-    A.depth_s = Xd + it * ntp;
-    if ((e = launch_tile_iterate<T>(A, tl.lds_bytes, st)) != hipSuccess) return e;
-    if ((e = gather()) != hipSuccess) return e;
-    if ((e = launch_adjoint_rhs<T>(tiles, tl.n_tiles, (const T*)c->U_s.p, (const T*)c->pscale_s.p, dbar,
-                                   (T*)c->part_vec.p, (const int*)tl.v_off.p, (const int2*)tl.v_src.p, c->n_free,
-                                   dxbar, stt, urhs, st)) != hipSuccess)
-      return e;
-    if (sparse && (e = launch_sparse_rows_in<T>(plan, urhs, (T*)c->rhs.p, st)) != hipSuccess) return e;
-    if ((e = solve(sparse ? (T*)c->rhs.p : urhs, up, status + DPVBA_MAX_ITERS + it, mb + DPVBA_MAX_ITERS + it)) != hipSuccess) return e;
-    if ((e = launch_adjoint_backsub<T>(tiles, tl.n_tiles, tl.max_w6, (const int*)tl.blk_pose.p,
-                                       (const T*)c->U_s.p, (const T*)c->pscale_s.p, dbar, up, dx_t, stt, ud, dd,
-                                       st)) != hipSuccess)
-      return e;
-    if ((e = launch_edge_adjoint<T>(xt, Xd + it * ntp, (const int*)c->patch_pos.p, g->patches, g->patch_size, g->ii,
-                                    g->jj, g->kk, g->target, g->weight, E, nf, (T)g->fx, (T)g->fy, (T)g->cx,
-                                    (T)g->cy, z_min, lam_diag, up, ud, dx_t, dd, stt, grad_target, grad_weight, exb,
-                                    st)) != hipSuccess)
-      return e;
-    if ((e = launch_adjoint_reduce<T>(exb, (const int*)c->pose_off.p, (const int*)c->pose_src.p, nf, N, pbar,
-                                      (const int*)tl.tile_patch.p, (const int*)c->pcount.p,
-                                      (const int*)c->pedges.p, (int)ntp, dbar, st)) != hipSuccess)
-      return e;
+    if (it < nit - 1) {
+      if ((e = launch_adj_tile<T>(G, m, tiles, lds_tile, it, false, st)) != hipSuccess) return e;
+      if ((e = gather()) != hipSuccess) return e;
+    } else if (sparse) {  // the replay's solve has overwritten it
+      if ((e = gather()) != hipSuccess) return e;
+    }
+    if ((e = launch_adjoint_rhs<T>(G, m, tiles, st)) != hipSuccess) return e;
+    if (small) {
+      e = launch_adj_system<T>(G, m, lds_small, it, true, st);
+    } else {
+      e = launch_vec_gather_add<T>(a.it.part_vec, a.it.v_off, a.it.v_src, c->n_free, a.dxbar, a.status + it, a.urhs, st);
+      if (e == hipSuccess && sparse) e = launch_sparse_rows_in<T>(plan, a.urhs, a.rhs, st);
+      if (e == hipSuccess)
+        e = solve(sparse ? a.rhs : a.urhs, a.up, a.status + DPVBA_MAX_ITERS + it, a.mb + DPVBA_MAX_ITERS + it);
+    }
+    if (e != hipSuccess) return e;
+    if ((e = launch_adjoint_backsub<T>(G, m, tiles, w6, it, st)) != hipSuccess) return e;
+    if ((e = launch_edge_adjoint<T>(G, m, edges, it, st)) != hipSuccess) return e;
+    if ((e = launch_adj_reduce<T>(G, m, free_, ntp, it - 1, st)) != hipSuccess) return e;
   }
   return hipSuccess;
+}
+
+template <typename T>
+static hipError_t backward_impl(dpvba_ctx* c, const dpvba_graph* g, const T* poses0, const T* depth0,
+                                const dpvba_opts* o, const T* grad_poses, const T* grad_depth, T* grad_target,
+                                T* grad_weight, hipStream_t st) {
+  hipError_t e;
+  if (o->n_iters == 0 || c->E == 0) {
+    if ((e = launch_fill<T>(grad_target, 2LL * c->E, (T)0, st)) != hipSuccess) return e;
+    return launch_fill<T>(grad_weight, 2LL * c->E, (T)0, st);
+  }
+  AdjGroup<T> G{};
+  if (!adj_args<T>(c, g, poses0, depth0, o, grad_poses, grad_depth, grad_target, grad_weight, &G.p[0]))
+    return hipErrorInvalidValue;
+  return backward_group<T>(G, 1, &c, st);
 }
 
 extern "C" {
@@ -2307,9 +2351,10 @@ static dpvba_status fan_out(int32_t n, dpvba_ctx* const* ctxs, hipStream_t st, F
 // valid arguments, so that they can share launches.  Anything else -- an
 // invalid problem among them, a traced context (its phases are timed one by
 // one) -- takes the general way, problem by problem.
-static bool can_group(int32_t n, dpvba_ctx* const* ctxs, const dpvba_graph* graphs, float* const* poses,
-                      float* const* inv_depth, const dpvba_opts* o) {
-  if (n < 2 || !ctxs || check_opts(o) != DPVBA_OK || o->n_iters < 1 || o->precision == DPVBA_MIXED) return false;
+template <typename T>
+static bool can_group(int32_t n, dpvba_ctx* const* ctxs, const dpvba_graph* graphs, const float* const* poses,
+                      const float* const* inv_depth, const dpvba_opts* o) {
+  if (n < 2 || !ctxs || check_opts(o) != DPVBA_OK || o->n_iters < 1) return false;
   for (int i = 0; i < n; ++i) {
     dpvba_ctx* c = ctxs[i];
     if (!c || c->device != ctxs[0]->device || c->coop_launch != ctxs[0]->coop_launch || c->tracing) return false;
@@ -2317,15 +2362,23 @@ static bool can_group(int32_t n, dpvba_ctx* const* ctxs, const dpvba_graph* grap
       if (ctxs[j] == c) return false;
     if (!graph_sizes_ok(&graphs[i]) || check_analysed(c, &graphs[i]) != DPVBA_OK) return false;
     if (!poses[i] || (!inv_depth[i] && c->P > 0) || recorded_failure(c)) return false;
-    if (!(o->precision == DPVBA_FP64 ? use_small_path<double>(c) : use_small_path<float>(c))) return false;
-    if (c->tl[o->precision == DPVBA_FP64 ? 1 : 0].n_tiles < 1) return false;
+    if (!adj_small<T>(c)) return false;
   }
   return true;
 }
 
+// The problems' places, most tiles first: a launch lasts as long as its
+// largest problem.
+static std::vector<int> by_size(int32_t n, dpvba_ctx* const* ctxs, int ti) {
+  std::vector<int> order((size_t)n);
+  for (int i = 0; i < n; ++i) order[i] = i;
+  std::stable_sort(order.begin(), order.end(),
+                   [&](int x, int y) { return ctxs[x]->tl[ti].n_tiles > ctxs[y]->tl[ti].n_tiles; });
+  return order;
+}
+
 // Small problems in launches of up to kSmallGroup, each launch's workgroups
-// within what the device holds at once.  Largest first: a launch lasts as
-// long as its largest problem.
+// within what the device holds at once.
 template <typename T>
 static hipError_t solve_groups(int32_t n, dpvba_ctx* const* ctxs, const dpvba_graph* graphs, float* const* poses,
                                float* const* inv_depth, const dpvba_opts* o, hipStream_t st) {
@@ -2334,10 +2387,7 @@ static hipError_t solve_groups(int32_t n, dpvba_ctx* const* ctxs, const dpvba_gr
   for (int i = 0; i < n; ++i) lds = std::max(lds, small_lds<T>(ctxs[i]));
   const int cap = small_solve_grid<T>(lds, true);
   if (cap < 1) return hipErrorCooperativeLaunchTooLarge;
-  std::vector<int> order((size_t)n);
-  for (int i = 0; i < n; ++i) order[i] = i;
-  std::stable_sort(order.begin(), order.end(),
-                   [&](int x, int y) { return ctxs[x]->tl[ti].n_tiles > ctxs[y]->tl[ti].n_tiles; });
+  const std::vector<int> order = by_size(n, ctxs, ti);
   for (int i = 0; i < n;) {
     SmallGroup<T> G{};
     for (; i < n && G.n < kSmallGroup; ++i) {
@@ -2355,18 +2405,51 @@ static hipError_t solve_groups(int32_t n, dpvba_ctx* const* ctxs, const dpvba_gr
   return hipSuccess;
 }
 
+// Adjoints of small problems, up to kAdjGroup to a launch; several groups each
+// on a stream of their first context.
+template <typename T>
+static dpvba_status backward_groups(int32_t n, dpvba_ctx* const* ctxs, const dpvba_graph* graphs,
+                                    const float* const* poses0, const float* const* inv_depth0, const dpvba_opts* o,
+                                    const float* const* grad_poses, const float* const* grad_inv_depth,
+                                    float* const* grad_target, float* const* grad_weight, hipStream_t st) {
+  const std::vector<int> order = by_size(n, ctxs, sizeof(T) == 8 ? 1 : 0);
+  const int n_group = (n + kAdjGroup - 1) / kAdjGroup;
+  std::vector<dpvba_ctx*> sorted((size_t)n), first((size_t)n_group);
+  for (int i = 0; i < n; ++i) sorted[i] = ctxs[order[i]];
+  for (int q = 0; q < n_group; ++q) first[q] = sorted[(size_t)((long long)n * q / n_group)];
+  auto run = [&](int q, void* s) -> dpvba_status {
+    dpvba_ctx* c = first[q];
+    const int lo = (int)((long long)n * q / n_group), hi = (int)((long long)n * (q + 1) / n_group);
+    AdjGroup<T> G{};
+    for (int i = lo; i < hi; ++i) {
+      const int k = order[i];
+      if (!adj_args<T>(ctxs[k], &graphs[k], (const T*)(const void*)poses0[k], (const T*)(const void*)inv_depth0[k], o,
+                       grad_poses ? (const T*)(const void*)grad_poses[k] : nullptr,
+                       grad_inv_depth ? (const T*)(const void*)grad_inv_depth[k] : nullptr,
+                       (T*)(void*)grad_target[k], (T*)(void*)grad_weight[k], &G.p[i - lo]))
+        HIP_TRY(hipErrorInvalidValue);
+    }
+    HIP_TRY(backward_group<T>(G, hi - lo, sorted.data() + lo, (hipStream_t)s));
+    return DPVBA_OK;
+  };
+  if (n_group > 1) return fan_out(n_group, first.data(), st, run);
+  dpvba_ctx* c = first[0];
+  HIP_TRY(hipSetDevice(c->device));
+  return run(0, (void*)st);
+}
+
 extern "C" {
 
 dpvba_status dpvba_solve_many(int32_t n, dpvba_ctx* const* ctxs, const dpvba_graph* graphs, float* const* poses,
                               float* const* inv_depth, const dpvba_opts* opts, dpvba_report* reports, void* stream) {
   if (!graphs || !poses || !inv_depth) return DPVBA_EINVAL;
-  if (!reports && can_group(n, ctxs, graphs, poses, inv_depth, opts)) {
+  const bool f64 = opts && opts->precision == DPVBA_FP64, f32 = opts && opts->precision == DPVBA_FP32;
+  if (!reports && ((f64 && can_group<double>(n, ctxs, graphs, poses, inv_depth, opts)) ||
+                   (f32 && can_group<float>(n, ctxs, graphs, poses, inv_depth, opts)))) {
     dpvba_ctx* c = ctxs[0];
     HIP_TRY(hipSetDevice(c->device));
-    if (opts->precision == DPVBA_FP64)
-      HIP_TRY(solve_groups<double>(n, ctxs, graphs, poses, inv_depth, opts, (hipStream_t)stream));
-    else
-      HIP_TRY(solve_groups<float>(n, ctxs, graphs, poses, inv_depth, opts, (hipStream_t)stream));
+    HIP_TRY(f64 ? solve_groups<double>(n, ctxs, graphs, poses, inv_depth, opts, (hipStream_t)stream)
+                : solve_groups<float>(n, ctxs, graphs, poses, inv_depth, opts, (hipStream_t)stream));
     return DPVBA_OK;
   }
   return fan_out(n, ctxs, (hipStream_t)stream, [&](int i, void* s) {
@@ -2380,6 +2463,15 @@ dpvba_status dpvba_solve_backward_many(int32_t n, dpvba_ctx* const* ctxs, const 
                                        const float* const* grad_inv_depth, float* const* grad_target,
                                        float* const* grad_weight, void* stream) {
   if (!graphs || !poses0 || !inv_depth0 || !grad_target || !grad_weight) return DPVBA_EINVAL;
+  bool outputs = n > 0;
+  for (int i = 0; i < n; ++i) outputs = outputs && grad_target[i] && grad_weight[i];
+  if (outputs && opts && opts->precision == DPVBA_FP64 &&
+      can_group<double>(n, ctxs, graphs, poses0, inv_depth0, opts))
+    return backward_groups<double>(n, ctxs, graphs, poses0, inv_depth0, opts, grad_poses, grad_inv_depth, grad_target,
+                                   grad_weight, (hipStream_t)stream);
+  if (outputs && opts && opts->precision == DPVBA_FP32 && can_group<float>(n, ctxs, graphs, poses0, inv_depth0, opts))
+    return backward_groups<float>(n, ctxs, graphs, poses0, inv_depth0, opts, grad_poses, grad_inv_depth, grad_target,
+                                  grad_weight, (hipStream_t)stream);
   return fan_out(n, ctxs, (hipStream_t)stream, [&](int i, void* s) {
     return dpvba_solve_backward(ctxs[i], &graphs[i], poses0[i], inv_depth0[i], opts,
                                 grad_poses ? grad_poses[i] : nullptr, grad_inv_depth ? grad_inv_depth[i] : nullptr,
@@ -2425,6 +2517,7 @@ static hipError_t batch_impl(dpvba_ctx* c, const dpvba_batch* b, T* poses, T* de
     A.poses_cur = cur;
     A.depth_in = depth;
     A.depth_s = (T*)c->depth_s.p;
+    A.depth_prev = A.depth_s;
     A.xh_s = (T*)c->xh_s.p;
     A.U_s = (T*)c->U_s.p;
     A.pscale_s = (T*)c->pscale_s.p;

@@ -219,7 +219,7 @@ __device__ __forceinline__ void tile_assemble(const IterArgs<T>& A, int tile, un
     } else {
       x0 = A.xh_s[2 * (pb + k)];
       x1 = A.xh_s[2 * (pb + k) + 1];
-      d = A.depth_s[pb + k];
+      d = A.depth_prev[pb + k];
       if (apply_prev) is = A.pscale_s[2 * (pb + k)];
     }
     sPatch[4 * k] = x0;
@@ -248,7 +248,7 @@ __device__ __forceinline__ void tile_assemble(const IterArgs<T>& A, int tile, un
       d -= sPs[8 * k] * sPatch[4 * k + 3];
       sPatch[4 * k + 2] = d;
     }
-    if (A.first || apply_prev) A.depth_s[pb + k] = d;
+    if (A.first || apply_prev || A.depth_prev != A.depth_s) A.depth_s[pb + k] = d;
     sPatch[4 * k + 3] = (T)0;
   }
   __syncthreads();
@@ -927,6 +927,114 @@ small_solve_group_kernel(SmallGroup<T> G) {
   small_solve<T>(G.p[i], blockIdx.x - G.first[i], G.first[i + 1] - G.first[i], lds);
 }
 
+// ---------------------------------------------------------------- adjoint
+
+// Tile arguments of iteration `it` of problem a: its replay (applies the step
+// before and stores the depths), or again at the stored iterate.
+template <typename T>
+__device__ __forceinline__ IterArgs<T> adj_iter(const AdjArgs<T>& a, int it, bool replay) {
+  IterArgs<T> A = a.it;
+  const int n = 6 * A.n_free;
+  const bool prev = replay && it > 0;
+  A.first = replay && it == 0;
+  A.poses_cur = a.Xp + (size_t)it * 7 * A.n_frames;
+  A.poses_next = a.Xp + (size_t)(it + 1) * 7 * A.n_frames;
+  A.depth_s = a.Xd + (size_t)it * a.n_tp;
+  A.depth_prev = prev ? a.Xd + (size_t)(it - 1) * a.n_tp : A.depth_s;
+  A.dx_prev = prev ? a.DX + (size_t)(it - 1) * n : nullptr;
+  A.status_prev = prev ? a.status + it - 1 : nullptr;
+  A.dx = a.DX + (size_t)it * n;
+  A.status = a.status + it;
+  A.min_bits = a.mb + it;
+  A.cost_out = nullptr;
+  return A;
+}
+
+template <typename T>
+__global__ void __launch_bounds__(tile_threads(sizeof(T))) adj_tile_kernel(AdjGroup<T> G, int it, int replay) {
+  extern __shared__ __align__(16) unsigned char lds[];
+  const AdjArgs<T>& a = G.p[blockIdx.y];
+  if ((int)blockIdx.x >= a.it.n_tiles) return;
+  tile_assemble<T, tile_threads(sizeof(T))>(adj_iter<T>(a, it, replay),
+                                            a.it.order ? a.it.order[blockIdx.x] : (int)blockIdx.x, lds);
+}
+
+template <typename T>
+__global__ void __launch_bounds__(256) adj_gather_kernel(AdjGroup<T> G) {
+  const AdjArgs<T>& a = G.p[blockIdx.y];
+  gather_slice<T>(a.it, a.Sp, a.rhs, a.d0, (int)(blockIdx.x * 4 + (threadIdx.x >> 6)), (int)gridDim.x * 4);
+}
+
+// Replayed step: factor, solve and retraction of iteration `it`.
+template <typename T>
+__global__ void __launch_bounds__(256) adj_step_kernel(AdjGroup<T> G, int it) {
+  extern __shared__ __align__(16) unsigned char lds[];
+  const AdjArgs<T>& a = G.p[blockIdx.y];
+  factor_solve_retract<T>(adj_iter<T>(a, it, true), a.Sp, a.rhs, a.d0, lds);
+}
+
+// Adjoint solve of iteration `it`: the right-hand side, Deltabar_xi plus the
+// tiles' shares (zero for a skipped step), and u_p = S^-1 of it.
+// The shares of a pose are summed by ten lanes a component, four poses of a
+// wavefront together, so the sum is a few loads deep instead of one a tile.
+template <typename T>
+__global__ void __launch_bounds__(256) adj_solve_kernel(AdjGroup<T> G, int it) {
+  extern __shared__ __align__(16) unsigned char lds[];
+  __shared__ int bad;
+  __shared__ float minr;
+  const AdjArgs<T>& a = G.p[blockIdx.y];
+  const int nf = a.it.n_free, n = 6 * nf, tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const int sub = lane / 6, m = lane - 6 * sub;
+  const bool skip = a.status[it] != 0;
+  for (int P0 = w; P0 < nf; P0 += 16) {
+    T v[4];
+    int lo[4], hi[4], most = 0;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int P = P0 + 4 * u;
+      lo[u] = P < nf ? a.it.v_off[P] : 0;
+      hi[u] = P < nf ? a.it.v_off[P + 1] : 0;
+      most = max(most, hi[u] - lo[u]);
+      v[u] = (T)0;
+    }
+    if (sub < 10)
+      for (int q0 = sub; q0 < most; q0 += 20) {
+        int at[8];
+        T x[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+          const int q = lo[u >> 1] + q0 + 10 * (u & 1);
+          at[u] = q < hi[u >> 1] ? a.it.v_src[q].x + m : -1;
+        }
+#pragma unroll
+        for (int u = 0; u < 8; ++u) x[u] = at[u] >= 0 ? a.it.part_vec[at[u]] : (T)0;
+#pragma unroll
+        for (int u = 0; u < 8; ++u) v[u >> 1] += x[u];
+      }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      T s = (T)0;
+#pragma unroll
+      for (int h = 0; h < 10; ++h) s += __shfl(v[u], 6 * h + m);
+      const int P = P0 + 4 * u;
+      if (P < nf && lane < 6) a.urhs[6 * P + m] = skip ? (T)0 : a.dxbar[6 * P + m] + s;
+    }
+  }
+  __syncthreads();
+  const int nr = small_solve_rows(n);
+  T* x = reinterpret_cast<T*>(lds) + 37 * nr + nr * nr;  // after the solver's own arrays
+  if (nr == 32) panel_chol_solve<T, 2>(n, a.Sp, a.urhs, a.d0, lds, x, &bad, &minr);
+  else if (nr == 64) panel_chol_solve<T, 4>(n, a.Sp, a.urhs, a.d0, lds, x, &bad, &minr);
+  else if (nr == 80) panel_chol_solve<T, 5>(n, a.Sp, a.urhs, a.d0, lds, x, &bad, &minr);
+  else panel_chol_solve<T, 6>(n, a.Sp, a.urhs, a.d0, lds, x, &bad, &minr);
+  __syncthreads();
+  for (int i = tid; i < n; i += blockDim.x) a.up[i] = x[i];  // zero when a pivot failed
+  if (tid == 0) {
+    a.status[DPVBA_MAX_ITERS + it] = bad;
+    a.mb[DPVBA_MAX_ITERS + it] = __float_as_uint(minr >= 0.f ? minr : 0.f);
+  }
+}
+
 // Apply the last iteration's depth step and write the results back.
 template <typename T>
 __global__ void __launch_bounds__(kTileThreads) tile_finalize_kernel(
@@ -1051,6 +1159,35 @@ hipError_t launch_small_solve_group(const SmallGroup<T>& G, int lds_bytes, bool 
                          st);
 }
 
+template <typename T>
+hipError_t launch_adj_tile(const AdjGroup<T>& G, int n, int max_tiles, int lds_bytes, int it, bool replay,
+                           hipStream_t st) {
+  if (max_tiles == 0) return hipSuccess;
+  hipError_t e = opt_in_lds((const void*)adj_tile_kernel<T>, lds_bytes);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL((adj_tile_kernel<T>), dim3(max_tiles, n), dim3(tile_threads(sizeof(T))), lds_bytes, st, G, it,
+                     replay ? 1 : 0);
+  return hipGetLastError();
+}
+
+// The small solver's system (max_free: the most free poses of a problem).
+template <typename T>
+hipError_t launch_adj_gather(const AdjGroup<T>& G, int n, int max_free, hipStream_t st) {
+  const int nlb = max_free * (max_free + 1) / 2;
+  hipLaunchKernelGGL((adj_gather_kernel<T>), dim3((nlb + 3) / 4, n), dim3(256), 0, st, G);
+  return hipGetLastError();
+}
+
+// Replayed step (solve = false) or adjoint solve of iteration `it`.
+template <typename T>
+hipError_t launch_adj_system(const AdjGroup<T>& G, int n, int lds_bytes, int it, bool solve, hipStream_t st) {
+  auto kernel = solve ? adj_solve_kernel<T> : adj_step_kernel<T>;
+  hipError_t e = opt_in_lds((const void*)kernel, lds_bytes);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(kernel, dim3(1, n), dim3(256), lds_bytes, st, G, it);
+  return hipGetLastError();
+}
+
 #define DPVBA_TILE_INSTANTIATE(T)                                                                          \
   template hipError_t launch_tile_iterate<T>(const IterArgs<T>&, int, hipStream_t);                       \
   template hipError_t launch_tile_finalize<T>(const TileInfo*, int, int, const int*, const int*, const T*, \
@@ -1058,6 +1195,9 @@ hipError_t launch_small_solve_group(const SmallGroup<T>& G, int lds_bytes, bool 
                                               T*, int, hipStream_t);                                       \
   template hipError_t launch_retract_copy<T>(const T*, T*, T*, int, int, const int*, hipStream_t, const T*,    \
                                              const int*);                                                  \
+  template hipError_t launch_adj_tile<T>(const AdjGroup<T>&, int, int, int, int, bool, hipStream_t);       \
+  template hipError_t launch_adj_gather<T>(const AdjGroup<T>&, int, int, hipStream_t);                     \
+  template hipError_t launch_adj_system<T>(const AdjGroup<T>&, int, int, int, bool, hipStream_t);          \
   template int small_solve_grid<T>(int, bool);                                                            \
   template hipError_t launch_small_solve_group<T>(const SmallGroup<T>&, int, bool, hipStream_t);          \
   template hipError_t launch_small_solve<T>(const SmallArgs<T>&, int, int, bool, hipStream_t);

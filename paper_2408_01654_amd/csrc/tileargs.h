@@ -20,7 +20,8 @@ struct IterArgs {
   const T* poses_cur;      // [N,7] x_t
   T* poses_next;           // [N,7] x_{t+1} (written by the last workgroup)
   const T* depth_in;       // caller's inverse depths (read when first)
-  T* depth_s;              // tile-ordered inverse depths
+  T* depth_s;              // tile-ordered inverse depths (written)
+  const T* depth_prev;     // those of the step before (depth_s, or an array of its own)
   T* xh_s;                 // tile-ordered patch rays [.,2]
   T* U_s;                  // stored Schur rows
   T* pscale_s;             // per patch: 1/sqrt(C~), w/sqrt(C~)
@@ -86,5 +87,33 @@ struct SmallGroup {
   SmallArgs<T> p[kSmallGroup];
 };
 static_assert(sizeof(SmallGroup<double>) <= 4096, "kernel arguments");
+
+// One problem of an adjoint launch: every launch of the adjoint takes up to
+// kAdjGroup problems, blockIdx.y (by value, within the 4 KB of a kernel's
+// arguments).  X and D hold the replayed iterates and steps, one after another.
+template <typename T>
+struct AdjArgs {
+  IterArgs<T> it;      // tile arguments; per-iteration fields set in the kernels (adj_iter)
+  int nit, n_edges, n_tp;
+  T* Xp;               // [nit + 1][N, 7] poses
+  T* Xd;               // [nit][n_tp] inverse depths, tile order
+  T* DX;               // [nit][6 n_free] steps
+  T *pbar, *dbar;      // adjoint of the poses [N, 7] and of the depths (tile order)
+  T *dxbar, *urhs;     // adjoint of the step, right-hand side of the solve
+  T *up, *ud, *dd;     // u = H~^-1 Deltabar (poses, depths), depth steps
+  T* exb;              // per edge: its 15 shares of the adjoint
+  int* status;         // [2 DPVBA_MAX_ITERS]: replayed steps, adjoint solves
+  unsigned int* mb;
+  T *Sp, *rhs, *d0;    // damped reduced system (packed for the small solver)
+  const T *poses0, *grad_poses, *grad_depth;
+  T *grad_target, *grad_weight;
+  const int *ii, *jj, *kk, *patch_pos, *pose_off, *pose_src, *pcount, *pedges;
+};
+constexpr int kAdjGroup = 6;
+template <typename T>
+struct AdjGroup {
+  AdjArgs<T> p[kAdjGroup];
+};
+static_assert(sizeof(AdjGroup<double>) + 64 <= 4096, "kernel arguments");
 
 }  // namespace dpvba
