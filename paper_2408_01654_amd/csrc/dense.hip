@@ -33,14 +33,11 @@ __global__ void __launch_bounds__(256) small_chol_solve_kernel(const T* S, const
   __shared__ int bad;
   __shared__ unsigned int minr_bits;
   const int tid = threadIdx.x;
-  if (n + 1 <= kSmallRows) {  // the register-resident panel solver
+  if (n + 1 <= kSmallRows) {  // the small panel solver
     __shared__ float minr;
     const int nr = small_solve_rows(n);
     T* xr = reinterpret_cast<T*>(dyn_lds) + 37 * nr + nr * nr;  // after the solver's own arrays
-    if (nr == 32) panel_chol_solve<T, 2>(n, S, rhs, nullptr, dyn_lds, xr, &bad, &minr, n);
-    else if (nr == 64) panel_chol_solve<T, 4>(n, S, rhs, nullptr, dyn_lds, xr, &bad, &minr, n);
-    else if (nr == 80) panel_chol_solve<T, 5>(n, S, rhs, nullptr, dyn_lds, xr, &bad, &minr, n);
-    else panel_chol_solve<T, 6>(n, S, rhs, nullptr, dyn_lds, xr, &bad, &minr, n);
+    panel_chol_solve<T>(n, S, rhs, nullptr, dyn_lds, xr, &bad, &minr, n, [] {});
     for (int i = tid; i < n; i += blockDim.x) dx[i] = xr[i];  // zero when a pivot failed
     if (tid == 0) {
       if (bad) atomicOr(status, 1);

@@ -148,20 +148,21 @@ struct BatchInst {
 };
 
 // Largest system (n + 1 <= kSmallRows) handled by the single-launch solver,
-// whose workgroup 0 factors it in registers (panel_chol_solve); larger
+// whose workgroup 0 factors it (panel_chol_solve); larger
 // systems take the separate dense solve.
 constexpr int kSmallRows = 96;
 
-// Row capacity 16 MB of the register-blocked dense solve of n unknowns
-// (augmented with the right-hand side: n + 1 rows).
+// Row capacity of the one-workgroup panel solve of n unknowns (augmented
+// with the right-hand side: n + 1 rows).
 __host__ __device__ inline int small_solve_rows(int n) {
   const int n1 = n + 1;
   return n1 <= 32 ? 32 : (n1 <= 64 ? 64 : (n1 <= 80 ? 80 : 96));
 }
 
-// Shared memory of the one-workgroup dense solve (register-blocked panels):
-// two published panels (2 x NR x 17), the reciprocal diagonal, the damped
-// diagonal, the pivots, the factor's rows (NR x NR) and the step.
+// Shared memory of the one-workgroup panel solve: within 37 nr + nr^2 entries
+// the padded matrix with the right-hand side's block ((m + 16) (m + 1), m = n
+// rounded up to 16), the factored diagonal blocks (17 m) and the damped
+// diagonal (m); then the step.
 __host__ __device__ inline int small_solve_lds_bytes(int n, int tsize) {
   const int nr = small_solve_rows(n);
   return (38 * nr + nr * nr) * tsize;

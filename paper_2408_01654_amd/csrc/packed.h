@@ -5,6 +5,7 @@
 #pragma once
 
 #include "common.h"
+#include "mfma.h"
 
 namespace dpvba {
 
@@ -149,450 +150,6 @@ __device__ void packed_solve(const TA* L, TB* b, int n) {
 #pragma unroll
     for (int q = 0; q < 4; ++q)
       if (lane + 64 * q < n) b[lane + 64 * q] = r[q];
-  }
-  __syncthreads();
-}
-
-// Cholesky of the augmented matrix [[S, .], [s^T, .]] (n + 1 <= NMAX rows)
-// by the first wavefront alone, with no workgroup barrier: lane l keeps rows
-// l and l + 64 in registers (entry k of a row in register k, so every index
-// is a compile-time constant).  Column j: the pivot is read from its lane
-// (v_readlane), every lane scales its column-j entries, then subtracts
-// l_ij l_kj from its entries k > j, taking each l_kj from lane k mod 64 by
-// v_readlane (no LDS round trip on the elimination's critical path).  Entries above a row's diagonal receive the
-// same arithmetic and are never read, so no lane needs a predicate.  The
-// last row ends as y = L^-1 s.  Then L^T dxi = y on the same wavefront with
-// one pivot broadcast per row.  Returns the step in x[0..n) (LDS, zero if a
-// pivot was not positive).
-template <int NMAX>
-__device__ __forceinline__ void wave_chol_solve(int n_in, const float* Sp_g, const float* rhs_g, const float* d0_g, float* cb,
-                                float* Lrow, float* x, float* invd, int* bad_out, float* minr_out) {
-  constexpr int N1 = NMAX < 64 ? NMAX : 64;  // columns held for rows < 64
-  constexpr int N2 = NMAX > 64 ? NMAX : 1;   // columns held for rows >= 64
-  const int n = __builtin_amdgcn_readfirstlane(n_in);  // uniform: loop guards stay scalar
-  const int lane = threadIdx.x;
-  const int r0 = lane, r1 = lane + 64;
-  float a0[N1], a1[N2];
-#pragma unroll
-  for (int k = 0; k < N1; ++k) {
-    float v = 0.f;
-    if (k <= r0 && r0 < n) v = Sp_g[r0 * (r0 + 1) / 2 + k];
-    else if (r0 == n && k < n) v = rhs_g[k];
-    a0[k] = v;
-  }
-#pragma unroll
-  for (int k = 0; k < N2; ++k) {
-    float v = 0.f;
-    if (NMAX > 64) {
-      if (k <= r1 && r1 < n) v = Sp_g[r1 * (r1 + 1) / 2 + k];
-      else if (r1 == n && k < n) v = rhs_g[k];
-    }
-    a1[k] = v;
-  }
-  const float dd0 = r0 < n ? d0_g[r0] : 1.f;
-  const float dd1 = r1 < n ? d0_g[r1] : 1.f;
-  int bad = 0;
-  float minr = 3.0e38f;
-#pragma unroll
-  for (int j = 0; j < NMAX - 1; ++j) {
-    if (j >= n) continue;  // uniform; keeps the loop fully unrolled
-    float d, d0j;
-    if (j < 64) {
-      d = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(a0[j < N1 ? j : 0]), j & 63));
-      d0j = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(dd0), j & 63));
-    } else {
-      d = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(a1[j < N2 ? j : 0]), j & 63));
-      d0j = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(dd1), j & 63));
-    }
-    const float ratio = d / d0j;
-    if (!(ratio >= minr)) minr = ratio == ratio ? fmaxf(ratio, 0.f) : 0.f;
-    if (!(d > 0.f) || !(d < 3.0e38f)) {
-      bad = 1;
-      d = 1.f;
-    }
-    const float rs = 1.f / sqrtf(d);
-    if (lane == 0) invd[j] = rs;
-    // scale column j (row j's diagonal becomes L_jj = sqrt(d)) and publish it
-    float l0 = 0.f, l1 = 0.f;
-    if (j < N1) {
-      l0 = a0[j < N1 ? j : 0] * rs;
-      a0[j < N1 ? j : 0] = l0;
-    }
-    if (NMAX > 64) {
-      l1 = a1[j < N2 ? j : 0] * rs;
-      a1[j < N2 ? j : 0] = l1;
-    }
-    // trailing update of entries k > j; l_kj comes from lane k mod 64 by
-    // v_readlane (rows above k receive arithmetic on entries above their
-    // diagonal, which are never read; columns k > n touch unused entries)
-#pragma unroll
-    for (int k = j + 1; k < NMAX; ++k) {
-      const float lk = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(k < 64 ? l0 : l1), k & 63));
-      if (k < N1) a0[k < N1 ? k : 0] -= l0 * lk;
-      if (NMAX > 64) a1[k < N2 ? k : 0] -= l1 * lk;
-    }
-  }
-  // rows of L (and y in row n) to LDS, row-major with stride NMAX
-#pragma unroll
-  for (int k = 0; k < N1; ++k)
-    if (r0 < NMAX) Lrow[r0 * NMAX + k] = a0[k];
-  if (NMAX > 64) {
-#pragma unroll
-    for (int k = 0; k < N2; ++k)
-      if (r1 < NMAX) Lrow[r1 * NMAX + k] = a1[k];
-  }
-  __builtin_amdgcn_s_waitcnt(0);
-  __builtin_amdgcn_wave_barrier();
-  // backward substitution L^T x = y; lane l holds entries l and l + 64
-  float y0 = r0 < n ? Lrow[n * NMAX + r0] : 0.f;
-  float y1 = (NMAX > 64 && r1 < n) ? Lrow[n * NMAX + r1] : 0.f;
-  for (int i = n - 1; i >= 0; --i) {
-    const float yv = i >= 64 ? y1 : y0;
-    const float xi = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(yv), i & 63)) * invd[i];
-    const float* Li = Lrow + i * NMAX;
-    if (r0 < i) y0 -= Li[r0] * xi;
-    if (r1 < i) y1 -= Li[r1] * xi;
-    if (r0 == i) y0 = xi;
-    if (r1 == i) y1 = xi;
-  }
-  if (r0 < n) x[r0] = bad ? 0.f : y0;
-  if (r1 < n) x[r1] = bad ? 0.f : y1;
-  if (lane == 0) {
-    *bad_out = bad;
-    *minr_out = minr;
-  }
-}
-
-
-// Cholesky of the augmented matrix [[S, .], [s^T, .]] (n + 1 <= 16 MB rows)
-// by a 256-thread workgroup with the matrix in registers: thread
-// (ty, tx) = (tid mod 16, tid / 16) holds entries (16 bi + ty, 16 bk + tx)
-// for all bi, bk < MB, so every register index is a compile-time constant.
-// Column j (loop fully unrolled): the 16 owners of column j (one wavefront)
-// take the pivot by v_readlane, scale their column-j entries and publish the
-// scaled column in a double-buffered LDS vector with zeros at rows <= j;
-// after one barrier every thread subtracts cb_i cb_k from all of its
-// entries.  The zeros make the update a no-op wherever it must not act
-// (finished columns and rows), so no thread needs a predicate, and entries
-// above the diagonal receive arithmetic that is never read.  The last row
-// ends as y = L^-1 s; then L^T x = y on one wavefront.  Returns the step in
-// x[0..n) (LDS; zero if a pivot was not positive).
-template <typename T, int MB>
-__device__ __forceinline__ void block_chol_solve(int n_in, const T* Sp_g, const T* rhs_g, const T* d0_g,
-                                                 unsigned char* lds, T* x, int* bad_out, float* minr_out) {
-  constexpr int NR = 16 * MB;
-  const int n = __builtin_amdgcn_readfirstlane(n_in);
-  const int tid = threadIdx.x;
-  const int ty = tid & 15, tx = tid >> 4;
-  T* cb = reinterpret_cast<T*>(lds);  // [2][NR]
-  T* invd = cb + 2 * NR;             // [NR]
-  T* dd = invd + NR;                 // [NR] damped diagonal (pivot monitor)
-  T* Lrow = dd + NR;                 // [NR][NR] rows of L, then y
-  for (int i = tid; i < n; i += blockDim.x) dd[i] = d0_g[i];
-  T a[MB][MB];
-#pragma unroll
-  for (int bi = 0; bi < MB; ++bi)
-#pragma unroll
-    for (int bk = 0; bk < MB; ++bk) {
-      const int i = 16 * bi + ty, k = 16 * bk + tx;
-      T v = (T)0;
-      if (k <= i && i < n) v = Sp_g[i * (i + 1) / 2 + k];
-      else if (i == n && k < n) v = rhs_g[k];
-      a[bi][bk] = v;
-    }
-  int bad = 0;
-  float minr = 3.0e38f;
-  __syncthreads();
-#pragma unroll
-  for (int j = 0; j < NR - 1; ++j) {
-    if (j >= n) continue;  // uniform
-    const int bj = j >> 4, jm = j & 15;
-    T* cbj = cb + (j & 1) * NR;
-    if (tx == jm) {  // one wavefront: threads 16 jm .. 16 jm + 15
-      // pivot a_jj lives on the owner with ty == jm: lane (16 jm + jm) mod 64
-      T d;
-      if constexpr (sizeof(T) == 4) {
-        d = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(a[bj][bj]), (16 * jm + jm) & 63));
-      } else {
-        const long long bits = __double_as_longlong(a[bj][bj]);
-        const int lo = __builtin_amdgcn_readlane((int)(bits & 0xffffffffLL), (16 * jm + jm) & 63);
-        const int hi = __builtin_amdgcn_readlane((int)(bits >> 32), (16 * jm + jm) & 63);
-        d = __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
-      }
-      if (ty == jm) {
-        const float ratio = (float)(d / dd[j]);
-        if (!(ratio >= minr)) minr = ratio == ratio ? fmaxf(ratio, 0.f) : 0.f;
-        if (!(d > (T)0) || !(d < (T)3.0e38)) bad = 1;
-      }
-      if (!(d > (T)0) || !(d < (T)3.0e38)) d = (T)1;
-      const T rs = (T)1 / dsqrt(d);
-      if (ty == jm) invd[j] = rs;
-#pragma unroll
-      for (int bi = 0; bi < MB; ++bi) {
-        const int i = 16 * bi + ty;
-        const T l = a[bi][bj] * rs;
-        if (i >= j) a[bi][bj] = l;
-        cbj[i] = i > j ? l : (T)0;
-      }
-    }
-    __syncthreads();
-    T ci[MB], ck[MB];
-#pragma unroll
-    for (int b = 0; b < MB; ++b) {
-      ci[b] = cbj[16 * b + ty];
-      ck[b] = cbj[16 * b + tx];
-    }
-#pragma unroll
-    for (int bi = 0; bi < MB; ++bi)
-#pragma unroll
-      for (int bk = 0; bk < MB; ++bk) a[bi][bk] -= ci[bi] * ck[bk];
-  }
-  // rows of L (and y in row n) to LDS
-#pragma unroll
-  for (int bi = 0; bi < MB; ++bi)
-#pragma unroll
-    for (int bk = 0; bk < MB; ++bk) Lrow[(16 * bi + ty) * NR + 16 * bk + tx] = a[bi][bk];
-  __syncthreads();
-  if (tid < 64) {  // backward substitution L^T x = y; lane l holds entries l, l + 64
-    const int r0 = tid, r1 = tid + 64;
-    T y0 = r0 < n ? Lrow[n * NR + r0] : (T)0;
-    T y1 = r1 < n ? Lrow[n * NR + r1] : (T)0;
-    for (int i = n - 1; i >= 0; --i) {
-      const T yv = i >= 64 ? y1 : y0;
-      T yi;
-      if constexpr (sizeof(T) == 4) {
-        yi = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(yv), i & 63));
-      } else {
-        const long long bits = __double_as_longlong(yv);
-        const int lo = __builtin_amdgcn_readlane((int)(bits & 0xffffffffLL), i & 63);
-        const int hi = __builtin_amdgcn_readlane((int)(bits >> 32), i & 63);
-        yi = __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
-      }
-      const T xi = yi * invd[i];
-      const T* Li = Lrow + i * NR;
-      if (r0 < i) y0 -= Li[r0] * xi;
-      if (r1 < i) y1 -= Li[r1] * xi;
-      if (r0 == i) y0 = xi;
-      if (r1 == i) y1 = xi;
-    }
-    if (r0 < n) x[r0] = y0;
-    if (r1 < n) x[r1] = y1;
-  }
-  // bad and minr are known to the owners' threads: combine through LDS
-  __shared__ int bad_s;
-  __shared__ float minr_s;
-  if (tid == 0) { bad_s = 0; minr_s = 3.0e38f; }
-  __syncthreads();
-  if (bad) atomicOr(&bad_s, 1);
-  if (minr < 3.0e38f) atomicMin(reinterpret_cast<unsigned int*>(&minr_s), __float_as_uint(minr));
-  __syncthreads();
-  if (tid < n && bad_s) x[tid] = (T)0;
-  if (tid + 256 < n && bad_s) x[tid + 256] = (T)0;
-  if (tid == 0) {
-    *bad_out = bad_s;
-    *minr_out = minr_s;
-  }
-  __syncthreads();
-}
-
-
-// Sixteen steps i = i_hi, i_hi - 1, ... (i < n) of L^T x = y on one
-// wavefront: x_i = y_i / L_ii with y_i broadcast from `src` (the half that
-// holds rows i), then y_r -= L_ir x_i (l0 / l1: L_ir of the lane's two
-// rows, zero unless r < i).  x_i is kept by the lane of row i, off the chain.
-template <typename T>
-__device__ __forceinline__ void back_sub16(int i_hi, int n, const T* l0, const T* l1, const T* iv, const T& src,
-                                           T& y0, T& y1, T& x0, T& x1, int r0, int r1) {
-#pragma unroll
-  for (int c = 0; c < 16; ++c) {
-    const int i = i_hi - c;
-    if (i >= n) continue;  // uniform
-    T yi;
-    if constexpr (sizeof(T) == 4) {
-      yi = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(src), i & 63));
-    } else {
-      const long long bits = __double_as_longlong(src);
-      const int lo = __builtin_amdgcn_readlane((int)(bits & 0xffffffffLL), i & 63);
-      const int hi = __builtin_amdgcn_readlane((int)(bits >> 32), i & 63);
-      yi = __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
-    }
-    const T xi = yi * iv[c];
-    y0 -= l0[c] * xi;
-    y1 -= l1[c] * xi;
-    x0 = r0 == i ? xi : x0;
-    x1 = r1 == i ? xi : x1;
-  }
-}
-
-// Cholesky of the augmented matrix [[S, .], [s^T, .]] (n + 1 <= 16 MB rows)
-// in panels of 16 columns, by a 256-thread workgroup with the matrix in
-// registers: thread (ty, tx) = (tid mod 16, tid / 16) holds entries
-// (16 bi + ty, 16 bk + tx), bi, bk < MB (the panel loop is unrolled, so every
-// register index is a compile-time constant).  Panel p: the threads publish
-// its column block in LDS; one wavefront factors the 16 columns on its own
-// (rows on lanes, pivots and column entries broadcast by v_readlane, no
-// barrier inside); after one barrier every thread takes back its factored
-// entries and applies the rank-16 update to its blocks right of and below
-// the panel.  Two barriers per panel instead of one per column.  The last
-// row ends as y = L^-1 s; then L^T x = y on one wavefront.  Returns the step
-// in x[0..n) (LDS; zero if a pivot was not positive).
-// ld > 0: Sp_g is instead a dense row-major matrix with row stride ld (its
-// lower triangle is read) and d0_g may be null (the damped diagonal is then
-// that matrix's diagonal).
-template <typename T, int MB>
-__device__ __forceinline__ void panel_chol_solve(int n_in, const T* Sp_g, const T* rhs_g, const T* d0_g,
-                                                 unsigned char* lds, T* x, int* bad_out, float* minr_out,
-                                                 int ld = 0) {
-  constexpr int NR = 16 * MB;
-  const int n = __builtin_amdgcn_readfirstlane(n_in);
-  const int tid = threadIdx.x;
-  const int ty = tid & 15, tx = tid >> 4;
-  const int lane = tid & 63, wave = tid >> 6;
-  const bool grid = tid < 256;  // the 16 x 16 register grid (larger workgroups: the rest only meet the barriers)
-  T* PB = reinterpret_cast<T*>(lds);  // [2][NR][17] published panel
-  T* invd = PB + 2 * NR * 17;         // [NR] 1 / L_jj
-  T* dd = invd + NR;                  // [NR] damped diagonal (pivot report)
-  T* piv = dd + NR;                   // [NR] pivots before the square root
-  T* Lrow = piv + NR;                 // [NR][NR]
-  for (int i = tid; i < n; i += blockDim.x) dd[i] = d0_g ? d0_g[i] : Sp_g[(size_t)i * ld + i];
-  T a[MB][MB];
-#pragma unroll
-  for (int bi = 0; bi < MB; ++bi)
-#pragma unroll
-    for (int bk = 0; bk < MB; ++bk) {
-      const int i = 16 * bi + ty, k = 16 * bk + tx;
-      T v = (T)0;
-      if (grid && k <= i && i < n) v = ld > 0 ? Sp_g[(size_t)i * ld + k] : Sp_g[i * (i + 1) / 2 + k];
-      else if (grid && i == n && k < n) v = rhs_g[k];
-      a[bi][bk] = v;
-    }
-  int bad = 0;
-#pragma unroll
-  for (int p = 0; p < MB; ++p) {
-    if (16 * p >= n) continue;  // uniform: no pivot left
-    T* P = PB + (p & 1) * NR * 17;
-    // publish the panel's column block (rows >= 16 p)
-    if (grid)
-#pragma unroll
-      for (int bi = p; bi < MB; ++bi) P[(16 * bi + ty) * 17 + tx] = a[bi][p];
-    __syncthreads();
-    if (wave == (p & 3)) {
-      // lane l holds rows 16 p + l and 16 p + l + 64 of the panel
-      const int rA = 16 * p + lane, rB = rA + 64;
-      const bool hasB = 16 * p + 64 < NR;  // compile-time: rows in the second half exist
-      T ra[16], rb[16];
-#pragma unroll
-      for (int c = 0; c < 16; ++c) {
-        ra[c] = rA < NR ? P[rA * 17 + c] : (T)0;
-        rb[c] = (hasB && rB < NR) ? P[rB * 17 + c] : (T)0;
-      }
-#pragma unroll
-      for (int c = 0; c < 16; ++c) {
-        const int j = 16 * p + c;
-        if (j >= n) continue;  // uniform
-        T d;
-        if constexpr (sizeof(T) == 4) {
-          d = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(ra[c]), c));
-        } else {
-          const long long bits = __double_as_longlong(ra[c]);
-          const int lo = __builtin_amdgcn_readlane((int)(bits & 0xffffffffLL), c);
-          const int hi = __builtin_amdgcn_readlane((int)(bits >> 32), c);
-          d = __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
-        }
-        if (lane == 0) piv[j] = d;
-        if (!(d > (T)0) || !(d < (T)3.0e38)) {
-          bad = 1;
-          d = (T)1;
-        }
-        const T rs = pivot_rsqrt<T>(d);
-        if (lane == 0) invd[j] = rs;
-        ra[c] *= rs;  // row j's own entry becomes L_jj = sqrt(d)
-        if (hasB) rb[c] *= rs;
-#pragma unroll
-        for (int c2 = c + 1; c2 < 16; ++c2) {
-          T lk;  // l_{16p + c2, j}: lane c2's entry of column c
-          if constexpr (sizeof(T) == 4) {
-            lk = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(ra[c]), c2));
-          } else {
-            const long long bits = __double_as_longlong(ra[c]);
-            const int lo = __builtin_amdgcn_readlane((int)(bits & 0xffffffffLL), c2);
-            const int hi = __builtin_amdgcn_readlane((int)(bits >> 32), c2);
-            lk = __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
-          }
-          ra[c2] -= ra[c] * lk;
-          if (hasB) rb[c2] -= rb[c] * lk;
-        }
-      }
-#pragma unroll
-      for (int c = 0; c < 16; ++c) {
-        if (rA < NR) P[rA * 17 + c] = ra[c];
-        if (hasB && rB < NR) P[rB * 17 + c] = rb[c];
-      }
-    }
-    __syncthreads();
-    // factored entries back, then the rank-16 update right of and below the panel
-    if (grid) {
-#pragma unroll
-      for (int bi = p; bi < MB; ++bi) a[bi][p] = P[(16 * bi + ty) * 17 + tx];
-#pragma unroll
-      for (int bi = p + 1; bi < MB; ++bi) {
-        T li[16];
-#pragma unroll
-        for (int c = 0; c < 16; ++c) li[c] = P[(16 * bi + ty) * 17 + c];
-#pragma unroll
-        for (int bk = p + 1; bk <= bi; ++bk) {
-          T acc = (T)0;
-#pragma unroll
-          for (int c = 0; c < 16; ++c) acc += li[c] * P[(16 * bk + tx) * 17 + c];
-          a[bi][bk] -= acc;
-        }
-      }
-    }
-  }
-  // rows of L (and y in row n) to LDS
-  if (grid)
-#pragma unroll
-    for (int bi = 0; bi < MB; ++bi)
-#pragma unroll
-      for (int bk = 0; bk < MB; ++bk) Lrow[(16 * bi + ty) * NR + 16 * bk + tx] = a[bi][bk];
-  __shared__ int bad_s;
-  __shared__ unsigned int minr_s;
-  if (tid == 0) { bad_s = 0; minr_s = __float_as_uint(3.0e38f); }
-  __syncthreads();
-  if (bad) atomicOr(&bad_s, 1);
-  // pivot report (smallest pivot / damped diagonal) on the wavefronts other
-  // than the first, while the first runs the backward substitution
-  if (tid >= 64) pivot_ratio_min<T>(piv, dd, n, &minr_s, tid - 64, (int)blockDim.x - 64);
-  if (tid < 64) {  // backward substitution L^T x = y; lane l holds entries l, l + 64
-    const int r0 = tid, r1 = tid + 64;
-    T y0 = r0 < n ? Lrow[n * NR + r0] : (T)0;
-    T y1 = r1 < n ? Lrow[n * NR + r1] : (T)0;
-    T x0 = (T)0, x1 = (T)0;
-    // blocks of 16 rows from the last; a block lies in one half (64 is a
-    // multiple of 16), so the broadcast source is fixed per block
-#pragma unroll
-    for (int blk = MB - 1; blk >= 0; --blk) {
-      if (16 * blk >= n) continue;  // uniform
-      T l0[16], l1[16], iv[16];
-#pragma unroll
-      for (int c = 0; c < 16; ++c) {  // L_ir for r < i only (zero otherwise), loaded off the chain
-        const int i = 16 * blk + 15 - c;
-        const int ic = min(i, NR - 1);
-        l0[c] = r0 < i && i < n ? Lrow[ic * NR + r0] : (T)0;
-        l1[c] = r1 < i && i < n ? Lrow[ic * NR + r1] : (T)0;
-        iv[c] = invd[ic];
-      }
-      if (blk >= 4) back_sub16<T>(16 * blk + 15, n, l0, l1, iv, y1, y0, y1, x0, x1, r0, r1);
-      else back_sub16<T>(16 * blk + 15, n, l0, l1, iv, y0, y0, y1, x0, x1, r0, r1);
-    }
-    if (r0 < n) x[r0] = x0;
-    if (r1 < n) x[r1] = x1;
-  }
-  __syncthreads();
-  if (tid < n && bad_s) x[tid] = (T)0;
-  if (tid == 0) {
-    *bad_out = bad_s;
-    *minr_out = __uint_as_float(minr_s);
   }
   __syncthreads();
 }
@@ -840,6 +397,188 @@ __device__ __forceinline__ T lane_bcast(T v, int l) {
     const int hi = __builtin_amdgcn_readlane((int)(bits >> 32), l);
     return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
   }
+}
+
+// Rank-16 update of a small system's matrix by panel p: the 16 x 16 blocks
+// (bi, bk), bk = bk_lo .. bk_hi, bi = bk .. mb (the right-hand side's block),
+// go to the wavefronts first, first + nwav, ...: W_(bi,bk) -= W_(bi,p) W_(bk,p)^T.
+template <typename T>
+__device__ __forceinline__ void panel_update(T* W, int ldw, int mb, int p, int bk_lo, int bk_hi, int first, int nwav) {
+  const int lane = threadIdx.x & 63, c0 = 16 * p;
+  int bk = bk_lo, bi = bk + first;
+#pragma unroll 1
+  for (;;) {
+    while (bk <= bk_hi && bi > mb) {  // past this column block: on into the next
+      bi += bk - mb;
+      ++bk;
+    }
+    if (bk > bk_hi) break;
+    const T* xr = W + (16 * bi + (lane & 15)) * ldw + c0 + (lane >> 4);
+    const T* yr = W + (16 * bk + (lane & 15)) * ldw + c0 + (lane >> 4);
+    typename Mfma<T>::acc_t acc = {0, 0, 0, 0};
+#pragma unroll
+    for (int k = 0; k < 16; k += 4) acc = Mfma<T>::step(xr[k], yr[k], acc);
+#pragma unroll
+    for (int v = 0; v < 4; ++v) W[(16 * bi + Mfma<T>::row(lane, v)) * ldw + 16 * bk + (lane & 15)] -= acc[v];
+    bi += nwav;
+  }
+}
+
+// Cholesky solve S x = s of a small system (n <= 95) by one workgroup of at
+// least four wavefronts: the matrix in LDS, padded to mb 16-column panels with
+// an identity, the right-hand side as row block mb (its first row, which ends
+// as y = L^-1 s; its other rows are never looked at).  Panel p: each of the
+// first one or two wavefronts factors the 16 x 16 diagonal block and takes four
+// of the row blocks below it (chol16), while the others finish the update
+// by panel p - 1 on the matrix cores; after one barrier everyone updates the
+// next column block, and a second closes the panel.  The factored diagonal
+// blocks are kept apart, since the second wavefront may still read the block.
+// Then L^T x = y on wavefront 0, the pivot report on wavefront 1, and
+// beside() on all but the first.  The loops over panels are rolled: the code
+// runs once or twice a launch, and with the matrix in registers and everything
+// unrolled most of the time went into fetching instructions (factor, solve and
+// retraction of 90 float64 unknowns in a launch of their own: 31.4 -> 22.8 us; a
+// 22-frame window of two iterations in float32: 153.4 -> 124.2 us).
+// x [n] (LDS): zero if a pivot was not positive.  ld > 0: Sp_g is a dense
+// row-major matrix with row stride ld (its lower triangle is read), else
+// packed; d0_g null: the damped diagonal is that of S.  The arrays fit the
+// 37 nr + nr^2 entries of small_solve_lds_bytes (nr = small_solve_rows(n)).
+template <typename T, typename F>
+__device__ __forceinline__ void panel_chol_solve(int n_in, const T* Sp_g, const T* rhs_g, const T* d0_g,
+                                                 unsigned char* lds, T* x, int* bad_out, float* minr_out, int ld,
+                                                 F&& beside) {
+  constexpr int kDs = 16 * 17;
+  const int n = __builtin_amdgcn_readfirstlane(n_in);
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6), nwav = (int)blockDim.x >> 6;
+  const int mb = (n + 15) >> 4, nrp = 16 * mb, ldw = nrp + 1;
+  T* W = reinterpret_cast<T*>(lds);  // [nrp + 16][ldw]
+  T* Ld = W + (nrp + 16) * ldw;      // [mb][16][17] factored diagonal blocks
+  T* dd = Ld + mb * kDs;             // [nrp] damped diagonal
+  for (int k = tid; k < nrp; k += blockDim.x) {
+    W[nrp * ldw + k] = k < n ? rhs_g[k] : (T)0;
+    if (d0_g && k < n) dd[k] = d0_g[k];
+  }
+  {
+    const int ty = (tid >> 4) & 15, tx = tid & 15, parts = (int)blockDim.x >> 8;
+    const int nt = mb * (mb + 1) / 2;
+    for (int t0 = w >> 2; t0 < nt; t0 += 8 * parts) {  // eight 16 x 16 tiles' loads in flight
+      T v[8];
+      int at[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        const int t = min(t0 + u * parts, nt - 1);
+        int bi = 0;
+        while ((bi + 1) * (bi + 2) / 2 <= t) ++bi;
+        const int i = 16 * bi + ty, k = 16 * (t - bi * (bi + 1) / 2) + tx;
+        at[u] = i * ldw + k;
+        if (i < n && k <= i) v[u] = ld > 0 ? Sp_g[(size_t)i * ld + k] : Sp_g[i * (i + 1) / 2 + k];
+        else v[u] = (T)(i == k ? 1 : 0);
+      }
+#pragma unroll
+      for (int u = 0; u < 8; ++u) W[at[u]] = v[u];
+    }
+  }
+  __syncthreads();
+  if (!d0_g) {
+    if (tid < n) dd[tid] = W[tid * ldw + tid];
+    __syncthreads();
+  }
+  int bad = 0;
+#pragma unroll 1
+  for (int p = 0; p < mb; ++p) {
+    const int act = mb - p > 4 ? 2 : 1;  // wavefronts on the panel
+    if (w < act) {
+      const int s = lane & 15, q = lane >> 4, bq = p + 1 + 4 * w + q;
+      const T* wa = W + (16 * p + s) * ldw + 16 * p;
+      T* wb = W + (bq <= mb ? 16 * bq + s : nrp + 15) * ldw + 16 * p;  // else a row nobody looks at
+      T ra[16], rb[16];
+#pragma unroll
+      for (int c = 0; c < 16; ++c) {
+        ra[c] = wa[c];
+        rb[c] = wb[c];
+      }
+      chol16<T>(ra, rb, bad);
+      // (the stores that depend on the lane come last: a branch here would sink
+      // the rows' updates below it)
+#pragma unroll
+      for (int c = 0; c < 16; ++c) wb[c] = rb[c];
+      if (lane < 16 && w == 0) {
+#pragma unroll
+        for (int c = 0; c < 16; ++c) Ld[p * kDs + s * 17 + c] = ra[c];
+      }
+    } else if (p > 0) {
+      panel_update<T>(W, ldw, mb, p - 1, p + 1, mb - 1, w - act, nwav - act);
+    }
+    __syncthreads();
+    if (p + 1 < mb) panel_update<T>(W, ldw, mb, p, p + 1, p + 1, w, nwav);
+    __syncthreads();
+  }
+  if (w == 0) {  // backward substitution; lane l holds entries l, l + 64
+    const int r0 = lane, r1 = lane + 64;
+    T y0 = r0 < n ? W[nrp * ldw + r0] : (T)0, y1 = r1 < n ? W[nrp * ldw + r1] : (T)0;
+    const T i0 = r0 < n ? (T)1 / Ld[(r0 >> 4) * kDs + (r0 & 15) * 18] : (T)0;
+    const T i1 = r1 < n ? (T)1 / Ld[(r1 >> 4) * kDs + (r1 & 15) * 18] : (T)0;
+    T x0 = (T)0, x1 = (T)0;
+    // rows from the last, a block of 16 at a time (entries L_ir for r < i
+    // only, zero otherwise, loaded off the chain); first those of the upper half
+#pragma unroll 1
+    for (int b = mb - 1; b >= 4; --b) {
+      const T* p0 = W + 16 * b * ldw + r0;
+      const bool in = r1 >> 4 == b;
+      const T* p1 = in ? Ld + b * kDs + (r1 & 15) : W + 16 * b * ldw + min(r1, nrp - 1);
+      const int s1 = in ? 17 : ldw;
+      T l0[16], l1[16];
+#pragma unroll
+      for (int c = 0; c < 16; ++c) {
+        l0[c] = p0[c * ldw];
+        l1[c] = r1 < 16 * b + c ? p1[c * s1] : (T)0;
+      }
+#pragma unroll
+      for (int c = 15; c >= 0; --c) {
+        const int i = 16 * b + c;
+        if (i >= n) continue;  // uniform
+        const T xi = lane_bcast(y1 * i1, i - 64);
+        y0 -= l0[c] * xi;
+        y1 -= l1[c] * xi;
+        x1 = r1 == i ? xi : x1;
+      }
+    }
+#pragma unroll 1
+    for (int b = min(mb, 4) - 1; b >= 0; --b) {
+      const bool in = r0 >> 4 == b;
+      const T* p0 = in ? Ld + b * kDs + (r0 & 15) : W + 16 * b * ldw + min(r0, nrp - 1);
+      const int s0 = in ? 17 : ldw;
+      T l0[16];
+#pragma unroll
+      for (int c = 0; c < 16; ++c) l0[c] = r0 < 16 * b + c ? p0[c * s0] : (T)0;
+#pragma unroll
+      for (int c = 15; c >= 0; --c) {
+        const int i = 16 * b + c;
+        if (i >= n) continue;  // uniform
+        const T xi = lane_bcast(y0 * i0, i);
+        y0 -= l0[c] * xi;
+        x0 = r0 == i ? xi : x0;
+      }
+    }
+    if (r0 < n) x[r0] = bad ? (T)0 : x0;
+    if (r1 < n) x[r1] = bad ? (T)0 : x1;
+    if (lane == 0) *bad_out = bad;
+  } else {
+    if (w == 1) {  // smallest L_jj^2 / S_jj
+      unsigned int m = __float_as_uint(3.0e38f);
+      for (int j = lane; j < n; j += 64) {
+        const T l = Ld[(j >> 4) * kDs + (j & 15) * 18];
+        const float ratio = (float)(l * l / dd[j]);
+        m = min(m, __float_as_uint(l > (T)0 && ratio == ratio ? fmaxf(ratio, 0.f) : 0.f));
+      }
+#pragma unroll
+      for (int o = 32; o > 0; o >>= 1) m = min(m, (unsigned int)__shfl_xor((int)m, o));
+      if (lane == 0) *minr_out = __uint_as_float(m);
+    }
+    beside();
+  }
+  __syncthreads();
 }
 
 // In-place Cholesky of the packed lower triangle of rows 0..nr-1 of an

@@ -732,8 +732,7 @@ __device__ __forceinline__ void gather_slice(const IterArgs<T>& A, T* Sp, T* rhs
 }
 
 // Factor and solve the gathered system in workgroup 0 and retract the free
-// poses (panel_chol_solve: matrix in registers, 16-column panels factored by
-// one wavefront, two barriers per panel; n + 1 <= 96).  A non-positive
+// poses (panel_chol_solve; n + 1 <= 96).  A non-positive
 // pivot discards the step (dxi = 0, *A.status = 1).
 template <typename T>
 __device__ __forceinline__ void factor_solve_retract(const IterArgs<T>& A, const T* Sp_g, const T* rhs_g,
@@ -744,29 +743,27 @@ __device__ __forceinline__ void factor_solve_retract(const IterArgs<T>& A, const
   __shared__ float minr;
   const int nr = small_solve_rows(n);
   T* x = reinterpret_cast<T*>(lds) + 37 * nr + nr * nr;  // after the solver's own arrays
-  // The tiles' costs and invalid-edge counts of this iteration: loaded in
-  // parallel before the factor (their latency overlaps it), summed in tile
-  // order after it.  At most 256 are staged; any beyond are read in order.
-  const int n_cost = A.cost_out ? A.n_tiles : 0;
-  const int n_stage = n_cost < 256 ? n_cost : 256;
-  double pcost = 0.0;
-  int pinv = 0;
-  if (tid < n_stage) {
-    pcost = A.part_cost[tid];
-    pinv = A.part_invalid[tid];
-  }
-  if (nr == 32) panel_chol_solve<T, 2>(n, Sp_g, rhs_g, d0_g, lds, x, &bad, &minr);
-  else if (nr == 64) panel_chol_solve<T, 4>(n, Sp_g, rhs_g, d0_g, lds, x, &bad, &minr);
-  else if (nr == 80) panel_chol_solve<T, 5>(n, Sp_g, rhs_g, d0_g, lds, x, &bad, &minr);
-  else panel_chol_solve<T, 6>(n, Sp_g, rhs_g, d0_g, lds, x, &bad, &minr);
-  // the published-panel area (2 x 32 x 17 values or more) is free after the factor
-  double* cost_s = reinterpret_cast<double*>(lds);
-  int* inv_s = reinterpret_cast<int*>(cost_s + 256);
-  if (tid < n_stage) {
-    cost_s[tid] = pcost;
-    inv_s[tid] = pinv;
-  }
-  __syncthreads();
+  // The tiles' costs and invalid-edge counts of this iteration, summed in tile
+  // order by the third wavefront beside the backward substitution.
+  const int n_cost = A.cost_out ? A.n_tiles : 0, lane = tid & 63;
+  panel_chol_solve<T>(n, Sp_g, rhs_g, d0_g, lds, x, &bad, &minr, 0, [&] {
+    if (tid >> 6 != 2 || n_cost == 0) return;
+    double cc = 0.0;
+    int inv = 0;
+    for (int t0 = 0; t0 < n_cost; t0 += 64) {
+      const int m = min(64, n_cost - t0);
+      const double pc = lane < m ? A.part_cost[t0 + lane] : 0.0;
+      const int pi = lane < m ? A.part_invalid[t0 + lane] : 0;
+      for (int u = 0; u < m; ++u) {
+        cc += lane_bcast(pc, u);
+        inv += __builtin_amdgcn_readlane(pi, u);
+      }
+    }
+    if (lane == 0) {
+      *A.cost_out = cc;
+      if (A.invalid_out) *A.invalid_out = inv;
+    }
+  });
   for (int i = tid; i < n; i += blockDim.x) A.dx[i] = x[i];
   for (int i = tid; i < A.n_frames; i += blockDim.x) {
     const T* pc = A.poses_cur + 7 * (size_t)i;
@@ -777,20 +774,6 @@ __device__ __forceinline__ void factor_solve_retract(const IterArgs<T>& A, const
   if (tid == 0) {
     *A.status = bad;
     *A.min_bits = __float_as_uint(minr >= 0.f ? minr : 0.f);
-    if (A.cost_out) {
-      double cc = 0.0;
-      int inv = 0;
-      for (int t = 0; t < n_stage; ++t) {
-        cc += cost_s[t];
-        inv += inv_s[t];
-      }
-      for (int t = n_stage; t < n_cost; ++t) {
-        cc += A.part_cost[t];
-        inv += A.part_invalid[t];
-      }
-      *A.cost_out = cc;
-      if (A.invalid_out) *A.invalid_out = inv;
-    }
   }
   __syncthreads();
 }
@@ -1023,11 +1006,7 @@ __global__ void __launch_bounds__(256) adj_solve_kernel(AdjGroup<T> G, int it) {
   __syncthreads();
   const int nr = small_solve_rows(n);
   T* x = reinterpret_cast<T*>(lds) + 37 * nr + nr * nr;  // after the solver's own arrays
-  if (nr == 32) panel_chol_solve<T, 2>(n, a.Sp, a.urhs, a.d0, lds, x, &bad, &minr);
-  else if (nr == 64) panel_chol_solve<T, 4>(n, a.Sp, a.urhs, a.d0, lds, x, &bad, &minr);
-  else if (nr == 80) panel_chol_solve<T, 5>(n, a.Sp, a.urhs, a.d0, lds, x, &bad, &minr);
-  else panel_chol_solve<T, 6>(n, a.Sp, a.urhs, a.d0, lds, x, &bad, &minr);
-  __syncthreads();
+  panel_chol_solve<T>(n, a.Sp, a.urhs, a.d0, lds, x, &bad, &minr, 0, [] {});
   for (int i = tid; i < n; i += blockDim.x) a.up[i] = x[i];  // zero when a pivot failed
   if (tid == 0) {
     a.status[DPVBA_MAX_ITERS + it] = bad;
