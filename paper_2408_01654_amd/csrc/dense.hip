@@ -21,8 +21,9 @@ __device__ __forceinline__ void pivot_min(unsigned int* min_bits, float ratio) {
   atomicMin(min_bits, __float_as_uint(ratio));
 }
 
+constexpr int kSmallCholThreads = 512;
 template <typename T>
-__global__ void __launch_bounds__(256) small_chol_solve_kernel(const T* S, const T* rhs, int n, T* dx,
+__global__ void __launch_bounds__(kSmallCholThreads) small_chol_solve_kernel(const T* S, const T* rhs, int n, T* dx,
                                                                int* status, unsigned int* min_bits) {
   extern __shared__ __align__(16) unsigned char dyn_lds[];
   T* d0 = reinterpret_cast<T*>(dyn_lds);  // [n] damped diagonal (pivot report)
@@ -98,7 +99,7 @@ hipError_t launch_small_chol(const T* S, const T* rhs, int n, T* dx, int* status
                       : packed_solve_lds_bytes(n, sizeof(T));
   hipError_t e = opt_in_lds((const void*)small_chol_solve_kernel<T>, lds);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((small_chol_solve_kernel<T>), dim3(1), dim3(256), lds, st, S, rhs, n, dx, status, min_bits);
+  hipLaunchKernelGGL((small_chol_solve_kernel<T>), dim3(1), dim3(kSmallCholThreads), lds, st, S, rhs, n, dx, status, min_bits);
   return hipGetLastError();
 }
 

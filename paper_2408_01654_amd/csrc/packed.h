@@ -583,88 +583,91 @@ __device__ __forceinline__ void panel_chol_solve(int n_in, const T* Sp_g, const 
 
 // In-place Cholesky of the packed lower triangle of rows 0..nr-1 of an
 // n-column system (nr = n, or n + 1 with the right-hand side appended as row
-// n, which then ends as y = L^-1 s; nr <= 256), in panels of 16 columns.
-// Panel j0: the first wavefront takes the panel's rows (row j0 + l + 64 t on
-// lane l, t < 4), factors its 16 columns alone (pivots and column entries
-// broadcast by v_readlane) and writes them back; after a barrier the first
-// 256 threads subtract the panel's rank-16 product from the trailing
-// triangle, thread (ty, tx) = (tid mod 16, tid / 16 mod 16) owning entry
-// (16 bi + ty, 16 bk + tx) of each 16 x 16 block.  Two barriers per panel.
-// invd[j] = 1 / L_jj and piv[j] = the pivot before its square root; a pivot
-// that is not positive or not finite is replaced by 1 and sets *bad (shared,
-// cleared by the caller).
+// n, which then ends as y = L^-1 s; nr <= 256) by at least four wavefronts, in
+// panels of 16 columns.  Panel j0: every wavefront that has rows below the 16 x
+// 16 diagonal block loads the block (an identity beyond column n) and four
+// 16-row blocks, and after a barrier factors and stores its rows (chol16); then
+// all update the trailing triangle on the matrix cores, one 16 x 16 tile at a
+// time.  Three barriers a panel.  256 systems of up to 234 unknowns, one
+// to a CU, on eight wavefronts: 96 us with their solve (one wavefront with
+// four rows a lane and entries broadcast through scalar registers, the update
+// by dot products in vector registers: 172 us).  invd[j] = 1 / L_jj and piv[j] =
+// L_jj^2; a pivot that is not positive or not finite leaves its column
+// unscaled (invd 1, piv the pivot) and sets *bad (shared, cleared by the caller).
 template <typename T>
 __device__ __forceinline__ void packed_panel_factor(T* A, int n_in, int nr_in, T* invd, T* piv, int* bad) {
   const int n = __builtin_amdgcn_readfirstlane(n_in);
   const int nr = __builtin_amdgcn_readfirstlane(nr_in);
-  const int tid = threadIdx.x;
-  const int lane = tid & 63;
-  const int ty = tid & 15, tx = (tid >> 4) & 15;
+  const int tid = threadIdx.x, lane = tid & 63, s = lane & 15, q = lane >> 4;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6), nwav = (int)blockDim.x >> 6;
+  int badl = 0;
+#pragma unroll 1
   for (int j0 = 0; j0 < n; j0 += 16) {
-    if (tid < 64) {
-      T ra[4][16];
-#pragma unroll
-      for (int t = 0; t < 4; ++t) {
-        const int i = j0 + lane + 64 * t;
-#pragma unroll
-        for (int c = 0; c < 16; ++c)
-          ra[t][c] = (i < nr && j0 + c <= i && j0 + c < n) ? A[packed_index(i, j0 + c)] : (T)0;
-      }
-      int badl = 0;
+    const int s0 = j0 + 16, below = min(s0, n);  // first row below the panel (row n after a partial one)
+    const int i = j0 + s, r = below + 16 * (4 * w + q) + s;
+    const bool on = w == 0 || below + 64 * w < nr;
+    T ra[16], rb[16];
+    if (on) {
+      const T* Ai = A + packed_index(min(i, n - 1), j0);
+      const T* Ar = A + packed_index(min(r, nr - 1), j0);
 #pragma unroll
       for (int c = 0; c < 16; ++c) {
-        const int j = j0 + c;
-        if (j >= n) continue;  // uniform
-        T d = lane_bcast(ra[0][c], c);
-        if (lane == 0) piv[j] = d;
-        if (!(d > (T)0) || !(d < (T)3.0e38)) {
-          badl = 1;
-          d = (T)1;
-        }
-        const T rs = pivot_rsqrt<T>(d);
-        if (lane == 0) invd[j] = rs;
-#pragma unroll
-        for (int t = 0; t < 4; ++t) ra[t][c] *= rs;
-#pragma unroll
-        for (int c2 = c + 1; c2 < 16; ++c2) {
-          const T lk = lane_bcast(ra[0][c], c2);  // entry (j0 + c2, j) of the panel
-#pragma unroll
-          for (int t = 0; t < 4; ++t) ra[t][c2] -= ra[t][c] * lk;
-        }
+        ra[c] = i < n && c <= s ? Ai[c] : (T)(i >= n && c == s ? 1 : 0);
+        rb[c] = r < nr && j0 + c < n ? Ar[c] : (T)0;
       }
-#pragma unroll
-      for (int t = 0; t < 4; ++t) {
-        const int i = j0 + lane + 64 * t;
-#pragma unroll
-        for (int c = 0; c < 16; ++c)
-          if (i < nr && j0 + c <= i && j0 + c < n) A[packed_index(i, j0 + c)] = ra[t][c];
-      }
-      if (badl && lane == 0) *bad = 1;
     }
     __syncthreads();
-    const int s0 = j0 + 16;  // trailing rows s0 .. nr - 1, columns s0 .. min(i, n - 1)
-    if (tid < 256 && s0 < nr) {
-      const int nbr = (nr - s0 + 15) >> 4;
-      for (int bi = 0; bi < nbr; ++bi) {
-        const int i = s0 + 16 * bi + ty;
-        if (i >= nr) continue;
-        T li[16];
-        const T* Li = A + packed_index(i, j0);
+    if (on) {
+      chol16<T>(ra, rb, badl);
+      if (r < nr) {
+        T* Ar = A + packed_index(r, j0);
 #pragma unroll
-        for (int c = 0; c < 16; ++c) li[c] = Li[c];
-        for (int bk = 0; bk <= bi; ++bk) {
-          const int k = s0 + 16 * bk + tx;
-          if (k > i || k >= n) continue;
-          const T* Lk = A + packed_index(k, j0);
-          T acc = (T)0;
+        for (int c = 0; c < 16; ++c)
+          if (j0 + c < n) Ar[c] = rb[c];
+      }
+      if (w == 0 && q == 0 && i < n) {
+        T* Ai = A + packed_index(i, j0);
 #pragma unroll
-          for (int c = 0; c < 16; ++c) acc += li[c] * Lk[c];
-          A[packed_index(i, k)] -= acc;
+        for (int c = 0; c < 16; ++c)
+          if (c <= s) Ai[c] = ra[c];
+      }
+    }
+    __syncthreads();
+    if (s0 < n) {
+      // tile (bi, bk), bk <= bi, of the trailing rows s0 .. nr - 1, columns s0 .. n - 1
+      const int nbr = (nr - s0 + 15) >> 4, nbc = (n - s0 + 15) >> 4;
+      int bi = 0, bk = w;
+#pragma unroll 1
+      for (;;) {
+        while (bi < nbr && bk > min(bi, nbc - 1)) {
+          bk -= min(bi, nbc - 1) + 1;
+          ++bi;
         }
+        if (bi >= nbr) break;
+        const T* xr = A + packed_index(min(s0 + 16 * bi + s, nr - 1), j0) + q;
+        const T* yr = A + packed_index(min(s0 + 16 * bk + s, n - 1), j0) + q;
+        typename Mfma<T>::acc_t acc = {0, 0, 0, 0};
+#pragma unroll
+        for (int k = 0; k < 16; k += 4) acc = Mfma<T>::step(xr[k], yr[k], acc);
+        const int k = s0 + 16 * bk + s;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          const int row = s0 + 16 * bi + Mfma<T>::row(lane, v);
+          if (row < nr && k <= row && k < n) A[packed_index(row, k)] -= acc[v];
+        }
+        bk += nwav;
       }
     }
     __syncthreads();
   }
+  if (badl && lane == 0) *bad = 1;
+  for (int j = tid; j < n; j += blockDim.x) {
+    const T l = A[packed_index(j, j)];
+    const bool ok = l > (T)0 && l < (T)3.0e38;
+    invd[j] = ok ? (T)1 / l : (T)1;
+    piv[j] = ok ? l * l : l;
+  }
+  __syncthreads();
 }
 
 // Sixteen backward steps i = i_hi, i_hi - 1, ... (i < n) with row i held in
