@@ -666,6 +666,10 @@ __global__ void __launch_bounds__(tile_threads(sizeof(T))) tile_iterate_kernel(I
 // i (i + 1) / 2), summed from the tiles' shares in tile order.  One
 // wavefront per lower 6x6 block (P >= Q): the block's share offsets are
 // loaded once and broadcast, so every share load of a lane is independent.
+// Bound by the latency of a block's shares: 8 are in flight, 16 in float64,
+// where the sums cost more, and a diagonal block's vectors load beside them
+// (alone in a launch, 15 free poses in float64: 16.0 -> 10.9 us; 17-frame
+// window 147.0 -> 139.4 us; in float32 16 measured like 8).
 // Diagonal entries get lam (Diag(B) + 1) and are kept in d0; the diagonal
 // blocks also produce s.
 template <typename T>
@@ -680,52 +684,45 @@ __device__ __forceinline__ void gather_slice(const IterArgs<T>& A, T* Sp, T* rhs
     const int lo = A.s_off[blk], hi = A.s_off[blk + 1];
     const bool lower = lane < 36 && (P > Q || r >= c);
     const int eo = c * 6 + r;  // the shares hold upper entries: (r, c) of S_PQ is [c][r] of a share
-    T v = (T)0;
-    for (int b0 = lo; b0 < hi; b0 += 64) {
-      const int o_l = b0 + lane < hi ? A.s_src[b0 + lane] : 0;
-      const int nq = min(64, hi - b0);
-      for (int q0 = 0; q0 < nq; q0 += 8) {  // 8 independent loads in flight, summed in order
-        T part[8];
+    const int row = 6 * P + r, col = 6 * Q + c;
+    // Diag(B) (lanes on the diagonal) and s (lanes 36..41) of pose P, with its diagonal block
+    const bool diag = P == Q;
+    const int m = lane < 36 ? r : lane - 36;
+    const bool want_d = diag && lane < 36 && r == c, want_s = diag && lane >= 36 && lane < 42;
+    const int vlo = diag ? A.v_off[P] : 0, vhi = diag ? A.v_off[P + 1] : 0;
+    constexpr int U = sizeof(T) == 8 ? 16 : 8;
+    T v = (T)0, vec = (T)0;
+    const int cnt = max(hi - lo, vhi - vlo);
+    for (int b0 = 0; b0 < cnt; b0 += 64) {
+      const int o_l = lo + b0 + lane < hi ? A.s_src[lo + b0 + lane] : 0;
+      const int2 p_l = vlo + b0 + lane < vhi ? A.v_src[vlo + b0 + lane] : make_int2(0, 0);
+      const int nq = min(64, hi - lo - b0), nv = min(64, vhi - vlo - b0);
+      for (int q0 = 0; q0 < min(64, cnt - b0); q0 += U) {  // U independent loads in flight, summed in order
+        T part[U], pv[U];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) {
+        for (int u = 0; u < U; ++u) {
           const int o = __shfl(o_l, (q0 + u) & 63);
           part[u] = (lower && q0 + u < nq) ? A.part_S[o + eo] : (T)0;
         }
+        if (diag) {
 #pragma unroll
-        for (int u = 0; u < 8; ++u) v += part[u];
-      }
-    }
-    const int row = 6 * P + r, col = 6 * Q + c;
-    if (P == Q) {
-      // Diag(B) (lanes on the diagonal) and s (lanes 36..41) of pose P
-      const int m = lane < 36 ? r : lane - 36;
-      const bool want_d = lane < 36 && r == c, want_s = lane >= 36 && lane < 42;
-      const int vlo = A.v_off[P], vhi = A.v_off[P + 1];
-      T db = (T)0, sv = (T)0;
-      for (int b0 = vlo; b0 < vhi; b0 += 64) {
-        const int2 o_l = b0 + lane < vhi ? A.v_src[b0 + lane] : make_int2(0, 0);
-        const int nq = min(64, vhi - b0);
-        for (int q0 = 0; q0 < nq; q0 += 8) {
-          T pd[8], ps[8];
-#pragma unroll
-          for (int u = 0; u < 8; ++u) {
-            const int ox = __shfl(o_l.x, (q0 + u) & 63), oy = __shfl(o_l.y, (q0 + u) & 63);
-            const bool in = q0 + u < nq;
-            pd[u] = (want_d && in) ? A.part_vec[oy + m] : (T)0;
-            ps[u] = (want_s && in) ? A.part_vec[ox + m] : (T)0;
-          }
-#pragma unroll
-          for (int u = 0; u < 8; ++u) {
-            db += pd[u];
-            sv += ps[u];
+          for (int u = 0; u < U; ++u) {
+            const int ox = __shfl(p_l.x, (q0 + u) & 63), oy = __shfl(p_l.y, (q0 + u) & 63);
+            pv[u] = (want_d || want_s) && q0 + u < nv ? A.part_vec[(want_s ? ox : oy) + m] : (T)0;
           }
         }
+#pragma unroll
+        for (int u = 0; u < U; ++u) v += part[u];
+        if (diag) {
+#pragma unroll
+          for (int u = 0; u < U; ++u) vec += pv[u];
+        }
       }
-      if (want_s) rhs[6 * P + m] = sv;
-      if (want_d) {
-        v += A.lam_diag * db + A.lambda;
-        d0[row] = v;
-      }
+    }
+    if (want_s) rhs[6 * P + m] = vec;
+    if (want_d) {
+      v += A.lam_diag * vec + A.lambda;
+      d0[row] = v;
     }
     if (lower) Sp[row * (row + 1) / 2 + col] = v;
   }
@@ -949,8 +946,9 @@ __global__ void __launch_bounds__(256) adj_gather_kernel(AdjGroup<T> G) {
 }
 
 // Replayed step: factor, solve and retraction of iteration `it`.
+constexpr int kAdjSolveThreads = 512;
 template <typename T>
-__global__ void __launch_bounds__(256) adj_step_kernel(AdjGroup<T> G, int it) {
+__global__ void __launch_bounds__(kAdjSolveThreads) adj_step_kernel(AdjGroup<T> G, int it) {
   extern __shared__ __align__(16) unsigned char lds[];
   const AdjArgs<T>& a = G.p[blockIdx.y];
   factor_solve_retract<T>(adj_iter<T>(a, it, true), a.Sp, a.rhs, a.d0, lds);
@@ -961,7 +959,7 @@ __global__ void __launch_bounds__(256) adj_step_kernel(AdjGroup<T> G, int it) {
 // The shares of a pose are summed by ten lanes a component, four poses of a
 // wavefront together, so the sum is a few loads deep instead of one a tile.
 template <typename T>
-__global__ void __launch_bounds__(256) adj_solve_kernel(AdjGroup<T> G, int it) {
+__global__ void __launch_bounds__(kAdjSolveThreads) adj_solve_kernel(AdjGroup<T> G, int it) {
   extern __shared__ __align__(16) unsigned char lds[];
   __shared__ int bad;
   __shared__ float minr;
@@ -969,12 +967,13 @@ __global__ void __launch_bounds__(256) adj_solve_kernel(AdjGroup<T> G, int it) {
   const int nf = a.it.n_free, n = 6 * nf, tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const int sub = lane / 6, m = lane - 6 * sub;
   const bool skip = a.status[it] != 0;
-  for (int P0 = w; P0 < nf; P0 += 16) {
+  constexpr int nw = kAdjSolveThreads / 64;
+  for (int P0 = w; P0 < nf; P0 += 4 * nw) {
     T v[4];
     int lo[4], hi[4], most = 0;
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
-      const int P = P0 + 4 * u;
+      const int P = P0 + nw * u;
       lo[u] = P < nf ? a.it.v_off[P] : 0;
       hi[u] = P < nf ? a.it.v_off[P + 1] : 0;
       most = max(most, hi[u] - lo[u]);
@@ -999,7 +998,7 @@ __global__ void __launch_bounds__(256) adj_solve_kernel(AdjGroup<T> G, int it) {
       T s = (T)0;
 #pragma unroll
       for (int h = 0; h < 10; ++h) s += __shfl(v[u], 6 * h + m);
-      const int P = P0 + 4 * u;
+      const int P = P0 + nw * u;
       if (P < nf && lane < 6) a.urhs[6 * P + m] = skip ? (T)0 : a.dxbar[6 * P + m] + s;
     }
   }
@@ -1163,7 +1162,7 @@ hipError_t launch_adj_system(const AdjGroup<T>& G, int n, int lds_bytes, int it,
   auto kernel = solve ? adj_solve_kernel<T> : adj_step_kernel<T>;
   hipError_t e = opt_in_lds((const void*)kernel, lds_bytes);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(kernel, dim3(1, n), dim3(256), lds_bytes, st, G, it);
+  hipLaunchKernelGGL(kernel, dim3(1, n), dim3(kAdjSolveThreads), lds_bytes, st, G, it);
   return hipGetLastError();
 }
 
