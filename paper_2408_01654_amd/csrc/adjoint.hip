@@ -20,8 +20,9 @@
 //        taubar_c += w_c a_c            (r = pi - tau),
 //        Jbar_c    = w_c (-(r_c + b_c) u - a_c Delta - 2 lam J_c o u o Delta),
 //        rbar_c    = -w_c a_c;
-//   5. xbar_t += d/dx [sum_c Jbar_c . J_c(x) + rbar_c r_c(x)], one dual
-//      evaluation of the edge per coordinate of (t_i, q_i, t_j, q_j, d_k).
+//   5. xbar_t += d/dx [sum_c Jbar_c . J_c(x) + rbar_c r_c(x)] for the
+//      coordinates (t_i, q_i, t_j, q_j, d_k), by walking the edge's evaluation
+//      backwards (edge_pullback).
 // Per-edge results are summed per pose and per patch in a fixed order.
 #include <algorithm>
 
@@ -35,29 +36,108 @@ namespace dpvba {
 
 constexpr int kEdgeAdj = 15;  // (t_i, q_i) 7, (t_j, q_j) 7, d_k 1
 
-// Residual and the 2 x 13 Jacobian (J_i | J_j | J_d) of one edge at poses
-// (t, q) of frames i and j and inverse depth d; false if the edge is invalid.
+// Rotation of a quaternion (x, y, z, w) with its unit quaternion u and the
+// reciprocal norm n.
 template <typename T>
-__device__ __forceinline__ bool edge_full(const T* pi, const T* pj, T d, T xh0, T xh1, T fx, T fy, T cx, T cy,
-                                          T z_min, float tx, float ty, T r[2], T J[2][13]) {
-  T Ri[9], Rj[9], ti[3], tj[3], Rt[12];
-  quat_to_rot<T, T>(pi + 3, Ri);
-  quat_to_rot<T, T>(pj + 3, Rj);
-  for (int m = 0; m < 3; ++m) { ti[m] = pi[m]; tj[m] = pj[m]; }
-  relative_pose<T>(Ri, ti, Rj, tj, Rt, Rt + 9);
-  EdgeTerms<T> o;
-  if (!edge_eval<T>(Rt, xh0, xh1, d, fx, fy, cx, cy, z_min, tx, ty, 1.f, 1.f, o)) return false;
-  for (int c = 0; c < 2; ++c) {
-    T ji[6];
-    adjoint_transpose_apply<T>(Rt, Rt + 9, o.Jj[c], ji);
-    for (int m = 0; m < 6; ++m) {
-      J[c][m] = -ji[m];
-      J[c][6 + m] = o.Jj[c][m];
+__device__ __forceinline__ void unit_quat(const T* q, T u[4], T& n) {
+  n = (T)1 / dsqrt(q[0] * q[0] + q[1] * q[1] + q[2] * q[2] + q[3] * q[3]);
+  for (int m = 0; m < 4; ++m) u[m] = q[m] * n;
+}
+
+// Adjoint of quat_to_rot: B the adjoint of the rotation matrix, out [4] that
+// of the stored quaternion (the component along it is projected out).
+template <typename T>
+__device__ __forceinline__ void rot_pullback(const T* q, const T B[9], T* out) {
+  T u[4], n;
+  unit_quat<T>(q, u, n);
+  const T x = u[0], y = u[1], z = u[2], w = u[3];
+  const T s01 = B[1] + B[3], s02 = B[2] + B[6], s12 = B[5] + B[7];
+  const T d01 = B[3] - B[1], d02 = B[2] - B[6], d12 = B[7] - B[5];
+  T g[4];
+  g[0] = 2 * (y * s01 + z * s02 + w * d12) - 4 * x * (B[4] + B[8]);
+  g[1] = 2 * (x * s01 + z * s12 + w * d02) - 4 * y * (B[0] + B[8]);
+  g[2] = 2 * (x * s02 + y * s12 + w * d01) - 4 * z * (B[0] + B[4]);
+  g[3] = 2 * (z * d01 + y * d02 + x * d12);
+  const T dot = x * g[0] + y * g[1] + z * g[2] + w * g[3];
+  for (int m = 0; m < 4; ++m) out[m] = n * (g[m] - u[m] * dot);
+}
+
+// Gradient of sum_c Jb_c . J_c + rb_c r_c with respect to the stored (t, q)
+// of both poses and the depth, xb [15]: the steps of the edge's evaluation
+// (edge_eval, the source pose's Jacobian, relative_pose, quat_to_rot) in
+// reverse.  Ri, Rj, Rt: the rotations and the relative pose; o: the edge's
+// terms.  (J is the 2 x 13 (J_i | J_j | J_d).)
+template <typename T>
+__device__ __forceinline__ void edge_pullback(const T* pi, const T* pj, const T Ri[9], const T Rj[9], const T Rt[12],
+                                              const EdgeTerms<T>& o, T d, T xh0, T xh1, T fx, T fy, const T rb[2],
+                                              const T Jb[2][13], T* xb) {
+  const T *R = Rt, *t = Rt + 9;
+  T Rb[9], tb[3], G[2][6];
+  for (int m = 0; m < 9; ++m) Rb[m] = (T)0;
+  for (int m = 0; m < 3; ++m) tb[m] = (T)0;
+  for (int c = 0; c < 2; ++c) {  // J_i = -(R^T a ; R^T (b - t x a)) of J_j = (a ; b)
+    const T* a = o.Jj[c];
+    const T b[3] = {a[3] - (t[1] * a[2] - t[2] * a[1]), a[4] - (t[2] * a[0] - t[0] * a[2]),
+                    a[5] - (t[0] * a[1] - t[1] * a[0])};
+    const T* g = Jb[c];  // o1 = -g[0..2], o2 = -g[3..5]
+    T bb[3];
+    for (int r = 0; r < 3; ++r) bb[r] = -(R[3 * r] * g[3] + R[3 * r + 1] * g[4] + R[3 * r + 2] * g[5]);
+    for (int r = 0; r < 3; ++r)
+      for (int k = 0; k < 3; ++k) Rb[3 * r + k] -= a[r] * g[k] + b[r] * g[3 + k];
+    // -bb . (t x a): to t -(a x bb), to a -(bb x t)
+    tb[0] -= a[1] * bb[2] - a[2] * bb[1];
+    tb[1] -= a[2] * bb[0] - a[0] * bb[2];
+    tb[2] -= a[0] * bb[1] - a[1] * bb[0];
+    for (int r = 0; r < 3; ++r) {
+      const T ra = -(R[3 * r] * g[0] + R[3 * r + 1] * g[1] + R[3 * r + 2] * g[2]);
+      const T bt = bb[(r + 1) % 3] * t[(r + 2) % 3] - bb[(r + 2) % 3] * t[(r + 1) % 3];
+      G[c][r] = g[6 + r] + ra - bt;
+      G[c][3 + r] = g[9 + r] + bb[r];
     }
-    J[c][12] = o.Jd[c];
-    r[c] = o.r[c];
   }
-  return true;
+  const T q0 = R[0] * xh0 + R[1] * xh1 + R[2] + t[0] * d;
+  const T q1 = R[3] * xh0 + R[4] * xh1 + R[5] + t[1] * d;
+  const T q2 = R[6] * xh0 + R[7] * xh1 + R[8] + t[2] * d;
+  const T iz = (T)1 / q2;
+  const T ax0 = fx * iz, ax2 = -fx * q0 * iz * iz, by1 = fy * iz, by2 = -fy * q1 * iz * iz;
+  const T gd0 = Jb[0][12], gd1 = Jb[1][12];
+  const T ax0b = -d * G[0][0] - q2 * G[0][4] + q1 * G[0][5] + t[0] * gd0;
+  const T ax2b = -d * G[0][2] - q1 * G[0][3] + q0 * G[0][4] + t[2] * gd0;
+  const T by1b = -d * G[1][1] + q2 * G[1][3] - q0 * G[1][5] + t[1] * gd1;
+  const T by2b = -d * G[1][2] - q1 * G[1][3] + q0 * G[1][4] + t[2] * gd1;
+  T db = -ax0 * G[0][0] - ax2 * G[0][2] - by1 * G[1][1] - by2 * G[1][2];
+  tb[0] += ax0 * gd0;
+  tb[1] += by1 * gd1;
+  tb[2] += ax2 * gd0 + by2 * gd1;
+  T qb[3] = {ax2 * G[0][4] + by2 * G[1][4] - by1 * G[1][5], ax0 * G[0][5] - ax2 * G[0][3] - by2 * G[1][3],
+             by1 * G[1][3] - ax0 * G[0][4]};
+  const T iz2 = iz * iz;
+  const T izb = fx * (q0 * rb[0] + ax0b - 2 * q0 * iz * ax2b) + fy * (q1 * rb[1] + by1b - 2 * q1 * iz * by2b);
+  qb[0] += fx * (iz * rb[0] - iz2 * ax2b);
+  qb[1] += fy * (iz * rb[1] - iz2 * by2b);
+  qb[2] -= iz2 * izb;
+  const T xh[3] = {xh0, xh1, (T)1};
+  for (int r = 0; r < 3; ++r) {
+    for (int k = 0; k < 3; ++k) Rb[3 * r + k] += qb[r] * xh[k];
+    tb[r] += d * qb[r];
+    db += t[r] * qb[r];
+  }
+  // R = R_j^T R_i, t = R_j^T (t_i - t_j)
+  T Rib[9], Rjb[9];
+  for (int k = 0; k < 3; ++k) {
+    const T dk = pi[k] - pj[k];
+    T s = (T)0;
+    for (int r = 0; r < 3; ++r) {
+      Rib[3 * k + r] = Rj[3 * k] * Rb[r] + Rj[3 * k + 1] * Rb[3 + r] + Rj[3 * k + 2] * Rb[6 + r];
+      Rjb[3 * k + r] = Rb[3 * r] * Ri[3 * k] + Rb[3 * r + 1] * Ri[3 * k + 1] + Rb[3 * r + 2] * Ri[3 * k + 2] + tb[r] * dk;
+      s += Rj[3 * k + r] * tb[r];
+    }
+    xb[k] = s;
+    xb[7 + k] = -s;
+  }
+  rot_pullback<T>(pi + 3, Rib, xb + 3);
+  rot_pullback<T>(pj + 3, Rjb, xb + 10);
+  xb[14] = db;
 }
 
 // Start of the walk: cleared status words, x_0, and the adjoint of x_T in
@@ -81,18 +161,19 @@ __global__ void __launch_bounds__(256) adj_begin_kernel(AdjGroup<T> G) {
 // Steps 4 and 5 for every edge.  u and Delta of the poses are indexed by free
 // pose, of the depths by tile-order position.  Adds taubar and wbar to the
 // caller's gradients (the walk's first iteration, the last one, stores them)
-// and writes the edge's xbar contributions.  Bound by the dependent
-// arithmetic of the 15 dual evaluations: four lanes share an edge, so a
-// window's 20 thousand edges fill the SIMDs (@E@).
+// and writes the edge's xbar contributions.  Bound by an edge's dependent
+// arithmetic and its 120 scattered bytes; the reverse walk is about three
+// evaluations of the edge, where a dual evaluation for each of the 15
+// coordinates took @E@.
 template <typename T>
-__global__ void __launch_bounds__(256) edge_adjoint_kernel(AdjGroup<T> G, int it) {
+__global__ void __launch_bounds__(128) edge_adjoint_kernel(AdjGroup<T> G, int it) {
   const AdjArgs<T>& a = G.p[blockIdx.y];
-  const int e = (blockIdx.x * blockDim.x + threadIdx.x) >> 2, part = threadIdx.x & 3;
+  const int e = blockIdx.x * blockDim.x + threadIdx.x;
   if (e >= a.n_edges) return;
   const bool first = it == a.nit - 1;
   const int n_fixed = a.it.n_fixed, p = a.it.p;
   const T *poses = a.Xp + (size_t)it * 7 * a.it.n_frames, *dxi = a.DX + (size_t)it * 6 * a.it.n_free;
-  const T fx = a.it.fx, fy = a.it.fy, cx = a.it.cx, cy = a.it.cy, z_min = a.it.z_min, lam_diag = a.it.lam_diag;
+  const T fx = a.it.fx, fy = a.it.fy, cx = a.it.cx, cy = a.it.cy, lam_diag = a.it.lam_diag;
   T* xb = a.exb + (size_t)kEdgeAdj * e;
   const bool skip = a.status[it] != 0;
   const int i = a.ii[e], j = a.jj[e], k = a.kk[e];
@@ -100,18 +181,27 @@ __global__ void __launch_bounds__(256) edge_adjoint_kernel(AdjGroup<T> G, int it
   const int c0 = (p - 1) / 2;
   const float* cen = a.it.patches + ((size_t)k * p * p + (size_t)c0 * p + c0) * 2;
   const T xh0 = ((T)cen[0] - cx) / fx, xh1 = ((T)cen[1] - cy) / fy;
-  const T* pi = poses + 7 * (size_t)i;
-  const T* pj = poses + 7 * (size_t)j;
+  T pi[7], pj[7];
+  for (int m = 0; m < 7; ++m) {
+    pi[m] = poses[7 * (size_t)i + m];
+    pj[m] = poses[7 * (size_t)j + m];
+  }
   const T d = a.Xd[(size_t)it * a.n_tp + pos];
-  const float tx = a.it.target[2 * e], ty = a.it.target[2 * e + 1];
-  T r[2], J[2][13];
-  const bool ok = !skip && edge_full<T>(pi, pj, d, xh0, xh1, fx, fy, cx, cy, z_min, tx, ty, r, J);
+  const float w0 = a.it.weight[2 * e], w1 = a.it.weight[2 * e + 1];
+  T Ri[9], Rj[9], Rt[12];
+  quat_to_rot<T, T>(pi + 3, Ri);
+  quat_to_rot<T, T>(pj + 3, Rj);
+  relative_pose<T>(Ri, pi, Rj, pj, Rt, Rt + 9);
+  EdgeTerms<T> o;
+  const bool ok = !skip && edge_eval<T>(Rt, xh0, xh1, d, fx, fy, cx, cy, a.it.z_min, a.it.target[2 * e],
+                                        a.it.target[2 * e + 1], w0, w1, o);
   if (!ok) {
-    for (int m = part; m < kEdgeAdj; m += 4) xb[m] = (T)0;
-    if (first && part < 2) {
-      a.grad_weight[2 * e + part] = (T)0;
-      a.grad_target[2 * e + part] = (T)0;
-    }
+    for (int m = 0; m < kEdgeAdj; ++m) xb[m] = (T)0;
+    if (first)
+      for (int c = 0; c < 2; ++c) {
+        a.grad_weight[2 * e + c] = (T)0;
+        a.grad_target[2 * e + c] = (T)0;
+      }
     return;
   }
   const bool fi = i >= n_fixed, fj = j >= n_fixed;
@@ -126,45 +216,30 @@ __global__ void __launch_bounds__(256) edge_adjoint_kernel(AdjGroup<T> G, int it
   D[12] = a.dd[pos];
   T Jb[2][13], rb[2];
   for (int c = 0; c < 2; ++c) {
-    const T w = (T)a.it.weight[2 * e + c];
+    T J[13], ji[6];
+    adjoint_transpose_apply<T>(Rt, Rt + 9, o.Jj[c], ji);
+    for (int m = 0; m < 6; ++m) {
+      J[m] = -ji[m];
+      J[6 + m] = o.Jj[c][m];
+    }
+    J[12] = o.Jd[c];
+    const T w = o.w[c];
     T av = (T)0, b = (T)0, sd = (T)0;
     for (int m = 0; m < 13; ++m) {
-      av += J[c][m] * u[m];
-      b += J[c][m] * D[m];
-      sd += J[c][m] * J[c][m] * u[m] * D[m];
+      av += J[m] * u[m];
+      b += J[m] * D[m];
+      sd += J[m] * J[m] * u[m] * D[m];
     }
-    if (part == 0) {
-      const T gw = -av * b - lam_diag * sd - r[c] * av, gt = w * av;
-      a.grad_weight[2 * e + c] = first ? gw : a.grad_weight[2 * e + c] + gw;
-      a.grad_target[2 * e + c] = first ? gt : a.grad_target[2 * e + c] + gt;
-    }
+    const T gw = -av * b - lam_diag * sd - o.r[c] * av, gt = w * av;
+    a.grad_weight[2 * e + c] = first ? gw : a.grad_weight[2 * e + c] + gw;
+    a.grad_target[2 * e + c] = first ? gt : a.grad_target[2 * e + c] + gt;
     rb[c] = -w * av;
     for (int m = 0; m < 13; ++m)
-      Jb[c][m] = w * (-(r[c] + b) * u[m] - av * D[m] - (T)2 * lam_diag * J[c][m] * u[m] * D[m]);
+      Jb[c][m] = w * (-(o.r[c] + b) * u[m] - av * D[m] - (T)2 * lam_diag * J[m] * u[m] * D[m]);
   }
-  // directional derivatives of (r, J) along each stored coordinate
-  using D1 = Dual<T>;
-  for (int dir = part; dir < kEdgeAdj; dir += 4) {
-    if ((dir < 7 && !fi) || (dir >= 7 && dir < 14 && !fj)) {
-      xb[dir] = (T)0;
-      continue;
-    }
-    D1 Pi[7], Pj[7];
-    for (int m = 0; m < 7; ++m) {
-      Pi[m] = D1(pi[m], dir == m ? (T)1 : (T)0);
-      Pj[m] = D1(pj[m], dir == 7 + m ? (T)1 : (T)0);
-    }
-    const D1 dD(d, dir == 14 ? (T)1 : (T)0);
-    D1 rD[2], JD[2][13];
-    edge_full<D1>(Pi, Pj, dD, D1(xh0, (T)0), D1(xh1, (T)0), D1(fx, (T)0), D1(fy, (T)0), D1(cx, (T)0),
-                  D1(cy, (T)0), D1(z_min, (T)0), tx, ty, rD, JD);
-    T acc = (T)0;
-    for (int c = 0; c < 2; ++c) {
-      acc += rb[c] * rD[c].d;
-      for (int m = 0; m < 13; ++m) acc += Jb[c][m] * JD[c][m].d;
-    }
-    xb[dir] = acc;
-  }
+  T x[kEdgeAdj];
+  edge_pullback<T>(pi, pj, Ri, Rj, Rt, o, d, xh0, xh1, fx, fy, rb, Jb, x);
+  for (int m = 0; m < kEdgeAdj; ++m) xb[m] = (m < 7 && !fi) || (m >= 7 && m < 14 && !fj) ? (T)0 : x[m];
 }
 
 // Step 2, first half: per tile and block column x, the tile's share of
@@ -356,7 +431,7 @@ hipError_t launch_adj_begin(const AdjGroup<T>& G, int n, int n_frames, int n_tp,
 template <typename T>
 hipError_t launch_edge_adjoint(const AdjGroup<T>& G, int n, int n_edges, int it, hipStream_t st) {
   if (n_edges == 0) return hipSuccess;
-  hipLaunchKernelGGL((edge_adjoint_kernel<T>), dim3(blocks_for(4LL * n_edges, 256), n), dim3(256), 0, st, G, it);
+  hipLaunchKernelGGL((edge_adjoint_kernel<T>), dim3(blocks_for(n_edges, 128), n), dim3(128), 0, st, G, it);
   return hipGetLastError();
 }
 
