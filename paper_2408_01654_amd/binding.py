@@ -566,6 +566,7 @@ class _BundleAdjust(torch.autograd.Function):
         poses, d = p0.clone(), d0.clone()
         context.solve(g, poses, d, n_iters, lam, z_min, precision, report=False)
         ctx.save_for_backward(p0, d0)
+        ctx.set_materialize_grads(False)  # an unused output is a null adjoint, not a filled one
         ctx.g, ctx.context = g, context
         ctx.args = (n_iters, lam, z_min, precision)
         ctx.dtypes = (target.dtype, weight.dtype)
@@ -618,6 +619,7 @@ class _BundleAdjustMany(torch.autograd.Function):
             for c, g, p, d in zip(contexts, gs, poses, ds):
                 c.solve(g, p, d, n_iters, lam, z_min, precision, report=False)
         ctx.save_for_backward(*p0, *d0)
+        ctx.set_materialize_grads(False)  # an unused output is a null adjoint, not a filled one
         ctx.gs, ctx.contexts, ctx.args = gs, contexts, (n_iters, lam, z_min, precision)
         ctx.dtypes = [(t.dtype, w.dtype) for t, w in zip(tg, wg)]
         return (*poses, *ds)
