@@ -2095,15 +2095,17 @@ dpvba_status dpvba_pgo_sim3(dpvba_ctx* c, int32_t n_frames, int32_t n_fixed, con
   HIP_TRY(launch_report_init(status, (unsigned int*)c->pg_mb.p, DPVBA_MAX_PGO_ITERS + 1, st, err));
   HIP_TRY(launch_pgo_init(poses, n_frames, sims, loop_rel, n_loops, (double*)c->pg_C.p, st));
   for (int it = 0; it < n_iters; ++it) {
+    const bool beside = sparse;  // the cost is summed beside the cleared blocks
     HIP_TRY(launch_pgo_linearise(sims, (const double*)c->pg_C.p, (const int*)c->pg_ea.p, (const int*)c->pg_eb.p, E,
-                                 (double*)c->pg_r.p, (double*)c->pg_J.p, costd + it, st));
+                                 (double*)c->pg_r.p, (double*)c->pg_J.p, beside ? nullptr : costd + it, st));
     if (nf == 0) continue;
     double* rhs = (double*)c->pg_rhs.p;
     double* dx = (double*)c->pg_dx.p;
     const double* d0 = (const double*)c->pg_d0.p;
     unsigned int* mb = (unsigned int*)c->pg_mb.p + it;
     const int* row0 = sparse ? plan.row0 : nullptr;
-    HIP_TRY(sparse ? launch_sparse_clear<double>(plan, H, rhs, st) : launch_fill<double>(H, (long long)(n * n), 0.0, st));
+    HIP_TRY(sparse ? launch_sparse_clear<double>(plan, H, rhs, (const double*)c->pg_r.p, 7 * E, costd + it, st)
+                   : launch_fill<double>(H, (long long)(n * n), 0.0, st));
     HIP_TRY(launch_pgo_normal((const double*)c->pg_J.p, (const double*)c->pg_r.p, (const int2*)c->pg_blk_pq.p,
                               (const int*)c->pg_blk_off.p, (const int*)c->pg_blk_src.p, (int)blocks.size(),
                               sparse ? kBlk : (int)n, (const int*)c->pg_pose_off.p, (const int*)c->pg_pose_src.p, nf,

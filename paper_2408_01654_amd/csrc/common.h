@@ -34,6 +34,21 @@ __device__ __forceinline__ void report_device_error(int* dev_err, int* host_err,
   }
 }
 
+// Sum of r^2 over n values by a workgroup of 256 threads in a fixed order.
+__device__ __forceinline__ void sum_squares_256(const double* r, int n, double* out) {
+  __shared__ double part[256];
+  double s = 0.0;
+#pragma unroll 8
+  for (int i = threadIdx.x; i < n; i += 256) s += r[i] * r[i];
+  part[threadIdx.x] = s;
+  __syncthreads();
+  for (int h = 128; h > 0; h >>= 1) {
+    if ((int)threadIdx.x < h) part[threadIdx.x] += part[threadIdx.x + h];
+    __syncthreads();
+  }
+  if (threadIdx.x == 0) *out = part[0];
+}
+
 // Rotation matrix (row-major) of a quaternion (x, y, z, w), normalised first.
 template <typename T, typename Q>
 __device__ __forceinline__ void quat_to_rot(const Q* q, T R[9]) {

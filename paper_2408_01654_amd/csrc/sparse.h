@@ -49,7 +49,8 @@ hipError_t launch_sparse_gather(const SparsePlan& p, const TP* part_S, const int
                                 hipStream_t st);
 // A <- zero blocks with identity on unused rows; v [64 nb] and d0 zero.
 template <typename T>
-hipError_t launch_sparse_clear(const SparsePlan& p, T* A, T* v, hipStream_t st);
+hipError_t launch_sparse_clear(const SparsePlan& p, T* A, T* v, const double* r, int nr, double* cost,
+                               hipStream_t st);
 // A <- its Cholesky factor (off-diagonal blocks; the diagonal blocks keep
 // their input), Linv [nb][64][64] the inverses of the factor's diagonal
 // blocks, v <- L^-1 v.  *status is set by a pivot that is not positive,

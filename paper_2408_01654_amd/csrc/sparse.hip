@@ -656,14 +656,31 @@ __global__ void __launch_bounds__(kGatherThreads) sparse_gather_kernel(SparsePla
     for (int e = tid; e < kBB; e += kGatherThreads) A32[(size_t)id * kBB + e] = (float)tile[e];
 }
 
+// Zero blocks (identity in unused rows) and right-hand side, 16 bytes a store;
+// one more workgroup, the first, sums a pose graph's squared residuals beside them (cost
+// null: none).
 template <typename T>
-__global__ void __launch_bounds__(256) sparse_clear_kernel(SparsePlan P, T* A, T* v) {
-  const int id = blockIdx.x;
+__global__ void __launch_bounds__(256) sparse_clear_kernel(SparsePlan P, T* A, T* v, const double* r, int nr,
+                                                           double* cost) {
+  const int id = (int)blockIdx.x - (cost ? 1 : 0);
+  if (id < 0) {
+    sum_squares_256(r, nr, cost);
+    return;
+  }
   const int I = P.rowidx[id];
   const bool diag = id == P.colptr[I];
   const int size = diag ? P.size[I] : kBlk;
-  T* o = A + (size_t)id * kBB;
-  for (int e = threadIdx.x; e < kBB; e += 256) o[e] = (T)((e >> 6) == (e & 63) && (e >> 6) >= size ? 1 : 0);
+  typedef typename V16<T>::type vec_t;
+  constexpr int V = 16 / (int)sizeof(T);
+  vec_t* o = reinterpret_cast<vec_t*>(A + (size_t)id * kBB);
+#pragma unroll
+  for (int u = 0; u < kBB / V / 256; ++u) {
+    const int e = V * (u * 256 + (int)threadIdx.x);
+    vec_t x;
+#pragma unroll
+    for (int m = 0; m < V; ++m) x[m] = (T)(((e + m) >> 6) == ((e + m) & 63) && ((e + m) >> 6) >= size ? 1 : 0);
+    o[e / V] = x;
+  }
   if (diag && (int)threadIdx.x < kBlk) v[kBlk * I + threadIdx.x] = (T)0;
 }
 
@@ -779,9 +796,10 @@ hipError_t launch_sparse_gather(const SparsePlan& p, const TP* part_S, const int
 }
 
 template <typename T>
-hipError_t launch_sparse_clear(const SparsePlan& p, T* A, T* v, hipStream_t st) {
+hipError_t launch_sparse_clear(const SparsePlan& p, T* A, T* v, const double* r, int nr, double* cost, hipStream_t st) {
   if (p.nb == 0) return hipSuccess;
-  hipLaunchKernelGGL((sparse_clear_kernel<T>), dim3(p.n_blocks), dim3(256), 0, st, p, A, v);
+  hipLaunchKernelGGL((sparse_clear_kernel<T>), dim3(p.n_blocks + (cost ? 1 : 0)), dim3(256), 0, st, p, A, v, r, nr,
+                     cost);
   return hipGetLastError();
 }
 
@@ -885,7 +903,8 @@ template hipError_t launch_sparse_gather<double, double>(const SparsePlan&, cons
 template hipError_t launch_sparse_gather<float, double>(const SparsePlan&, const float*, const int*, const int*,
                                                         double*, const double*, double, double, double*, double*,
                                                         float*, float*, hipStream_t);
-template hipError_t launch_sparse_clear<double>(const SparsePlan&, double*, double*, hipStream_t);
+template hipError_t launch_sparse_clear<double>(const SparsePlan&, double*, double*, const double*, int, double*,
+                                                hipStream_t);
 #define DPVBA_SPARSE_INSTANTIATE(T)                                                                                  \
   template hipError_t launch_sparse_factor<T>(const SparsePlan&, T*, T*, T*, const T*, int*, unsigned int*,           \
                                               hipStream_t);                                                          \
