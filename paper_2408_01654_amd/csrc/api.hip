@@ -209,6 +209,19 @@ hipError_t upload(DevBuf& b, const std::vector<X>& v, hipStream_t st) {
   return hipStreamSynchronize(st);
 }
 
+// Several host lists uploaded as one: a synchronous copy of a few kilobytes
+// costs about 15 us, whatever it holds.
+struct Pack {
+  std::vector<unsigned char> host;
+  template <typename X>
+  size_t add(const std::vector<X>& v) {  // place of the list, 256-byte aligned
+    const size_t at = (host.size() + 255) / 256 * 256, bytes = v.size() * sizeof(X);
+    host.resize(at + bytes);
+    if (bytes) memcpy(host.data() + at, v.data(), bytes);
+    return at;
+  }
+};
+
 // Static workspace of dpvba_solve_noalloc: the per-call buffers of a
 // single-launch solve, carved from one fixed array per device instead of
 // the context's allocations.  In host code `scratch` names a host-side
@@ -265,10 +278,8 @@ static int writeback_lds_bytes(const Tiling& tl, int tsize) {
 // An elimination plan (blockplan.h) and its device lists.
 struct PlanStore {
   BlockPlan h;
-  DevBuf row0, size, colptr, rowidx, level, tasks, children, updates, srcs, by_level, rptr, rlist, nptr, nlist,
-      pair_off, pairs;
-  DevBuf* bufs[16] = {&row0, &size, &colptr, &rowidx, &level, &tasks, &children, &updates, &srcs, &by_level, &rptr,
-                      &rlist, &nptr, &nlist, &pair_off, &pairs};
+  DevBuf lists;  // every list of the plan, one after another
+  DevBuf* bufs[1] = {&lists};
   SparsePlan plan{};
   bool valid = false;
 };
@@ -285,18 +296,12 @@ static hipError_t upload_plan(PlanStore& ps, const std::vector<PosePair>* pairs,
   const BlockPlan& h = ps.h;
   hipError_t e;
   ps.valid = false;
-  if ((e = upload(ps.row0, h.row0, st)) != hipSuccess) return e;
-  if ((e = upload(ps.size, h.size, st)) != hipSuccess) return e;
-  if ((e = upload(ps.colptr, h.colptr, st)) != hipSuccess) return e;
-  if ((e = upload(ps.rowidx, h.rowidx, st)) != hipSuccess) return e;
-  if ((e = upload(ps.level, h.level, st)) != hipSuccess) return e;
-  if ((e = upload(ps.tasks, h.tasks, st)) != hipSuccess) return e;
-  if ((e = upload(ps.children, h.children, st)) != hipSuccess) return e;
-  if ((e = upload(ps.updates, h.updates, st)) != hipSuccess) return e;
-  if ((e = upload(ps.srcs, h.srcs, st)) != hipSuccess) return e;
-  if ((e = upload(ps.by_level, h.by_level, st)) != hipSuccess) return e;
-  if ((e = upload(ps.rptr, h.rptr, st)) != hipSuccess) return e;
-  if ((e = upload(ps.rlist, h.rlist, st)) != hipSuccess) return e;
+  Pack pack;
+  const size_t row0 = pack.add(h.row0), size = pack.add(h.size), colptr = pack.add(h.colptr),
+               rowidx = pack.add(h.rowidx), level = pack.add(h.level), tasks = pack.add(h.tasks),
+               children = pack.add(h.children), updates = pack.add(h.updates), srcs = pack.add(h.srcs),
+               by_level = pack.add(h.by_level), rptr = pack.add(h.rptr), rlist = pack.add(h.rlist);
+  size_t pair_off = 0, pair_list = 0, nptr_at = 0, nlist_at = 0;
   if (pairs) {
     struct Entry { int32_t id, x, y; };
     std::vector<Entry> v;
@@ -333,33 +338,35 @@ static hipError_t upload_plan(PlanStore& ps, const std::vector<PosePair>* pairs,
       nlist.insert(nlist.end(), rows[I].begin(), rows[I].end());
       nptr[I + 1] = (int32_t)(nlist.size() / 2);
     }
-    if ((e = upload(ps.pair_off, off, st)) != hipSuccess) return e;
-    if ((e = upload(ps.pairs, flat, st)) != hipSuccess) return e;
-    if ((e = upload(ps.nptr, nptr, st)) != hipSuccess) return e;
-    if ((e = upload(ps.nlist, nlist, st)) != hipSuccess) return e;
+    pair_off = pack.add(off);
+    pair_list = pack.add(flat);
+    nptr_at = pack.add(nptr);
+    nlist_at = pack.add(nlist);
   }
+  if ((e = upload(ps.lists, pack.host, st)) != hipSuccess) return e;
+  const unsigned char* base = (const unsigned char*)ps.lists.p;
   SparsePlan& p = ps.plan;
   p.bw = h.bw;
   p.n_pose = h.n_pose;
   p.nb = h.nb;
   p.n_level = h.n_level;
   p.n_blocks = h.n_blocks();
-  p.row0 = (const int*)ps.row0.p;
-  p.size = (const int*)ps.size.p;
-  p.colptr = (const int*)ps.colptr.p;
-  p.rowidx = (const int*)ps.rowidx.p;
-  p.level = (const int*)ps.level.p;
-  p.tasks = (const LevelTask*)ps.tasks.p;
-  p.children = (const LevelChild*)ps.children.p;
-  p.updates = (const UpdateTask*)ps.updates.p;
-  p.srcs = (const UpdateSrc*)ps.srcs.p;
-  p.by_level = (const int*)ps.by_level.p;
-  p.rptr = (const int*)ps.rptr.p;
-  p.rlist = (const int2*)ps.rlist.p;
-  p.nptr = (const int*)ps.nptr.p;
-  p.nlist = (const int2*)ps.nlist.p;
-  p.pair_off = (const int*)ps.pair_off.p;
-  p.pairs = (const int2*)ps.pairs.p;
+  p.row0 = (const int*)(base + row0);
+  p.size = (const int*)(base + size);
+  p.colptr = (const int*)(base + colptr);
+  p.rowidx = (const int*)(base + rowidx);
+  p.level = (const int*)(base + level);
+  p.tasks = (const LevelTask*)(base + tasks);
+  p.children = (const LevelChild*)(base + children);
+  p.updates = (const UpdateTask*)(base + updates);
+  p.srcs = (const UpdateSrc*)(base + srcs);
+  p.by_level = (const int*)(base + by_level);
+  p.rptr = (const int*)(base + rptr);
+  p.rlist = (const int2*)(base + rlist);
+  p.nptr = pairs ? (const int*)(base + nptr_at) : nullptr;
+  p.nlist = pairs ? (const int2*)(base + nlist_at) : nullptr;
+  p.pair_off = pairs ? (const int*)(base + pair_off) : nullptr;
+  p.pairs = pairs ? (const int2*)(base + pair_list) : nullptr;
   p.task_off = h.task_off.data();
   p.upd_off = h.upd_off.data();
   p.implicit_col = h.implicit_col.data();
@@ -429,8 +436,8 @@ struct dpvba_ctx {
   } bt;
   // adjoint workspace
   // Sim(3) pose-graph optimisation workspace
-  DevBuf pg_C, pg_ea, pg_eb, pg_r, pg_J, pg_H, pg_rhs, pg_dx, pg_d0, pg_Linv, pg_flags, pg_status, pg_mb,
-      pg_cost, pg_blk_pq, pg_blk_off, pg_blk_src, pg_pose_off, pg_pose_src;
+  DevBuf pg_C, pg_r, pg_J, pg_H, pg_rhs, pg_dx, pg_d0, pg_Linv, pg_flags, pg_status, pg_mb,
+      pg_cost, pg_lists;
   int pg_epoch = 0;
   DevBuf bw_poses, bw_depth, bw_dx, bw_pbar, bw_dbar, bw_dxbar, bw_rhs, bw_up, bw_ud, bw_dd, bw_edge, bw_status,
       bw_minbits;
@@ -734,10 +741,9 @@ void dpvba_destroy(dpvba_ctx* c) {
                     &c->pcount, &c->pedges, &c->pose_off, &c->pose_src, &c->patch_pos, &c->bw_poses, &c->bw_depth,
                     &c->bw_dx, &c->bw_pbar, &c->bw_dbar, &c->bw_dxbar, &c->bw_rhs, &c->bw_up, &c->bw_ud, &c->bw_dd,
                     &c->bw_edge, &c->bw_status, &c->bw_minbits, &c->S32, &c->x64, &c->x64b, &c->rhs32, &c->c32,
-                    &c->d0_32, &c->mx_max, &c->mx_resid, &c->mx_fb, &c->mx_flag, &c->pg_C, &c->pg_ea, &c->pg_eb,
+                    &c->d0_32, &c->mx_max, &c->mx_resid, &c->mx_fb, &c->mx_flag, &c->pg_C,
                     &c->pg_r, &c->pg_J, &c->pg_H, &c->pg_rhs, &c->pg_dx, &c->pg_d0, &c->pg_Linv,
-                    &c->pg_flags, &c->pg_status, &c->pg_mb, &c->pg_cost, &c->pg_blk_pq, &c->pg_blk_off,
-                    &c->pg_blk_src, &c->pg_pose_off, &c->pg_pose_src};
+                    &c->pg_flags, &c->pg_status, &c->pg_mb, &c->pg_cost, &c->pg_lists};
   for (DevBuf* b : bufs)
     if (b->p) (void)hipFree(b->p);
   for (Tiling& t : c->tl)
@@ -2028,21 +2034,37 @@ dpvba_status dpvba_pgo_sim3(dpvba_ctx* c, int32_t n_frames, int32_t n_fixed, con
   }
   // block lists of the free poses' normal equations (by first row and first
   // column), contributions in residual order
-  std::map<std::pair<int, int>, std::vector<int32_t>> blocks;
-  std::vector<std::vector<int32_t>> pose_list(std::max(nf, 0));
+  struct Entry { int32_t r, q, src; };
+  std::vector<Entry> entries;
+  entries.reserve(4 * (size_t)E);
+  std::vector<int32_t> pose_off(nf + 1, 0), pose_src(2 * (size_t)E);
   for (int e = 0; e < E; ++e) {
     const int fa = ea[e] - n_fixed, fb = eb[e] - n_fixed;
     const int pa = fa >= 0 ? row_of[fa] : -1, pb = fb >= 0 ? row_of[fb] : -1;
-    if (fa >= 0) { blocks[{pa, pa}].push_back(4 * e + 0); pose_list[fa].push_back(2 * e); }
-    if (fb >= 0) { blocks[{pb, pb}].push_back(4 * e + 3); pose_list[fb].push_back(2 * e + 1); }
+    if (fa >= 0) { entries.push_back({pa, pa, 4 * e + 0}); pose_off[fa + 1]++; }
+    if (fb >= 0) { entries.push_back({pb, pb, 4 * e + 3}); pose_off[fb + 1]++; }
     if (fa >= 0 && fb >= 0) {
-      if (pa > pb) blocks[{pa, pb}].push_back(4 * e + 1);
-      else blocks[{pb, pa}].push_back(4 * e + 2);
+      if (pa > pb) entries.push_back({pa, pb, 4 * e + 1});
+      else entries.push_back({pb, pa, 4 * e + 2});
     }
   }
-  std::vector<int32_t> blk_to, blk_off{0}, blk_src, pose_off{0}, pose_src;
-  for (auto& kv : blocks) {
-    const int r = kv.first.first, q = kv.first.second;
+  std::stable_sort(entries.begin(), entries.end(),
+                   [](const Entry& x, const Entry& y) { return x.r != y.r ? x.r < y.r : x.q < y.q; });
+  for (int f = 0; f < nf; ++f) pose_off[f + 1] += pose_off[f];
+  pose_src.resize(pose_off[nf]);
+  {
+    std::vector<int32_t> cur(pose_off.begin(), pose_off.end() - 1);
+    for (int e = 0; e < E; ++e) {
+      const int fa = ea[e] - n_fixed, fb = eb[e] - n_fixed;
+      if (fa >= 0) pose_src[cur[fa]++] = 2 * e;
+      if (fb >= 0) pose_src[cur[fb]++] = 2 * e + 1;
+    }
+  }
+  std::vector<int32_t> blk_to, blk_off{0}, blk_src(entries.size());
+  for (size_t x = 0; x < entries.size(); ++x) {
+    const int r = entries[x].r, q = entries[x].q;
+    blk_src[x] = entries[x].src;
+    if (x + 1 < entries.size() && entries[x + 1].r == r && entries[x + 1].q == q) continue;
     int to = r * (int)n + q;  // dense, row-major
     if (sparse) {
       const int id = c->pg_plan.h.find(r / kBlk, q / kBlk);
@@ -2051,23 +2073,18 @@ dpvba_status dpvba_pgo_sim3(dpvba_ctx* c, int32_t n_frames, int32_t n_fixed, con
     }
     blk_to.push_back(to);
     blk_to.push_back(r == q ? r : -1);
-    blk_src.insert(blk_src.end(), kv.second.begin(), kv.second.end());
-    blk_off.push_back((int32_t)blk_src.size());
+    blk_off.push_back((int32_t)x + 1);
   }
-  for (auto& l : pose_list) {
-    pose_src.insert(pose_src.end(), l.begin(), l.end());
-    pose_off.push_back((int32_t)pose_src.size());
-  }
+  const int n_blk = (int)blk_to.size() / 2;
   const SparsePlan& plan = c->pg_plan.plan;
   const size_t npad = sparse ? (size_t)kBlk * plan.nb : n;
   const size_t h_elems = sparse ? (size_t)plan.n_blocks * kBlk * kBlk : n * n;
-  HIP_TRY(upload(c->pg_ea, ea, st));
-  HIP_TRY(upload(c->pg_eb, eb, st));
-  HIP_TRY(upload(c->pg_blk_pq, blk_to, st));
-  HIP_TRY(upload(c->pg_blk_off, blk_off, st));
-  HIP_TRY(upload(c->pg_blk_src, blk_src, st));
-  HIP_TRY(upload(c->pg_pose_off, pose_off, st));
-  HIP_TRY(upload(c->pg_pose_src, pose_src, st));
+  Pack pack;
+  const size_t at_ea = pack.add(ea), at_eb = pack.add(eb), at_to = pack.add(blk_to), at_off = pack.add(blk_off),
+               at_src = pack.add(blk_src), at_poff = pack.add(pose_off), at_psrc = pack.add(pose_src);
+  HIP_TRY(upload(c->pg_lists, pack.host, st));
+  const unsigned char* lists = (const unsigned char*)c->pg_lists.p;
+  const int *d_ea = (const int*)(lists + at_ea), *d_eb = (const int*)(lists + at_eb);
   HIP_TRY(ensure(c->pg_C, (size_t)std::max(E, 1) * 13 * 8));
   HIP_TRY(ensure(c->pg_r, (size_t)std::max(E, 1) * 7 * 8));
   HIP_TRY(ensure(c->pg_J, (size_t)std::max(E, 1) * 7 * 14 * 8));
@@ -2096,7 +2113,7 @@ dpvba_status dpvba_pgo_sim3(dpvba_ctx* c, int32_t n_frames, int32_t n_fixed, con
   HIP_TRY(launch_pgo_init(poses, n_frames, sims, loop_rel, n_loops, (double*)c->pg_C.p, st));
   for (int it = 0; it < n_iters; ++it) {
     const bool beside = sparse;  // the cost is summed beside the cleared blocks
-    HIP_TRY(launch_pgo_linearise(sims, (const double*)c->pg_C.p, (const int*)c->pg_ea.p, (const int*)c->pg_eb.p, E,
+    HIP_TRY(launch_pgo_linearise(sims, (const double*)c->pg_C.p, d_ea, d_eb, E,
                                  (double*)c->pg_r.p, (double*)c->pg_J.p, beside ? nullptr : costd + it, st));
     if (nf == 0) continue;
     double* rhs = (double*)c->pg_rhs.p;
@@ -2106,9 +2123,9 @@ dpvba_status dpvba_pgo_sim3(dpvba_ctx* c, int32_t n_frames, int32_t n_fixed, con
     const int* row0 = sparse ? plan.row0 : nullptr;
     HIP_TRY(sparse ? launch_sparse_clear<double>(plan, H, rhs, (const double*)c->pg_r.p, 7 * E, costd + it, st)
                    : launch_fill<double>(H, (long long)(n * n), 0.0, st));
-    HIP_TRY(launch_pgo_normal((const double*)c->pg_J.p, (const double*)c->pg_r.p, (const int2*)c->pg_blk_pq.p,
-                              (const int*)c->pg_blk_off.p, (const int*)c->pg_blk_src.p, (int)blocks.size(),
-                              sparse ? kBlk : (int)n, (const int*)c->pg_pose_off.p, (const int*)c->pg_pose_src.p, nf,
+    HIP_TRY(launch_pgo_normal((const double*)c->pg_J.p, (const double*)c->pg_r.p, (const int2*)(lists + at_to),
+                              (const int*)(lists + at_off), (const int*)(lists + at_src), n_blk,
+                              sparse ? kBlk : (int)n, (const int*)(lists + at_poff), (const int*)(lists + at_psrc), nf,
                               row0, lambda, lam_diag, H, (double*)c->pg_d0.p, rhs, st));
     if (sparse) {
       c->pg_epoch = c->pg_epoch >= 0x3fffffff ? 1 : c->pg_epoch + 1;
@@ -2121,7 +2138,7 @@ dpvba_status dpvba_pgo_sim3(dpvba_ctx* c, int32_t n_frames, int32_t n_fixed, con
     }
     HIP_TRY(launch_pgo_retract(sims, n_frames, n_fixed, dx, row0, status + it, st));
   }
-  HIP_TRY(launch_pgo_linearise(sims, (const double*)c->pg_C.p, (const int*)c->pg_ea.p, (const int*)c->pg_eb.p, E,
+  HIP_TRY(launch_pgo_linearise(sims, (const double*)c->pg_C.p, d_ea, d_eb, E,
                                (double*)c->pg_r.p, (double*)c->pg_J.p, costd + n_iters, st));
   std::vector<int32_t> hs(DPVBA_MAX_PGO_ITERS + 1);
   std::vector<double> hc(DPVBA_MAX_PGO_ITERS + 1);
