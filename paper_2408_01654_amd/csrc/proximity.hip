@@ -13,9 +13,8 @@
 // explicitly rounded operations (no fused multiply-add), compared strictly
 // with r2 = radius*radius rounded to float32.
 //
-// Three launches: selection (one wavefront per old frame, max_targets rounds
-// of a wavefront minimum over the frame's candidates: no per-lane lists, no
-// sort), an exclusive scan of the edge counts, and the edge writes.
+// Three launches: selection (one wavefront per old frame), an exclusive scan of
+// the edge counts, and the edge writes.
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
@@ -42,13 +41,66 @@ __device__ __forceinline__ float centre_d2(const float* a, const float* b) {
 
 // Four wavefronts per workgroup, one old frame each.  Keys order the
 // candidates by (d2, j): d2 >= 0, so its bit pattern orders like its value.
+// One pass over the later frames lists a frame's candidates in LDS (in frame
+// order, four distances in flight); each one's rank among them then says
+// whether it is kept, and the kept ones before it where it goes.  Bound by the
+// latency of that pass (1000 frames, ten targets: 5.2 us; a pass for
+// every target took 22.6 us).  More candidates than the list holds: max_t
+// rounds of a wavefront minimum over all of them.
+constexpr int kLoopList = 256;
+
 __global__ void __launch_bounds__(256) loop_select_kernel(const float* poses, int n, int first_recent, int min_gap,
                                                           float r2, int max_t, int* counts, int* targets) {
+  __shared__ unsigned long long lists[4][kLoopList];
   const int lane = threadIdx.x & 63;
   const int i = blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (i >= n) return;  // whole wavefront
+  if (i >= n) return;  // whole wavefront; no barrier below
+  unsigned long long* list = lists[threadIdx.x >> 6];
   const float* ci = poses + 7 * (size_t)i;
   const int j0 = max(first_recent, i + min_gap + 1);
+  int* out = targets + (size_t)i * max_t;
+  int m = 0;  // candidates so far
+  for (int jb = j0; jb < n && m <= kLoopList; jb += 256) {
+    float d2[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) d2[u] = centre_d2(ci, poses + 7 * (size_t)min(jb + 64 * u + lane, n - 1));
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int j = jb + 64 * u + lane;
+      const bool in = j < n && d2[u] < r2;
+      const unsigned long long mask = __ballot(in);
+      const int at = m + __popcll(mask & ((1ull << lane) - 1ull));
+      if (in && at < kLoopList) list[at] = ((unsigned long long)__float_as_uint(d2[u]) << 32) | (unsigned int)j;
+      m += __popcll(mask);
+    }
+  }
+  if (m <= kLoopList) {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    unsigned long long key[4];
+    int rank[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      key[u] = 64 * u + lane < m ? list[64 * u + lane] : ~0ull;
+      rank[u] = 0;
+    }
+    for (int s = 0; s < m; ++s) {
+      const unsigned long long ks = list[s];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) rank[u] += ks < key[u] ? 1 : 0;
+    }
+    int cnt = 0;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const bool keep = 64 * u + lane < m && rank[u] < max_t;
+      const unsigned long long mask = __ballot(keep);
+      if (keep) out[cnt + __popcll(mask & ((1ull << lane) - 1ull))] = (int)(key[u] & 0xffffffffu);
+      cnt += __popcll(mask);
+    }
+    for (int t = cnt + lane; t < max_t; t += 64) out[t] = -1;
+    if (lane == 0) counts[i] = cnt;
+    return;
+  }
   unsigned long long last = 0ull;  // keys above the previous pick (none is 0: j0 >= 1)
   int cnt = 0, mine = -1;          // lane t keeps the t-th pick's frame
   for (int t = 0; t < max_t; ++t) {
@@ -71,7 +123,6 @@ __global__ void __launch_bounds__(256) loop_select_kernel(const float* poses, in
     const int js = __shfl(mine, s);
     rank += (lane < cnt && js < mine) ? 1 : 0;
   }
-  int* out = targets + (size_t)i * max_t;
   if (lane < cnt) out[rank] = mine;
   for (int t = cnt + lane; t < max_t; t += 64) out[t] = -1;
   if (lane == 0) counts[i] = cnt;
