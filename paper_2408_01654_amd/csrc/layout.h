@@ -23,14 +23,16 @@ constexpr int kErrInput = 4;    // a non-finite target / weight or a negative we
 constexpr int kHostErrWords = 3;
 
 constexpr int kMaxSlots = 64;     // slots per tile (one wavefront)
-constexpr int kTileThreads = 256;      // float64 tile work and the depth write-back
-constexpr int kTileThreadsWide = 512;  // float32 tile work
+constexpr int kFinalizeThreads = 256;  // depth write-back
 
-// Workgroup size of the tile kernel and of the single-launch solver for a
-// compute type of tsize bytes (float64 keeps 256: its per-thread partials
-// would not fit).  The solver's dense factor works on a 16 x 16 register
-// grid of the first 256 threads; the others only meet its barriers.
-__host__ __device__ constexpr int tile_threads(int tsize) { return tsize == 4 ? kTileThreadsWide : kTileThreads; }
+// Workgroup size of the tile kernel and of the single-launch solver.  Eight
+// wavefronts in either precision: half of them (256 threads) measured 10 %
+// slower on the float32 workloads and 6 % on a float64 window (139 against
+// 131 us), 1024 threads 5 to 60 % slower.
+constexpr int kTileThreads = 512;
+// Wavefronts whose per-slot partial sums are held at a time: all in float32,
+// four in float64, where all eight would not fit beside the largest tiles.
+__host__ __device__ constexpr int tile_part_waves(int tsize) { return tsize == 4 ? kTileThreads / 64 : 4; }
 constexpr int kRedWidth = 28;     // per-slot partial: 21 (M upper) + 6 (v) + 1 (cost)
 
 struct TileInfo {
@@ -99,10 +101,7 @@ constexpr int kSrcSums = 48;
 // side and Diag(B) terms of each row (2 x 6 n_blk), then one zero.
 __host__ __device__ inline int tile_bterm_entries(int nb) { return 72 * nb + 12 * nb + 1; }
 
-// nthreads: the workgroup size (the per-thread partial sums of phase 1
-// share the U region).  Host plans use tile_threads(tsize), never fewer
-// than the single-launch solver's, so one allocation fits both kernels.
-__host__ __device__ inline TileLds tile_lds_plan(int K, int Tn, int nb, int tsize, int nthreads) {
+__host__ __device__ inline TileLds tile_lds_plan(int K, int Tn, int nb, int tsize) {
   TileLds L;
   L.K_pad = tile_u_rows(K);
   L.W_pad = tile_u_stride(nb);
@@ -114,7 +113,7 @@ __host__ __device__ inline TileLds tile_lds_plan(int K, int Tn, int nb, int tsiz
   L.psum = L.hp + (tsize == 4 ? Tn * 24 + K * 4 : 0);
   L.m = L.psum + K * 8;
   L.u = round_up(L.m + Tn * kRedWidth, 4);
-  L.total_T = L.u + imax(L.K_pad * L.W_pad, (nthreads / 64) * Tn * kRedWidth);  // U, or the wavefronts' slot partials
+  L.total_T = L.u + imax(L.K_pad * L.W_pad, tile_part_waves(tsize) * Tn * kRedWidth);  // U, or the wavefronts' slot partials
   L.slot_ld = Tn | 1;
   L.plane = K * L.slot_ld;
   L.rec_bytes = imax(8 * L.plane * tsize, imax(Tn * kSlotBlk + kSrcSums + tile_bterm_entries(nb), L.W_pad) * tsize);
@@ -128,7 +127,7 @@ __host__ __device__ inline TileLds tile_lds_plan(int K, int Tn, int nb, int tsiz
 __host__ __device__ inline int align16(int b) { return (b + 15) / 16 * 16; }
 
 __host__ __device__ inline int tile_lds_bytes(int K, int Tn, int nb, int tsize) {
-  TileLds L = tile_lds_plan(K, Tn, nb, tsize, tile_threads(tsize));
+  TileLds L = tile_lds_plan(K, Tn, nb, tsize);
   return align16(L.total_T * tsize) + align16(L.rec_bytes) + align16(L.tables);
 }
 

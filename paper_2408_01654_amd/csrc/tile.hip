@@ -134,7 +134,7 @@ __device__ __forceinline__ void tile_assemble(const IterArgs<T>& A, int tile, un
   const TileInfo ti = A.tiles[tile];
   const int tid = threadIdx.x;
   const int K = ti.n_patch, Tn = ti.n_slot, nb = ti.n_blk, W6 = 6 * nb;
-  const TileLds L = tile_lds_plan(K, Tn, nb, (int)sizeof(T), NT);
+  const TileLds L = tile_lds_plan(K, Tn, nb, (int)sizeof(T));
   const int Kp = L.K_pad, Wp = L.W_pad;
   T* base = reinterpret_cast<T*>(lds);
   T* sSlot = base + L.slot;   // [Tn][18]: R_ji (9), t_ji (3)
@@ -352,42 +352,49 @@ __device__ __forceinline__ void tile_assemble(const IterArgs<T>& A, int tile, un
   // hold the same slot, so a tree over offsets Tn, 2 Tn, 4 Tn leaves the
   // wavefront's total of each slot on its first Tn lanes (partners past the
   // last thread group, or past the wavefront, add nothing)
-  {
-    const int lane = tid & 63, wv = tid >> 6;
-    const int valid_lanes = min(64, G * Tn - 64 * wv);  // lanes of this wavefront holding a thread group
-    for (int off = Tn; off < 64; off <<= 1) {
-      const bool take = lane + off < valid_lanes;
+  const int lane1 = tid & 63, wave1 = tid >> 6;
+  const int valid_lanes = min(64, G * Tn - 64 * wave1);  // lanes of this wavefront holding a thread group
+  for (int off = Tn; off < 64; off <<= 1) {
+    const bool take = lane1 + off < valid_lanes;
 #pragma unroll
-      for (int m = 0; m < kRedWidth; ++m) {
-        const T o = __shfl(acc[m], min(lane + off, 63));
-        acc[m] += take ? o : (T)0;
-      }
-    }
-    if (lane < Tn && lane < valid_lanes) {
-      const int ss = (64 * wv + lane) % Tn;
-#pragma unroll
-      for (int m = 0; m < kRedWidth; ++m) sWork[(wv * Tn + ss) * kRedWidth + m] = acc[m];
+    for (int m = 0; m < kRedWidth; ++m) {
+      const T o = __shfl(acc[m], min(lane1 + off, 63));
+      acc[m] += take ? o : (T)0;
     }
   }
-  __syncthreads();
 
-  // ---- phase 2a: per-slot totals, the wavefronts' partials summed in order
+  // ---- phase 2a: per-slot totals, the wavefronts' partials summed in order,
+  // tile_part_waves of them at a time
   {
+    constexpr int NP = tile_part_waves((int)sizeof(T));
     const int nwv = (G * Tn + 63) / 64;  // wavefronts holding thread groups
     const int step = 64 - (64 / Tn) * Tn;
-    for (int idx = tid; idx < Tn * kRedWidth; idx += blockDim.x) {
-      const int ss = idx / kRedWidth, m = idx % kRedWidth;
-      T v = (T)0;
-      int o = 0;  // slot of wavefront w's first lane: 64 w mod Tn
-      for (int w = 0; w < nwv; ++w) {
-        // slot ss appears among the first Tn lanes of wavefront w unless the
-        // wavefront holds fewer lanes than that
-        const int first = ss >= o ? ss - o : ss - o + Tn;  // its first lane in wavefront w
-        if (first < min(64, G * Tn - 64 * w)) v += sWork[(w * Tn + ss) * kRedWidth + m];
-        o += step;
-        if (o >= Tn) o -= Tn;
+    int o0 = 0;  // slot of wavefront w0's first lane: 64 w0 mod Tn
+    for (int w0 = 0;; w0 += NP) {
+      if (w0) __syncthreads();  // the partials before are still read
+      if (wave1 >= w0 && wave1 < w0 + NP && lane1 < Tn && lane1 < valid_lanes) {
+        const int ss = (64 * wave1 + lane1) % Tn;
+#pragma unroll
+        for (int m = 0; m < kRedWidth; ++m) sWork[((wave1 - w0) * Tn + ss) * kRedWidth + m] = acc[m];
       }
-      sM[ss * kRedWidth + m] = v;
+      __syncthreads();
+      const int w1 = min(nwv, w0 + NP);
+      for (int idx = tid; idx < Tn * kRedWidth; idx += blockDim.x) {
+        const int ss = idx / kRedWidth, m = idx % kRedWidth;
+        T v = w0 ? sM[ss * kRedWidth + m] : (T)0;
+        int o = o0;
+        for (int w = w0; w < w1; ++w) {
+          // slot ss appears among the first Tn lanes of wavefront w unless the
+          // wavefront holds fewer lanes than that
+          const int first = ss >= o ? ss - o : ss - o + Tn;  // its first lane in wavefront w
+          if (first < min(64, G * Tn - 64 * w)) v += sWork[((w - w0) * Tn + ss) * kRedWidth + m];
+          o += step;
+          if (o >= Tn) o -= Tn;
+        }
+        sM[ss * kRedWidth + m] = v;
+      }
+      if (NP == kTileThreads / 64 || w0 + NP >= nwv) break;  // float32: one round
+      o0 = (o0 + NP * 64) % Tn;
     }
   }
   __syncthreads();
@@ -657,9 +664,9 @@ __device__ __forceinline__ void tile_assemble(const IterArgs<T>& A, int tile, un
 }
 
 template <typename T>
-__global__ void __launch_bounds__(tile_threads(sizeof(T))) tile_iterate_kernel(IterArgs<T> A) {
+__global__ void __launch_bounds__(kTileThreads) tile_iterate_kernel(IterArgs<T> A) {
   extern __shared__ __align__(16) unsigned char lds[];
-  tile_assemble<T, tile_threads(sizeof(T))>(A, A.order ? A.order[blockIdx.x] : (int)blockIdx.x, lds);
+  tile_assemble<T, kTileThreads>(A, A.order ? A.order[blockIdx.x] : (int)blockIdx.x, lds);
 }
 
 // Damped reduced system of a small problem (packed lower triangle, row i at
@@ -866,7 +873,7 @@ __device__ __forceinline__ void small_solve(const SmallArgs<T>& S, const unsigne
     A.cost_out = S.cost ? S.cost + t : nullptr;
     A.invalid_out = S.invalid ? S.invalid + t : nullptr;
     for (int tile = block; tile < A.n_tiles; tile += nb) {
-      tile_assemble<T, tile_threads(sizeof(T))>(A, tile, lds);
+      tile_assemble<T, kTileThreads>(A, tile, lds);
       __syncthreads();
     }
     if (!grid_sync(S.bar, nb, S.err, A.host_err)) return;
@@ -886,8 +893,8 @@ __device__ __forceinline__ void small_solve(const SmallArgs<T>& S, const unsigne
 }
 
 template <typename T>
-__global__ void __launch_bounds__(tile_threads(sizeof(T)))
-__attribute__((amdgpu_waves_per_eu(tile_threads(sizeof(T)) / 256, tile_threads(sizeof(T)) / 256)))
+__global__ void __launch_bounds__(kTileThreads)
+__attribute__((amdgpu_waves_per_eu(kTileThreads / 256, kTileThreads / 256)))
 small_solve_kernel(SmallArgs<T> S) {
   extern __shared__ __align__(16) unsigned char lds[];
   small_solve<T>(S, blockIdx.x, gridDim.x, lds);
@@ -898,8 +905,8 @@ small_solve_kernel(SmallArgs<T> S) {
 // its largest problem (sixteen float64 windows of 12 to 22 frames: 3.04 ms one
 // after another, 0.75 ms in four groups).
 template <typename T>
-__global__ void __launch_bounds__(tile_threads(sizeof(T)))
-__attribute__((amdgpu_waves_per_eu(tile_threads(sizeof(T)) / 256, tile_threads(sizeof(T)) / 256)))
+__global__ void __launch_bounds__(kTileThreads)
+__attribute__((amdgpu_waves_per_eu(kTileThreads / 256, kTileThreads / 256)))
 small_solve_group_kernel(SmallGroup<T> G) {
   extern __shared__ __align__(16) unsigned char lds[];
   int i = 0;
@@ -931,11 +938,11 @@ __device__ __forceinline__ IterArgs<T> adj_iter(const AdjArgs<T>& a, int it, boo
 }
 
 template <typename T>
-__global__ void __launch_bounds__(tile_threads(sizeof(T))) adj_tile_kernel(AdjGroup<T> G, int it, int replay) {
+__global__ void __launch_bounds__(kTileThreads) adj_tile_kernel(AdjGroup<T> G, int it, int replay) {
   extern __shared__ __align__(16) unsigned char lds[];
   const AdjArgs<T>& a = G.p[blockIdx.y];
   if ((int)blockIdx.x >= a.it.n_tiles) return;
-  tile_assemble<T, tile_threads(sizeof(T))>(adj_iter<T>(a, it, replay),
+  tile_assemble<T, kTileThreads>(adj_iter<T>(a, it, replay),
                                             a.it.order ? a.it.order[blockIdx.x] : (int)blockIdx.x, lds);
 }
 
@@ -1015,7 +1022,7 @@ __global__ void __launch_bounds__(kAdjSolveThreads) adj_solve_kernel(AdjGroup<T>
 
 // Apply the last iteration's depth step and write the results back.
 template <typename T>
-__global__ void __launch_bounds__(kTileThreads) tile_finalize_kernel(
+__global__ void __launch_bounds__(kFinalizeThreads) tile_finalize_kernel(
     const TileInfo* tiles, const int* tile_patch, const int* blk_pose, const T* U_s, const T* pscale_s,
     const T* depth_s, const T* dx, const int* status, int status_stride, T* depth_out, const T* poses_final,
     T* poses_out, int n_frames) {
@@ -1058,7 +1065,7 @@ hipError_t launch_tile_iterate(const IterArgs<T>& A, int lds_bytes, hipStream_t 
   if (A.n_tiles == 0) return hipSuccess;
   hipError_t e = opt_in_lds((const void*)tile_iterate_kernel<T>, lds_bytes);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((tile_iterate_kernel<T>), dim3(A.n_tiles), dim3(tile_threads(sizeof(T))), lds_bytes, st, A);
+  hipLaunchKernelGGL((tile_iterate_kernel<T>), dim3(A.n_tiles), dim3(kTileThreads), lds_bytes, st, A);
   return hipGetLastError();
 }
 
@@ -1074,7 +1081,7 @@ hipError_t launch_tile_finalize(const TileInfo* tiles, int n_tiles, int lds_byte
   }
   hipError_t e = opt_in_lds((const void*)tile_finalize_kernel<T>, lds_bytes);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((tile_finalize_kernel<T>), dim3(n_tiles), dim3(kTileThreads), lds_bytes, st, tiles,
+  hipLaunchKernelGGL((tile_finalize_kernel<T>), dim3(n_tiles), dim3(kFinalizeThreads), lds_bytes, st, tiles,
                      tile_patch, blk_pose, U_s, pscale_s, depth_s, dx, status, status_stride, depth_out, poses_final,
                      poses_out, n_frames);
   return hipGetLastError();
@@ -1115,8 +1122,8 @@ static hipError_t launch_resident(K kernel, const Args& a, int grid, int threads
 
 template <typename T>
 int small_solve_grid(int lds_bytes, bool group) {
-  return group ? resident_workgroups(small_solve_group_kernel<T>, tile_threads(sizeof(T)), lds_bytes)
-               : resident_workgroups(small_solve_kernel<T>, tile_threads(sizeof(T)), lds_bytes);
+  return group ? resident_workgroups(small_solve_group_kernel<T>, kTileThreads, lds_bytes)
+               : resident_workgroups(small_solve_kernel<T>, kTileThreads, lds_bytes);
 }
 
 // grid never exceeds small_solve_grid (the workgroups the device holds at
@@ -1127,13 +1134,13 @@ int small_solve_grid(int lds_bytes, bool group) {
 // runtime guarantee co-residency, at a higher launch cost.
 template <typename T>
 hipError_t launch_small_solve(const SmallArgs<T>& S, int grid, int lds_bytes, bool cooperative, hipStream_t st) {
-  return launch_resident(small_solve_kernel<T>, S, grid, tile_threads(sizeof(T)), lds_bytes, cooperative, st);
+  return launch_resident(small_solve_kernel<T>, S, grid, kTileThreads, lds_bytes, cooperative, st);
 }
 
 // The problems' workgroups together: the same bound, first[n] workgroups.
 template <typename T>
 hipError_t launch_small_solve_group(const SmallGroup<T>& G, int lds_bytes, bool cooperative, hipStream_t st) {
-  return launch_resident(small_solve_group_kernel<T>, G, G.first[G.n], tile_threads(sizeof(T)), lds_bytes, cooperative,
+  return launch_resident(small_solve_group_kernel<T>, G, G.first[G.n], kTileThreads, lds_bytes, cooperative,
                          st);
 }
 
@@ -1143,7 +1150,7 @@ hipError_t launch_adj_tile(const AdjGroup<T>& G, int n, int max_tiles, int lds_b
   if (max_tiles == 0) return hipSuccess;
   hipError_t e = opt_in_lds((const void*)adj_tile_kernel<T>, lds_bytes);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((adj_tile_kernel<T>), dim3(max_tiles, n), dim3(tile_threads(sizeof(T))), lds_bytes, st, G, it,
+  hipLaunchKernelGGL((adj_tile_kernel<T>), dim3(max_tiles, n), dim3(kTileThreads), lds_bytes, st, G, it,
                      replay ? 1 : 0);
   return hipGetLastError();
 }
