@@ -255,7 +255,7 @@ def bench_global(steps, warmup=1, precision=None, scene=None, n_upper=None, keep
                                  "alg_bytes_per_launch": alg, "unique_upper_blocks": n_upper},
            "cholesky_roofline": {"bound": "mfma", "achieved": tf, "peak": MFMA_FP32_PEAK_TFS, "unit": "TFLOP/s",
                                  "frac": tf / MFMA_FP32_PEAK_TFS, "traffic": None,
-                                 "kernel": "blocked Cholesky and triangular solves of the 5994-wide camera system "
+                                 "kernel": "block-sparse Cholesky and triangular solves of the 5994-wide camera system "
                                            "(factor phase: all of its launches)",
                                  "avg_launch_us": avg["factor"], "alg_flop_per_launch": flops,
                                  "alg_flop_basis": "envelope of the reduced system in its factored order "
@@ -556,14 +556,15 @@ def bench_correlation(steps=20):
                                                                xs)
         ratio = float((np.abs(out.cpu().numpy()[sample] - want) / (bound + 1e-30)).max())
     E, P = s.n_edges, s.n_patches
-    alg = P * 9 * D * 4 + E * (100 * D * 4 + 72 + 9 * 49 * 4 + 8)
+    # compulsory bytes: every map and patch feature once, then each edge's pixels, ids and samples
+    alg = (P * 9 + s.n_frames * H * W) * D * 4 + E * (72 + 9 * 49 * 4 + 8)
     ach = alg / (us * 1e-6) / 1e9
     rec = {"workload": "patch correlation (eq. 4), one sliding window: 37,440 edges, 3x3 patches, 7x7 grid, "
                        "128 channels, 22 maps of 120x160",
            "us_per_call": us, "edges_per_s": E / (us * 1e-6),
            "roofline": {"bound": "hbm", "achieved": ach, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                         "frac": ach / HBM_PEAK_GBS, "alg_bytes_per_launch": alg,
-                        "kernel": "patch_corr_kernel<2>", "avg_launch_us": us},
+                        "kernel": "patch_corr3_kernel", "avg_launch_us": us},
            "sampled_edges": 64, "max_err_over_bound": ratio, "ok": ratio <= 1.0}
     log(f"[bench] correlation: {us:.1f} us per call ({ach:.0f} GB/s algorithmic), err/bound {ratio:.3f}")
     return rec

@@ -903,7 +903,7 @@ small_solve_kernel(SmallArgs<T> S) {
 // Several problems side by side: one problem's tiles fill a tenth of the
 // chip, and its gather and factor less, so a group takes little longer than
 // its largest problem (sixteen float64 windows of 12 to 22 frames: 3.04 ms one
-// after another, 0.75 ms in four groups).
+// after another, 0.61 ms in four groups).
 template <typename T>
 __global__ void __launch_bounds__(kTileThreads)
 __attribute__((amdgpu_waves_per_eu(kTileThreads / 256, kTileThreads / 256)))
