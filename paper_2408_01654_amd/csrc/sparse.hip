@@ -73,16 +73,23 @@ struct Stage {
   }
 };
 
-// acc += X Y^T for rows rx .. of X and ry .. of Y (staged blocks).
+// acc += X Y^T for rows rx .. of X and ry .. of Y (staged blocks).  A lane reads
+// 16 bytes of its row, the operands of four (two) product steps at once: the
+// steps take the columns in another order, the same one for X and Y.
 template <typename T>
 __device__ __forceinline__ typename Mfma<T>::acc_t staged_mma(const T* X, int rx, const T* Y, int ry,
                                                               typename Mfma<T>::acc_t acc) {
-  constexpr int ld = staged_ld<T>();
+  constexpr int ld = staged_ld<T>(), V = 16 / (int)sizeof(T);
+  typedef typename V16<T>::type vec_t;
   const int lane = threadIdx.x & 63;
-  const T* x = X + (rx + (lane & 15)) * ld + (lane >> 4);
-  const T* y = Y + (ry + (lane & 15)) * ld + (lane >> 4);
+  const T* x = X + (rx + (lane & 15)) * ld + V * (lane >> 4);
+  const T* y = Y + (ry + (lane & 15)) * ld + V * (lane >> 4);
 #pragma unroll
-  for (int k = 0; k < kBlk; k += 4) acc = Mfma<T>::step(x[k], y[k], acc);
+  for (int k = 0; k < kBlk; k += 4 * V) {
+    const vec_t a = *reinterpret_cast<const vec_t*>(x + k), b = *reinterpret_cast<const vec_t*>(y + k);
+#pragma unroll
+    for (int u = 0; u < V; ++u) acc = Mfma<T>::step(a[u], b[u], acc);
+  }
   return acc;
 }
 
