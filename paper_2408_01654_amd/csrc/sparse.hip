@@ -265,25 +265,28 @@ sparse_level_kernel(T* A, T* Linv, T* v, const T* d0, SparsePlan P, const LevelT
   T* tgt = A + (size_t)t.blk * kBB;
   if (w == 0) __builtin_amdgcn_s_setprio(3);
   // everything that the task reads starts to load at once: the first child's
-  // blocks, the diagonal block (wavefronts 0..3: three, three, two and two of its
-  // ten lower 16 x 16 tiles) and A_IK (wavefronts 4..7: 16 rows each)
+  // blocks, the diagonal block (its ten lower 16 x 16 tiles: one a wavefront,
+  // a second on wavefronts 2 and 3) and A_IK (wavefronts 4..7: 16 rows each)
   Stage<T> gk, gi;
   bool has_i = !is_diag && t.nj > 0 && t.first.ij >= 0;
   if (t.nj > 0) gk.load(A + (size_t)t.first.kj * kBB);
   if (has_i) gi.load(A + (size_t)t.first.ij * kBB);
   const int r0m = 16 * (w & 3);
-  const int nt = w < 2 ? 3 : 2;
-  auto ti = [&](int h) { return w == 0 ? (h ? 1 : 0) : (w == 1 ? 2 : 3); };
-  auto tj = [&](int h) { return w == 0 ? (h == 2 ? 1 : 0) : (w == 1 ? h : (w == 2 ? 2 + h : h)); };
-  T own[16];
-  if (w < 4) {
+  const int nt = w == 2 || w == 3 ? 2 : 1;
+  // tiles 0 .. 9 by rows: (0,0) (1,0) (1,1) (2,0) (2,1) (2,2) (3,0) .. (3,3)
+  const int ti0 = w < 1 ? 0 : (w < 3 ? 1 : (w < 6 ? 2 : 3)), tj0 = w - ti0 * (ti0 + 1) / 2;
+  auto ti = [&](int h) { return h ? 3 : ti0; };
+  auto tj = [&](int h) { return h ? w : tj0; };
+  T own[16], dk[8];
+  {
     const T* DK = A + (size_t)t.dblk * kBB;
 #pragma unroll
-    for (int h = 0; h < 3; ++h)
+    for (int h = 0; h < 2; ++h)
 #pragma unroll
       for (int m = 0; m < 4; ++m)
-        own[4 * h + m] = h < nt ? DK[(16 * ti(h) + Mfma<T>::row(lane, m)) * kBlk + 16 * tj(h) + (lane & 15)] : (T)0;
-  } else if (!is_diag) {
+        dk[4 * h + m] = h < nt ? DK[(16 * ti(h) + Mfma<T>::row(lane, m)) * kBlk + 16 * tj(h) + (lane & 15)] : (T)0;
+  }
+  if (w >= 4 && !is_diag) {
 #pragma unroll
     for (int h = 0; h < 4; ++h)
 #pragma unroll
@@ -296,7 +299,7 @@ sparse_level_kernel(T* A, T* Linv, T* v, const T* d0, SparsePlan P, const LevelT
 #pragma unroll
     for (int c = 0; c < 8; ++c) wr[c] = (T)(c0 + c == r ? 1 : 0);
   }
-  acc_t acc[4] = {zero, zero, zero, zero};
+  acc_t acc[4] = {zero, zero, zero, zero}, dacc[2] = {zero, zero};
   T bsum = (T)0;
   int J = t.first.J;
   // A_IK's (or, for the diagonal block's task, the right-hand side's) share of
@@ -327,21 +330,17 @@ sparse_level_kernel(T* A, T* Linv, T* v, const T* d0, SparsePlan P, const LevelT
     gk.store(sK);
     if (has_i) gi.store(sM);
     __syncthreads();
-    if (w < 4) {
 #pragma unroll
-      for (int h = 0; h < 3; ++h)
-        if (h < nt) acc[h] = staged_mma<T>(sK, 16 * ti(h), sK, 16 * tj(h), acc[h]);
+    for (int h = 0; h < 2; ++h)
+      if (h < nt) dacc[h] = staged_mma<T>(sK, 16 * ti(h), sK, 16 * tj(h), dacc[h]);
+  }
+#pragma unroll
+  for (int h = 0; h < 2; ++h)
+    if (h < nt) {
+#pragma unroll
+      for (int m = 0; m < 4; ++m)
+        W[(16 * ti(h) + Mfma<T>::row(lane, m)) * kLd + 16 * tj(h) + (lane & 15)] = dk[4 * h + m] - dacc[h][m];
     }
-  }
-  if (w < 4) {
-#pragma unroll
-    for (int h = 0; h < 3; ++h)
-      if (h < nt) {
-#pragma unroll
-        for (int m = 0; m < 4; ++m)
-          W[(16 * ti(h) + Mfma<T>::row(lane, m)) * kLd + 16 * tj(h) + (lane & 15)] = own[4 * h + m] - acc[h][m];
-      }
-  }
   __syncthreads();
   int bad = 0;
   for (int p = 0; p < np; ++p) {
