@@ -37,7 +37,6 @@
 
 namespace dpvba {
 
-constexpr int kLd = kBlk + 1;  // row stride of the diagonal factor's working matrix
 constexpr int kBB = kBlk * kBlk;
 constexpr int kLevelThreads = 512;
 
@@ -45,13 +44,14 @@ template <typename T> struct V16;
 template <> struct V16<float> { typedef float type __attribute__((ext_vector_type(4))); };
 template <> struct V16<double> { typedef double type __attribute__((ext_vector_type(2))); };
 
-// stride of a staged block: 16-row operand reads on different LDS banks
+// row stride of a staged block and of the diagonal factor's working matrix:
+// 16-byte rows, and 16-row operand reads on different LDS banks
 template <typename T>
 __host__ __device__ constexpr int staged_ld() { return sizeof(T) == 4 ? kBlk + 4 : kBlk + 2; }
 
 template <typename T>
 __host__ __device__ constexpr int level_lds_elems() {
-  return 2 * kBlk * kLd + 2 * kBlk * staged_ld<T>() + kBlk + 8 * kBlk;
+  return 4 * kBlk * staged_ld<T>() + kBlk + 8 * kBlk;
 }
 
 // A block on its way from memory to LDS: 16-byte vectors of 512 threads.
@@ -98,6 +98,7 @@ __device__ __forceinline__ typename Mfma<T>::acc_t staged_mma(const T* X, int rx
 // go to the wavefronts first, first + nwav, ...: W_(bi,bk) -= W_(bi,p) W_(bk,p)^T.
 template <typename T>
 __device__ __forceinline__ void diag_update_blocks(T* W, int p, int bk_lo, int bk_hi, int first, int nwav) {
+  constexpr int kLd = staged_ld<T>();
   const int lane = threadIdx.x & 63, c0 = 16 * p;
   int count = 0;
   for (int bk = bk_lo; bk <= bk_hi; ++bk) count += 5 + p - bk;
@@ -110,11 +111,15 @@ __device__ __forceinline__ void diag_update_blocks(T* W, int p, int bk_lo, int b
     const int bi = bk + rem;
     const T* xr = W + (16 * bi + (lane & 15)) * kLd + c0 + (lane >> 4);
     const T* yr = W + (16 * bk + (lane & 15)) * kLd + c0 + (lane >> 4);
+    T* out = W + 16 * bi * kLd + 16 * bk + (lane & 15);
+    T old[4];
+#pragma unroll
+    for (int v = 0; v < 4; ++v) old[v] = out[Mfma<T>::row(lane, v) * kLd];
     typename Mfma<T>::acc_t acc = {0, 0, 0, 0};
 #pragma unroll
     for (int k = 0; k < 16; k += 4) acc = Mfma<T>::step(xr[k], yr[k], acc);
 #pragma unroll
-    for (int v = 0; v < 4; ++v) W[(16 * bi + Mfma<T>::row(lane, v)) * kLd + 16 * bk + (lane & 15)] -= acc[v];
+    for (int v = 0; v < 4; ++v) out[Mfma<T>::row(lane, v) * kLd] = old[v] - acc[v];
   }
 }
 
@@ -131,25 +136,36 @@ __device__ __forceinline__ void diag_update_blocks(T* W, int p, int bk_lo, int b
 // (chol16), so the chain of 16 pivots takes no scalar registers and no barrier.
 template <typename T>
 __device__ __forceinline__ void diag_panel(T* W, int p, int& bad) {
+  constexpr int kLd = staged_ld<T>(), V = 16 / (int)sizeof(T);
+  typedef typename V16<T>::type vec_t;
   const int lane = threadIdx.x & 63, s = lane & 15, q = lane >> 4, c0 = 16 * p;
   const int bq = q < 3 - p ? p + 1 + q : 4 + (q - (3 - p));
-  T* wa = W + (c0 + s) * kLd + c0;
-  T* wb = W + (16 * bq + s) * kLd + c0;
+  vec_t* wa = reinterpret_cast<vec_t*>(W + (c0 + s) * kLd + c0);
+  vec_t* wb = reinterpret_cast<vec_t*>(W + (16 * bq + s) * kLd + c0);
   T ra[16], rb[16];
 #pragma unroll
-  for (int c = 0; c < 16; ++c) {
-    ra[c] = wa[c];
-    rb[c] = wb[c];
+  for (int c = 0; c < 16; c += V) {
+    const vec_t va = wa[c / V], vb = wb[c / V];
+#pragma unroll
+    for (int u = 0; u < V; ++u) {
+      ra[c + u] = va[u];
+      rb[c + u] = vb[u];
+    }
   }
   chol16<T>(ra, rb, bad);
   // (the stores that depend on the lane come last: a branch here would sink
   // the rows' updates below it)
+  auto put = [](vec_t* w, const T* r) {
 #pragma unroll
-  for (int c = 0; c < 16; ++c) wb[c] = rb[c];
-  if (q == 0) {
+    for (int c = 0; c < 16; c += V) {
+      vec_t v;
 #pragma unroll
-    for (int c = 0; c < 16; ++c) wa[c] = ra[c];
-  }
+      for (int u = 0; u < V; ++u) v[u] = r[c + u];
+      w[c / V] = v;
+    }
+  };
+  put(wb, rb);
+  if (q == 0) put(wa, ra);
 }
 
 // One launch of the factor: workgroups [0, n_task) are the level's tasks,
@@ -161,12 +177,12 @@ __global__ void __launch_bounds__(kLevelThreads) __attribute__((amdgpu_waves_per
 sparse_level_kernel(T* A, T* Linv, T* v, const T* d0, SparsePlan P, const LevelTask* tasks, int n_task,
                     const UpdateTask* updates, int impl, int lev, int* status, unsigned int* min_bits) {
   extern __shared__ __align__(16) unsigned char dyn_lds[];
+  constexpr int ldM = staged_ld<T>(), kLd = ldM;
   T* sM = reinterpret_cast<T*>(dyn_lds);  // staged block of row I, then A_IK
   T* sK = sM + kBlk * staged_ld<T>();     // staged block of row K
-  T* W = sK + kBlk * staged_ld<T>();      // 128 x 64, row stride kLd
+  T* W = sK + kBlk * staged_ld<T>();      // 128 x 64
   T* sb = W + 2 * kBlk * kLd;             // 64: the column's right-hand side
   T* part = sb + kBlk;                    // 8 x 64 partial sums
-  constexpr int ldM = staged_ld<T>();
   const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
   typedef typename Mfma<T>::acc_t acc_t;
   const acc_t zero = {0, 0, 0, 0};
