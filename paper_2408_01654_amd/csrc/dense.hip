@@ -37,7 +37,7 @@ __global__ void __launch_bounds__(kSmallCholThreads) small_chol_solve_kernel(con
   if (n + 1 <= kSmallRows) {  // the small panel solver
     __shared__ float minr;
     const int nr = small_solve_rows(n);
-    T* xr = reinterpret_cast<T*>(dyn_lds) + 37 * nr + nr * nr;  // after the solver's own arrays
+    T* xr = reinterpret_cast<T*>(dyn_lds) + small_solve_x(nr);  // after the solver's own arrays
     panel_chol_solve<T>(n, S, rhs, nullptr, dyn_lds, xr, &bad, &minr, n, [] {});
     for (int i = tid; i < n; i += blockDim.x) dx[i] = xr[i];  // zero when a pivot failed
     if (tid == 0) {

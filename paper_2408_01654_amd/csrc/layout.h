@@ -158,13 +158,14 @@ __host__ __device__ inline int small_solve_rows(int n) {
   return n1 <= 32 ? 32 : (n1 <= 64 ? 64 : (n1 <= 80 ? 80 : 96));
 }
 
-// Shared memory of the one-workgroup panel solve: within 37 nr + nr^2 entries
-// the padded matrix with the right-hand side's block ((m + 16) (m + 1), m = n
-// rounded up to 16), the factored diagonal blocks (17 m) and the damped
-// diagonal (m); then the step.
+// Shared memory of the one-workgroup panel solve: before the step x, within 40
+// nr + nr^2 entries, the padded matrix with the right-hand side's block ((m + 16)
+// (m + 4), m = n rounded up to 16), the factored diagonal blocks (17 m) and the
+// damped diagonal (m).
+__host__ __device__ inline int small_solve_x(int nr) { return 40 * nr + nr * nr; }
 __host__ __device__ inline int small_solve_lds_bytes(int n, int tsize) {
   const int nr = small_solve_rows(n);
-  return (38 * nr + nr * nr) * tsize;
+  return (small_solve_x(nr) + nr) * tsize;
 }
 
 // Shared memory of the one-workgroup packed solve (small_chol_solve_kernel):

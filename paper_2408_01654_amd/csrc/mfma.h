@@ -28,20 +28,31 @@ template <> struct Mfma<double> {
   static __device__ __forceinline__ int row(int lane, int v) { return (lane >> 4) + 4 * v; }
 };
 
+// 16 bytes of a row.
+template <typename T> struct V16;
+template <> struct V16<float> { typedef float type __attribute__((ext_vector_type(4))); };
+template <> struct V16<double> { typedef double type __attribute__((ext_vector_type(2))); };
 
-// C (64 x 64) = X Y^T for row-major 64 x 64 blocks X, Y in LDS with row
-// stride ld: wavefront w computes rows 16 w .. 16 w + 15 as four 16 x 16
-// tiles; acc[t] holds tile t (columns 16 t .. 16 t + 15).
-template <typename T>
-__device__ __forceinline__ void gemm_nt_64(const T* X, const T* Y, int ld, int kdim,
-                                           typename Mfma<T>::acc_t acc[4]) {
-  const int lane = threadIdx.x & 63, w = (threadIdx.x >> 6) & 3;
-  const T* xr = X + (16 * w + (lane & 15)) * ld + (lane >> 4);
-  const T* yr = Y + (lane & 15) * ld + (lane >> 4);
-  for (int k0 = 0; k0 < kdim; k0 += 4) {
-    const T a = xr[k0];
+// N entries between registers and a 16-byte aligned row in LDS.
+template <typename T, int N>
+__device__ __forceinline__ void get_row(const T* row, T* r) {
+  constexpr int V = 16 / (int)sizeof(T);
 #pragma unroll
-    for (int t = 0; t < 4; ++t) acc[t] = Mfma<T>::step(a, yr[16 * t * ld + k0], acc[t]);
+  for (int c = 0; c < N; c += V) {
+    const typename V16<T>::type v = *reinterpret_cast<const typename V16<T>::type*>(row + c);
+#pragma unroll
+    for (int u = 0; u < V; ++u) r[c + u] = v[u];
+  }
+}
+template <typename T, int N>
+__device__ __forceinline__ void put_row(T* row, const T* r) {
+  constexpr int V = 16 / (int)sizeof(T);
+#pragma unroll
+  for (int c = 0; c < N; c += V) {
+    typename V16<T>::type v;
+#pragma unroll
+    for (int u = 0; u < V; ++u) v[u] = r[c + u];
+    *reinterpret_cast<typename V16<T>::type*>(row + c) = v;
   }
 }
 

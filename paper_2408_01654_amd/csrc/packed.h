@@ -415,11 +415,15 @@ __device__ __forceinline__ void panel_update(T* W, int ldw, int mb, int p, int b
     if (bk > bk_hi) break;
     const T* xr = W + (16 * bi + (lane & 15)) * ldw + c0 + (lane >> 4);
     const T* yr = W + (16 * bk + (lane & 15)) * ldw + c0 + (lane >> 4);
+    T* out = W + 16 * bi * ldw + 16 * bk + (lane & 15);
+    T old[4];
+#pragma unroll
+    for (int v = 0; v < 4; ++v) old[v] = out[Mfma<T>::row(lane, v) * ldw];
     typename Mfma<T>::acc_t acc = {0, 0, 0, 0};
 #pragma unroll
     for (int k = 0; k < 16; k += 4) acc = Mfma<T>::step(xr[k], yr[k], acc);
 #pragma unroll
-    for (int v = 0; v < 4; ++v) W[(16 * bi + Mfma<T>::row(lane, v)) * ldw + 16 * bk + (lane & 15)] -= acc[v];
+    for (int v = 0; v < 4; ++v) out[Mfma<T>::row(lane, v) * ldw] = old[v] - acc[v];
     bi += nwav;
   }
 }
@@ -442,7 +446,7 @@ __device__ __forceinline__ void panel_update(T* W, int ldw, int mb, int p, int b
 // x [n] (LDS): zero if a pivot was not positive.  ld > 0: Sp_g is a dense
 // row-major matrix with row stride ld (its lower triangle is read), else
 // packed; d0_g null: the damped diagonal is that of S.  The arrays fit the
-// 37 nr + nr^2 entries of small_solve_lds_bytes (nr = small_solve_rows(n)).
+// small_solve_x(nr) entries before x (nr = small_solve_rows(n)).
 template <typename T, typename F>
 __device__ __forceinline__ void panel_chol_solve(int n_in, const T* Sp_g, const T* rhs_g, const T* d0_g,
                                                  unsigned char* lds, T* x, int* bad_out, float* minr_out, int ld,
@@ -451,7 +455,8 @@ __device__ __forceinline__ void panel_chol_solve(int n_in, const T* Sp_g, const 
   const int n = __builtin_amdgcn_readfirstlane(n_in);
   const int tid = threadIdx.x, lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6), nwav = (int)blockDim.x >> 6;
-  const int mb = (n + 15) >> 4, nrp = 16 * mb, ldw = nrp + 1;
+  // rows on 16 bytes, and 16-row operand reads on different banks
+  const int mb = (n + 15) >> 4, nrp = 16 * mb, ldw = nrp + 16 / (int)sizeof(T);
   T* W = reinterpret_cast<T*>(lds);  // [nrp + 16][ldw]
   T* Ld = W + (nrp + 16) * ldw;      // [mb][16][17] factored diagonal blocks
   T* dd = Ld + mb * kDs;             // [nrp] damped diagonal
@@ -493,16 +498,12 @@ __device__ __forceinline__ void panel_chol_solve(int n_in, const T* Sp_g, const 
       const T* wa = W + (16 * p + s) * ldw + 16 * p;
       T* wb = W + (bq <= mb ? 16 * bq + s : nrp + 15) * ldw + 16 * p;  // else a row nobody looks at
       T ra[16], rb[16];
-#pragma unroll
-      for (int c = 0; c < 16; ++c) {
-        ra[c] = wa[c];
-        rb[c] = wb[c];
-      }
+      get_row<T, 16>(wa, ra);
+      get_row<T, 16>(wb, rb);
       chol16<T>(ra, rb, bad);
       // (the stores that depend on the lane come last: a branch here would sink
       // the rows' updates below it)
-#pragma unroll
-      for (int c = 0; c < 16; ++c) wb[c] = rb[c];
+      put_row<T, 16>(wb, rb);
       if (lane < 16 && w == 0) {
 #pragma unroll
         for (int c = 0; c < 16; ++c) Ld[p * kDs + s * 17 + c] = ra[c];

@@ -40,10 +40,6 @@ namespace dpvba {
 constexpr int kBB = kBlk * kBlk;
 constexpr int kLevelThreads = 512;
 
-template <typename T> struct V16;
-template <> struct V16<float> { typedef float type __attribute__((ext_vector_type(4))); };
-template <> struct V16<double> { typedef double type __attribute__((ext_vector_type(2))); };
-
 // row stride of a staged block and of the diagonal factor's working matrix:
 // 16-byte rows, and 16-row operand reads on different LDS banks
 template <typename T>
@@ -136,36 +132,19 @@ __device__ __forceinline__ void diag_update_blocks(T* W, int p, int bk_lo, int b
 // (chol16), so the chain of 16 pivots takes no scalar registers and no barrier.
 template <typename T>
 __device__ __forceinline__ void diag_panel(T* W, int p, int& bad) {
-  constexpr int kLd = staged_ld<T>(), V = 16 / (int)sizeof(T);
-  typedef typename V16<T>::type vec_t;
+  constexpr int kLd = staged_ld<T>();
   const int lane = threadIdx.x & 63, s = lane & 15, q = lane >> 4, c0 = 16 * p;
   const int bq = q < 3 - p ? p + 1 + q : 4 + (q - (3 - p));
-  vec_t* wa = reinterpret_cast<vec_t*>(W + (c0 + s) * kLd + c0);
-  vec_t* wb = reinterpret_cast<vec_t*>(W + (16 * bq + s) * kLd + c0);
+  T* wa = W + (c0 + s) * kLd + c0;
+  T* wb = W + (16 * bq + s) * kLd + c0;
   T ra[16], rb[16];
-#pragma unroll
-  for (int c = 0; c < 16; c += V) {
-    const vec_t va = wa[c / V], vb = wb[c / V];
-#pragma unroll
-    for (int u = 0; u < V; ++u) {
-      ra[c + u] = va[u];
-      rb[c + u] = vb[u];
-    }
-  }
+  get_row<T, 16>(wa, ra);
+  get_row<T, 16>(wb, rb);
   chol16<T>(ra, rb, bad);
   // (the stores that depend on the lane come last: a branch here would sink
   // the rows' updates below it)
-  auto put = [](vec_t* w, const T* r) {
-#pragma unroll
-    for (int c = 0; c < 16; c += V) {
-      vec_t v;
-#pragma unroll
-      for (int u = 0; u < V; ++u) v[u] = r[c + u];
-      w[c / V] = v;
-    }
-  };
-  put(wb, rb);
-  if (q == 0) put(wa, ra);
+  put_row<T, 16>(wb, rb);
+  if (q == 0) put_row<T, 16>(wa, ra);
 }
 
 // One launch of the factor: workgroups [0, n_task) are the level's tasks,

@@ -746,7 +746,7 @@ __device__ __forceinline__ void factor_solve_retract(const IterArgs<T>& A, const
   __shared__ int bad;
   __shared__ float minr;
   const int nr = small_solve_rows(n);
-  T* x = reinterpret_cast<T*>(lds) + 37 * nr + nr * nr;  // after the solver's own arrays
+  T* x = reinterpret_cast<T*>(lds) + small_solve_x(nr);  // after the solver's own arrays
   // The tiles' costs and invalid-edge counts of this iteration, summed in tile
   // order by the third wavefront beside the backward substitution.
   const int n_cost = A.cost_out ? A.n_tiles : 0, lane = tid & 63;
@@ -1011,7 +1011,7 @@ __global__ void __launch_bounds__(kAdjSolveThreads) adj_solve_kernel(AdjGroup<T>
   }
   __syncthreads();
   const int nr = small_solve_rows(n);
-  T* x = reinterpret_cast<T*>(lds) + 37 * nr + nr * nr;  // after the solver's own arrays
+  T* x = reinterpret_cast<T*>(lds) + small_solve_x(nr);  // after the solver's own arrays
   panel_chol_solve<T>(n, a.Sp, a.urhs, a.d0, lds, x, &bad, &minr, 0, [] {});
   for (int i = tid; i < n; i += blockDim.x) a.up[i] = x[i];  // zero when a pivot failed
   if (tid == 0) {
