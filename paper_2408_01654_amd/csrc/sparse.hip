@@ -13,15 +13,14 @@
 //  * update tasks, one per block that is eliminated later: subtract the
 //    products of the columns of the level before.
 // The chain per level is one launch: loads, the diagonal block's update, four
-// 16-column panels, one product; the panels' pivot chain is what bounds it
-// (14.2 of 33 thousand cycles before the columns were updated by fused
-// broadcast multiply-adds).  On 1000 keyframes with loop closures (5,994
-// unknowns) an iteration's factor and solve take 26 launches of 12.6 us and one
-// of 34 us, against 94 dependent pairs of launches (10.4 + 5.5 us) and a
+// 16-column panels, one product; two dependent round trips to memory and the
+// panels' pivot chain are what bounds it.  On 1000 keyframes with loop closures
+// (5,994 unknowns) an iteration's factor and solve take 26 launches of 11.5 us
+// and one of 35 us, against 94 dependent pairs of launches (10.4 + 5.5 us) and a
 // triangular chain of 118 us when the blocks were eliminated one after another:
-// 9.09 -> 2.80 ms for five iterations.  A Sim(3) pose graph of 1000 keyframes
-// (float64) takes 8 levels of 14.3 us instead of 109 pairs of 22.4 + 5.0 us:
-// 36.1 -> 3.0 ms for ten iterations.
+// 9.09 -> 2.43 ms for five iterations.  A Sim(3) pose graph of 1000 keyframes
+// (float64) takes 8 levels of 13.8 us instead of 109 pairs of 22.4 + 5.0 us:
+// 36.1 -> 2.1 ms for ten iterations.
 //
 // Blocks are staged in LDS by the whole workgroup (16 bytes a thread,
 // coalesced) and the matrix-core operands read from there: straight from
