@@ -186,8 +186,9 @@ void dpvba_destroy(dpvba_ctx* ctx);
 dpvba_status dpvba_analyze(dpvba_ctx* ctx, const dpvba_graph* g, void* stream);
 
 /* Tile-shape choice of the analysis (host).  A tile is a run of at most
- * tile_patches_* patches of one source frame; 0 selects the default (96 for
- * the float32 plan, 32 for the float64 plan).  Larger tiles write smaller
+ * tile_patches_* patches of one source frame, evenly many where a frame needs
+ * several; 0 selects the default (96 for the float32 plan, 56 for the float64
+ * plan).  Larger tiles write smaller
  * partial systems; smaller tiles expose more workgroups.  Both plans are
  * built by every analysis.
  * keep_order: 0 lets the analysis factor a reduced system of more than 252

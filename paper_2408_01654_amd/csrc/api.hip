@@ -170,7 +170,11 @@ constexpr int kLdsBudget = 150 * 1024;
 // prefers fewer, larger tiles.
 constexpr int kLdsBudgetTwoPerCu = 80 * 1024;
 constexpr int kDefaultTilePatches32 = 96;
-constexpr int kDefaultTilePatches64 = 32;
+// float64: one tile of a frame is faster than two up to about 56 patches
+// (12 frames: 99.9 us against 102 at 49 patches; 8 frames of 64: 93.3 against
+// 92.6).  Measured against tiles of 32 filled one after the other: 24 frames
+// of 110 patches 168 -> 153 us, 22 of 72 140 -> 130, 12 of 49 equal.
+constexpr int kDefaultTilePatches64 = 56;
 // Largest reduced system of one problem of a batch (its workgroup keeps the
 // right-hand side on one wavefront, at most 4 entries per lane).
 constexpr int kBatchMaxUnknowns = 252;
@@ -845,7 +849,10 @@ static bool index_problem(int N, int P, int E, const int32_t* ii, const int32_t*
 
 // Split each source frame's patches into tiles of at most `kcap` patches
 // whose shared-memory plan (element size tsize) fits the budget, then build
-// the gather lists.  Returns false if one patch alone does not fit.
+// the gather lists.  A frame over the limit is cut into the fewest tiles and
+// these are made even: a full tile with a short one after it costs what the
+// full one does (float32, 20 frames of 97 patches: 130.6 us as 96 + 1, 117.2
+// as 49 + 48).  Returns false if one patch alone does not fit.
 static bool plan_tiling(int N, int nf, const std::vector<int32_t>& jj, const std::vector<int32_t>& pcount,
                         const std::vector<int32_t>& pedges, const std::vector<std::vector<int32_t>>& frame_patches,
                         int kcap, int tsize, HostTiling& H, int lds_budget = kLdsBudget) {
@@ -923,6 +930,8 @@ static bool plan_tiling(int N, int nf, const std::vector<int32_t>& jj, const std
   for (int f = 0; f < N; ++f) {
     std::vector<int32_t> cur;
     std::map<int, int> cur_mult;
+    const int n = (int)frame_patches[f].size();
+    const int cap = n ? (n - 1) / ((n - 1) / kcap + 1) + 1 : kcap;
     for (int k : frame_patches[f]) {
       std::map<int, int> km;
       patch_mult(k, km);
@@ -930,7 +939,7 @@ static bool plan_tiling(int N, int nf, const std::vector<int32_t>& jj, const std
       for (auto& kv : km) merged[kv.first] = std::max(merged[kv.first], kv.second);
       int Tn, nb, mm;
       plan_of(merged, f, Tn, nb, mm);
-      const bool fits = Tn <= kMaxSlots && (int)cur.size() + 1 <= kcap &&
+      const bool fits = Tn <= kMaxSlots && (int)cur.size() + 1 <= cap &&
                         tile_lds_bytes((int)cur.size() + 1, Tn, nb, tsize) <= lds_budget;
       if (!fits) {
         if (cur.empty()) return false;
