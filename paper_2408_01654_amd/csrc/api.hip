@@ -939,16 +939,16 @@ static bool plan_tiling(int N, int nf, const std::vector<int32_t>& jj, const std
       for (auto& kv : km) merged[kv.first] = std::max(merged[kv.first], kv.second);
       int Tn, nb, mm;
       plan_of(merged, f, Tn, nb, mm);
-      const bool fits = Tn <= kMaxSlots && (int)cur.size() + 1 <= cap &&
-                        tile_lds_bytes((int)cur.size() + 1, Tn, nb, tsize) <= lds_budget;
+      const bool alone = cur.empty();
+      const bool fits = (int)cur.size() + 1 <= cap && tile_fits((int)cur.size() + 1, Tn, nb, tsize, lds_budget, !alone);
       if (!fits) {
-        if (cur.empty()) return false;
+        if (alone) return false;
         emit(f, cur, cur_mult);
         cur.clear();
         cur_mult.clear();
         merged = km;
         plan_of(merged, f, Tn, nb, mm);
-        if (!(Tn <= kMaxSlots && tile_lds_bytes(1, Tn, nb, tsize) <= lds_budget)) return false;
+        if (!tile_fits(1, Tn, nb, tsize, lds_budget, false)) return false;
       }
       cur.push_back(k);
       cur_mult = merged;

@@ -75,6 +75,9 @@ __host__ __device__ inline int imax(int a, int b) { return a > b ? a : b; }
 // patches (per-patch sums): cells of eight consecutive values put a
 // wavefront on 8 banks, and on 2 with 12 slots.  Then the block -> slot
 // range tables and the rows' places in the share.
+// padded = false: the same without what is there for speed alone (the odd
+// strides and the rows' places).  It sets which graphs fit (tile_fits); the
+// kernels always use the padded plan.
 struct TileLds {
   int slot, patch, hp, psum, m, u, total_T; // T offsets
   int K_pad, W_pad;
@@ -101,10 +104,10 @@ constexpr int kSrcSums = 48;
 // side and Diag(B) terms of each row (2 x 6 n_blk), then one zero.
 __host__ __device__ inline int tile_bterm_entries(int nb) { return 72 * nb + 12 * nb + 1; }
 
-__host__ __device__ inline TileLds tile_lds_plan(int K, int Tn, int nb, int tsize) {
+__host__ __device__ inline TileLds tile_lds_plan(int K, int Tn, int nb, int tsize, bool padded = true) {
   TileLds L;
   L.K_pad = tile_u_rows(K);
-  L.W_pad = tile_u_stride(nb);
+  L.W_pad = padded ? tile_u_stride(nb) : round_up(6 * nb + 1, 16);
   L.slot = 0;
   L.patch = L.slot + Tn * 18;
   // float32 plans: the slots' relative poses (12 doubles) and the patches'
@@ -114,21 +117,32 @@ __host__ __device__ inline TileLds tile_lds_plan(int K, int Tn, int nb, int tsiz
   L.m = L.psum + K * 8;
   L.u = round_up(L.m + Tn * kRedWidth, 4);
   L.total_T = L.u + imax(L.K_pad * L.W_pad, tile_part_waves(tsize) * Tn * kRedWidth);  // U, or the wavefronts' slot partials
-  L.slot_ld = Tn | 1;
+  L.slot_ld = padded ? Tn | 1 : Tn;
   L.plane = K * L.slot_ld;
   L.rec_bytes = imax(8 * L.plane * tsize, imax(Tn * kSlotBlk + kSrcSums + tile_bterm_entries(nb), L.W_pad) * tsize);
   L.blk_s0 = 0;
   L.blk_s1 = L.blk_s0 + nb;
   L.row_base = round_up(L.blk_s1 + nb, 16);  // per row of the 6 n_blk: its part of an entry's place in the share
-  L.tables = L.row_base + 4 * round_up(6 * nb, 16);
+  L.tables = padded ? L.row_base + 4 * round_up(6 * nb, 16) : L.blk_s1 + nb;
   return L;
 }
 
 __host__ __device__ inline int align16(int b) { return (b + 15) / 16 * 16; }
 
-__host__ __device__ inline int tile_lds_bytes(int K, int Tn, int nb, int tsize) {
-  TileLds L = tile_lds_plan(K, Tn, nb, tsize);
+__host__ __device__ inline int tile_lds_bytes(int K, int Tn, int nb, int tsize, bool padded = true) {
+  TileLds L = tile_lds_plan(K, Tn, nb, tsize, padded);
   return align16(L.total_T * tsize) + align16(L.rec_bytes) + align16(L.tables);
+}
+
+// Whether a tile of K patches fits a shared-memory budget.  strict = false, for
+// the tile of one patch that has nowhere else to go: the budget counts what the
+// tile cannot do without, and the padding (up to 1.6 KB) may go beyond it,
+// within the 160 KiB of a compute unit.
+constexpr int kMaxLds = 159 * 1024;  // 160 KiB less the kernels' few static words
+inline bool tile_fits(int K, int Tn, int nb, int tsize, int budget, bool strict) {
+  if (Tn > kMaxSlots) return false;
+  const int bytes = tile_lds_bytes(K, Tn, nb, tsize);
+  return strict ? bytes <= budget : bytes <= kMaxLds && tile_lds_bytes(K, Tn, nb, tsize, false) <= budget;
 }
 
 // One problem of a batch: its ranges in the packed arrays and in the
