@@ -135,7 +135,7 @@ __device__ __forceinline__ void tile_assemble(const IterArgs<T>& A, int tile, un
   const int tid = threadIdx.x;
   const int K = ti.n_patch, Tn = ti.n_slot, nb = ti.n_blk, W6 = 6 * nb;
   const TileLds L = tile_lds_plan(K, Tn, nb, (int)sizeof(T));
-  const int Kp = L.K_pad, Wp = L.W_pad;
+  const int Kp = L.K_pad, Wp = L.W_pad, Ws = tile_u_stride(nb);  // row strides of U in LDS and stored
   T* base = reinterpret_cast<T*>(lds);
   T* sSlot = base + L.slot;   // [Tn][18]: R_ji (9), t_ji (3)
   T* sPatch = base + L.patch; // [K][4]: x^0, x^1, d, w / sqrt(C~)
@@ -149,7 +149,7 @@ __device__ __forceinline__ void tile_assemble(const IterArgs<T>& A, int tile, un
   const int ldS = L.slot_ld, PS = L.plane;
   T* sCell = reinterpret_cast<T*>(rec);  // 8 planes of [K][ldS]
   T* sB = reinterpret_cast<T*>(rec);     // phase 2c: [Tn][kSlotBlk], then kSrcSums sums
-  T* sDx = reinterpret_cast<T*>(rec);    // phase 0: [Wp] block step
+  T* sDx = reinterpret_cast<T*>(rec);    // phase 0: [Ws] block step
   unsigned char* tab = rec + align16(L.rec_bytes);
   unsigned char* sBlkS0 = tab + L.blk_s0;  // first slot of each block (its slots are consecutive)
   unsigned char* sBlkS1 = tab + L.blk_s1;  // one past its last slot
@@ -235,11 +235,11 @@ __device__ __forceinline__ void tile_assemble(const IterArgs<T>& A, int tile, un
     }
   }
   if (apply_prev)  // [dxi of the tile's blocks | 1 | 0 ...]
-    for (int x = tid; x < Wp; x += blockDim.x)
+    for (int x = tid; x < Ws; x += blockDim.x)
       sDx[x] = x < W6 ? A.dx_prev[6 * A.blk_pose[ti.blk_begin + x / 6] + x % 6] : (x == W6 ? (T)1 : (T)0);
   __syncthreads();
   if (apply_prev) {
-    schur_row_dots<T>(A.U_s + ti.u_begin, K, Wp, sDx, sPs, 8);
+    schur_row_dots<T>(A.U_s + ti.u_begin, K, Ws, sDx, sPs, 8);
     __syncthreads();
   }
   for (int k = tid; k < K; k += blockDim.x) {
@@ -483,15 +483,22 @@ __device__ __forceinline__ void tile_assemble(const IterArgs<T>& A, int tile, un
   }
   __syncthreads();
 
-  // ---- phase 2c: stored rows (the padded matrix as 16-byte vectors); per-slot
+  // ---- phase 2c: stored rows (without the odd column tile, as 16-byte vectors); per-slot
   // source blocks Ad^T M, Ad^T M Ad and Ad^T v, then their sums over the
   // slots in slot order
   {
     typedef typename Vec16<T>::type vec_t;
-    const int nvec = Kp * Wp * (int)sizeof(T) / 16;
+    constexpr int V = 16 / (int)sizeof(T);
+    const int rv = Ws / V, skip = (Wp - Ws) / V, nvec = Kp * rv;
+    const float r_rv = 1.f / (float)rv;
     const vec_t* from = reinterpret_cast<const vec_t*>(sU);
     vec_t* to = reinterpret_cast<vec_t*>(A.U_s + ti.u_begin);
-    for (int x = tid; x < nvec; x += blockDim.x) to[x] = from[x];
+    if (skip == 0) {
+      for (int x = tid; x < nvec; x += blockDim.x) to[x] = from[x];
+    } else {
+      for (int x = tid; x < nvec; x += blockDim.x)
+        to[x] = from[x + (int)(((float)x + 0.5f) * r_rv) * skip];  // row x / rv: exact, x < 2^20
+    }
   }
   for (int idx = tid; idx < Tn * 7; idx += blockDim.x) {  // column c of Ad^T M (c = 6: Ad^T v)
     const int ss = idx / 7, c = idx - ss * 7;
