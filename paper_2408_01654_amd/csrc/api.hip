@@ -175,6 +175,8 @@ constexpr int kDefaultTilePatches32 = 96;
 // 92.6).  Measured against tiles of 32 filled one after the other: 24 frames
 // of 110 patches 168 -> 153 us, 22 of 72 140 -> 130, 12 of 49 equal.
 constexpr int kDefaultTilePatches64 = 56;
+// float64 tiles of a problem whose even tiles do not fit (plan_tiling).
+constexpr int kFullTilePatches64 = 32;
 // Largest reduced system of one problem of a batch (its workgroup keeps the
 // right-hand side on one wavefront, at most 4 entries per lane).
 constexpr int kBatchMaxUnknowns = 252;
@@ -852,10 +854,15 @@ static bool index_problem(int N, int P, int E, const int32_t* ii, const int32_t*
 // the gather lists.  A frame over the limit is cut into the fewest tiles and
 // these are made even: a full tile with a short one after it costs what the
 // full one does (float32, 20 frames of 97 patches: 130.6 us as 96 + 1, 117.2
-// as 49 + 48).  Returns false if one patch alone does not fit.
+// as 49 + 48).  even = false fills the tiles one after another instead, to
+// the limits without the padding: a short last tile reaches fewer poses and
+// its share is smaller (260 such frames over 15 free poses: 14.3 MiB of
+// workspace against 19.0), so this is the plan of problems that the other
+// takes beyond a fixed capacity.  Returns false if one patch alone does not
+// fit, or the offsets exceed 32 bits.
 static bool plan_tiling(int N, int nf, const std::vector<int32_t>& jj, const std::vector<int32_t>& pcount,
                         const std::vector<int32_t>& pedges, const std::vector<std::vector<int32_t>>& frame_patches,
-                        int kcap, int tsize, HostTiling& H, int lds_budget = kLdsBudget) {
+                        int kcap, int tsize, HostTiling& H, int lds_budget = kLdsBudget, bool even = true) {
   const int n_free = N - nf;
   auto patch_mult = [&](int k, std::map<int, int>& m) {
     for (int q = pcount[k]; q < pcount[k + 1]; ++q) m[jj[pedges[q]]]++;
@@ -931,7 +938,7 @@ static bool plan_tiling(int N, int nf, const std::vector<int32_t>& jj, const std
     std::vector<int32_t> cur;
     std::map<int, int> cur_mult;
     const int n = (int)frame_patches[f].size();
-    const int cap = n ? (n - 1) / ((n - 1) / kcap + 1) + 1 : kcap;
+    const int cap = n && even ? (n - 1) / ((n - 1) / kcap + 1) + 1 : kcap;
     for (int k : frame_patches[f]) {
       std::map<int, int> km;
       patch_mult(k, km);
@@ -940,7 +947,7 @@ static bool plan_tiling(int N, int nf, const std::vector<int32_t>& jj, const std
       int Tn, nb, mm;
       plan_of(merged, f, Tn, nb, mm);
       const bool alone = cur.empty();
-      const bool fits = (int)cur.size() + 1 <= cap && tile_fits((int)cur.size() + 1, Tn, nb, tsize, lds_budget, !alone);
+      const bool fits = (int)cur.size() + 1 <= cap && tile_fits((int)cur.size() + 1, Tn, nb, tsize, lds_budget, even && !alone);
       if (!fits) {
         if (alone) return false;
         emit(f, cur, cur_mult);
@@ -986,6 +993,9 @@ static bool plan_tiling(int N, int nf, const std::vector<int32_t>& jj, const std
   }
   return true;
 }
+
+// Bytes of a single-launch solve's buffers under a plan (elements of tsize).
+static size_t solve_ws_bytes(int N, int P, int E, int n_free, const HostTiling& H, int tsize);
 
 static hipError_t upload_tiling(Tiling& T_, const HostTiling& H, hipStream_t st) {
   hipError_t e;
@@ -1060,10 +1070,23 @@ dpvba_status dpvba_analyze_ex(dpvba_ctx* c, const dpvba_graph* g, const dpvba_tu
   const std::vector<std::vector<int32_t>>& frame_patches = X.frame_patches;
   HostTiling H32, H64;
   const bool single_launch = 6 * (long long)n_free + 1 <= kSmallRows;
-  if (!plan_tiling(N, nf, jj, pcount, pedges, frame_patches, kcap32, 4, H32,
-                   single_launch ? kLdsBudget : kLdsBudgetTwoPerCu))
-    return DPVBA_EINVAL;
-  if (!plan_tiling(N, nf, jj, pcount, pedges, frame_patches, kcap64, 8, H64)) return DPVBA_EINVAL;
+  // Even tiles; full ones where even tiles do not fit or take the single-launch
+  // solver's buffers beyond the static scratch of dpvba_solve_noalloc.
+  auto plan = [&](int tsize, int kcap, int kcap_full, HostTiling& H) {
+    const int budget = tsize == 4 && !single_launch ? kLdsBudgetTwoPerCu : kLdsBudget;
+    auto scratch_need = [&](const HostTiling& h) { return solve_ws_bytes(N, P, E, n_free, h, tsize); };
+    const bool ok = plan_tiling(N, nf, jj, pcount, pedges, frame_patches, kcap, tsize, H, budget);
+    if (ok && (!single_launch || scratch_need(H) <= kScratchBytes)) return true;
+    HostTiling F;
+    if (plan_tiling(N, nf, jj, pcount, pedges, frame_patches, kcap_full, tsize, F, budget, false) &&
+        (!ok || scratch_need(F) < scratch_need(H))) {
+      H = std::move(F);
+      return true;
+    }
+    return ok;
+  };
+  if (!plan(4, kcap32, kcap32, H32)) return DPVBA_EINVAL;
+  if (!plan(8, kcap64, tune && tune->tile_patches_fp64 > 0 ? kcap64 : kFullTilePatches64, H64)) return DPVBA_EINVAL;
   HIP_TRY(upload_tiling(c->tl[0], H32, st));
   HIP_TRY(upload_tiling(c->tl[1], H64, st));
   {
@@ -1257,18 +1280,18 @@ static SolveWs<T> ctx_ws(dpvba_ctx* c) {
   return w;
 }
 
-// Lays the buffers of a single-launch solve of the analysed problem (plan
-// tl, element type T) out from `base` at 256-byte boundaries; returns the
-// bytes needed.  With base == nullptr only the size is computed.
-template <typename T>
-static size_t carve_ws(const dpvba_ctx* c, const Tiling& tl, unsigned char* base, SolveWs<T>* w) {
+// Lays the buffers of a single-launch solve (element type T, plan sizes of tl)
+// out from `base` at 256-byte boundaries; returns the bytes needed.  With base
+// == nullptr only the size is computed.
+template <typename T, typename Plan>
+static size_t carve_ws(size_t N, size_t P, size_t E, size_t n, const Plan& tl, size_t n_tiles, unsigned char* base,
+                       SolveWs<T>* w) {
   size_t off = 0;
   auto take = [&](size_t bytes) {
     unsigned char* q = base ? base + off : nullptr;
     off += (std::max<size_t>(bytes, 16) + 255) & ~(size_t)255;
     return (void*)q;
   };
-  const size_t n = 6 * (size_t)c->n_free, P = (size_t)c->P, N = (size_t)c->N;
   const size_t ts = sizeof(T);
   SolveWs<T> v;
   v.part_S = (T*)take((size_t)tl.part_S * ts);
@@ -1283,14 +1306,26 @@ static size_t carve_ws(const dpvba_ctx* c, const Tiling& tl, unsigned char* base
   v.rhs = (T*)take(n * ts);
   v.d0 = (T*)take(n * ts);
   v.dx = (T*)take(n * ts);
-  v.part_cost = (double*)take((size_t)tl.n_tiles * 8);
-  v.edge_part = (double*)take(((size_t)c->E + 255) / 256 * 8);
-  v.part_invalid = (int*)take((size_t)tl.n_tiles * 4);
+  v.part_cost = (double*)take(n_tiles * 8);
+  v.edge_part = (double*)take((E + 255) / 256 * 8);
+  v.part_invalid = (int*)take(n_tiles * 4);
   v.status = (int*)take(DPVBA_MAX_ITERS * 4);
   v.min_bits = (unsigned int*)take(DPVBA_MAX_ITERS * 4);
   v.devrep = (dpvba_report*)take(sizeof(dpvba_report));
   if (w) *w = v;
   return off;
+}
+
+// The same for the analysed problem.
+template <typename T>
+static size_t carve_ws(const dpvba_ctx* c, const Tiling& tl, unsigned char* base, SolveWs<T>* w) {
+  return carve_ws<T>((size_t)c->N, (size_t)c->P, (size_t)c->E, 6 * (size_t)c->n_free, tl, (size_t)tl.n_tiles, base, w);
+}
+
+static size_t solve_ws_bytes(int N, int P, int E, int n_free, const HostTiling& H, int tsize) {
+  const size_t n = 6 * (size_t)n_free, nt = H.tiles.size();
+  return tsize == 8 ? carve_ws<double>((size_t)N, (size_t)P, (size_t)E, n, H, nt, nullptr, nullptr)
+                    : carve_ws<float>((size_t)N, (size_t)P, (size_t)E, n, H, nt, nullptr, nullptr);
 }
 
 template <typename T>
