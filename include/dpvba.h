@@ -449,8 +449,8 @@ dpvba_status dpvba_solve_backward(dpvba_ctx* ctx, const dpvba_graph* g, const fl
  * completed).  The problems run concurrently: small problems of a
  * dpvba_solve_many without reports or of dpvba_solve_backward_many
  * (6 x free poses + 1 <= 96 for all of them, DPVBA_FP32 or DPVBA_FP64) several
- * to a launch (dpvba_solve_many: on `stream`, cooperative when
- * the contexts are set so); all others each on a stream of its own context,
+ * to a launch (dpvba_solve_many: on `stream`), in launches whose workgroups do
+ * not wait for each other; all others each on a stream of its own context,
  * ordered after the work already on `stream`, and `stream` waits for all of
  * them.  There, launches whose workgroups wait for each other are cooperative
  * (dpvba_set_cooperative(1) for the duration of the call), so concurrent

@@ -34,9 +34,10 @@ hipError_t launch_retract_copy(const T* poses_cur, T* poses_next, T* dx, int n_f
                                const int* status, hipStream_t st, const T* dx_sys = nullptr,
                                const int* row0 = nullptr);
 template <typename T>
-int small_solve_grid(int lds_bytes, bool group);
+int small_solve_grid(int lds_bytes);
 template <typename T>
-hipError_t launch_small_solve_group(const SmallGroup<T>& G, int lds_bytes, bool cooperative, hipStream_t st);
+hipError_t launch_small_group(const SmallGroup<T>& G, int n, int max_tiles, int max_free, int n_iters, int lds_tile,
+                              int lds_step, int lds_finish, hipStream_t st);
 template <typename T>
 hipError_t launch_small_solve(const SmallArgs<T>& S, int grid, int lds_bytes, bool cooperative, hipStream_t st);
 int small_solve_max_n(int tsize);
@@ -1531,7 +1532,7 @@ static hipError_t solve_impl(dpvba_ctx* c, const dpvba_graph* g, T* poses, T* de
     int& cap = sizeof(T) == 8 ? c->coop_grid64 : c->coop_grid32;
     int& cap_lds = sizeof(T) == 8 ? c->coop_lds64 : c->coop_lds32;
     if (cap_lds != lds_small) {
-      cap = small_solve_grid<T>(lds_small, false);
+      cap = small_solve_grid<T>(lds_small);
       cap_lds = lds_small;
     }
     const int grid = std::min(tl.n_tiles, cap);
@@ -2410,8 +2411,8 @@ static dpvba_status fan_out(int32_t n, dpvba_ctx* const* ctxs, hipStream_t st, F
   return first;
 }
 
-// Whether every problem of a call is a small one (single-launch solver) with
-// valid arguments, so that they can share launches.  Anything else -- an
+// Whether every problem of a call is a small one (of the single-launch solver's
+// size) with valid arguments, so that they can share launches.  Anything else -- an
 // invalid problem among them, a traced context (its phases are timed one by
 // one) -- takes the general way, problem by problem.
 template <typename T>
@@ -2420,7 +2421,7 @@ static bool can_group(int32_t n, dpvba_ctx* const* ctxs, const dpvba_graph* grap
   if (n < 2 || !ctxs || check_opts(o) != DPVBA_OK || o->n_iters < 1) return false;
   for (int i = 0; i < n; ++i) {
     dpvba_ctx* c = ctxs[i];
-    if (!c || c->device != ctxs[0]->device || c->coop_launch != ctxs[0]->coop_launch || c->tracing) return false;
+    if (!c || c->device != ctxs[0]->device || c->tracing) return false;
     for (int j = 0; j < i; ++j)
       if (ctxs[j] == c) return false;
     if (!graph_sizes_ok(&graphs[i]) || check_analysed(c, &graphs[i]) != DPVBA_OK) return false;
@@ -2440,30 +2441,35 @@ static std::vector<int> by_size(int32_t n, dpvba_ctx* const* ctxs, int ti) {
   return order;
 }
 
-// Small problems in launches of up to kSmallGroup, each launch's workgroups
-// within what the device holds at once.
+// Small problems in groups of up to kSmallGroup, a group's launches on `st`
+// (launch_small_group).
 template <typename T>
 static hipError_t solve_groups(int32_t n, dpvba_ctx* const* ctxs, const dpvba_graph* graphs, float* const* poses,
                                float* const* inv_depth, const dpvba_opts* o, hipStream_t st) {
   const int ti = sizeof(T) == 8 ? 1 : 0;
-  int lds = 0;
-  for (int i = 0; i < n; ++i) lds = std::max(lds, small_lds<T>(ctxs[i]));
-  const int cap = small_solve_grid<T>(lds, true);
-  if (cap < 1) return hipErrorCooperativeLaunchTooLarge;
   const std::vector<int> order = by_size(n, ctxs, ti);
-  for (int i = 0; i < n;) {
+  const int n_group = (n + kSmallGroup - 1) / kSmallGroup;
+  for (int q = 0; q < n_group; ++q) {
+    const int lo = (int)((long long)n * q / n_group), hi = (int)((long long)n * (q + 1) / n_group);
     SmallGroup<T> G{};
-    for (; i < n && G.n < kSmallGroup; ++i) {
-      const int k = order[i], grid = std::min(ctxs[k]->tl[ti].n_tiles, cap);
-      if (G.n > 0 && G.first[G.n] + grid > cap) break;
-      G.p[G.n] = small_args<T>(ctxs[k], &graphs[k], ctx_ws<T>(ctxs[k]), (T*)(void*)poses[k],
-                               (T*)(void*)inv_depth[k], o);
-      G.first[G.n + 1] = G.first[G.n] + grid;
-      ++G.n;
+    int tiles = 0, free_ = 0, lds_tile = 0, lds_step = 0, lds_finish = 0;
+    for (int i = lo; i < hi; ++i) {
+      const int k = order[i];
+      dpvba_ctx* c = ctxs[k];
+      const Tiling& tl = c->tl[ti];
+      SmallArgs<T>& S = G.p[i - lo];
+      S = small_args<T>(c, &graphs[k], ctx_ws<T>(c), (T*)(void*)poses[k], (T*)(void*)inv_depth[k], o);
+      S.cost = nullptr;  // no reports here
+      S.invalid = nullptr;
+      tiles = std::max(tiles, tl.n_tiles);
+      free_ = std::max(free_, c->n_free);
+      lds_tile = std::max(lds_tile, tl.lds_bytes);
+      lds_step = std::max(lds_step, small_solve_lds_bytes(6 * c->n_free, (int)sizeof(T)));
+      lds_finish = std::max(lds_finish, writeback_lds_bytes(tl, (int)sizeof(T)));
     }
-    const hipError_t e = launch_small_solve_group<T>(G, lds, ctxs[0]->coop_launch, st);
+    const hipError_t e =
+        launch_small_group<T>(G, hi - lo, tiles, free_, o->n_iters, lds_tile, lds_step, lds_finish, st);
     if (e != hipSuccess) return e;
-    for (int q = i - G.n; q < i; ++q) ++ctxs[order[q]]->small_launches;
   }
   return hipSuccess;
 }

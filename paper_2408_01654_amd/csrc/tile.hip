@@ -854,14 +854,32 @@ __device__ void tile_writeback(const TileInfo& ti, const int* tile_patch, const 
   __syncthreads();
 }
 
+// The fields of iteration t of a small problem (poses ping-pong between two
+// buffers).
+template <typename T>
+__device__ __forceinline__ void small_iter(IterArgs<T>& A, const SmallArgs<T>& S, int t) {
+  A.first = t == 0;
+  A.poses_cur = t == 0 ? S.poses_io : ((t - 1) & 1 ? S.pbuf1 : S.pbuf0);
+  A.poses_next = (t & 1) ? S.pbuf1 : S.pbuf0;
+  A.depth_in = S.depth_io;
+  A.dx_prev = t ? A.dx : nullptr;
+  A.status_prev = t ? S.status + t - 1 : nullptr;
+  A.status = S.status + t;
+  A.min_bits = S.min_bits + t;
+  A.cost_out = S.cost ? S.cost + t : nullptr;
+  A.invalid_out = S.invalid ? S.invalid + t : nullptr;
+}
+
 // Whole solve of a small problem in one launch: per iteration
 // every workgroup assembles its tiles, all wavefronts gather the damped
 // reduced system, workgroup 0 factors, solves and retracts; finally the
-// depths are written back.  Poses ping-pong between two buffers.
-// (block, nb: this workgroup among the problem's.)
+// depths are written back.
 template <typename T>
-__device__ __forceinline__ void small_solve(const SmallArgs<T>& S, const unsigned int block, const unsigned int nb,
-                                            unsigned char* lds) {
+__global__ void __launch_bounds__(kTileThreads)
+__attribute__((amdgpu_waves_per_eu(kTileThreads / 256, kTileThreads / 256)))
+small_solve_kernel(SmallArgs<T> S) {
+  extern __shared__ __align__(16) unsigned char lds[];
+  const unsigned int block = blockIdx.x, nb = gridDim.x;
   IterArgs<T> A = S.it;
   const int w = block * blockDim.x + threadIdx.x, nw = nb * blockDim.x;
   const int wave = w >> 6, nwaves = nw >> 6;
@@ -869,16 +887,7 @@ __device__ __forceinline__ void small_solve(const SmallArgs<T>& S, const unsigne
   if (block == 0 && threadIdx.x < 2) S.bar_next[threadIdx.x] = 0u;
   if (block == 0 && threadIdx.x == 2) *S.err_next = 0;
   for (int t = 0; t < S.n_iters; ++t) {
-    A.first = t == 0;
-    A.poses_cur = t == 0 ? S.poses_io : ((t - 1) & 1 ? S.pbuf1 : S.pbuf0);
-    A.poses_next = (t & 1) ? S.pbuf1 : S.pbuf0;
-    A.depth_in = S.depth_io;
-    A.dx_prev = t ? A.dx : nullptr;
-    A.status_prev = t ? S.status + t - 1 : nullptr;
-    A.status = S.status + t;
-    A.min_bits = S.min_bits + t;
-    A.cost_out = S.cost ? S.cost + t : nullptr;
-    A.invalid_out = S.invalid ? S.invalid + t : nullptr;
+    small_iter<T>(A, S, t);
     for (int tile = block; tile < A.n_tiles; tile += nb) {
       tile_assemble<T, kTileThreads>(A, tile, lds);
       __syncthreads();
@@ -899,26 +908,51 @@ __device__ __forceinline__ void small_solve(const SmallArgs<T>& S, const unsigne
   for (int x = w; x < 7 * A.n_frames; x += nw) S.poses_io[x] = fin[x];
 }
 
+// Several small problems side by side (blockIdx.y): one problem's tiles fill a
+// tenth of the chip, and its gather and factor less.  The phases of an
+// iteration are launches of their own, so that no workgroup waits for another
+// and any number of such calls can share the device: the single launch of a
+// problem meets at grid barriers, and two of many problems each could hold half
+// of the device and wait for the other half.  Sixteen float64 windows of 12 to
+// 22 frames: 332 us in two groups of seven launches, 1,950 us one after
+// another.
 template <typename T>
-__global__ void __launch_bounds__(kTileThreads)
-__attribute__((amdgpu_waves_per_eu(kTileThreads / 256, kTileThreads / 256)))
-small_solve_kernel(SmallArgs<T> S) {
+__global__ void __launch_bounds__(kTileThreads) group_tile_kernel(SmallGroup<T> G, int t) {
   extern __shared__ __align__(16) unsigned char lds[];
-  small_solve<T>(S, blockIdx.x, gridDim.x, lds);
+  const SmallArgs<T>& S = G.p[blockIdx.y];
+  if ((int)blockIdx.x >= S.it.n_tiles) return;
+  IterArgs<T> A = S.it;
+  small_iter<T>(A, S, t);
+  tile_assemble<T, kTileThreads>(A, A.order[blockIdx.x], lds);
 }
 
-// Several problems side by side: one problem's tiles fill a tenth of the
-// chip, and its gather and factor less, so a group takes little longer than
-// its largest problem (sixteen float64 windows of 12 to 22 frames: 3.04 ms one
-// after another, 0.61 ms in four groups).
 template <typename T>
-__global__ void __launch_bounds__(kTileThreads)
-__attribute__((amdgpu_waves_per_eu(kTileThreads / 256, kTileThreads / 256)))
-small_solve_group_kernel(SmallGroup<T> G) {
+__global__ void __launch_bounds__(256) group_gather_kernel(SmallGroup<T> G) {
+  const SmallArgs<T>& S = G.p[blockIdx.y];
+  gather_slice<T>(S.it, S.Sp, S.rhs, S.d0, (int)(blockIdx.x * 4 + (threadIdx.x >> 6)), (int)gridDim.x * 4);
+}
+
+template <typename T>
+__global__ void __launch_bounds__(kTileThreads) group_step_kernel(SmallGroup<T> G, int t) {
   extern __shared__ __align__(16) unsigned char lds[];
-  int i = 0;
-  while (i + 1 < G.n && (int)blockIdx.x >= G.first[i + 1]) ++i;
-  small_solve<T>(G.p[i], blockIdx.x - G.first[i], G.first[i + 1] - G.first[i], lds);
+  const SmallArgs<T>& S = G.p[blockIdx.y];
+  IterArgs<T> A = S.it;
+  small_iter<T>(A, S, t);
+  factor_solve_retract<T>(A, S.Sp, S.rhs, S.d0, lds);
+}
+
+template <typename T>
+__global__ void __launch_bounds__(kFinalizeThreads) group_finish_kernel(SmallGroup<T> G) {
+  extern __shared__ __align__(16) unsigned char lds[];
+  const SmallArgs<T>& S = G.p[blockIdx.y];
+  const IterArgs<T>& A = S.it;
+  if ((int)blockIdx.x >= A.n_tiles) return;
+  tile_writeback<T>(A.tiles[blockIdx.x], A.tile_patch, A.blk_pose, A.U_s, A.pscale_s, A.depth_s, A.dx,
+                    !S.status[S.n_iters - 1], S.depth_io, reinterpret_cast<T*>(lds));
+  if (blockIdx.x == 0) {
+    const T* fin = ((S.n_iters - 1) & 1) ? S.pbuf1 : S.pbuf0;
+    for (int x = threadIdx.x; x < 7 * A.n_frames; x += blockDim.x) S.poses_io[x] = fin[x];
+  }
 }
 
 // ---------------------------------------------------------------- adjoint
@@ -1102,35 +1136,16 @@ hipError_t launch_retract_copy(const T* poses_cur, T* poses_next, T* dx, int n_f
   return hipGetLastError();
 }
 
-template <typename K>
-static int resident_workgroups(K kernel, int threads, int lds_bytes) {
+template <typename T>
+int small_solve_grid(int lds_bytes) {
   int dev = 0, cus = 0, per_cu = 0;
   if (hipGetDevice(&dev) != hipSuccess) return 0;
   if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return 0;
-  if (opt_in_lds((const void*)kernel, lds_bytes) != hipSuccess) return 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void*)kernel, threads, lds_bytes) != hipSuccess)
+  if (opt_in_lds((const void*)small_solve_kernel<T>, lds_bytes) != hipSuccess) return 0;
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void*)small_solve_kernel<T>, kTileThreads,
+                                                   lds_bytes) != hipSuccess)
     return 0;
   return cus * per_cu;
-}
-
-template <typename K, typename Args>
-static hipError_t launch_resident(K kernel, const Args& a, int grid, int threads, int lds_bytes, bool cooperative,
-                                  hipStream_t st) {
-  hipError_t e = opt_in_lds((const void*)kernel, lds_bytes);
-  if (e != hipSuccess) return e;
-  Args copy = a;
-  if (!cooperative) {
-    hipLaunchKernelGGL(kernel, dim3(grid), dim3(threads), lds_bytes, st, copy);
-    return hipGetLastError();
-  }
-  void* args[] = {&copy};
-  return hipLaunchCooperativeKernel((const void*)kernel, dim3(grid), dim3(threads), args, lds_bytes, st);
-}
-
-template <typename T>
-int small_solve_grid(int lds_bytes, bool group) {
-  return group ? resident_workgroups(small_solve_group_kernel<T>, kTileThreads, lds_bytes)
-               : resident_workgroups(small_solve_kernel<T>, kTileThreads, lds_bytes);
 }
 
 // grid never exceeds small_solve_grid (the workgroups the device holds at
@@ -1141,14 +1156,35 @@ int small_solve_grid(int lds_bytes, bool group) {
 // runtime guarantee co-residency, at a higher launch cost.
 template <typename T>
 hipError_t launch_small_solve(const SmallArgs<T>& S, int grid, int lds_bytes, bool cooperative, hipStream_t st) {
-  return launch_resident(small_solve_kernel<T>, S, grid, kTileThreads, lds_bytes, cooperative, st);
+  hipError_t e = opt_in_lds((const void*)small_solve_kernel<T>, lds_bytes);
+  if (e != hipSuccess) return e;
+  SmallArgs<T> copy = S;
+  if (!cooperative) {
+    hipLaunchKernelGGL((small_solve_kernel<T>), dim3(grid), dim3(kTileThreads), lds_bytes, st, copy);
+    return hipGetLastError();
+  }
+  void* args[] = {&copy};
+  return hipLaunchCooperativeKernel((const void*)small_solve_kernel<T>, dim3(grid), dim3(kTileThreads), args,
+                                    lds_bytes, st);
 }
 
-// The problems' workgroups together: the same bound, first[n] workgroups.
+// All iterations of the n problems of G: the sizes are their largest (tiles,
+// free poses, shared memory of a tile, of the step and of the write-back).
 template <typename T>
-hipError_t launch_small_solve_group(const SmallGroup<T>& G, int lds_bytes, bool cooperative, hipStream_t st) {
-  return launch_resident(small_solve_group_kernel<T>, G, G.first[G.n], kTileThreads, lds_bytes, cooperative,
-                         st);
+hipError_t launch_small_group(const SmallGroup<T>& G, int n, int max_tiles, int max_free, int n_iters, int lds_tile,
+                              int lds_step, int lds_finish, hipStream_t st) {
+  hipError_t e = opt_in_lds((const void*)group_tile_kernel<T>, lds_tile);
+  if (e == hipSuccess) e = opt_in_lds((const void*)group_step_kernel<T>, lds_step);
+  if (e == hipSuccess) e = opt_in_lds((const void*)group_finish_kernel<T>, lds_finish);
+  if (e != hipSuccess) return e;
+  const int nlb = max_free * (max_free + 1) / 2;
+  for (int t = 0; t < n_iters; ++t) {
+    hipLaunchKernelGGL((group_tile_kernel<T>), dim3(max_tiles, n), dim3(kTileThreads), lds_tile, st, G, t);
+    hipLaunchKernelGGL((group_gather_kernel<T>), dim3((nlb + 3) / 4, n), dim3(256), 0, st, G);
+    hipLaunchKernelGGL((group_step_kernel<T>), dim3(1, n), dim3(kTileThreads), lds_step, st, G, t);
+  }
+  hipLaunchKernelGGL((group_finish_kernel<T>), dim3(max_tiles, n), dim3(kFinalizeThreads), lds_finish, st, G);
+  return hipGetLastError();
 }
 
 template <typename T>
@@ -1190,8 +1226,8 @@ hipError_t launch_adj_system(const AdjGroup<T>& G, int n, int lds_bytes, int it,
   template hipError_t launch_adj_tile<T>(const AdjGroup<T>&, int, int, int, int, bool, hipStream_t);       \
   template hipError_t launch_adj_gather<T>(const AdjGroup<T>&, int, int, hipStream_t);                     \
   template hipError_t launch_adj_system<T>(const AdjGroup<T>&, int, int, int, bool, hipStream_t);          \
-  template int small_solve_grid<T>(int, bool);                                                            \
-  template hipError_t launch_small_solve_group<T>(const SmallGroup<T>&, int, bool, hipStream_t);          \
+  template int small_solve_grid<T>(int);                                                                  \
+  template hipError_t launch_small_group<T>(const SmallGroup<T>&, int, int, int, int, int, int, int, hipStream_t); \
   template hipError_t launch_small_solve<T>(const SmallArgs<T>&, int, int, bool, hipStream_t);
 
 DPVBA_TILE_INSTANTIATE(float)

@@ -76,17 +76,15 @@ struct SmallArgs {
   int* err_next;           // the next launch's failure word, cleared by this one
 };
 
-// Several small problems in one launch: problem i takes workgroups
-// first[i] .. first[i + 1] - 1.  Passed by value, so it has to fit the 4 KB of
-// a kernel's arguments.
+// Several small problems side by side: every launch takes up to kSmallGroup,
+// blockIdx.y.  Passed by value, so it has to fit the 4 KB of a kernel's
+// arguments.
 constexpr int kSmallGroup = 8;
 template <typename T>
 struct SmallGroup {
-  int n;
-  int first[kSmallGroup + 1];
   SmallArgs<T> p[kSmallGroup];
 };
-static_assert(sizeof(SmallGroup<double>) <= 4096, "kernel arguments");
+static_assert(sizeof(SmallGroup<double>) + 64 <= 4096, "kernel arguments");
 
 // One problem of an adjoint launch: every launch of the adjoint takes up to
 // kAdjGroup problems, blockIdx.y (by value, within the 4 KB of a kernel's
