@@ -53,35 +53,3 @@ int main() {
     rows = [tuple(map(int, line.split())) for line in r.stdout.splitlines()]
     assert {k: row[0] for k, row in zip(keys, rows)} == LIMITS
     assert all(row[1:] == (0, 0) for row in rows)
-
-
-def test_group_rounds_keep_a_launch_within_its_share(tmp_path):
-    """Problems that share a launch: the fewest rounds whose workgroups fit."""
-    cxx = shutil.which("g++") or shutil.which("c++")
-    if cxx is None:
-        pytest.skip("no host compiler")
-    src = tmp_path / "rounds.cpp"
-    src.write_text("""
-#define __host__
-#define __device__
-#include <cstdio>
-#include "layout.h"
-int main() {
-  int n, limit;
-  while (scanf("%d %d", &n, &limit) == 2) {
-    int t[8];
-    for (int i = 0; i < n; ++i)
-      if (scanf("%d", t + i) != 1) return 1;
-    printf("%d\\n", dpvba::group_rounds(t, n, limit));
-  }
-}
-""".replace("\\\\n", "\\n"))
-    exe = str(tmp_path / "rounds")
-    subprocess.run([cxx, "-std=c++17", "-I", CSRC, str(src), "-o", exe], check=True)
-    cases = [([1], 8), ([8] * 8, 8), ([9] + [1] * 7, 8), ([128], 128), ([129], 128), ([44] * 8, 128), ([16] * 8, 128),
-             ([17] * 8, 128), ([44, 40, 30, 22, 16, 12, 9, 1], 128), ([5000, 3], 8)]
-    r = subprocess.run([exe], input="\n".join(f"{len(t)} {m} " + " ".join(map(str, t)) for t, m in cases),
-                       capture_output=True, text=True, check=True)
-    fits = lambda t, m, k: sum(-(-x // k) for x in t) <= m
-    for (t, m), k in zip(cases, map(int, r.stdout.split())):
-        assert fits(t, m, k) and (k == 1 or not fits(t, m, k - 1)), (t, m, k)
