@@ -267,6 +267,7 @@ class Context:
         self._h = ctypes.c_void_p(0)
         _check(lib().dpvba_create(ctypes.byref(self._h), int(device)), "dpvba_create")
         self.device = device
+        self.tracing = False
         self._graph = None
 
     def close(self):
@@ -300,7 +301,7 @@ class Context:
         return {f: getattr(info, f) for f, _ in AnalysisInfo._fields_}
 
     def system_order(self) -> np.ndarray:
-        """dpvba_get_system_order: free pose at each block row of the factor."""
+        """dpvba_get_system_order: free pose at each place of the banded order."""
         n = int(self.analysis_info()["n_free"])
         out = np.zeros(max(n, 1), dtype=np.int32)
         _check(lib().dpvba_get_system_order(self._h, out.ctypes.data_as(ctypes.c_void_p), n),
@@ -490,10 +491,12 @@ class Context:
 
     def trace_begin(self, sample_every: int = 1, max_pairs: int = 1 << 16):
         _check(lib().dpvba_trace_begin(self._h, int(sample_every), int(max_pairs)), "dpvba_trace_begin", self._h)
+        self.tracing = True
 
     def trace_end(self):
         """Per phase: (summed ms of sampled launches, sampled count, launches seen)."""
         n = len(PHASES)
+        self.tracing = False
         ms = (ctypes.c_double * n)()
         ns = (ctypes.c_int32 * n)()
         nl = (ctypes.c_int64 * n)()
@@ -592,10 +595,23 @@ def bundle_adjust(context: Context, graph: GraphTensors, poses0, inv_depth0, tar
     return _BundleAdjust.apply(target, weight, poses0, inv_depth0, context, graph, n_iters, lam, z_min, precision)
 
 
+def _share_launches(contexts, graphs, n_iters, precision):
+    """Places of the problems whose forwards share launches
+    (dpvba_solve_many): at least two small ones (6 free poses + 1 <= 96) with
+    something to solve, on distinct contexts of one device that are not
+    traced (a traced context's phases are timed one by one)."""
+    if precision == MIXED or n_iters < 1 or len({id(c) for c in contexts}) < len(contexts) \
+            or len({c.device for c in contexts}) > 1:
+        return []
+    small = [i for i, (c, g) in enumerate(zip(contexts, graphs))
+             if 0 < 6 * (g.n_frames - g.n_fixed) <= 95 and g.ii.shape[0] > 0 and not c.tracing]
+    return small if len(small) > 1 else []
+
+
 class _BundleAdjustMany(torch.autograd.Function):
     """bundle_adjust over several problems: the forwards of small problems
-    (6 free poses + 1 <= 96) share launches (dpvba_solve_many), others run one
-    after another on the current stream; the adjoints run concurrently
+    share launches (_share_launches), others run one after another on the
+    current stream; the adjoints run concurrently
     (dpvba_solve_backward_many).  Inputs: the per-problem targets and
     weights, then the starting points; outputs: poses and inverse depths of
     every problem."""
@@ -612,11 +628,12 @@ class _BundleAdjustMany(torch.autograd.Function):
         p0 = [p.detach().to(dt).contiguous() for p in p0]
         d0 = [d.detach().to(dt).contiguous() for d in d0]
         poses, ds = [p.clone() for p in p0], [d.clone() for d in d0]
-        if (precision != MIXED and len({id(c) for c in contexts}) == n > 1
-                and all(6 * (g.n_frames - g.n_fixed) + 1 <= 96 for g in gs)):
-            solve_many(contexts, gs, poses, ds, n_iters, lam, z_min, precision)
-        else:
-            for c, g, p, d in zip(contexts, gs, poses, ds):
+        shared = _share_launches(contexts, gs, n_iters, precision)
+        if shared:
+            pick = lambda xs: [xs[i] for i in shared]
+            solve_many(pick(contexts), pick(gs), pick(poses), pick(ds), n_iters, lam, z_min, precision)
+        for i, (c, g, p, d) in enumerate(zip(contexts, gs, poses, ds)):
+            if i not in shared:
                 c.solve(g, p, d, n_iters, lam, z_min, precision, report=False)
         ctx.save_for_backward(*p0, *d0)
         ctx.set_materialize_grads(False)  # an unused output is a null adjoint, not a filled one
