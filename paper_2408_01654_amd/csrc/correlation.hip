@@ -104,14 +104,23 @@ __global__ void __launch_bounds__(256) patch_corr_kernel(int n_items, int p2, co
 // float32.  Lane l holds row l % 16 of the patch features and pixel l % 16 of
 // the union at channels 16 s + 4 (l / 16) + c: both operands take the same
 // order of the channels, so they arrive as 16-byte loads straight into the
-// operand registers (two wavefronts per SIMD at least: the products then
-// stay in ordinary registers, without a move out of the accumulators).  The dots [9][union] go to LDS, and the 441 outputs of the edge
+// operand registers (two wavefronts per SIMD at least, four at up to 128
+// channels: the products then stay in ordinary registers, without a move out of
+// the accumulators).  The dots [9][union] go to LDS, and the 441 outputs of the edge
 // are combined from them and written contiguously.  Patches whose union
-// holds more than kCorrUnion pixels take their nine windows one by one.
+// holds more than kCorrUnion pixels (scattered: seen at more than four times
+// their size) take their nine windows one by one, and where there are few edges
+// each has a workgroup of its own, whose four wavefronts share those windows.
 // Against one wavefront per (edge, pixel) this reads 100 to 144 map pixels an
 // edge instead of 576 and needs no reduction over lanes: 37,440 edges of 128
 // channels took 1,564 us and take 229 us (the products alone 109 us at the float32
 // matrix rate), 2.0 GB of map pixels read from the caches instead of 11 GB.
+
+// Edges up to which each has a workgroup of its own: they all run at once either
+// way (128 channels, points 6 pixels apart: 64 edges 44.0 -> 10.1 us, 512 edges
+// 46.9 -> 20.8 us; compact patches the same or 5 % faster).  At 768 edges of 256
+// channels compact patches take 25 us so, 21 us four to a workgroup.
+constexpr int kCorrSpread = 512;
 constexpr int kCorrUnion = 256;            // pixels of a union window
 constexpr int kCorrLd = kCorrUnion + 4;    // row stride of the dots (the four row groups of a store on different banks)
 
@@ -127,8 +136,25 @@ __device__ __forceinline__ floatx4_t corr_tree(const float4* g, const float4* f)
   }
 }
 
+// Sum of the products of N groups of 4 channels, as a binary tree.
+template <int N>
+__device__ __forceinline__ float dot_tree(const float4* g, const float4* f) {
+  if constexpr (N == 1) return (g->x * f->x + g->y * f->y) + (g->z * f->z + g->w * f->w);
+  else return dot_tree<N / 2>(g, f) + dot_tree<N - N / 2>(g + N / 2, f + N / 2);
+}
+
+// Sum over the 16 lanes of a row, on every lane of it (rotations within the row).
+__device__ __forceinline__ float row_sum(float v) {
+  v += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x128, 0xF, 0xF, true));
+  v += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x124, 0xF, 0xF, true));
+  v += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x122, 0xF, 0xF, true));
+  v += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x121, 0xF, 0xF, true));
+  return v;
+}
+
 template <int VPL>  // channels per lane quarter of 16 (D = 64 VPL)
-__global__ void __launch_bounds__(256, 2) patch_corr3_kernel(int n_edges, const float* __restrict__ gmap, int n_patches,
+__global__ void __launch_bounds__(256, VPL <= 2 ? 4 : 2) patch_corr3_kernel(int n_edges, int per_group,
+                                                          const float* __restrict__ gmap, int n_patches,
                                                           const float* __restrict__ fmaps, int n_maps, int H, int W,
                                                           const int* __restrict__ kk, const int* __restrict__ jj,
                                                           const float* __restrict__ coords, float* __restrict__ corr,
@@ -137,11 +163,13 @@ __global__ void __launch_bounds__(256, 2) patch_corr3_kernel(int n_edges, const 
   __shared__ float dots_s[4][P2 * kCorrLd];
   __shared__ float4 pix_s[4][P2];  // window origin (x, y) as integers, fractional position
   const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int e = blockIdx.x * 4 + wv;
+  const int e = per_group == 4 ? (int)blockIdx.x * 4 + wv : (int)blockIdx.x;
+  const int g0 = per_group == 4 ? 0 : wv, dg = per_group == 4 ? 1 : 4;  // this wavefront's windows of a scattered patch
   if (e >= n_edges) return;  // whole wavefront; no workgroup barrier below
   const int k = kk[e], fj = jj[e];
   float* out = corr + (size_t)e * (P2 * G2);
   if (k < 0 || k >= n_patches || fj < 0 || fj >= n_maps) {
+    if (g0 != 0) return;
     for (int o = lane; o < P2 * G2; o += 64) out[o] = 0.f;
     if (lane == 0) report_device_error(dev_err, host_err, kErrInput);
     return;
@@ -184,13 +212,31 @@ __global__ void __launch_bounds__(256, 2) patch_corr3_kernel(int n_edges, const 
   const float* fm = fmaps + (size_t)fj * H * W * D + 4 * q;
   // an empty union (every window outside) has no pixels, and dots stays unread
   const bool one = ux1 <= ux0 || (long long)(ux1 - ux0) * (uy1 - uy0) <= kCorrUnion;
-  const int n_group = one ? 1 : P2;
-  for (int gi = 0; gi < n_group; ++gi) {
-    // uniform over the wavefront
-    const int x0 = __builtin_amdgcn_readfirstlane(one ? ux0 : __shfl(xl, gi));
-    const int x1 = __builtin_amdgcn_readfirstlane(one ? ux1 : __shfl(xh, gi));
-    const int y0 = __builtin_amdgcn_readfirstlane(one ? uy0 : __shfl(yl, gi));
-    const int y1 = __builtin_amdgcn_readfirstlane(one ? uy1 : __shfl(yh, gi));
+  // outputs o0 .. o1 - 1 from the dots of the window (x0, y0), w pixels wide
+  auto combine = [&](int o0, int o1, int x0, int y0, int w) {
+    // the wavefront's own LDS writes, in order: only the compiler must not
+    // move the reads above them
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    for (int o = o0 + lane; o < o1; o += 64) {
+      const int px = o / G2, ab = o - px * G2, a = ab / kCorrGrid, b = ab - a * kCorrGrid;
+      const float4 pp = pixs[px];
+      const int xx = __float_as_int(pp.x) + a, yy = __float_as_int(pp.y) + b;
+      const bool in0 = xx >= 0 && xx < W, in1 = xx + 1 >= 0 && xx + 1 < W;
+      const bool jn0 = yy >= 0 && yy < H, jn1 = yy + 1 >= 0 && yy + 1 < H;
+      const float* d = dots + px * kCorrLd + (yy - y0) * w + (xx - x0);
+      const float d00 = in0 && jn0 ? d[0] : 0.f, d01 = in1 && jn0 ? d[1] : 0.f;
+      const float d10 = in0 && jn1 ? d[w] : 0.f, d11 = in1 && jn1 ? d[w + 1] : 0.f;
+      const float fx = pp.z, fy = pp.w;
+      out[o] = (1.f - fx) * (1.f - fy) * d00 + fx * (1.f - fy) * d01 + (1.f - fx) * fy * d10 + fx * fy * d11;
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+  };
+  if (one) {
+    if (g0 != 0) return;
+    const int x0 = __builtin_amdgcn_readfirstlane(ux0), x1 = __builtin_amdgcn_readfirstlane(ux1);
+    const int y0 = __builtin_amdgcn_readfirstlane(uy0), y1 = __builtin_amdgcn_readfirstlane(uy1);
     const int w = x1 - x0, n = x1 > x0 ? w * (y1 - y0) : 0;
     const float rw = 1.f / (float)max(w, 1);
     // pixel t of the union (row-major): t < 256, so the quotient is exact
@@ -214,6 +260,9 @@ __global__ void __launch_bounds__(256, 2) patch_corr3_kernel(int n_edges, const 
         // every product step starts from zero and the steps are summed as a
         // binary tree over the channels, like the sum over lanes that this
         // replaces (one chain of 32 steps had 1.7 times its error)
+        // (the loads all go out before the products; at up to 128 channels that
+        // keeps to the registers of four wavefronts a SIMD, 241 -> 232 us)
+        if constexpr (VPL <= 2) __builtin_amdgcn_sched_barrier(0);
         const floatx4_t acc = corr_tree<NS>(g, f);
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
@@ -224,25 +273,52 @@ __global__ void __launch_bounds__(256, 2) patch_corr3_kernel(int n_edges, const 
         for (int s = 0; s < NS; ++s) f[s] = nf[s];
       }
     }
-    // the wavefront's own LDS writes, in order: only the compiler must not
-    // move the reads above them
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    const int o0 = one ? 0 : gi * G2, o1 = one ? P2 * G2 : o0 + G2;
-    for (int o = o0 + lane; o < o1; o += 64) {
-      const int px = o / G2, ab = o - px * G2, a = ab / kCorrGrid, b = ab - a * kCorrGrid;
-      const float4 pp = pixs[px];
-      const int xx = __float_as_int(pp.x) + a, yy = __float_as_int(pp.y) + b;
-      const bool in0 = xx >= 0 && xx < W, in1 = xx + 1 >= 0 && xx + 1 < W;
-      const bool jn0 = yy >= 0 && yy < H, jn1 = yy + 1 >= 0 && yy + 1 < H;
-      const float* d = dots + px * kCorrLd + (yy - y0) * w + (xx - x0);
-      const float d00 = in0 && jn0 ? d[0] : 0.f, d01 = in1 && jn0 ? d[1] : 0.f;
-      const float d10 = in0 && jn1 ? d[w] : 0.f, d11 = in1 && jn1 ? d[w + 1] : 0.f;
-      const float fx = pp.z, fy = pp.w;
-      out[o] = (1.f - fx) * (1.f - fy) * d00 + fx * (1.f - fy) * d01 + (1.f - fx) * fy * d10 + fx * fy * d11;
+    combine(0, P2 * G2, x0, y0, w);
+    return;
+  }
+  const float* fw = fmaps + (size_t)fj * H * W * D;
+  for (int gi = g0; gi < P2; gi += dg) {
+    // uniform over the wavefront
+    const int x0 = __builtin_amdgcn_readfirstlane(__shfl(xl, gi)), x1 = __builtin_amdgcn_readfirstlane(__shfl(xh, gi));
+    const int y0 = __builtin_amdgcn_readfirstlane(__shfl(yl, gi)), y1 = __builtin_amdgcn_readfirstlane(__shfl(yh, gi));
+    const int w = x1 - x0, n = x1 > x0 ? w * (y1 - y0) : 0;
+    const float rw = 1.f / (float)max(w, 1);
+    // one row of products would leave 15 of 16 matrix rows idle: four pixels at
+    // a time on the vector units, 16 lanes a pixel, so that a load covers 256
+    // contiguous bytes of each; 16 pixels in flight.  Bound by those loads (128
+    // channels, points 6 pixels apart: 1,000 edges 49 -> 40 us, 12,000 edges 470 -> 474;
+    // one wavefront per point of every edge takes 57 and 584; at 256 channels 12,000
+    // edges take 924 us so and 820 by points, which read neighbouring windows together).
+    if (n > 0) {
+      float4 h[VPL], f[4][VPL];
+      const float4* hp = reinterpret_cast<const float4*>(gmap + ((size_t)k * P2 + gi) * D) + r;
+      auto load = [&](int t0, float4(*o)[VPL]) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          const int t = min(t0 + 4 * u + q, n - 1), y = (int)(((float)t + 0.5f) * rw), x = t - y * w;
+          const float4* fp = reinterpret_cast<const float4*>(fw + ((size_t)(y0 + y) * W + (x0 + x)) * D) + r;
+#pragma unroll
+          for (int j = 0; j < VPL; ++j) o[u][j] = fp[16 * j];
+        }
+      };
+#pragma unroll
+      for (int j = 0; j < VPL; ++j) h[j] = hp[16 * j];
+      load(0, f);
+      for (int t0 = 0; t0 < n; t0 += 16) {
+        float4 nf[4][VPL];
+        load(t0 + 16, nf);
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          const float d = row_sum(dot_tree<VPL>(h, f[u]));
+          if (r == 0) dots[gi * kCorrLd + t0 + 4 * u + q] = d;
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+#pragma unroll
+          for (int j = 0; j < VPL; ++j) f[u][j] = nf[u][j];
+      }
     }
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    __builtin_amdgcn_wave_barrier();
+    combine(gi * G2, (gi + 1) * G2, x0, y0, w);
   }
 }
 
@@ -257,13 +333,18 @@ hipError_t launch_patch_correlation(int n_edges, int p, int dim, const float* gm
   // the 16 rows empty (1 x 1) or need several row tiles, and keep one
   // wavefront per patch pixel.
   const bool aligned = (((uintptr_t)gmap | (uintptr_t)fmaps) & 15) == 0 && ((uintptr_t)coords & 7) == 0;
-  if (p == 3 && aligned) {
-    const int grid3 = (n_edges + 3) / 4;
+  // Nor do a few edges of 256 channels, which are over when one wavefront has
+  // loaded its first pixels (64 edges: 14.3 us by points, 17.5 by edges; 128
+  // edges: 23.0 and 17.6; 192 channels: 14.6 and 14.4 at 64 edges).
+  const int few = dim == 256 ? 96 : 0;
+  if (p == 3 && aligned && n_edges > few) {
+    const int per_group = n_edges <= kCorrSpread ? 1 : 4;
+    const int grid3 = (n_edges + per_group - 1) / per_group;
     switch (dim / 64) {
 #define DPVBA_CORR3_CASE(V)                                                                                        \
   case V:                                                                                                          \
-    hipLaunchKernelGGL(patch_corr3_kernel<V>, dim3(grid3), dim3(256), 0, st, n_edges, gmap, n_patches, fmaps,      \
-                       n_maps, H, W, kk, jj, coords, corr, dev_err, host_err);                                     \
+    hipLaunchKernelGGL(patch_corr3_kernel<V>, dim3(grid3), dim3(256), 0, st, n_edges, per_group, gmap, n_patches,  \
+                       fmaps, n_maps, H, W, kk, jj, coords, corr, dev_err, host_err);                                     \
     break;
       DPVBA_CORR3_CASE(1)
       DPVBA_CORR3_CASE(2)
