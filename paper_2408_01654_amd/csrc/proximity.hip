@@ -45,8 +45,10 @@ __device__ __forceinline__ float centre_d2(const float* a, const float* b) {
 // order, four distances in flight); each one's rank among them then says
 // whether it is kept, and the kept ones before it where it goes.  Bound by the
 // latency of that pass (1000 frames, ten targets: 5.2 us; a pass for
-// every target took 22.6 us).  More candidates than the list holds: max_t
-// rounds of a wavefront minimum over all of them.
+// every target took 22.6 us).  Where there are many more candidates than targets,
+// a wavefront minimum for each target takes the place of the ranks (300 frames,
+// one target: 69 -> 61 us a call).  More candidates than the list holds: max_t
+// rounds of a wavefront minimum over all of them, the first of which is that pass.
 constexpr int kLoopList = 256;
 
 __global__ void __launch_bounds__(256) loop_select_kernel(const float* poses, int n, int first_recent, int min_gap,
@@ -59,8 +61,9 @@ __global__ void __launch_bounds__(256) loop_select_kernel(const float* poses, in
   const float* ci = poses + 7 * (size_t)i;
   const int j0 = max(first_recent, i + min_gap + 1);
   int* out = targets + (size_t)i * max_t;
-  int m = 0;  // candidates so far
-  for (int jb = j0; jb < n && m <= kLoopList; jb += 256) {
+  int m = 0;  // candidates so far (beyond kLoopList: not counted)
+  unsigned long long best = ~0ull;  // the lane's nearest candidate
+  for (int jb = j0; jb < n; jb += 256) {
     float d2[4];
 #pragma unroll
     for (int u = 0; u < 4; ++u) d2[u] = centre_d2(ci, poses + 7 * (size_t)min(jb + 64 * u + lane, n - 1));
@@ -68,31 +71,45 @@ __global__ void __launch_bounds__(256) loop_select_kernel(const float* poses, in
     for (int u = 0; u < 4; ++u) {
       const int j = jb + 64 * u + lane;
       const bool in = j < n && d2[u] < r2;
+      const unsigned long long key = in ? ((unsigned long long)__float_as_uint(d2[u]) << 32) | (unsigned int)j : ~0ull;
+      best = key < best ? key : best;
+      if (m > kLoopList) continue;  // uniform
       const unsigned long long mask = __ballot(in);
       const int at = m + __popcll(mask & ((1ull << lane) - 1ull));
-      if (in && at < kLoopList) list[at] = ((unsigned long long)__float_as_uint(d2[u]) << 32) | (unsigned int)j;
+      if (in && at < kLoopList) list[at] = key;
       m += __popcll(mask);
     }
   }
   if (m <= kLoopList) {
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     __builtin_amdgcn_wave_barrier();
-    unsigned long long key[4];
-    int rank[4];
+    unsigned long long key[4], last = 0ull;  // no key is 0: j0 >= 1
+    bool kept[4];
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      key[u] = 64 * u + lane < m ? list[64 * u + lane] : ~0ull;
-      rank[u] = 0;
-    }
-    for (int s = 0; s < m; ++s) {
-      const unsigned long long ks = list[s];
+    for (int u = 0; u < 4; ++u) key[u] = 64 * u + lane < m ? list[64 * u + lane] : ~0ull;
+    if (m > 8 * max_t) {  // a step an entry costs an eighth of a wavefront minimum: find the last one kept
+      for (int t = 0; t < max_t; ++t) {
+        unsigned long long b = ~0ull;
 #pragma unroll
-      for (int u = 0; u < 4; ++u) rank[u] += ks < key[u] ? 1 : 0;
+        for (int u = 0; u < 4; ++u) b = key[u] > last && key[u] < b ? key[u] : b;
+        last = wave_min_u64(b);
+      }
+#pragma unroll
+      for (int u = 0; u < 4; ++u) kept[u] = key[u] <= last;
+    } else {
+      int rank[4] = {0, 0, 0, 0};
+      for (int s = 0; s < m; ++s) {
+        const unsigned long long ks = list[s];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) rank[u] += ks < key[u] ? 1 : 0;
+      }
+#pragma unroll
+      for (int u = 0; u < 4; ++u) kept[u] = rank[u] < max_t;
     }
     int cnt = 0;
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
-      const bool keep = 64 * u + lane < m && rank[u] < max_t;
+      const bool keep = 64 * u + lane < m && kept[u];
       const unsigned long long mask = __ballot(keep);
       if (keep) out[cnt + __popcll(mask & ((1ull << lane) - 1ull))] = (int)(key[u] & 0xffffffffu);
       cnt += __popcll(mask);
@@ -104,12 +121,14 @@ __global__ void __launch_bounds__(256) loop_select_kernel(const float* poses, in
   unsigned long long last = 0ull;  // keys above the previous pick (none is 0: j0 >= 1)
   int cnt = 0, mine = -1;          // lane t keeps the t-th pick's frame
   for (int t = 0; t < max_t; ++t) {
-    unsigned long long best = ~0ull;
-    for (int j = j0 + lane; j < n; j += 64) {
-      const float d2 = centre_d2(ci, poses + 7 * (size_t)j);
-      if (!(d2 < r2)) continue;
-      const unsigned long long key = ((unsigned long long)__float_as_uint(d2) << 32) | (unsigned int)j;
-      if (key > last && key < best) best = key;
+    if (t > 0) {
+      best = ~0ull;
+      for (int j = j0 + lane; j < n; j += 64) {
+        const float d2 = centre_d2(ci, poses + 7 * (size_t)j);
+        if (!(d2 < r2)) continue;
+        const unsigned long long key = ((unsigned long long)__float_as_uint(d2) << 32) | (unsigned int)j;
+        if (key > last && key < best) best = key;
+      }
     }
     best = wave_min_u64(best);
     if (best == ~0ull) break;  // uniform
