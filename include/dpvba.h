@@ -261,8 +261,8 @@ dpvba_status dpvba_reproject(dpvba_ctx* ctx, const dpvba_graph* g, const float* 
  * fixed lambda and no step rejection, right perturbations S <- S Exp(xi),
  * xi = (rho, phi, sigma), Exp(xi) = expm([[sigma I + [phi]x, rho], [0, 0]]).
  * The first n_fixed similarities are held (the objective is invariant to a
- * global similarity).  Float64 throughout; the dense 7 (N - n_fixed) system is
- * factored by the library's Cholesky.
+ * global similarity).  Float64 throughout; the 7 (N - n_fixed) system is factored
+ * by the library's block-sparse Cholesky.
  *   poses     [N, 7] float64 camera-to-world (t, q) (read).
  *   loop_j, loop_k  host [L] int32: loop frame pairs, j != k.
  *   loop_rel  [L, 8] float64 (t, q, s): DeltaS^loop_jk (read).
@@ -270,7 +270,7 @@ dpvba_status dpvba_reproject(dpvba_ctx* ctx, const dpvba_graph* g, const float* 
  *   cost      host [n_iters + 1] or NULL: sum |r|^2 before each iteration
  *             and at the end.
  * The call builds its block lists on the host, allocates its workspace in
- * the context (a dense (7 (N - n_fixed))^2 float64 system, N - n_fixed <=
+ * the context (the factor's float64 blocks, up to about 2 GB; N - n_fixed <=
  * 2857), and synchronises `stream` at the end.  Returns DPVBA_ENOTPD if an
  * iteration's system was not positive definite (its step was skipped).
  * EINVAL for bad sizes, indices or flags.                                  */

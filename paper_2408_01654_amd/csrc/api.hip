@@ -1051,7 +1051,7 @@ dpvba_status dpvba_analyze_ex(dpvba_ctx* c, const dpvba_graph* g, const dpvba_tu
   c->analysed = false;
   const int N = g->n_frames, P = g->n_patches, E = g->n_edges, nf = g->n_fixed;
   const int n_free = N - nf;
-  if ((long long)n_free * 6 > 46000) return DPVBA_EINVAL;  // dense reduced system must stay addressable
+  if ((long long)n_free * 6 > 46000) return DPVBA_EINVAL;  // 7,666 free poses: a full block storage of about 10 GB
   std::vector<int32_t> ii(E), jj(E), kk(E);
   if (E) {
     HIP_TRY(hipMemcpyAsync(ii.data(), g->ii, E * 4, hipMemcpyDeviceToHost, st));
@@ -2035,7 +2035,7 @@ dpvba_status dpvba_pgo_sim3(dpvba_ctx* c, int32_t n_frames, int32_t n_fixed, con
   if (flags & ~DPVBA_FLAG_LEVENBERG) return DPVBA_EINVAL;
   if (n_loops > 0 && (!loop_j || !loop_k || !loop_rel)) return DPVBA_EINVAL;
   const int nf = n_frames - n_fixed;
-  if ((long long)nf * 7 > 20000) return DPVBA_EINVAL;  // the dense system must stay a few GB
+  if ((long long)nf * 7 > 20000) return DPVBA_EINVAL;  // 2,857 free poses: a full block storage of about 2 GB
   for (int l = 0; l < n_loops; ++l)
     if (loop_j[l] < 0 || loop_j[l] >= n_frames || loop_k[l] < 0 || loop_k[l] >= n_frames || loop_j[l] == loop_k[l])
       return DPVBA_EINVAL;
@@ -2431,6 +2431,16 @@ static bool can_group(int32_t n, dpvba_ctx* const* ctxs, const dpvba_graph* grap
   return true;
 }
 
+// Runs f, whose lists are allocated on the host; no exception leaves it.
+template <typename F>
+static dpvba_status no_throw(F&& f) {
+  try {
+    return f();
+  } catch (const std::bad_alloc&) {
+    return DPVBA_ENOMEM;
+  }
+}
+
 // The problems' places, most tiles first: a launch lasts as long as its
 // largest problem.
 static std::vector<int> by_size(int32_t n, dpvba_ctx* const* ctxs, int ti) {
@@ -2517,9 +2527,11 @@ dpvba_status dpvba_solve_many(int32_t n, dpvba_ctx* const* ctxs, const dpvba_gra
                    (f32 && can_group<float>(n, ctxs, graphs, poses, inv_depth, opts)))) {
     dpvba_ctx* c = ctxs[0];
     HIP_TRY(hipSetDevice(c->device));
-    HIP_TRY(f64 ? solve_groups<double>(n, ctxs, graphs, poses, inv_depth, opts, (hipStream_t)stream)
-                : solve_groups<float>(n, ctxs, graphs, poses, inv_depth, opts, (hipStream_t)stream));
-    return DPVBA_OK;
+    return no_throw([&]() -> dpvba_status {
+      HIP_TRY(f64 ? solve_groups<double>(n, ctxs, graphs, poses, inv_depth, opts, (hipStream_t)stream)
+                  : solve_groups<float>(n, ctxs, graphs, poses, inv_depth, opts, (hipStream_t)stream));
+      return DPVBA_OK;
+    });
   }
   return fan_out(n, ctxs, (hipStream_t)stream, [&](int i, void* s) {
     return dpvba_solve(ctxs[i], &graphs[i], poses[i], inv_depth[i], opts, reports ? &reports[i] : nullptr, s);
@@ -2536,11 +2548,15 @@ dpvba_status dpvba_solve_backward_many(int32_t n, dpvba_ctx* const* ctxs, const 
   for (int i = 0; i < n; ++i) outputs = outputs && grad_target[i] && grad_weight[i];
   if (outputs && opts && opts->precision == DPVBA_FP64 &&
       can_group<double>(n, ctxs, graphs, poses0, inv_depth0, opts))
-    return backward_groups<double>(n, ctxs, graphs, poses0, inv_depth0, opts, grad_poses, grad_inv_depth, grad_target,
-                                   grad_weight, (hipStream_t)stream);
+    return no_throw([&] {
+      return backward_groups<double>(n, ctxs, graphs, poses0, inv_depth0, opts, grad_poses, grad_inv_depth,
+                                     grad_target, grad_weight, (hipStream_t)stream);
+    });
   if (outputs && opts && opts->precision == DPVBA_FP32 && can_group<float>(n, ctxs, graphs, poses0, inv_depth0, opts))
-    return backward_groups<float>(n, ctxs, graphs, poses0, inv_depth0, opts, grad_poses, grad_inv_depth, grad_target,
-                                  grad_weight, (hipStream_t)stream);
+    return no_throw([&] {
+      return backward_groups<float>(n, ctxs, graphs, poses0, inv_depth0, opts, grad_poses, grad_inv_depth, grad_target,
+                                    grad_weight, (hipStream_t)stream);
+    });
   return fan_out(n, ctxs, (hipStream_t)stream, [&](int i, void* s) {
     return dpvba_solve_backward(ctxs[i], &graphs[i], poses0[i], inv_depth0[i], opts,
                                 grad_poses ? grad_poses[i] : nullptr, grad_inv_depth ? grad_inv_depth[i] : nullptr,

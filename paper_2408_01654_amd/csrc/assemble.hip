@@ -160,7 +160,7 @@ __global__ void report_reduce_kernel(const double* part_cost, const int* part_in
 // order, one pixel a thread, so that a wavefront writes 512 contiguous bytes
 // (one thread per edge wrote 8 bytes every 8 p^2).  P2: the pixels of a patch
 // when known at compile time (0: p * p), for the division of the walk.
-// 1,505,568 edges of 3 x 3 patches: 137 us before, 46 us now (2.7 TB/s of the
+// 1,505,568 edges of 3 x 3 patches: 127 us before, 47 us now (2.7 TB/s of the
 // 125 MB it has to move).
 constexpr int kReprojLd = 13;  // R (9), t d (3), inverse depth d; odd, so neighbouring edges lie on different banks
 

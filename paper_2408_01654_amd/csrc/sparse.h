@@ -47,7 +47,8 @@ template <typename TP, typename T>
 hipError_t launch_sparse_gather(const SparsePlan& p, const TP* part_S, const int* off, const int* src, T* A,
                                 const T* dB, T lambda, T lam_diag, T* d0, T* rhs, float* A32, float* d032,
                                 hipStream_t st);
-// A <- zero blocks with identity on unused rows; v [64 nb] and d0 zero.
+// A <- zero blocks with identity on unused rows; v [64 nb] <- zero; *cost (if
+// given) <- the sum of the squares of r [nr].
 template <typename T>
 hipError_t launch_sparse_clear(const SparsePlan& p, T* A, T* v, const double* r, int nr, double* cost,
                                hipStream_t st);

@@ -603,9 +603,11 @@ __global__ void __launch_bounds__(256) sparse_solve_kernel(SparsePlan P, const T
 // the storage needs no clearing pass.  Bound by the chain offset, source,
 // value of each entry: a block near the diagonal has up to 100 pairs of 36
 // entries, and few blocks are that full, so sixteen wavefronts take one
-// with the loads of eight shares together: 62 -> 26 us on 1000 keyframes
-// (94 block rows), 55 -> 19 us on 317 in float64 (256 threads before, four
-// loads together and the rest one by one).
+// with the loads of eight shares together: 26 us on 1000 keyframes (902 blocks),
+// 19 us on 317 in float64 (227 blocks); with 256 threads, four loads together and
+// the rest one by one 62 and 55 us.  A workgroup a block leaves most of the chip
+// idle where blocks are few: at 100 keyframes (up to 55 of them) the gather phase
+// takes 55 us, where a thread an entry of the dense system took 31.
 constexpr int kGatherThreads = 1024;
 template <typename TP, typename T>
 __global__ void __launch_bounds__(kGatherThreads) sparse_gather_kernel(SparsePlan P, const TP* part_S, const int* off,
