@@ -489,15 +489,15 @@ __device__ __forceinline__ void tile_assemble(const IterArgs<T>& A, int tile, un
   {
     typedef typename Vec16<T>::type vec_t;
     constexpr int V = 16 / (int)sizeof(T);
-    const int rv = Ws / V, skip = (Wp - Ws) / V, nvec = Kp * rv;
-    const float r_rv = 1.f / (float)rv;
+    const int nvec = Kp * Ws / V;
     const vec_t* from = reinterpret_cast<const vec_t*>(sU);
     vec_t* to = reinterpret_cast<vec_t*>(A.U_s + ti.u_begin);
-    if (skip == 0) {
+    if (Wp == Ws) {
       for (int x = tid; x < nvec; x += blockDim.x) to[x] = from[x];
     } else {
+      const float r_rv = (float)V / (float)Ws;
       for (int x = tid; x < nvec; x += blockDim.x)
-        to[x] = from[x + (int)(((float)x + 0.5f) * r_rv) * skip];  // row x / rv: exact, x < 2^20
+        to[x] = from[x + (int)(((float)x + 0.5f) * r_rv) * (16 / V)];  // row x / (Ws / V): exact, x < 2^20
     }
   }
   for (int idx = tid; idx < Tn * 7; idx += blockDim.x) {  // column c of Ad^T M (c = 6: Ad^T v)
