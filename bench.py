@@ -154,13 +154,15 @@ def cholesky_flops(n):
 
 
 def envelope_cholesky_flops(s, sys_order=None):
-    """Algorithmic FLOP of the camera solve within the envelope of the
-    reduced system, the work the factor has to do: Cholesky fill stays
+    """FLOP of a Cholesky of the reduced system within its envelope, the
+    reference count of the camera solve's record (the library factors 64 x 64
+    blocks along a nested dissection of the same order, which is another
+    count: whole blocks, fewer dependent steps): Cholesky fill stays
     between a row's first coupled column and the diagonal, so column j of L
     has w_j = #{rows r > j whose envelope starts at or before j} entries
     below the diagonal; the factor costs sum_j w_j (w_j + 1) and the two
     triangular solves 4 sum_j (w_j + 1).  A row's envelope starts at the
-    first free pose (in the factored order: block row p is free pose
+    first free pose (in the banded order: block row p is free pose
     sys_order[p], the library's dpvba_get_system_order; None: the poses'
     own order) that shares a patch with its pose (a patch couples its
     source frame and all of its targets)."""
@@ -258,7 +260,9 @@ def bench_global(steps, warmup=1, precision=None, scene=None, n_upper=None, keep
                                  "kernel": "block-sparse Cholesky and triangular solves of the 5994-wide camera system "
                                            "(factor phase: all of its launches)",
                                  "avg_launch_us": avg["factor"], "alg_flop_per_launch": flops,
-                                 "alg_flop_basis": "envelope of the reduced system in its factored order "
+                                 "alg_flop_basis": "a reference algorithm's count, not the one run (64 x 64 blocks along a "
+                                                   "nested dissection): Cholesky within the envelope of the reduced "
+                                                   "system in its banded order "
                                                    + ("(reverse Cuthill-McKee of the free poses)" if permuted
                                                       else "(the poses' own order)")
                                                    + ": fill stays between a row's first coupled column and "
